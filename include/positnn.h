@@ -85,8 +85,9 @@ typedef enum {
  * preserved (partial quires of a split reduction; both operands rewritten once:
  * for posit<8,0> products of 2^28 multiply-adds and more as two int8 digit planes
  * each, 2 bytes per element; for posit<8,1> / posit<8,2> products of 2^25 and more
- * (128 outputs each way, K from 256 to 8192) as four / eight; for posit<16,1> and the 10- / 12-bit formats from
- * 96 x 96 outputs on as doubles, 8 bytes per element). */
+ * (128 outputs each way, K from 256 to 8192) as up to four / eight; for posit<16,1>, posit<10,1> and posit<12,1> from
+ * 96 x 96 outputs and K = 64 to 16352 on, and for posit<32,2> from 768 tiles of 16 x 16 outputs and K = 256 to 16352 on,
+ * as up to eight; for posit<10,2> and posit<12,2>, and beyond those reductions, as doubles, 8 bytes per element). */
 int posit_gemm(void* stream, int fin, int fout, int transA, int transB,
                int64_t M, int64_t N, int64_t K,
                const void* A, int64_t lda, const void* B, int64_t ldb,

@@ -7,7 +7,7 @@
 #include "conv_p8.h"
 #include "gemm_p8_w4.h"
 #include "gemm_p8_mfma.h"
-#include "gemm_b8_mfma.h"
+#include "gemm_dig_mfma.h"
 #include "conv_b8.h"
 #include "gemm_bucket_pre.h"
 #include "gemm_p16_window.h"
@@ -29,17 +29,39 @@ inline bool use_p8_w4(int64_t M, int64_t N, int64_t K) { return use_p8_kernel(M,
 template <class F>
 constexpr bool is_b8() { return F::N == 8 && F::ES != 0; }
 
+// Formats whose operands the digit kernels hold (posit<32,2> in a window; beyond it the LDS kernel does the work).
 template <class F>
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K) {
+constexpr bool is_dig() { return F::N == 32 || (F::ES != 0 && DigFormat<F>::COVER); }
+
+// Products that go to the integer matrix cores as base-256 digit planes, where the workspace may have up to `limit` bytes.
+template <class F>
+inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
+    if constexpr (!is_dig<F>()) return false;
+    else {
+        if (K > DIG_MAXK || M > ((int64_t)1 << 20) || N > ((int64_t)1 << 20)) return false;
+        if (F::N == 8) {
+            if (M < 128 || N < 128 || K < 256 || K > 8192 || M * N * K < ((int64_t)1 << 25) || ((M + 63) / 64) * ((N + 63) / 64) < 32) return false;
+        } else if (F::N == 32) {
+            if (!p32_lds_fits(M, N, K) || K < 256) return false;
+        } else if (M < 96 || N < 96 || K < 64) {
+            return false;
+        }
+        return dig_plan<F>(M, N, K).total <= limit;
+    }
+}
+
+template <class F>
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
+    if (dig_gemm_fits<F>(M, N, K, limit)) {
+        GemmPlan p;
+        p.splits = 1; p.k_per_split = K; p.ws_bytes = 0;
+        if constexpr (is_dig<F>()) p.ws_bytes = dig_plan<F>(M, N, K).total;
+        return p;
+    }
     if constexpr (is_b8<F>()) {
         if (p8_small_gemm_fits(M, N, K)) {  // one thread group per output: no workspace
             GemmPlan p;
             p.splits = 1; p.k_per_split = K; p.ws_bytes = 0;
-            return p;
-        }
-        if (b8_mfma_fits<F>(M, N, K)) {  // digit planes of both operands for the integer matrix cores
-            GemmPlan p;
-            p.splits = 1; p.k_per_split = K; p.ws_bytes = b8_mfma_layout<F>(M, N, K).total();
             return p;
         }
         if (M < ((int64_t)1 << 31) && N < ((int64_t)1 << 31) && K < ((int64_t)1 << 31)) return b8_conv_plan<F>((int)M, (int)N, (int)K);
@@ -75,14 +97,24 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K) {
 template <class F>
 int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, int64_t N, int64_t K,
                   const void* A, int64_t lda, const void* B, int64_t ldb, const void* bias, void* C, int64_t ldc,
-                  void* ws, size_t ws_bytes) {
+                  void* ws, size_t ws_bytes, size_t limit) {
     typedef typename Storage<F::N>::T T;
     constexpr int TM = GemmTile<F>::TM, TN = GemmTile<F>::TN;
-    const GemmPlan plan = gemm_plan<F>(M, N, K);
+    const GemmPlan plan = gemm_plan<F>(M, N, K, limit);
     if (plan.ws_bytes > 0 && (!ws || ws_bytes < plan.ws_bytes)) return PNN_EWORKSPACE;
     RowMajorOut out;
     out.ld = ldc;
     hipError_t e;
+    const int* served = nullptr;  // on the device: non-zero when the digit kernels did the work
+    if constexpr (is_dig<F>()) {
+        // (posit<32,2> with a bias: the LDS kernel, whose quire takes it at any scale)
+        if (dig_gemm_fits<F>(M, N, K, limit) && (F::N != 32 || !bias)) {
+            const DigInfo* decision;
+            e = launch_dig_gemm<F>(st, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, ws, &decision);
+            if (e != hipSuccess || DigFormat<F>::COVER) return hip_status(e);
+            served = &decision->np;
+        }
+    }
     if ((F::N == 8 && F::ES == 0) && p8_small_gemm_fits(M, N, K))
         return hip_status(launch_p8_small_gemm(st, transA, transB, (const uint8_t*)A, lda, (const uint8_t*)B, ldb, (const uint8_t*)bias, C, ldc,
                                                fout, M, N, K));
@@ -122,9 +154,6 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
         if (p8_small_gemm_fits(M, N, K))
             return hip_status(launch_b8_small_gemm<F>(st, transA, transB, (const uint8_t*)A, lda, (const uint8_t*)B, ldb, (const uint8_t*)bias, C,
                                                       ldc, fout, M, N, K));
-        if (b8_mfma_fits<F>(M, N, K))
-            return hip_status(launch_b8_mfma_gemm<F>(st, transA, transB, (const uint8_t*)A, lda, (const uint8_t*)B, ldb, (const uint8_t*)bias, C, ldc,
-                                                     fout, M, N, K, ws));
         if (p8_gemm_as_gather_fits(transA, transB, M, N, K, lda, ldb)) {
             const P8ConvProblem p = p8_gemm_problem(transA, transB, (int)M, (int)N, (int)K, A, (int)lda, B, (int)ldb, ldc);
             RowMajorOut mo{ldc};
@@ -136,19 +165,19 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
             if (!transA && !transB) {
                 MatrixOperand<T, true> a{(const T*)A, lda, M, K};
                 MatrixOperand<T, false> b{(const T*)B, ldb, N, K};
-                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout));
+                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout, served));
             } else if (!transA && transB) {
                 MatrixOperand<T, true> a{(const T*)A, lda, M, K};
                 MatrixOperand<T, true> b{(const T*)B, ldb, N, K};
-                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout));
+                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout, served));
             } else if (transA && !transB) {
                 MatrixOperand<T, false> a{(const T*)A, lda, M, K};
                 MatrixOperand<T, false> b{(const T*)B, ldb, N, K};
-                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout));
+                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout, served));
             } else {
                 MatrixOperand<T, false> a{(const T*)A, lda, M, K};
                 MatrixOperand<T, true> b{(const T*)B, ldb, N, K};
-                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout));
+                return hip_status(launch_p32_lds_gemm(st, a, b, M, N, K, bias, C, ldc, fout, served));
             }
         }
     }
@@ -216,7 +245,7 @@ extern "C" int posit_gemm(void* stream, int fin, int fout, int transA, int trans
     if (workspace && ((uintptr_t)workspace & 15u) != 0) return PNN_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     discard_stale_hip_error();
-    PNN_DISPATCH_POSIT(fin, return gemm_dispatch<F>(st, fout, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, workspace, workspace_bytes))
+    PNN_DISPATCH_POSIT(fin, return gemm_dispatch<F>(st, fout, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, workspace, workspace_bytes, SIZE_MAX))
     return PNN_EINVAL;
 }
 
@@ -255,7 +284,10 @@ extern "C" int posit_gemm_static(void* stream, int fin, int fout, int transA, in
     bool launch;
     const int rc = gemm_check_args(fin, fout, transA, transB, M, N, K, A, lda, B, ldb, C, ldc, &launch);
     if (!launch) return rc;
-    const size_t need = posit_gemm_workspace(fin, fout, transA, transB, M, N, K);
+    // a kernel that wants more than the fixed array gives way to an older one that does not
+    const size_t limit = PNN_GEMM_STATIC_SCRATCH_BYTES;
+    size_t need = 0;
+    PNN_DISPATCH_POSIT(fin, need = gemm_plan<F>(M, N, K, limit).ws_bytes)
     if (need > PNN_GEMM_STATIC_SCRATCH_BYTES) return PNN_EWORKSPACE;  // beyond the fixed array: posit_gemm with a caller's workspace
     void* ws = nullptr;
     if (need > 0) {
@@ -265,6 +297,6 @@ extern "C" int posit_gemm_static(void* stream, int fin, int fout, int transA, in
     hipStream_t st = (hipStream_t)stream;
     discard_stale_hip_error();
     const size_t ws_bytes = need > 0 ? (size_t)PNN_GEMM_STATIC_SCRATCH_BYTES : 0;
-    PNN_DISPATCH_POSIT(fin, return gemm_dispatch<F>(st, fout, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, ws, ws_bytes))
+    PNN_DISPATCH_POSIT(fin, return gemm_dispatch<F>(st, fout, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, ws, ws_bytes, limit))
     return PNN_EINVAL;
 }

@@ -26,22 +26,6 @@ namespace pnn {
 constexpr int PCM_MAXK16 = 512;  // most (tap, channel group) pairs, padding included (4 KB of LDS)
 constexpr int PCM_STAGES = 4;    // k blocks in flight per workgroup
 
-// s_waitcnt immediate: at most n vector-memory operations outstanding, the other counters unconstrained
-constexpr int pcm_vmcnt(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }
-
-// The barrier of the ring: the bare instruction.  __syncthreads() puts a fence in front of it that waits for EVERY
-// outstanding copy of the wave, the ones running ahead included, which would shorten the ring to one block.  What the
-// ring needs holds without a fence: a wave's copies of the block it is about to read have landed (the counted wait in
-// front of the barrier), and every wave's LDS reads of the block about to be overwritten have returned (their data was
-// consumed by matrix instructions earlier in program order; nothing may be scheduled across the barrier).
-__device__ __forceinline__ void pcm_ring_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 struct P8ConvMfmaPlan {
     bool ok;
     int which;                 // 0 forward, 1 backward-data

@@ -1,0 +1,479 @@
+// Posit operands as planes of int8 digits for the integer matrix cores, and the read-out of the sums: what the matrix
+// product (gemm_dig_mfma.h) and the convolutions (conv_dig_mfma.h) of every format other than posit<8,0> share.
+//
+// In units of minpos a posit is an integer v (paper Sec. 2; 2^(2 MAXS) for maxpos).  Written in balanced base-256 digits,
+//     v * 2^-base = sum_i d_i 256^i,  d_i in [-128, 127],  i = 0 .. NP - 1,
+// a product is  a b = 2^(base_a + base_b) sum_s 256^s sum_{i + j = s} a_i b_j : 2 NP - 1 int32 sums per output, NP^2 int8
+// products per posit product, exact.  With NP 2^14 at most added to a sum per reduction index, sums of up to 16352
+// indices stay below 2^31.  They are combined once per output, after the reduction, and rounded once.
+//
+// The window.  A tensor fills a few binades of its format: four planes hold 30 or 31 bits, a Gaussian tensor of a few million
+// posit<16,1> or posit(8,2) values from its largest to its smallest.  A first launch (dig_stat_kernel) takes the largest
+// and the smallest non-zero magnitude of each operand; both bits that matter follow from them, because the weight of a
+// pattern's last bit never falls when the magnitude grows.  All later launches of the call read the decision (dig_decide)
+// from the device, so nothing comes back to the host and the calls can be captured.  NP1 planes counted down from the
+// operand's own highest bit if both operands fit; otherwise NP2 planes, from minpos up where they hold the whole format;
+// for posit(8,1) and posit<32,2> NP2 planes from the highest bit.  Where that does not fit (posit<32,2> over more than 62
+// bits), nothing is done and the call's older kernel, launched last, does the work.
+//
+// Balanced digits cost one addition: (v + 0x80..80) ^ 0x80..80, byte by byte.  In an operand with NaR |v| < 2^(8 NP - 2) keeps
+// the top digit within [-64, 64], so -128 there marks NaR.
+#pragma once
+
+#include "gemm_p8_mfma.h"
+#include "quire_gemm.h"
+
+namespace pnn {
+
+constexpr int DIG_MAXK = 16352;      // longest reduction of one set of int32 sums: 8 digit pairs * 2^14 * K < 2^31
+constexpr int DIG_STAT_WGS = 128;    // workgroups that scan one operand
+constexpr size_t DIG_STAT_BYTES = 2 * DIG_STAT_WGS * 16;
+
+struct DigStat {
+    uint32_t low, high;  // smallest magnitude pattern minus one (all ones: none), largest magnitude pattern
+    uint32_t nar, pad;
+};
+
+// What the launches of one call agree on: the number of planes (0: the older kernel does the work) and per operand the
+// weight of digit 0 (as a power of two in minpos; may be negative) and whether NaR occurs.
+struct DigInfo {
+    int np;
+    int base[2];
+    int nar[2];
+};
+
+// Plane counts by format.  COVER: NP2 planes hold the whole format.  posit<32,2> has no narrow variant (NP1 = 0): six planes,
+// 46 bits, hold no Gaussian tensor of a million values, whose smallest ones end 2^-43 below one.
+template <class F>
+struct DigFormat {
+    static constexpr int BITS = 2 * F::MAXS + 1;        // bits of the largest magnitude
+    static constexpr int FULL = (BITS + 2 + 7) / 8;
+    static constexpr bool COVER = FULL <= 8;
+    static constexpr int NP2 = COVER ? FULL : 8;
+    static constexpr int NP1 = !COVER ? 0 : NP2 <= 4 ? 3 : 4;
+    static constexpr bool BASE0 = COVER && NP2 > 4;  // the wide kernel counts its planes from minpos
+};
+
+template <int NP> struct DigWord { typedef uint64_t T; };
+template <> struct DigWord<4> { typedef uint32_t T; };
+template <> struct DigWord<3> { typedef uint32_t T; };
+
+// Weight (power of two in minpos) of the last bit and of the leading bit of a magnitude pattern 1 .. maxpos.
+template <class F>
+PNN_HD int dig_low_bit(uint32_t mag) {
+    bool neg;
+    uint32_t sig;
+    int sh;
+    decode_fixed<F>(mag, neg, sig, sh);
+    return sh;
+}
+template <class F>
+PNN_HD int dig_high_bit(uint32_t mag) {
+    int nf;
+    const Real r = decode_fields<F>(mag, nf);
+    return r.scale + F::MAXS;
+}
+
+// Bits of magnitude that np planes hold of an operand with this largest magnitude pattern: one more where no NaR needs the
+// marker and the largest value's bytes stay within 0x7F7F..7F.  (That bit keeps a Gaussian posit(8,1) tensor, 15 bits, in two
+// planes.)
+template <class F>
+PNN_HD int dig_capacity(uint32_t high, bool nar, int np) {
+    if (high == 0) return 8 * np - 2;
+    int nf;
+    const uint32_t sig = 0x80000000u | (uint32_t)(decode_fields<F>(high, nf).frac >> 33);
+    return !nar && sig <= 0xFEFEFE00u ? 8 * np - 1 : 8 * np - 2;
+}
+
+// low, high: smallest and largest magnitude pattern of the two operands (high 0: all zero).  narrow: the call has a kernel
+// of NP1 planes.
+template <class F>
+PNN_HD DigInfo dig_decide(const uint32_t (&low)[2], const uint32_t (&high)[2], const uint32_t (&nar)[2], bool narrow) {
+    typedef DigFormat<F> D;
+    int lo[2], hi[2];
+    for (int o = 0; o < 2; ++o) {
+        lo[o] = high[o] ? dig_low_bit<F>(low[o]) : 0;
+        hi[o] = high[o] ? dig_high_bit<F>(high[o]) : 0;
+    }
+    auto fits = [&](int np) {
+        return hi[0] + 1 - lo[0] <= dig_capacity<F>(high[0], nar[0], np) && hi[1] + 1 - lo[1] <= dig_capacity<F>(high[1], nar[1], np);
+    };
+    DigInfo r;
+    r.np = 0;
+    if (D::NP1 != 0 && narrow && fits(D::NP1)) r.np = D::NP1;
+    else if (D::BASE0 || fits(D::NP2)) r.np = D::NP2;
+    for (int o = 0; o < 2; ++o) {
+        r.base[o] = D::BASE0 && r.np != D::NP1 ? 0 : hi[o] + 1 - dig_capacity<F>(high[o], nar[o], r.np);
+        r.nar[o] = nar[o] ? 1 : 0;
+    }
+    return r;
+}
+
+// The digits of a pattern as bytes, digit 0 lowest; NaR: -128 in the top one.  The leading bit goes to bit
+// scale + MAXS - base, all bits of a pattern that belongs in the window stay.
+template <class F, int NP>
+PNN_HD typename DigWord<NP>::T dig_word(uint32_t p, int base) {
+    typedef typename DigWord<NP>::T W;
+    constexpr W B = (W)(0x8080808080808080ull >> (64 - 8 * NP)), MASK = (W)(~0ull >> (64 - 8 * NP));
+    bool neg;
+    int scale, nf;
+    uint32_t fr;
+    decode_core(p, F::N, F::ES, neg, scale, fr, nf);
+    const uint32_t sig = 0x80000000u | (fr >> 1);
+    const int h = scale + F::MAXS - base;
+    W m;
+    if constexpr (sizeof(W) == 4) m = sig >> ((31 - h) & 31);
+    else m = ((uint64_t)sig << 32) >> ((63 - h) & 63);
+    const W v = neg ? (W)0 - m : m;
+    const W d = ((v + B) ^ B) & MASK;
+    return p == 0 ? (W)0 : p == F::NAR ? (W)0x80 << (8 * (NP - 1)) : d;
+}
+
+// ---- scan of the operands ----
+
+struct DigStatJob {
+    const void* src;
+    int64_t rows, cols, ld;  // a row-major matrix as stored
+};
+
+template <class F>
+struct DigScan {
+    uint32_t low = 0xFFFFFFFFu, high = 0, nar = 0;
+    __device__ __forceinline__ void add(uint32_t p) {
+        p &= F::MASK;
+        const uint32_t m = (p & F::NAR) ? (0u - p) & F::MASK : p;  // NaR stays NAR
+        const uint32_t l = m - 1u;
+        low = l < low ? l : low;
+        const uint32_t h = m & (F::NAR - 1u);
+        high = h > high ? h : high;
+        nar |= (uint32_t)(p == F::NAR);
+    }
+    __device__ __forceinline__ void merge(uint32_t l, uint32_t h, uint32_t n) {
+        low = l < low ? l : low;
+        high = h > high ? h : high;
+        nar |= n;
+    }
+};
+
+// posit(8,1) keeps what a workgroup saw in one word, so that the results of DIG_STAT_WGS8 workgroups fit beside the decision.
+constexpr int DIG_STAT_WGS8 = 28;
+template <class F>
+constexpr bool dig_stat_packed() { return F::N == 8 && !DigFormat<F>::BASE0; }
+template <class F>
+constexpr int dig_stat_wgs() { return dig_stat_packed<F>() ? DIG_STAT_WGS8 : DIG_STAT_WGS; }
+
+// Grid (dig_stat_wgs, 2), 1024 threads: workgroup (g, o) leaves what it saw of operand o in stats[o * wgs + g].  Bound by
+// memory: four 16-byte loads in flight per thread (one: 22 us for 2 x 16 MB, 1.5 TB/s).
+template <class F>
+__global__ __launch_bounds__(1024) void dig_stat_kernel(DigStatJob job0, DigStatJob job1, void* __restrict__ stats) {
+    typedef typename Storage<F::N>::T T;
+    constexpr int V = 16 / (int)sizeof(T);
+    const DigStatJob& job = blockIdx.y == 0 ? job0 : job1;
+    const T* src = (const T*)job.src;
+    const int t = threadIdx.x;
+    constexpr int WGS = dig_stat_wgs<F>();
+    const int64_t step = (int64_t)WGS * 1024, first = (int64_t)blockIdx.x * 1024 + t;
+    DigScan<F> s;
+    auto vec = [&](const uint4& v) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < 4 / (int)sizeof(T); ++b) s.add(w[i] >> (8 * (int)sizeof(T) * b));
+    };
+    const bool aligned = ((uintptr_t)src & 15u) == 0;
+    if (job.ld == job.cols && aligned) {
+        const int64_t n = job.rows * job.cols, nv = n / V;
+        const uint4* q = reinterpret_cast<const uint4*>(src);
+        int64_t i = first;
+        for (; i + 3 * step < nv; i += 4 * step) {
+            const uint4 v0 = q[i], v1 = q[i + step], v2 = q[i + 2 * step], v3 = q[i + 3 * step];
+            vec(v0);
+            vec(v1);
+            vec(v2);
+            vec(v3);
+        }
+        for (; i < nv; i += step) vec(q[i]);
+        const int64_t tail = nv * V + first;
+        if (tail < n) s.add(src[tail]);
+    } else if (aligned && job.ld % V == 0 && job.cols % V == 0) {
+        const int64_t per_row = job.cols / V, nv = job.rows * per_row;
+        for (int64_t i = first; i < nv; i += step) {
+            const int64_t r = i / per_row;
+            vec(*reinterpret_cast<const uint4*>(src + r * job.ld + (i - r * per_row) * V));
+        }
+    } else {
+        const int64_t n = job.rows * job.cols;
+        for (int64_t i = first; i < n; i += step) {
+            const int64_t r = i / job.cols;
+            s.add(src[r * job.ld + (i - r * job.cols)]);
+        }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+        s.merge((uint32_t)__shfl_xor((int)s.low, d), (uint32_t)__shfl_xor((int)s.high, d), (uint32_t)__shfl_xor((int)s.nar, d));
+    __shared__ DigStat part[16];
+    if ((t & 63) == 0) part[t >> 6] = DigStat{s.low, s.high, s.nar, 0};
+    __syncthreads();
+    if (t == 0) {
+#pragma unroll
+        for (int i = 1; i < 16; ++i) s.merge(part[i].low, part[i].high, part[i].nar);
+        const int at = blockIdx.y * WGS + blockIdx.x;
+        if constexpr (dig_stat_packed<F>()) ((uint32_t*)stats)[at] = (s.low < 0xFFu ? s.low : 0xFFu) | (s.high << 8) | (s.nar << 16);
+        else ((DigStat*)stats)[at] = DigStat{s.low, s.high, s.nar, 0};
+    }
+}
+
+// Every workgroup (256 threads) of a digit launch reads the partial results and decides; the first one stores the decision
+// for the launches that follow.
+template <class F>
+__device__ __forceinline__ DigInfo dig_read_decision(const void* __restrict__ stats, DigInfo* __restrict__ info, bool narrow, bool store) {
+    static_assert(DIG_STAT_WGS == 128 && DIG_STAT_WGS8 <= 128, "two waves per operand");
+    constexpr int WGS = dig_stat_wgs<F>();
+    __shared__ DigStat wave[4];
+    const int t = threadIdx.x, o = t >> 7, g = t & 127;
+    DigScan<F> s;
+    if (g < WGS) {
+        if constexpr (dig_stat_packed<F>()) {
+            const uint32_t v = ((const uint32_t*)stats)[o * WGS + g];
+            s.merge((v & 0xFFu) == 0xFFu ? 0xFFFFFFFFu : v & 0xFFu, (v >> 8) & 0xFFu, v >> 16);
+        } else {
+            const DigStat v = ((const DigStat*)stats)[o * WGS + g];
+            s.merge(v.low, v.high, v.nar);
+        }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+        s.merge((uint32_t)__shfl_xor((int)s.low, d), (uint32_t)__shfl_xor((int)s.high, d), (uint32_t)__shfl_xor((int)s.nar, d));
+    if ((t & 63) == 0) wave[t >> 6] = DigStat{s.low, s.high, s.nar, 0};
+    __syncthreads();
+    uint32_t low[2], high[2], nar[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        DigScan<F> u;
+        u.merge(wave[2 * k].low, wave[2 * k].high, wave[2 * k].nar);
+        u.merge(wave[2 * k + 1].low, wave[2 * k + 1].high, wave[2 * k + 1].nar);
+        low[k] = __builtin_amdgcn_readfirstlane(u.low + 1u);
+        high[k] = __builtin_amdgcn_readfirstlane(u.high);
+        nar[k] = __builtin_amdgcn_readfirstlane(u.nar);
+    }
+    const DigInfo r = dig_decide<F>(low, high, nar, narrow);
+    if (store && t == 0) *info = r;
+    return r;
+}
+
+// The planes of a block fall into groups, and a block carries one bit per group that holds anything.  A window counted from
+// the highest bit puts nearly all digits into its upper planes; only the rare small values reach the lower ones.  A
+// workgroup therefore multiplies the planes from some group on for every k block, straight-line and without a look at the
+// bits, and goes once more over the few k blocks that hold anything below.
+template <int NP>
+struct DigGroups {
+    static constexpr int G = NP <= 5 ? 3 : 4;
+    static constexpr int start(int g) {  // first plane of group g; start(G) = NP
+        return g == G ? NP : NP <= 6 ? g : g == 0 ? 0 : g + 1;
+    }
+};
+
+// 16 digit words (one lane's reduction indices) to NP planes of 16 bytes: 4 x 4 byte transpositions.
+template <int NP>
+__device__ __forceinline__ void dig_planes_of(const typename DigWord<NP>::T (&w)[16], uint32_t (&pl)[NP][4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int h = 0; h < (NP + 3) / 4; ++h) {
+            uint32_t a[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = (uint32_t)(w[4 * q + e] >> (32 * h));
+            const uint32_t x = __builtin_amdgcn_perm(a[1], a[0], 0x05010400u), y = __builtin_amdgcn_perm(a[3], a[2], 0x05010400u);
+            const uint32_t z = __builtin_amdgcn_perm(a[1], a[0], 0x07030602u), u = __builtin_amdgcn_perm(a[3], a[2], 0x07030602u);
+            pl[4 * h][q] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+            if (4 * h + 1 < NP) pl[4 * h + 1 < NP ? 4 * h + 1 : 0][q] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+            if (4 * h + 2 < NP) pl[4 * h + 2 < NP ? 4 * h + 2 : 0][q] = __builtin_amdgcn_perm(u, z, 0x05040100u);
+            if (4 * h + 3 < NP) pl[4 * h + 3 < NP ? 4 * h + 3 : 0][q] = __builtin_amdgcn_perm(u, z, 0x07060302u);
+        }
+    }
+}
+
+// ---- the inner step: one k block of 32, one 32 x 32 block of outputs per wave ----
+
+// Planes SP .. NP - 1 of the two blocks a wave multiplies in a step, as operand registers.
+template <int NP>
+struct DigFrag {
+    pm_v4i a[NP], b[NP];
+    template <int SP>
+    __device__ __forceinline__ void load(const uint4* sa, const uint4* sb) {
+#pragma unroll
+        for (int i = NP - 1; i >= SP; --i) {
+            b[i] = __builtin_bit_cast(pm_v4i, sb[i * 64]);
+            a[i] = __builtin_bit_cast(pm_v4i, sa[i * 64]);
+        }
+    }
+};
+
+// Planes IF .. IT - 1 of A against JF .. JT - 1 of B; the order keeps a sum from following itself.
+template <int NP, int IF, int IT, int JF, int JT>
+__device__ __forceinline__ void dig_mma(const DigFrag<NP>& f, pm_v16i (&acc)[2 * NP - 1]) {
+#pragma unroll
+    for (int i = IF; i < IT; ++i)
+#pragma unroll
+        for (int jj = JF; jj < JT; ++jj) {
+            const int j = ((i - IF) & 1) ? JT - 1 - (jj - JF) : jj;
+            acc[i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.a[i], f.b[j], acc[i + j], 0, 0, 0);
+        }
+}
+
+// The pairs of groups of which at least one lies below group g0 (ma, mb: the blocks' bits, uniform).
+template <int NP, int GA, int GB>
+__device__ __forceinline__ void dig_mma_below(int g0, uint32_t ma, uint32_t mb, const DigFrag<NP>& f, pm_v16i (&acc)[2 * NP - 1]) {
+    typedef DigGroups<NP> D;
+    if constexpr (GA < D::G) {
+        if constexpr (GB < D::G) {
+            if ((GA < g0 || GB < g0) && (ma & (1u << GA)) && (mb & (1u << GB)))
+                dig_mma<NP, D::start(GA), D::start(GA + 1), D::start(GB), D::start(GB + 1)>(f, acc);
+            dig_mma_below<NP, GA, GB + 1>(g0, ma, mb, f, acc);
+        } else {
+            dig_mma_below<NP, GA + 1, 0>(g0, ma, mb, f, acc);
+        }
+    }
+}
+
+// ---- the sums as one integer ----
+
+// Limbs that hold sum_s acc[s] 256^s: 2 NP - 2 bytes above int32 sums, and a sign.
+template <int NP>
+constexpr int dig_limbs() { return (8 * (2 * NP - 2) + 33 + 31) / 32; }
+
+// Four sums at a time into 64 bits by 32 x 32 + 64 multiply-adds (the powers of 256 are hidden from the compiler, which
+// would make pairs of shifts and adds of them), then the words with carries.
+template <int NP>
+__device__ __forceinline__ void dig_combine(const pm_v16i (&acc)[2 * NP - 1], int r, uint32_t (&q)[dig_limbs<NP>()]) {
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), W = (NC + 3) / 4;
+    int c8 = 1 << 8, c16 = 1 << 16, c24 = 1 << 24;
+    asm("" : "+s"(c8), "+s"(c16), "+s"(c24));
+    int64_t w[W];  // units of 2^(32 i)
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        int64_t v = acc[4 * i][r];
+        if (4 * i + 1 < NC) v += (int64_t)acc[4 * i + 1 < NC ? 4 * i + 1 : 0][r] * c8;
+        if (4 * i + 2 < NC) v += (int64_t)acc[4 * i + 2 < NC ? 4 * i + 2 : 0][r] * c16;
+        if (4 * i + 3 < NC) v += (int64_t)acc[4 * i + 3 < NC ? 4 * i + 3 : 0][r] * c24;
+        w[i] = v;
+    }
+    int64_t carry = 0;
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        if (l < W) carry += w[l < W ? l : 0];  // |w| < 2^56
+        q[l] = (uint32_t)carry;
+        carry >>= 32;
+    }
+}
+
+struct DigRound {
+    FmtRT fin, fout;
+    int at;          // base_a + base_b: weight of the sums' unit in minpos^2
+    PNN_HD int qfrac() const { return 2 * fin.maxs() - at; }
+};
+
+// A multi-limb integer in units of 2^-qfrac, rounded once: the rounding of quire_to_real and encode_core as straight-line
+// code, so that several outputs can be in flight in a wave (branches around each case cost most of a small product's time
+// at one or two waves per SIMD).  32 or more exact bits below the leading one and whether anything lies below them
+// decide the rounding of every format.  WIDE: f has more than 16 bits.
+template <int L, bool WIDE>
+PNN_HD uint32_t dig_round_limbs(const uint32_t (&q)[L], int qfrac, const FmtRT& f) {
+    const uint32_t s = (uint32_t)((int32_t)q[L - 1] >> 31);
+    uint32_t a[L];
+    unsigned carry = s & 1u;
+#pragma unroll
+    for (int l = 0; l < L; ++l) a[l] = __builtin_addc(q[l] ^ s, 0u, carry, &carry);
+    // x: the highest limb that is not zero (its bit 0 is bit `at`), y: the limb below, low: whatever lies below that
+    uint32_t x = a[0], y = 0, low = 0, below = 0;
+    int at = 0;
+#pragma unroll
+    for (int l = 1; l < L; ++l) {
+        const bool up = a[l] != 0;
+        x = up ? a[l] : x;
+        y = up ? a[l - 1] : y;
+        low = up ? below : low;
+        at = up ? 32 * l : at;
+        below |= a[l - 1];
+    }
+    const bool zero = x == 0;
+    const int lz = clz32(x | 1u);  // x = 0: the result is not used
+    const uint64_t t = (((uint64_t)x << 32) | y) << lz;
+    const int maxs = f.maxs();
+    int scale = at + 31 - lz - qfrac;
+    const bool over = scale >= maxs, under = scale < -maxs;
+    scale = over ? maxs - 1 : under ? -maxs : scale;  // these round to maxpos / minpos with an all-ones / zero fraction
+    uint64_t frac = over ? ~0ull : under ? 0ull : t << 1;
+    bool sticky = over || (!under && low != 0);
+    const int k = scale >> f.es;
+    const uint32_t e = (uint32_t)(scale & ((1 << f.es) - 1));
+    const bool pos = k >= 0;
+    const int hl = (pos ? k + 2 : 1 - k) + f.es;  // 2 .. n - 1 + es
+    uint32_t body;
+    if constexpr (!WIDE) {  // one 32-bit word holds regime, exponent, fraction and the bits that round them
+        const uint32_t fr = (uint32_t)(frac >> 32);
+        sticky = sticky || (uint32_t)frac != 0;
+        const uint32_t regime = pos ? (1u << ((k + 2) & 31)) - 2u : 1u;
+        const uint32_t w = (((regime << f.es) | e) << (32 - hl)) | (fr >> hl);
+        sticky = sticky || (fr << (32 - hl)) != 0 || (w << f.n) != 0;
+        body = w >> (33 - f.n);
+        body += (w >> (32 - f.n)) & 1u & ((sticky ? 1u : 0u) | body);
+    } else {
+        const uint64_t regime = pos ? (1ull << ((k + 2) & 63)) - 2ull : 1ull;
+        const uint64_t w = (((regime << f.es) | e) << (64 - hl)) | (frac >> hl);
+        sticky = sticky || (frac << (64 - hl)) != 0 || (w << f.n) != 0;
+        body = (uint32_t)(w >> (65 - f.n));
+        body += (uint32_t)(w >> (64 - f.n)) & 1u & ((sticky ? 1u : 0u) | body);
+    }
+    return zero ? 0u : s ? (0u - body) & f.mask() : body;
+}
+
+// The integer of L limbs in units of minpos^2 * 2^at as a 128-bit quire (units of minpos^2), plus bias * 1.  Formats of at
+// most 16 bits, where the sums fit 128 bits: either at < 0 and the low bits are zero, or the shift stays within.
+template <int L>
+PNN_HD void dig_add_bias(const uint32_t (&q)[L], const DigRound& d, uint32_t bias, uint32_t (&out)[4]) {
+    static_assert(L >= 3, "three limbs or more");
+    const uint32_t top = L >= 4 ? q[L >= 4 ? 3 : 0] : (uint32_t)((int32_t)q[L - 1] >> 31);
+    unsigned __int128 x = ((unsigned __int128)(((uint64_t)top << 32) | q[2]) << 64) | (((uint64_t)q[1] << 32) | q[0]);
+    x = d.at >= 0 ? x << d.at : (unsigned __int128)((__int128)x >> -d.at);
+    if (bias != 0 && bias != d.fin.nar()) {
+        bool neg;
+        int scale, nf;
+        uint32_t fr;
+        decode_core(bias, d.fin.n, d.fin.es, neg, scale, fr, nf);
+        const uint32_t sig = (1u << nf) | (nf ? fr >> (32 - nf) : 0u);
+        const unsigned __int128 v = (unsigned __int128)sig << (scale - nf + 2 * d.fin.maxs());
+        x = neg ? x - v : x + v;
+    }
+#pragma unroll
+    for (int l = 0; l < 4; ++l) out[l] = (uint32_t)(x >> (32 * l));
+}
+
+// Outputs of at most 16 bits or more, with a bias or without.  None of these sums leaves the range of its quire (at most
+// 16352 terms), so there is no wrap to reproduce.
+template <int L>
+__device__ __forceinline__ uint32_t dig_round(const uint32_t (&q)[L], const DigRound& d, bool nar, bool has_bias, uint32_t bias) {
+    uint32_t res;
+    if (has_bias) {
+        nar = nar || bias == d.fin.nar();
+        uint32_t u[4];
+        dig_add_bias<L>(q, d, bias, u);
+        const int qf = 2 * d.fin.maxs();
+        res = d.fout.n <= 16 ? dig_round_limbs<4, false>(u, qf, d.fout) : dig_round_limbs<4, true>(u, qf, d.fout);
+    } else {
+        res = d.fout.n <= 16 ? dig_round_limbs<L, false>(q, d.qfrac(), d.fout) : dig_round_limbs<L, true>(q, d.qfrac(), d.fout);
+    }
+    return nar ? d.fout.nar() : res;
+}
+
+__device__ __forceinline__ uint32_t dig_load_pattern(const void* p, int64_t i, int n) {
+    return n <= 8 ? ((const uint8_t*)p)[i] : n <= 16 ? ((const uint16_t*)p)[i] : ((const uint32_t*)p)[i];
+}
+__device__ __forceinline__ void dig_store_pattern(void* p, int64_t i, int n, uint32_t v) {
+    if (n <= 8) ((uint8_t*)p)[i] = (uint8_t)v;
+    else if (n <= 16) ((uint16_t*)p)[i] = (uint16_t)v;
+    else ((uint32_t*)p)[i] = v;
+}
+
+}  // namespace pnn

@@ -1,0 +1,573 @@
+// Matrix product with the exact quire (paper Sec. 2, Sec. 3.3) on the integer matrix cores for posit(8,1), posit(8,2), the
+// 10- / 12-bit formats that fit 64 bits, posit<16,1> and posit<32,2>: operands as planes of balanced base-256 digits
+// (dig_planes.h).
+//
+// Launches of a call: a scan of both operands (which window of digits serves), the digit planes of both, then one product
+// kernel per plane count, of which the one that was decided on does the work and the others return at once, and the
+// merge of a reduction cut into slices.
+//
+// Layout of the rewritten operands: [k block of 32][row block of 32][plane][lane][16 bytes] in the lane order of
+// v_mfma_i32_32x32x32_i8 (gemm_p8_mfma.h), and one byte per (k block, row block): the level of the block, that is the
+// lowest plane its multiplication has to start from.
+#pragma once
+
+#include <type_traits>
+
+#include "dig_planes.h"
+
+namespace pnn {
+
+struct DigMatrixJob {
+    const void* src;
+    int64_t s_r, s_k;   // element (row, k) at src[row * s_r + k * s_k]; one of the two is 1
+    int rows, K;
+    uint8_t* mask;      // [KB][RB]: which groups of planes of the block hold anything
+    int RB;
+};
+
+constexpr int DIG_ROWS = 128;  // rows of a workgroup of the digit launch: four row blocks, one wave each
+
+// Planes of one k block and four row blocks.  An operand stored reduction-index-major goes through an LDS tile.
+template <class F, int NP>
+__device__ __forceinline__ void dig_matrix_planes(const DigMatrixJob& job, uint8_t* __restrict__ dst, int base, int kb, int bx,
+                                                  const typename Storage<F::N>::T (*tile)[DIG_ROWS], uint64_t* tab) {
+    typedef typename Storage<F::N>::T T;
+    typedef typename DigWord<NP>::T W;
+    constexpr int V = 16 / (int)sizeof(T);
+    const int t = threadIdx.x;
+    const bool via_lds = job.s_k != 1;
+    if constexpr (F::N == 8) {
+        tab[t] = dig_word<F, NP>((uint32_t)t, base);
+        __syncthreads();
+    }
+    const int rb = bx * 4 + (t >> 6), lane = t & 63;  // a wave: one row block
+    if (rb >= job.RB) return;
+    const int row = rb * 32 + (lane & 31), k0 = kb * 32 + 16 * (lane >> 5);
+    uint32_t pat[16];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) pat[b] = 0;
+    if (via_lds) {
+#pragma unroll
+        for (int b = 0; b < 16; ++b) pat[b] = tile[16 * (lane >> 5) + b][(t >> 6) * 32 + (lane & 31)];
+    } else if (row < job.rows) {
+        const T* p = (const T*)job.src + (int64_t)row * job.s_r + k0;
+        if (k0 + 16 <= job.K && (((uintptr_t)p) & 15u) == 0) {
+#pragma unroll
+            for (int c = 0; c < 16 / V; ++c) {
+                const uint4 v = reinterpret_cast<const uint4*>(p)[c];
+                const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int b = 0; b < V; ++b)
+                    pat[c * V + b] = sizeof(T) == 4 ? wv[b & 3] : (wv[b * (int)sizeof(T) / 4] >> (8 * ((b * (int)sizeof(T)) & 3))) & (sizeof(T) == 1 ? 0xFFu : 0xFFFFu);
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < 16; ++b)
+                if (k0 + b < job.K) pat[b] = p[b];
+        }
+    }
+    W w[16];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        if constexpr (F::N == 8) w[b] = (W)tab[pat[b]];
+        else w[b] = dig_word<F, NP>(pat[b] & F::MASK, base);
+    }
+    uint32_t pl[NP][4];
+    dig_planes_of<NP>(w, pl);
+    uint4* out = reinterpret_cast<uint4*>(dst) + ((int64_t)(kb * job.RB + rb) * NP) * 64 + lane;
+    uint32_t mask = 0;
+#pragma unroll
+    for (int g = 0; g < DigGroups<NP>::G; ++g) {
+        uint32_t any = 0;
+#pragma unroll
+        for (int i = DigGroups<NP>::start(g); i < DigGroups<NP>::start(g + 1); ++i) any |= pl[i][0] | pl[i][1] | pl[i][2] | pl[i][3];
+        if (__ballot(any != 0) != 0) mask |= 1u << g;
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) out[i * 64] = make_uint4(pl[i][0], pl[i][1], pl[i][2], pl[i][3]);
+    if (lane == 0) job.mask[(int64_t)kb * job.RB + rb] = (uint8_t)mask;
+}
+
+// Both operands in one launch: the first blocks0 workgroups take job0, the rest job1.  planes: where the planes of A start;
+// those of B follow at the place the decided plane count gives.
+template <class F>
+__global__ __launch_bounds__(256) void dig_matrix_kernel(DigMatrixJob job0, DigMatrixJob job1, unsigned blocks0, const void* __restrict__ stats,
+                                                         DigInfo* __restrict__ info, uint8_t* __restrict__ planes, int KB, int narrow) {
+    typedef typename Storage<F::N>::T T;
+    typedef DigFormat<F> D;
+    __shared__ __attribute__((aligned(16))) T tile[32][DIG_ROWS];
+    __shared__ uint64_t tab[F::N == 8 ? 256 : 1];
+    const bool first = blockIdx.x < blocks0;
+    const DigMatrixJob& job = first ? job0 : job1;
+    const unsigned lin = first ? blockIdx.x : blockIdx.x - blocks0;
+    const unsigned gx = (unsigned)((job.RB + 3) / 4);
+    const int bx = (int)(lin % gx), kb = (int)(lin / gx);
+    const int t = threadIdx.x;
+    if (job.s_k != 1) {
+        constexpr int V = 16 / (int)sizeof(T), W = 16 / V;  // thread: 16 consecutive rows at one k, in W words of 16 bytes
+        const int kk = t >> 3, seg = (t & 7) * 16;
+        const int k = kb * 32 + kk;
+        const int row0 = bx * DIG_ROWS + seg;
+        const T* p = (const T*)job.src + (int64_t)k * job.s_k + row0;
+        T* dt = &tile[kk][seg];
+        if (k < job.K && row0 + 16 <= job.rows && (((uintptr_t)p) & 15u) == 0) {
+            uint4 v[W];
+#pragma unroll
+            for (int c = 0; c < W; ++c) v[c] = reinterpret_cast<const uint4*>(p)[c];
+#pragma unroll
+            for (int c = 0; c < W; ++c) reinterpret_cast<uint4*>(dt)[c] = v[c];
+        } else {
+            T v[16];
+#pragma unroll
+            for (int b = 0; b < 16; ++b) v[b] = (k < job.K && row0 + b < job.rows) ? p[b] : (T)0;
+#pragma unroll
+            for (int b = 0; b < 16; ++b) dt[b] = v[b];
+        }
+    }
+    const DigInfo d = dig_read_decision<F>(stats, info, narrow != 0, blockIdx.x == 0);
+    if (d.np == 0) return;
+    __syncthreads();
+    uint8_t* dst = first ? planes : planes + (int64_t)KB * job0.RB * d.np * 1024;
+    const int base = first ? d.base[0] : d.base[1];
+    if (D::NP1 != 0 && d.np == D::NP1) dig_matrix_planes<F, (D::NP1 ? D::NP1 : D::NP2)>(job, dst, base, kb, bx, tile, tab);
+    else dig_matrix_planes<F, D::NP2>(job, dst, base, kb, bx, tile, tab);
+}
+
+struct DigGemmArgs {
+    uint8_t* planes;              // A's planes, B's behind them
+    const uint8_t* ma;
+    const uint8_t* mb;
+    const DigInfo* info;
+    int RBA, RBB, KB;
+    int splits, kb_per_split;     // slices of the reduction (gridDim.y)
+    uint32_t* part;               // [slice][limb][M N], null without slices; flags behind them
+    uint32_t* rowflag;            // [slice][M]
+    uint32_t* colflag;            // [slice][N]
+    const void* bias;
+    void* C;
+    int64_t ldc;
+    FmtRT fin, fout;
+    int M, N, tiles_m, tiles_n;
+};
+
+template <int V>
+using dig_int = std::integral_constant<int, V>;
+
+// Rounds and stores rows first, first + STEP, ... of one column, four in flight.
+template <int L, class T, int STEP, class Value, class IsNar>
+__device__ __forceinline__ void dig_store_rows(int first, int rows, const DigRound& d, T* dst, int64_t ld, const Value& value, const IsNar& is_nar) {
+    const int qfrac = d.qfrac();
+#pragma unroll 1
+    for (int lr0 = first; lr0 < rows; lr0 += 4 * STEP) {
+        uint32_t res[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int lr = lr0 + u * STEP < 64 ? lr0 + u * STEP : 63;
+            uint32_t q[L];
+            value(lr, q);
+            const uint32_t v = dig_round_limbs<L, sizeof(T) == 4>(q, qfrac, d.fout);
+            res[u] = is_nar(lr) ? d.fout.nar() : v;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (lr0 + u * STEP < rows) dst[(int64_t)(lr0 + u * STEP) * ld] = (T)res[u];
+    }
+}
+
+// 64 x 64 outputs per workgroup: KG groups of four waves (2 x 2), a wave owns one block of 32 x 32 and its 2 NP - 1 sums
+// over the k blocks of its group (every KG-th).  The runs of a k block go straight into LDS, a ring of S blocks with copies
+// S - 1 blocks ahead.  The waves of a workgroup leave each barrier together and would all wait for their LDS reads
+// together, so the operand registers of a step are read during the step before (two sets).  What a step costs beside its
+// matrix instructions is scalar code, hence the straight-line loop over a fixed set of planes (DigGroups).  Registers decide
+// how many waves a SIMD holds: 5 sums three, 7 sums two, more one.
+template <int NP, int KG, int S>
+__global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig_gemm_kernel(DigGemmArgs g) {
+    typedef DigGroups<NP> D;
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
+    constexpr int RPB = 4 * NP;  // runs of 1 KB per k block: two row blocks and two column blocks of NP planes
+    constexpr int MAXKB = DIG_MAXK / 32 + 1;
+    if (__builtin_amdgcn_readfirstlane(g.info->np) != NP) return;
+    // One LDS object: beside a second one the compiler tells the objects apart and puts a wait for EVERY outstanding copy in
+    // front of each read of the ring (1024^3 posit<16,1>: 1.2 us a step).
+    constexpr int RING = KG * S * RPB * 64, MASKW = (4 * MAXKB + 15) / 16;  // words of 16 bytes
+    constexpr int LISTW = (2 * MAXKB + 15) / 16;
+    __shared__ uint4 lds[RING + MASKW + KG * 32 + 1 + LISTW];
+    uint4* const stage = lds;                                          // [KG * S][RPB * 64]
+    uint8_t* const masks = reinterpret_cast<uint8_t*>(lds + RING);     // [4][MAXKB]: the tile's row blocks 0, 1 and column blocks 0, 1 over the slice
+    uint32_t* const rowv = reinterpret_cast<uint32_t*>(lds + RING + MASKW);  // [KG][64]
+    uint32_t* const colv = rowv + KG * 64;
+    uint32_t* const present = colv + KG * 64;                          // k blocks that hold anything in groups 0 and 1; entries of the list
+    uint16_t* const list = reinterpret_cast<uint16_t*>(present + 4);   // k blocks that hold anything below the main loop's planes
+    static_assert(KG * L * 64 * 64 * 4 <= RING * 16, "the outputs' integers pass through the ring");
+
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int w = wave & 3, kg = wave >> 2;
+    const int wy = w >> 1, wx = w & 1;
+    // XCD-aware order, as in gemm_p8_mfma.h: each XCD a contiguous run of tiles, walked in bands of 8 tile-rows
+    const int nblk = g.tiles_m * g.tiles_n;
+    int lid = blockIdx.x;
+    if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+    const int band = lid / (8 * g.tiles_n);
+    const int band_rows = (g.tiles_m - band * 8) < 8 ? (g.tiles_m - band * 8) : 8;
+    const int in_band = lid - band * 8 * g.tiles_n;
+    const int tm = band * 8 + in_band % band_rows, tn = in_band / band_rows;
+    const int z = blockIdx.y;
+    const int kb0 = z * g.kb_per_split;
+    const int nkb = (kb0 + g.kb_per_split < g.KB ? kb0 + g.kb_per_split : g.KB) - kb0;
+    const int nst = (nkb + KG - 1) / KG;  // steps of the workgroup; group kg multiplies k blocks kb0 + step * KG + kg
+
+    // wave w of a group copies block w of the k block's four (A: row block 0, 1; B: column block 0, 1)
+    const int64_t rbx = (w < 2) ? g.RBA : g.RBB;
+    const int blk = (w < 2) ? tm * 2 + w : tn * 2 + (w - 2);
+    const uint4* const src0 = reinterpret_cast<const uint4*>(g.planes) + ((w < 2) ? 0 : (int64_t)g.KB * g.RBA * NP * 64) + (kb0 * rbx + blk) * (NP * 64) + lane;
+    const int64_t adv = rbx * (KG * NP * 64);
+    const uint4* src = src0 + kg * rbx * (NP * 64);
+    auto copy = [&](auto sp, const uint4* from, uint4* to) {
+#pragma unroll
+        for (int c = sp; c < NP; ++c)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(from + c * 64),
+                                             (__attribute__((address_space(3))) void*)(to + c * 64), 16, 0, 0);
+    };
+    uint4* const ring = stage + kg * S * (RPB * 64) + w * NP * 64;  // where this wave's block of buffer 0 goes
+    // The first S - 1 blocks are copied whole while the masks come in.
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) {
+        if (s * KG + kg < nkb) copy(dig_int<0>(), src, ring + s * (RPB * 64));
+        src += adv;
+    }
+    if (t < 3) present[t] = 0;
+    const int a_nar = __builtin_amdgcn_readfirstlane(g.info->nar[0]), b_nar = __builtin_amdgcn_readfirstlane(g.info->nar[1]);
+    const int at = __builtin_amdgcn_readfirstlane(g.info->base[0] + g.info->base[1]);
+    __syncthreads();
+    for (int k = t; k < nkb; k += 256 * KG) {
+        uint32_t any = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t m = b < 2 ? g.ma[(int64_t)(kb0 + k) * g.RBA + tm * 2 + b] : g.mb[(int64_t)(kb0 + k) * g.RBB + tn * 2 + (b - 2)];
+            masks[b * MAXKB + k] = (uint8_t)m;
+            any |= m;
+        }
+        if (any & 1u) atomicAdd(&present[0], 1u);
+        if (any & 2u) atomicAdd(&present[1], 1u);
+    }
+    __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));  // block 0 is read behind the barrier, ahead of the first step
+    __syncthreads();
+    // The straight-line loop starts at the first group that more than a quarter of the k blocks use: below that the second
+    // look at those blocks is cheaper than multiplying the group everywhere.
+    const uint32_t p0 = __builtin_amdgcn_readfirstlane(present[0]), p1 = __builtin_amdgcn_readfirstlane(present[1]);
+    const int g0 = 4 * p0 > (uint32_t)nkb ? 0 : 4 * p1 > (uint32_t)nkb ? 1 : 2;
+    const uint32_t below = (1u << g0) - 1u;
+    for (int k = t; k < nkb; k += 256 * KG)
+        if ((masks[k] | masks[MAXKB + k] | masks[2 * MAXKB + k] | masks[3 * MAXKB + k]) & below) list[atomicAdd(&present[2], 1u)] = (uint16_t)k;
+
+    pm_v16i acc[NC];
+#pragma unroll
+    for (int s = 0; s < NC; ++s)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[s][r] = 0;
+    uint32_t row_nar = 0, col_nar = 0;
+    const uint4* const sa0 = stage + kg * S * (RPB * 64) + wy * NP * 64 + lane;
+    const uint4* const sb0 = stage + kg * S * (RPB * 64) + (2 + wx) * NP * 64 + lane;
+    DigFrag<NP> f0, f1;
+    auto loop = [&](auto sp) {
+        constexpr int SP = sp;
+        // One step: block st is in cur.  Before the barrier this wave's copies of block st + 1 have landed; behind it
+        // everyone's have, and everyone's reads of block st - 1 (issued in step st - 2) have been consumed, so its buffer
+        // takes a copy.  Copies complete in order; near the end fewer are in flight, so all are waited for.
+        auto step = [&](int st, const DigFrag<NP>& cur, DigFrag<NP>& next) {
+            const int kb = st * KG + kg, kn = kb + (S - 1) * KG;
+            if (st > 0 && kb + (S - 2) * KG < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((S - 3) * (NP - SP)));
+            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+            pcm_ring_barrier();
+            if (kn < nkb) {
+                copy(sp, src, ring + ((st + S - 1) % S) * (RPB * 64));
+                src += adv;
+            }
+            const int nb = ((st + 1) % S) * (RPB * 64);
+            next.template load<SP>(sa0 + nb, sb0 + nb);  // beyond the last block: whatever the buffer holds, not used
+            if (kb < nkb) {
+                if (a_nar) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) row_nar |= pm_marker_bits((uint32_t)cur.a[NP - 1][i]);
+                }
+                if (b_nar) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) col_nar |= pm_marker_bits((uint32_t)cur.b[NP - 1][i]);
+                }
+                dig_mma<NP, SP, NP, SP, NP>(cur, acc);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        f0.template load<SP>(sa0, sb0);
+        for (int st = 0; st < nst; st += 2) {
+            step(st, f0, f1);
+            if (st + 1 < nst) step(st + 1, f1, f0);
+        }
+    };
+    if (g0 == 0) loop(dig_int<0>());
+    else if (g0 == 1) loop(dig_int<D::start(1)>());
+    else loop(dig_int<D::start(2)>());
+    __syncthreads();
+    // The k blocks with anything below: the first group's waves copy and multiply them once more, the pairs left out only;
+    // S at a time, so that their copies' latencies overlap.
+    const int extra = __builtin_amdgcn_readfirstlane((int)present[2]);
+    for (int e0 = 0; e0 < extra; e0 += S) {
+        const int ne = extra - e0 < S ? extra - e0 : S;
+        if (kg == 0)
+            for (int e = 0; e < ne; ++e) copy(dig_int<0>(), src0 + __builtin_amdgcn_readfirstlane((int)list[e0 + e]) * rbx * (NP * 64), ring + e * (RPB * 64));
+        __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll 1
+            for (int e = 0; e < ne; ++e) {
+                const int k = list[e0 + e];
+                f0.template load<0>(sa0 + e * (RPB * 64), sb0 + e * (RPB * 64));
+                dig_mma_below<NP, 0, 0>(g0, __builtin_amdgcn_readfirstlane((uint32_t)masks[wy * MAXKB + k]),
+                                        __builtin_amdgcn_readfirstlane((uint32_t)masks[(2 + wx) * MAXKB + k]), f0, acc);
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- NaR flags, and the sums as one integer per output, to LDS; then rounded and stored (or left for the merge) along
+    // the rows: the matrix instruction leaves a lane with 16 rows of one column, and one copy of the rounding code in a loop
+    // costs fewer instruction fetches than sixteen ----
+    uint32_t* vals = reinterpret_cast<uint32_t*>(stage) + kg * (L * 4096);
+    row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
+    col_nar = (col_nar | (uint32_t)__shfl_xor((int)col_nar, 32)) & 0x80808080u;
+    if (lane < 32) {
+        if (wx == 0) rowv[kg * 64 + wy * 32 + lane] = row_nar;  // the two waves of a row block saw the same rows
+        if (wy == 0) colv[kg * 64 + wx * 32 + lane] = col_nar;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int lr = wy * 32 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+        uint32_t q[L];
+        dig_combine<NP>(acc, r, q);
+#pragma unroll
+        for (int l = 0; l < L; ++l) vals[l * 4096 + lr * 64 + wx * 32 + (lane & 31)] = q[l];
+    }
+    __syncthreads();
+    const uint32_t* const all = reinterpret_cast<const uint32_t*>(stage);
+    const bool sliced = gridDim.y > 1;
+    const int n = tn * 64 + lane;
+    uint32_t cnar = colv[lane];
+    if (KG == 2) cnar |= colv[(KG - 1) * 64 + lane];
+    if (sliced) {
+        // the first tile column stores the row flags of its tile row, the first tile row the column flags: all of them
+        if (tn == 0 && t < 64 && tm * 64 + t < g.M) g.rowflag[(int64_t)z * g.M + tm * 64 + t] = rowv[t] | (KG == 2 ? rowv[(KG - 1) * 64 + t] : 0u);
+        if (tm == 0 && t < 64 && n < g.N) g.colflag[(int64_t)z * g.N + n] = cnar;
+    }
+    if (n >= g.N) return;
+    DigRound rd;
+    rd.fin = g.fin;
+    rd.fout = g.fout;
+    rd.at = at;
+    auto value = [&](int lr, uint32_t (&q)[L]) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) q[l] = all[l * 4096 + lr * 64 + lane];
+        if (KG == 2) {
+            uint32_t o[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) o[l] = all[(KG - 1) * (L * 4096) + l * 4096 + lr * 64 + lane];
+            quire_merge<L>(q, o);
+        }
+    };
+    auto is_nar = [&](int lr) { return (cnar | rowv[lr] | (KG == 2 ? rowv[(KG - 1) * 64 + lr] : 0u)) != 0; };
+    const int rows = g.M - tm * 64 < 64 ? g.M - tm * 64 : 64;
+    if (sliced) {
+        const int64_t MN = (int64_t)g.M * g.N;
+#pragma unroll 2
+        for (int lr = wave; lr < rows; lr += 4 * KG) {
+            uint32_t q[L];
+            value(lr, q);
+#pragma unroll
+            for (int l = 0; l < L; ++l) g.part[((int64_t)z * L + l) * MN + (int64_t)(tm * 64 + lr) * g.N + n] = q[l];
+        }
+    } else if (g.bias) {
+        const uint32_t bp = dig_load_pattern(g.bias, n, rd.fin.n);
+#pragma unroll 1
+        for (int lr = wave; lr < rows; lr += 4 * KG) {
+            uint32_t q[L];
+            value(lr, q);
+            dig_store_pattern(g.C, (int64_t)(tm * 64 + lr) * g.ldc + n, rd.fout.n, dig_round<L>(q, rd, is_nar(lr), true, bp));
+        }
+    } else if (rd.fout.n <= 8) {
+        dig_store_rows<L, uint8_t, 4 * KG>(wave, rows, rd, (uint8_t*)g.C + (int64_t)tm * 64 * g.ldc + n, g.ldc, value, is_nar);
+    } else if (rd.fout.n <= 16) {
+        dig_store_rows<L, uint16_t, 4 * KG>(wave, rows, rd, (uint16_t*)g.C + (int64_t)tm * 64 * g.ldc + n, g.ldc, value, is_nar);
+    } else {
+        dig_store_rows<L, uint32_t, 4 * KG>(wave, rows, rd, (uint32_t*)g.C + (int64_t)tm * 64 * g.ldc + n, g.ldc, value, is_nar);
+    }
+}
+
+// Adds the slices of every output, adds the bias, rounds once.  One output per thread; the slices' limbs are read along
+// the outputs.
+template <int NP>
+__global__ __launch_bounds__(256) void dig_merge_kernel(DigGemmArgs g) {
+    constexpr int L = dig_limbs<NP>();
+    if (__builtin_amdgcn_readfirstlane(g.info->np) != NP) return;
+    const int64_t MN = (int64_t)g.M * g.N;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= MN) return;
+    const int m = (int)(i / g.N), n = (int)(i - (int64_t)m * g.N);
+    uint32_t q[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) q[l] = 0;
+    uint32_t nar = 0;
+    for (int z = 0; z < g.splits; ++z) {
+        uint32_t o[L];
+#pragma unroll
+        for (int l = 0; l < L; ++l) o[l] = g.part[((int64_t)z * L + l) * MN + i];
+        quire_merge<L>(q, o);
+        nar |= g.rowflag[(int64_t)z * g.M + m] | g.colflag[(int64_t)z * g.N + n];
+    }
+    DigRound rd;
+    rd.fin = g.fin;
+    rd.fout = g.fout;
+    rd.at = g.info->base[0] + g.info->base[1];
+    const uint32_t bp = g.bias ? dig_load_pattern(g.bias, n, rd.fin.n) : 0u;
+    dig_store_pattern(g.C, (int64_t)m * g.ldc + n, rd.fout.n, dig_round<L>(q, rd, nar != 0, g.bias != nullptr, bp));
+}
+
+// ---- host side ----
+
+struct DigPlan {
+    int RBA, RBB, KB;
+    bool narrow;               // there is a kernel of NP1 planes in the call
+    int splits, kb_per_split;  // of the kernel that cuts the reduction (NPS planes)
+    int kg;                    // groups of waves per workgroup in that kernel
+    size_t planes_bytes, ma_bytes, mb_bytes, stat_off, part_off, total;
+};
+
+// posit(8,1): three planes (22 bits) hold what its Gaussian tensors use, and five sums leave room for a third wave per SIMD;
+// below this size the second product kernel's launch costs more than that saves.
+constexpr int64_t DIG_P8_1_NARROW = (int64_t)1 << 31;
+
+// The kernel that may cut the reduction: that of four planes, or the only one.
+template <class F>
+constexpr int dig_nps() { return DigFormat<F>::NP1 == 4 ? 4 : DigFormat<F>::NP2; }
+
+// Room for 8 planes of both operands (posit(8,1): 4), the masks, 256 bytes for the decision, and what is not found inside
+// on top: the scan's results take a slot that no kernel of posit(8,2) uses (posit(8,1): the rest of the 256 bytes), the partial sums of a cut reduction the slots
+// that the narrow kernel leaves free if they fit there (posit(8,2): only then).
+template <class F>
+inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K) {
+    typedef DigFormat<F> D;
+    constexpr int slots = F::N == 8 && !D::BASE0 ? D::NP2 : 8, NPS = dig_nps<F>();
+    static_assert(sizeof(DigInfo) <= 32 && 32 + 2 * DIG_STAT_WGS8 * 4 <= 256, "decision and packed scan results");
+    DigPlan p;
+    const int64_t tm = (M + 63) / 64, tn = (N + 63) / 64, tiles = tm * tn;
+    p.RBA = (int)tm * 2;
+    p.RBB = (int)tn * 2;
+    p.KB = (int)((K + 31) / 32);
+    const size_t blocks = (size_t)p.KB * (p.RBA + p.RBB);
+    p.planes_bytes = blocks * slots * 1024;
+    p.ma_bytes = ((size_t)p.KB * p.RBA + 255) / 256 * 256;
+    p.mb_bytes = ((size_t)p.KB * p.RBB + 255) / 256 * 256;
+    p.total = p.planes_bytes + p.ma_bytes + p.mb_bytes + 256;
+    p.stat_off = 0;
+    if (dig_stat_packed<F>()) {
+        p.stat_off = p.total - 256 + 32;
+    } else if (F::N == 8) {
+        p.stat_off = p.planes_bytes - DIG_STAT_BYTES;
+    } else {
+        p.stat_off = p.total;
+        p.total += DIG_STAT_BYTES;
+    }
+    // Few tiles and a long reduction: slices, so that about 256 workgroups (one per compute unit) share it; each keeps at
+    // least 16 k blocks, below which the merging launch costs more than it saves.
+    p.narrow = D::NP1 != 0 && (D::NP1 == 4 || M * N * K >= DIG_P8_1_NARROW);
+    p.splits = 1;
+    p.kb_per_split = p.KB;
+    p.part_off = blocks * NPS * 1024;
+    const size_t per = ((size_t)M * N * dig_limbs<NPS>() + M + N) * 4;
+    int64_t s = 256 / tiles;
+    if (s > p.KB / 16) s = p.KB / 16;
+    if (s > 16) s = 16;
+    if (F::N == 8 && s > (int64_t)((p.planes_bytes - p.part_off) / per)) s = (int64_t)((p.planes_bytes - p.part_off) / per);
+    if (s > 1) {
+        p.kb_per_split = (int)((p.KB + s - 1) / s);
+        p.splits = (p.KB + p.kb_per_split - 1) / p.kb_per_split;
+        if (p.splits * per > p.planes_bytes - p.part_off) {
+            p.part_off = p.total;
+            p.total += p.splits * per;
+        }
+    }
+    p.kg = NPS == 4 && tiles * p.splits <= 256 ? 2 : 1;
+    return p;
+}
+
+template <int NP, int KG, int S>
+inline hipError_t launch_dig_product(hipStream_t stream, const DigGemmArgs& g, int splits) {
+    hipLaunchKernelGGL((dig_gemm_kernel<NP, KG, S>), dim3((unsigned)(g.tiles_m * g.tiles_n), (unsigned)splits), dim3(256 * KG), 0, stream, g);
+    return hipGetLastError();
+}
+
+// One group of waves, a ring of four blocks (64 KB and two workgroups per compute unit for four planes).
+template <int NP>
+inline hipError_t launch_dig_whole(hipStream_t stream, const DigGemmArgs& g) {
+    return launch_dig_product<NP, 1, 4>(stream, g, g.splits);
+}
+
+template <class F>
+inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, const void* A, int64_t lda, const void* B, int64_t ldb,
+                                  const void* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace,
+                                  const DigInfo** decision) {
+    typedef DigFormat<F> D;
+    constexpr int NPS = dig_nps<F>();
+    const DigPlan p = dig_plan<F>(M, N, K);
+    uint8_t* base = (uint8_t*)workspace;
+    uint8_t* ma = base + p.planes_bytes;
+    uint8_t* mb = ma + p.ma_bytes;
+    DigInfo* info = (DigInfo*)(mb + p.mb_bytes);
+    void* stats = base + p.stat_off;
+    *decision = info;
+    const DigStatJob sa{A, transA ? K : M, transA ? M : K, lda}, sb{B, transB ? N : K, transB ? K : N, ldb};
+    hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sa, sb, stats);
+    PNN_CHECK_LAUNCH();
+    // op(A)[m,k] is A[m * lda + k] unless transA; op(B)[k,n] is B[k * ldb + n] unless transB
+    const DigMatrixJob ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, ma, p.RBA};
+    const DigMatrixJob jb{B, transB ? ldb : (int64_t)1, transB ? (int64_t)1 : ldb, (int)N, (int)K, mb, p.RBB};
+    const unsigned blocks0 = (unsigned)((p.RBA + 3) / 4) * (unsigned)p.KB, blocks1 = (unsigned)((p.RBB + 3) / 4) * (unsigned)p.KB;
+    hipLaunchKernelGGL(dig_matrix_kernel<F>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, stats, info, base, p.KB, p.narrow ? 1 : 0);
+    PNN_CHECK_LAUNCH();
+    DigGemmArgs g;
+    g.planes = base; g.ma = ma; g.mb = mb; g.info = info;
+    g.RBA = p.RBA; g.RBB = p.RBB; g.KB = p.KB;
+    g.bias = bias; g.C = C; g.ldc = ldc;
+    g.fin = fmt_of_code(code_of<F>()); g.fout = fmt_of_code(fout); g.M = (int)M; g.N = (int)N;
+    g.tiles_m = p.RBA / 2;
+    g.tiles_n = p.RBB / 2;
+    g.splits = p.splits;
+    g.kb_per_split = p.kb_per_split;
+    g.part = g.rowflag = g.colflag = nullptr;
+    if (p.splits > 1) {
+        g.part = (uint32_t*)(base + p.part_off);
+        g.rowflag = g.part + (size_t)p.splits * dig_limbs<NPS>() * M * N;
+        g.colflag = g.rowflag + (size_t)p.splits * M;
+    }
+    hipError_t e;
+    if constexpr (D::NP1 == 3) {
+        if (p.narrow) {
+            e = launch_dig_whole<D::NP1>(stream, g);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if constexpr (NPS == 4) e = p.kg == 2 ? launch_dig_product<4, 2, 4>(stream, g, p.splits) : launch_dig_whole<4>(stream, g);
+    else e = launch_dig_whole<NPS>(stream, g);
+    if (e != hipSuccess) return e;
+    if (p.splits > 1) {
+        hipLaunchKernelGGL(dig_merge_kernel<NPS>, dim3((unsigned)((M * N + 255) / 256)), dim3(256), 0, stream, g);
+        PNN_CHECK_LAUNCH();
+    }
+    if constexpr (D::NP1 == 4) {
+        g.splits = 1;
+        g.kb_per_split = p.KB;
+        e = launch_dig_whole<D::NP2>(stream, g);
+    }
+    return e;
+}
+
+}  // namespace pnn

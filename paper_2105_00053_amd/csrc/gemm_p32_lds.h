@@ -25,7 +25,9 @@ constexpr int P32L_LIMBS = 18;    // 16 limbs of the quire + 2 that catch the wo
 
 template <class OpA, class OpB>
 __global__ __launch_bounds__(256) void p32_lds_gemm_kernel(OpA opa, OpB opb, int64_t M, int64_t N, int64_t K, const uint32_t* __restrict__ bias,
-                                                           void* __restrict__ C, int64_t ldc, int fout, int tiles_n) {
+                                                           void* __restrict__ C, int64_t ldc, int fout, int tiles_n,
+                                                           const int* __restrict__ served) {
+    if (served && __builtin_amdgcn_readfirstlane(*served) != 0) return;  // an earlier launch of the call did the work
     typedef Arith<P32> AR;
     typedef AR::Elem Elem;
     constexpr int T = P32L_T, KT = P32L_KT;
@@ -116,10 +118,10 @@ inline bool p32_lds_fits(int64_t M, int64_t N, int64_t K) {
 
 template <class OpA, class OpB>
 hipError_t launch_p32_lds_gemm(hipStream_t st, const OpA& a, const OpB& b, int64_t M, int64_t N, int64_t K, const void* bias, void* C, int64_t ldc,
-                               int fout) {
+                               int fout, const int* served) {
     const int64_t tiles_m = (M + P32L_T - 1) / P32L_T, tiles_n = (N + P32L_T - 1) / P32L_T;
     hipLaunchKernelGGL((p32_lds_gemm_kernel<OpA, OpB>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, st, a, b, M, N, K,
-                       (const uint32_t*)bias, C, ldc, fout, (int)tiles_n);
+                       (const uint32_t*)bias, C, ldc, fout, (int)tiles_n, served);
     return hipGetLastError();
 }
 

@@ -45,6 +45,22 @@ constexpr int PM_NAR_HI = -128;  // high digit that marks NaR
 // [-32, 32]: top bits 00 or 11) only the NaR marker.  The other bits of the result are noise, masked when read.
 __device__ __forceinline__ uint32_t pm_marker_bits(uint32_t w) { return w & ~(w << 1); }
 
+// s_waitcnt immediate: at most n vector-memory operations outstanding, the other counters unconstrained
+constexpr int pcm_vmcnt(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }
+
+// The barrier of the ring: the bare instruction.  __syncthreads() puts a fence in front of it that waits for EVERY
+// outstanding copy of the wave, the ones running ahead included, which would shorten the ring to one block.  What the
+// ring needs holds without a fence: a wave's copies of the block it is about to read have landed (the counted wait in
+// front of the barrier), and every wave's LDS reads of the block about to be overwritten have returned (their data was
+// consumed by matrix instructions earlier in program order; nothing may be scheduled across the barrier).
+__device__ __forceinline__ void pcm_ring_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 struct P8DigitJob {
     const uint8_t* src;
     int64_t s_r, s_k;   // element (row, k) at src[row * s_r + k * s_k]; one of the two is 1

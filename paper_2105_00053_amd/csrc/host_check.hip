@@ -4,6 +4,8 @@
 #include "elementwise_fast.h"
 #include "quire_arith.h"
 #include "conv_p8.h"
+#include "api_common.h"
+#include "dig_planes.h"
 #include "p16_window_arith.h"
 #include "noquire_arith.h"
 #include "loss_ops.h"
@@ -178,6 +180,38 @@ int split_one(uint32_t a, uint32_t b, double* parts, int* cuts) {
 }
 
 }  // namespace
+
+template <class F, int NP>
+int host_digits_np(const DigInfo& d, int64_t n, const uint32_t* p, int8_t* digits, int* base) {
+    for (int64_t i = 0; i < n; ++i) {
+        const uint64_t w = dig_word<F, NP>(p[i], d.base[0]);
+        for (int k = 0; k < 8; ++k) digits[8 * i + k] = (int8_t)(w >> (8 * k));
+    }
+    *base = d.base[0];
+    return NP;
+}
+
+template <class F>
+int host_digits(uint32_t lo, uint32_t hi, int nar, int narrow, int64_t n, const uint32_t* p, int8_t* digits, int* base) {
+    typedef DigFormat<F> D;
+    if constexpr (F::N == 8 && F::ES == 0) return -1;
+    else {
+        const uint32_t low[2] = {lo, lo}, high[2] = {hi, hi}, flags[2] = {(uint32_t)nar, (uint32_t)nar};
+        const DigInfo d = dig_decide<F>(low, high, flags, narrow != 0);
+        if (d.np == 0) return 0;
+        if constexpr (D::NP1 != 0) {
+            if (d.np == D::NP1) return host_digits_np<F, D::NP1>(d, n, p, digits, base);
+        }
+        return host_digits_np<F, D::NP2>(d, n, p, digits, base);
+    }
+}
+
+template <int L>
+uint32_t host_round(const uint32_t* q, int qfrac, const FmtRT& f) {
+    uint32_t l[L];
+    for (int i = 0; i < L; ++i) l[i] = q[i];
+    return f.n <= 16 ? dig_round_limbs<L, false>(l, qfrac, f) : dig_round_limbs<L, true>(l, qfrac, f);
+}
 
 extern "C" {
 
@@ -455,4 +489,17 @@ int hostcheck_conv_gather(int which, const int64_t* geom, int operand_b, int64_t
     return ((uint32_t)(ry + ky) < (uint32_t)op.LY) && ((uint32_t)(rx + kx) < (uint32_t)op.LX);
 }
 
+// Digits of n patterns in the window that dig_decide chooses for operands whose magnitude patterns lie in lo .. hi:
+// digits[8 i + d] = digit d of pattern i.  Returns the plane count (0: none fits), *base the weight of digit 0.
+int hostcheck_digits(int fmt, uint32_t lo, uint32_t hi, int nar, int narrow, int64_t n, const uint32_t* p, int8_t* digits, int* base) {
+    PNN_DISPATCH_POSIT(fmt, return host_digits<F>(lo, hi, nar, narrow, n, p, digits, base))
+    return -1;
+}
+
+// The digit kernels' rounding of n integers of `limbs` (3, 4, 5) 32-bit limbs in units of 2^-qfrac.
+void hostcheck_round_limbs(int limbs, int qfrac, int fout, int64_t n, const uint32_t* q, uint32_t* out) {
+    const FmtRT f = fmt_of_code(fout);
+    for (int64_t i = 0; i < n; ++i)
+        out[i] = limbs == 3 ? host_round<3>(q + 3 * i, qfrac, f) : limbs == 4 ? host_round<4>(q + 4 * i, qfrac, f) : host_round<5>(q + 5 * i, qfrac, f);
+}
 }  // extern "C"

@@ -71,6 +71,11 @@ PNN_HD void fmt_params(int code, int& n, int& es) {
     }
 }
 
+template <class F>
+constexpr int code_of() {
+    return F::N == 32 ? 2 : F::N == 16 ? 1 : F::N == 8 ? (F::ES == 0 ? 0 : 2 + F::ES) : F::N == 10 ? 4 + F::ES : 6 + F::ES;
+}
+
 // A format known only at run time (elementwise kernels on the non-standard formats,
 // output format of the GEMM epilogues).
 struct FmtRT {

@@ -1,0 +1,82 @@
+"""The digit decomposition behind the matrix-core products of the formats other than posit<8,0> (dig_planes.h), compiled
+for the host: the window chosen for a range of magnitudes holds every pattern of that range exactly, and the rounding of
+the combined sums is the oracle's."""
+import ctypes
+from fractions import Fraction
+
+import numpy as np
+import pytest
+
+from oracle import posit_oracle as po
+
+from test_host_logic import BITS, CODE, _p, hc  # noqa: F401
+
+FORMATS = ["p8_1", "p8_2", "p10_1", "p12_1", "p16", "p32"]
+
+
+def _lib(L):
+    vp, i64, ci, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32
+    L.hostcheck_digits.argtypes = [ci, u32, u32, ci, ci, i64, vp, vp, vp]
+    L.hostcheck_round_limbs.argtypes = [ci, ci, ci, i64, vp, vp]
+    return L
+
+
+@pytest.mark.parametrize("nar", [0, 1])
+@pytest.mark.parametrize("narrow", [0, 1])
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_window_holds_every_pattern_of_its_range(hc, fmt, narrow, nar):  # noqa: F811
+    L = _lib(hc)
+    top = (1 << (BITS[fmt] - 1)) - 1
+    f = po.FORMATS[fmt]
+    maxs = (f.n - 2) << f.es
+    rng = np.random.default_rng(len(fmt) + 2 * narrow + nar)
+    plane_counts = set()
+    for trial in range(60):
+        lo = int(rng.integers(1, top + 1)) if trial else 1
+        hi = int(rng.integers(lo, top + 1)) if trial % 3 else min(top, lo + int(rng.integers(0, max(2, top // 3))))
+        if trial == 0:
+            hi = top
+        mags = sorted({lo, hi} | {int(v) for v in rng.integers(lo, hi + 1, size=30)})
+        pats = np.array([m for m in mags] + [(1 << BITS[fmt]) - m for m in mags] + [0], dtype=np.uint32)
+        digits = np.zeros((len(pats), 8), dtype=np.int8)
+        base = ctypes.c_int(0)
+        np_ = L.hostcheck_digits(CODE[fmt], lo, hi, nar, narrow, len(pats), _p(pats), _p(digits), ctypes.byref(base))
+        plane_counts.add(np_)
+        if np_ == 0:  # nothing written
+            assert fmt == "p32"  # every other format fits as a whole
+            continue
+        assert (digits[:, np_:] == 0).all()
+        for p, d in zip(pats.tolist(), digits.tolist()):
+            value = Fraction(0) if p == 0 else po.decode(p, f) * Fraction(2) ** maxs
+            got = sum(Fraction(x) * 256 ** i for i, x in enumerate(d)) * Fraction(2) ** base.value
+            assert got == value, (fmt, hex(p), d, base.value)
+            if nar:
+                assert -64 <= d[np_ - 1] <= 64  # -128 is the marker
+    assert len(plane_counts) >= (2 if fmt == "p32" or narrow else 1)
+    nar_pattern = np.array([1 << (BITS[fmt] - 1)], dtype=np.uint32)
+    digits = np.zeros((1, 8), dtype=np.int8)
+    np_ = L.hostcheck_digits(CODE[fmt], 1 << (BITS[fmt] - 2), 1 << (BITS[fmt] - 2), 1, narrow, 1, _p(nar_pattern), _p(digits), ctypes.byref(ctypes.c_int(0)))
+    assert digits[0, np_ - 1] == -128 and (np.delete(digits[0], np_ - 1) == 0).all()
+
+
+@pytest.mark.parametrize("limbs", [3, 4, 5])
+def test_rounding_of_the_sums(hc, limbs):  # noqa: F811
+    L = _lib(hc)
+    rng = np.random.default_rng(limbs)
+    formats = {0: po.P8, 1: po.P16, 2: po.P32, 4: po.P8_2, 7: po.P12_1}
+    for code, f in formats.items():
+        for qfrac in (0, 37, 56, 240):
+            vals = [0, 1, -1, 3, -5]
+            for _ in range(200):
+                b = int(rng.integers(1, 32 * limbs - 1))
+                v = int.from_bytes(rng.bytes(20), "little") & ((1 << b) - 1) | (1 << b - 1)
+                if rng.random() < 0.5:  # ties and their neighbours: few significant bits
+                    keep = int(rng.integers(1, 34))
+                    v = (v >> max(0, b - keep)) << max(0, b - keep)
+                    v += int(rng.integers(-1, 2))
+                vals.append(-v if rng.random() < 0.5 else v)
+            q = np.array([[(v >> (32 * l)) & 0xFFFFFFFF for l in range(limbs)] for v in vals], dtype=np.uint32)
+            got = np.zeros(len(vals), dtype=np.uint32)
+            L.hostcheck_round_limbs(limbs, qfrac, code, len(vals), _p(q), _p(got))
+            for v, g in zip(vals, got.tolist()):
+                assert g == po.round_to_posit(Fraction(v) / Fraction(2) ** qfrac, f), (code, qfrac, v)
