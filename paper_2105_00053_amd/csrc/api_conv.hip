@@ -10,6 +10,7 @@
 #include "conv_p8_pre.h"
 #include "conv_p8_mfma.h"
 #include "conv_b8.h"
+#include "conv_dig_mfma.h"
 
 namespace pnn {
 
@@ -150,6 +151,15 @@ size_t conv_ws(int which, const ConvGeom& g) {
             b = b8_conv_plan<F>(p.M, p.N, p.K).ws_bytes;
         }
     }
+    if constexpr (dig_conv_format<F>()) {
+        if (which == 2) {
+            const DigConvBwPlan bp = dig_conv_bw_plan<F>(g, true);
+            if (bp.ok) b = bp.total();
+        } else {
+            const DigConvPlan dp = dig_conv_plan<F>(which, g);
+            if (dp.ok) b = dp.total();
+        }
+    }
     if (which == 2) {  // the bias gradient runs after the weight gradient and reuses the start of the workspace
         const size_t b2 = bias_grad_ws_bytes<F>(g.N, g.K, g.OH * g.OW);
         if (b2 > b) b = b2;
@@ -162,6 +172,13 @@ int conv_fwd(hipStream_t st, int fout, const ConvGeom& g, const void* x, const v
              void* ws, size_t ws_bytes) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(0, g);
+    if constexpr (dig_conv_format<F>()) {
+        const DigConvPlan dp = dig_conv_plan<F>(0, g);
+        if (dp.ok) {  // integer matrix cores
+            if (!ws || ws_bytes < dp.total()) return PNN_EWORKSPACE;
+            return hip_status(launch_dig_conv<F>(st, dp, x, w, bias, y, fout, ws));
+        }
+    }
     if ((F::N == 8 && F::ES == 0) && p8_conv_eligible(0, g)) {
         const P8ConvMfmaPlan mp = p8_conv_mfma_plan(0, g);
         if (mp.ok) {  // integer matrix cores
@@ -204,6 +221,13 @@ template <class F>
 int conv_bwd_data_product(hipStream_t st, int fout, const ConvGeom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(1, g);
+    if constexpr (dig_conv_format<F>()) {
+        const DigConvPlan dp = dig_conv_plan<F>(1, g);
+        if (dp.ok) {  // integer matrix cores
+            if (!ws || ws_bytes < dp.total()) return PNN_EWORKSPACE;
+            return hip_status(launch_dig_conv<F>(st, dp, dy, w, nullptr, dx, fout, ws));
+        }
+    }
     if ((F::N == 8 && F::ES == 0) && p8_conv_eligible(1, g)) {
         const P8ConvMfmaPlan mp = p8_conv_mfma_plan(1, g);
         if (mp.ok) {  // integer matrix cores
@@ -254,6 +278,13 @@ int conv_bwd_weight(hipStream_t st, int fout, const ConvGeom& g, const void* dy,
                     void* ws, size_t ws_bytes) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(2, g);
+    if constexpr (dig_conv_format<F>()) {
+        const DigConvBwPlan bp = dig_conv_bw_plan<F>(g, dbias != nullptr);
+        if (bp.ok) {  // integer matrix cores, split reduction; the bias gradient rides along as a column of ones
+            if (!ws || ws_bytes < bp.total()) return PNN_EWORKSPACE;
+            return hip_status(launch_dig_conv_bw<F>(st, bp, dy, x, dw, dbias, fout, ws));
+        }
+    }
     const bool fastp8 = (F::N == 8 && F::ES == 0) && p8_conv_eligible(2, g);
     const size_t bias_ws = bias_grad_ws_bytes<F>(g.N, g.K, g.OH * g.OW);
     GemmPlan plan = conv_plan<F>(d);

@@ -1,0 +1,984 @@
+// Convolution with the exact quire (paper Sec. 2, Sec. 3.1, Sec. 3.3) on the integer matrix cores for posit(8,1), posit(8,2),
+// posit(10,1), posit(12,1) and posit<16,1>: the implicit-GEMM form of conv_p8_mfma.h with the digit planes of dig_planes.h.
+//
+// Forward and backward-data: rows of the product are output channels, columns output positions (n, oh, ow), the reduction
+// runs tap-major, channel-minor, so that 16 consecutive reduction indices are 16 channels of ONE input pixel.  One launch
+// rewrites the gathered tensor as [pixel (n, h, w)][group of 16 channels][plane][16 bytes] and the weights in the row-block
+// layout of the matrix product; the product kernel gathers: every lane of a copy names its own 16 bytes (the pixel its
+// column reads for that tap, or a block of zeros), and the copy lands in LDS in lane order, which is the operand layout.
+// Backward-data takes the weights transposed and flipped, NaR as zero (the outputs a NaR weight reaches are marked by the
+// pass that follows, as for the other backward-data kernels).
+//
+// Backward-weight: rows are output channels, columns (c, r, s) and, for the bias gradient, one column of ones; the reduction
+// runs position-major, image-minor, so that 16 consecutive indices are 16 images at one pixel, and x is gathered likewise.
+// The reduction is cut into slices whose sums a merging launch adds and rounds.
+//
+// Which window of digits serves is decided on the device as for the matrix product: a kernel of four planes and one of
+// eight are launched, the one decided on does the work.
+#pragma once
+
+#include "gemm_dig_mfma.h"
+
+namespace pnn {
+
+// Formats these kernels serve, and the planes of their wide kernel.
+template <class F>
+constexpr bool dig_conv_format() { return F::N <= 16 && F::ES != 0 && DigFormat<F>::COVER; }
+template <class F>
+constexpr int dig_conv_wide() { return DigFormat<F>::NP2 <= 4 ? 4 : 8; }
+
+constexpr int DCM_MAXK16 = 512;  // most (tap, channel group) pairs, padding included
+
+struct DigConvPlan {
+    bool ok;
+    int which;                 // 0 forward, 1 backward-data
+    int NI, CI, HI, WI;        // the gathered tensor: x (forward) or dy (backward-data)
+    int HO, WO, MO;            // output extents per image and output channels
+    int R, S, offh, offw;      // tap (r, s) of output (oh, ow) reads input (oh sh + r - offh, ow sw + s - offw)
+    int sh, sw;
+    int WK, WC;                // the weight tensor is [WK][WC][R][S]
+    int Cg, K16, KB;           // channel groups of 16, reduction length in 16s, k blocks of 32
+    int WY, RBA;               // waves along the rows, padded row blocks of the weights
+    int64_t P;                 // output positions NI * HO * WO
+    size_t w_bytes, act_bytes;
+    // behind the planes: 256 bytes of zeros, 256 of decision, the scan's results
+    size_t total() const { return w_bytes + act_bytes + 512 + DIG_STAT_BYTES; }
+};
+
+template <class F>
+inline DigConvPlan dig_conv_plan(int which, const ConvGeom& g) {
+    DigConvPlan p;
+    p.ok = false;
+    p.which = which;
+    if (!dig_conv_format<F>() || which > 1 || (which == 1 && (g.sh != 1 || g.sw != 1))) return p;
+    p.NI = g.N; p.R = g.R; p.S = g.S; p.WK = g.K; p.WC = g.C; p.sh = g.sh; p.sw = g.sw;
+    if (which == 0) {
+        p.CI = g.C; p.HI = g.H; p.WI = g.W; p.HO = g.OH; p.WO = g.OW; p.MO = g.K; p.offh = g.ph; p.offw = g.pw;
+    } else {
+        p.CI = g.K; p.HI = g.OH; p.WI = g.OW; p.HO = g.H; p.WO = g.W; p.MO = g.C; p.offh = g.R - 1 - g.ph; p.offw = g.S - 1 - g.pw;
+    }
+    if (p.NI <= 0 || p.CI <= 0 || p.HI <= 0 || p.WI <= 0 || p.HO <= 0 || p.WO <= 0 || p.MO <= 0) return p;
+    constexpr int slots = dig_conv_wide<F>();
+    p.Cg = (p.CI + 15) / 16;
+    p.P = (int64_t)p.NI * p.HO * p.WO;
+    const int64_t pin = (int64_t)p.NI * p.HI * p.WI, k16 = (int64_t)g.R * g.S * p.Cg;
+    if (k16 + 1 > DCM_MAXK16 || p.HI > 16384 || p.WI > 16384 || p.HO > 16384 || p.WO > 16384 || g.R > 4096 || g.S > 4096) return p;
+    if (pin * p.Cg * slots >= ((int64_t)1 << 30) || p.P >= ((int64_t)1 << 30) || p.MO > 65536 || p.P * p.MO >= ((int64_t)1 << 40)) return p;
+    p.K16 = (int)k16;
+    p.KB = (p.K16 + 1) / 2;
+    // Four launches: below these sizes the byte-gather kernel of the 8-bit formats is faster forward (15 M products: 25 against
+    // 28 us; its backward-data takes 75), the generic kernel of the others is not (97 against 28 us).
+    const int64_t least = F::N == 8 && which == 0 ? (int64_t)1 << 25 : (int64_t)1 << 22;
+    if (p.P * p.MO * p.CI * g.R * g.S < least || p.P < 2048) return p;
+    p.WY = p.MO > 32 ? 2 : 1;
+    p.RBA = (int)((p.MO + 32 * p.WY - 1) / (32 * p.WY)) * p.WY;
+    p.w_bytes = (size_t)p.KB * p.RBA * slots * 1024;
+    p.act_bytes = (size_t)pin * p.Cg * slots * 16;
+    p.ok = true;
+    return p;
+}
+
+// The digit word of a pattern: through a table in LDS for the 8-bit formats.
+template <class F, int NP>
+struct DigLookup {
+    typedef typename DigWord<NP>::T W;
+    const uint64_t* tab;
+    int base;
+    __device__ __forceinline__ W operator()(uint32_t p) const {
+        if constexpr (F::N == 8) return (W)tab[p];
+        else return dig_word<F, NP>(p & F::MASK, base);
+    }
+};
+
+// 16 patterns a fixed step apart; beyond n: zeros.
+template <class T>
+__device__ __forceinline__ void dig_load16(const T* q, int64_t step, int n, uint32_t (&pat)[16]) {
+#pragma unroll
+    for (int b = 0; b < 16; ++b) pat[b] = b < n ? (uint32_t)q[b * step] : 0u;
+}
+
+template <class F, int NP, int PX>
+__device__ __forceinline__ void dig_conv_planes(const typename Storage<F::N>::T* __restrict__ src, int HW, int64_t pixels, uint4* __restrict__ act,
+                                                const typename Storage<F::N>::T* __restrict__ w, const DigConvPlan& p, uint4* __restrict__ wdst,
+                                                uint4* __restrict__ zero, unsigned wblocks, const DigInfo& d, uint64_t* tab) {
+    typedef typename Storage<F::N>::T T;
+    typedef typename DigWord<NP>::T W;
+    const int t = threadIdx.x;
+    const bool weights = blockIdx.x < wblocks;
+    const DigLookup<F, NP> word{tab, weights ? d.base[1] : d.base[0]};
+    if constexpr (F::N == 8) {
+        tab[t] = dig_word<F, NP>((uint32_t)t, word.base);
+        __syncthreads();
+    }
+    if (weights) {
+        const int64_t idx = (int64_t)blockIdx.x * 256 + t;
+        if (idx < 16) zero[idx] = make_uint4(0, 0, 0, 0);  // what the product kernel reads for padding (no memset: graph capture)
+        if (idx >= (int64_t)p.KB * p.RBA * 64) return;
+        const int lane = (int)(idx & 63);
+        const int rb = (int)((idx >> 6) % p.RBA), kb = (int)((idx >> 6) / p.RBA);
+        const int row = rb * 32 + (lane & 31), k16 = kb * 2 + (lane >> 5);
+        uint32_t pat[16];
+#pragma unroll
+        for (int b = 0; b < 16; ++b) pat[b] = 0;
+        if (row < p.MO && k16 < p.K16) {
+            const int tap = k16 / p.Cg, cg = k16 - tap * p.Cg;
+            const int r = tap / p.S, s = tap - r * p.S;
+            const int nch = p.CI - cg * 16 < 16 ? p.CI - cg * 16 : 16;
+            // forward: w[row][ch][r][s]; backward-data: w[ch][row][R-1-r][S-1-s]
+            const int64_t rs = (int64_t)p.R * p.S;
+            const T* q = p.which == 0 ? w + ((int64_t)row * p.WC + cg * 16) * rs + r * p.S + s
+                                      : w + ((int64_t)cg * 16 * p.WC + row) * rs + (p.R - 1 - r) * p.S + (p.S - 1 - s);
+            dig_load16<T>(q, p.which == 0 ? rs : rs * p.WC, nch, pat);
+        }
+        W wd[16];
+#pragma unroll
+        for (int b = 0; b < 16; ++b) wd[b] = p.which != 0 && (pat[b] & F::MASK) == F::NAR ? (W)0 : word(pat[b]);
+        uint32_t pl[NP][4];
+        dig_planes_of<NP>(wd, pl);
+        uint4* out = wdst + ((int64_t)(kb * p.RBA + rb) * NP) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) out[i * 64] = make_uint4(pl[i][0], pl[i][1], pl[i][2], pl[i][3]);
+        return;
+    }
+    const int64_t groups = pixels / PX;  // PX divides HW, hence pixels
+    const int64_t idx = (int64_t)(blockIdx.x - wblocks) * 256 + t;
+    if (idx >= groups * p.Cg) return;
+    const int cg = (int)(idx / groups);
+    const int64_t pix = (idx - (int64_t)cg * groups) * PX;
+    const int64_t img = pix / HW, hw = pix - img * HW;
+    const T* q = src + (img * p.CI + cg * 16) * (int64_t)HW + hw;
+    const int nch = p.CI - cg * 16 < 16 ? p.CI - cg * 16 : 16;
+    uint32_t in[16];  // PX patterns of one channel
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        if (b >= nch) in[b] = 0;
+        else if (PX > 1) in[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * HW);
+        else in[b] = q[(int64_t)b * HW];
+    }
+#pragma unroll
+    for (int px = 0; px < PX; ++px) {
+        W wd[16];
+#pragma unroll
+        for (int b = 0; b < 16; ++b) wd[b] = word((in[b] >> (8 * (int)sizeof(T) * px)) & (sizeof(T) == 1 ? 0xFFu : 0xFFFFu));
+        uint32_t pl[NP][4];
+        dig_planes_of<NP>(wd, pl);
+        uint4* out = act + ((pix + px) * p.Cg + cg) * NP;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) out[i] = make_uint4(pl[i][0], pl[i][1], pl[i][2], pl[i][3]);
+    }
+}
+
+// One launch rewrites both operands; the first wblocks workgroups take the weights (few threads, long chains of loads:
+// started first), the rest the gathered tensor, one thread per channel group and PX consecutive pixels (as many as a 32-bit
+// load holds, or one); consecutive threads take consecutive pixels.
+template <class F, int PX>
+__global__ __launch_bounds__(256) void dig_conv_digits_kernel(const typename Storage<F::N>::T* __restrict__ src, int HW, int64_t pixels, uint4* __restrict__ act,
+                                                              const typename Storage<F::N>::T* __restrict__ w, DigConvPlan p, uint4* __restrict__ wdst,
+                                                              uint4* __restrict__ zero, unsigned wblocks, const void* __restrict__ stats,
+                                                              DigInfo* __restrict__ info) {
+    typedef DigFormat<F> D;
+    __shared__ uint64_t tab[F::N == 8 ? 256 : 1];
+    const DigInfo d = dig_read_decision<F>(stats, info, D::NP1 == 4, blockIdx.x == 0);
+    if (D::NP1 == 4 && d.np == 4) dig_conv_planes<F, 4, PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab);
+    else dig_conv_planes<F, dig_conv_wide<F>(), PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab);
+}
+
+struct DigConvArgs {
+    const uint4* Ad;      // weight planes
+    const uint4* act;     // planes of the gathered tensor
+    const uint4* zero;    // 256 bytes of zeros
+    const DigInfo* info;
+    int np;               // the decision this kernel serves
+    int RBA, KB, K16, Cg;
+    int HI, WI, HO, WO, S, offh, offw, sh, sw, MO, P;
+    const void* bias;
+    void* out;
+    FmtRT fin, fout;
+    int tiles_m;
+};
+
+// 128-bit quire from the sums' integer (units of minpos^2 2^at), for adding a bias: at < 0 drops zero bits, at >= 0 stays
+// within 128 bits (see dig_add_bias).
+template <int L>
+__device__ __forceinline__ unsigned __int128 dig_to_quire(const uint32_t (&q)[L], int at) {
+    const uint32_t top = L >= 4 ? q[L >= 4 ? 3 : 0] : (uint32_t)((int32_t)q[L - 1] >> 31);
+    const unsigned __int128 x = ((unsigned __int128)(((uint64_t)top << 32) | q[2]) << 64) | (((uint64_t)q[1] << 32) | q[0]);
+    return at >= 0 ? x << at : (unsigned __int128)((__int128)x >> -at);
+}
+
+// Rounds and stores rows first, first + STEP, ... of one column, two in flight; bias: 128-bit addends by row, in LDS.
+template <int L, class T, int STEP, class Value, class IsNar>
+__device__ __forceinline__ void dig_store_rows_bias(int first, int rows, const DigRound& d, T* dst, int64_t ld, const uint4* bias, const Value& value,
+                                                    const IsNar& is_nar) {
+    const int qfrac = 2 * d.fin.maxs();
+#pragma unroll 1
+    for (int lr0 = first; lr0 < rows; lr0 += 2 * STEP) {
+        uint32_t res[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int lr = lr0 + u * STEP < rows ? lr0 + u * STEP : rows - 1;
+            uint32_t q[L];
+            value(lr, q);
+            const uint4 b = bias[lr];
+            const unsigned __int128 x = dig_to_quire<L>(q, d.at) + (((unsigned __int128)(((uint64_t)b.w << 32) | b.z) << 64) | (((uint64_t)b.y << 32) | b.x));
+            const uint32_t s[4] = {(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)(x >> 64), (uint32_t)(x >> 96)};
+            const uint32_t v = dig_round_limbs<4, sizeof(T) == 4>(s, qfrac, d.fout);
+            res[u] = is_nar(lr) ? d.fout.nar() : v;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (lr0 + u * STEP < rows) dst[(int64_t)(lr0 + u * STEP) * ld] = (T)res[u];
+    }
+}
+
+// Four waves as WY x (4 / WY), one block of 32 x 32 outputs each (rows: output channels, columns: positions).  WY = 1 (32 x
+// 128 outputs) serves layers of at most 32 output channels.  A ring of ST k blocks as in dig_gemm_kernel; operand registers
+// are read a step ahead.  A convolution's reduction is short, so prologue and rounding weigh as much as the matrix
+// instructions: all planes are multiplied.
+template <int NP, int WY, int ST>
+__global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigConvArgs a) {
+    if (__builtin_amdgcn_readfirstlane(a.info->np) != a.np) return;
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
+    constexpr int WX = 4 / WY, NB = WX;          // column blocks
+    constexpr int NA = WY;                        // row blocks
+    constexpr int RPB = (NA + NB) * NP;           // runs of 1 KB per k block
+    constexpr int TR = 32 * WY, TC = 32 * WX;
+    static_assert(NP % 4 == 0, "copies spread evenly over the waves");
+    constexpr int ARUNS = NA * NP / 4;            // weight runs copied by a wave
+    constexpr int GRUNS = NB * NP / 4;            // gathered runs: planes of one column block
+    constexpr int LOADS = ARUNS + GRUNS;
+    constexpr int RING = ST * RPB * 64, KTAB = DCM_MAXK16 / 2;  // words of 16 bytes
+    // one LDS object (see dig_gemm_kernel): ring, (tap, channel group) table, NaR flags, bias addends
+    __shared__ uint4 lds[RING + KTAB + (TR + TC) / 4 + TR];
+    uint4* const stage = lds;
+    int2* const ktab = reinterpret_cast<int2*>(lds + RING);
+    uint32_t* const rowv = reinterpret_cast<uint32_t*>(lds + RING + KTAB);
+    uint32_t* const colv = rowv + TR;
+    uint4* const badd = lds + RING + KTAB + (TR + TC) / 4;
+    static_assert(L * TR * TC * 4 <= RING * 16, "the outputs' integers pass through the ring");
+
+    const int t = threadIdx.x;
+    const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wy = WY == 2 ? w >> 1 : 0, wx = WY == 2 ? (w & 1) : w;
+    const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
+
+    for (int k = t; k < 2 * a.KB; k += 256) {
+        int2 e = make_int2(0, 0x7FFF);  // beyond the reduction: a row offset no pixel has
+        if (k < a.K16) {
+            const int tap = k / a.Cg, cg = k - tap * a.Cg;
+            const int r = tap / a.S, s = tap - r * a.S;
+            const int dh = r - a.offh, dw = s - a.offw;
+            e.x = ((dh * a.WI + dw) * a.Cg + cg) * NP;
+            e.y = (int)(((uint32_t)dh & 0xFFFFu) | ((uint32_t)dw << 16));
+        }
+        ktab[k] = e;
+    }
+
+    // weights: wave w copies ARUNS of the k block's NA NP runs, wave-uniform addresses
+    const uint4* asrc = a.Ad + ((int64_t)tm * NA * NP + w * ARUNS) * 64 + lane;
+    const int64_t a_kb = (int64_t)a.RBA * NP * 64;
+    // gathered tensor: wave w takes GRUNS planes of column block w / (4 / NB); lane l of a copy serves column l % 32 of the
+    // block and the 16 reduction indices of half l / 32
+    constexpr int WPB = 4 / NB;  // waves per column block
+    const int cb = w / WPB, pl0 = (w % WPB) * GRUNS;
+    const int hw_o = a.HO * a.WO;
+    int oh = -40000, ow = 0, base = 0;  // beyond the positions: no tap brings this into the tensor
+    {
+        const int pos = tn * TC + cb * 32 + (lane & 31);
+        if (pos < a.P) {
+            const int img = pos / hw_o, rem = pos - img * hw_o;
+            const int h = rem / a.WO;
+            oh = h * a.sh;
+            ow = (rem - h * a.WO) * a.sw;
+            base = ((img * a.HI + oh) * a.WI + ow) * a.Cg * NP;
+        }
+    }
+    const uint4* const actq = a.act + pl0;
+    const uint4* const zeroq = a.zero;
+    auto issue = [&](int kb) {
+        uint4* buf = stage + (kb % ST) * (RPB * 64);
+#pragma unroll
+        for (int c = 0; c < ARUNS; ++c)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64),
+                                             (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
+        asrc += a_kb;
+        const int2 e = ktab[kb * 2 + (lane >> 5)];
+        const int dh = (int)(short)(e.y & 0xFFFF), dw = e.y >> 16;
+        const int ih = oh + dh, iw = ow + dw;
+        const bool inside = (unsigned)ih < (unsigned)a.HI && (unsigned)iw < (unsigned)a.WI;
+        const uint4* s = inside ? actq + (base + e.x) : zeroq;
+#pragma unroll
+        for (int c = 0; c < GRUNS; ++c)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + c),
+                                             (__attribute__((address_space(3))) void*)(buf + (NA * NP + cb * NP + pl0 + c) * 64), 16, 0, 0);
+    };
+
+    const int a_nar = __builtin_amdgcn_readfirstlane(a.info->nar[1]), b_nar = __builtin_amdgcn_readfirstlane(a.info->nar[0]);
+    const int at = __builtin_amdgcn_readfirstlane(a.info->base[0] + a.info->base[1]);
+    __syncthreads();  // ktab
+#pragma unroll
+    for (int k = 0; k < ST - 1; ++k)
+        if (k < a.KB) issue(k);
+    // bias addends and row flags while the first blocks come in
+    if (t < TR) {
+        uint32_t nar = 0;
+        uint4 add = make_uint4(0, 0, 0, 0);
+        const int m = tm * TR + t;
+        if (a.bias && m < a.MO) {
+            const uint32_t bp = dig_load_pattern(a.bias, m, a.fin.n);
+            DigRound rd;
+            rd.fin = a.fin;
+            rd.at = 0;
+            const uint32_t none[3] = {0, 0, 0};
+            uint32_t u[4];
+            dig_add_bias<3>(none, rd, bp, u);
+            nar = bp == a.fin.nar() ? 1u : 0u;
+            add = make_uint4(u[0], u[1], u[2], u[3]);
+        }
+        rowv[t] = nar;
+        badd[t] = add;
+    }
+
+    pm_v16i acc[NC];
+#pragma unroll
+    for (int s = 0; s < NC; ++s)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[s][r] = 0;
+    uint32_t row_nar = 0, col_nar = 0;
+    const uint4* const sa0 = stage + wy * NP * 64 + lane;
+    const uint4* const sb0 = stage + (NA + wx) * NP * 64 + lane;
+    DigFrag<NP> f0, f1;
+    auto markers = [&](const DigFrag<NP>& f) {
+        if (a_nar) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) row_nar |= pm_marker_bits((uint32_t)f.a[NP - 1][i]);
+        }
+        if (b_nar) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) col_nar |= pm_marker_bits((uint32_t)f.b[NP - 1][i]);
+        }
+    };
+    __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+    __syncthreads();
+    if constexpr (NP <= 4) {
+        // one step: block kb is in cur; see dig_gemm_kernel for what the waits and the barrier stand for
+        auto step = [&](int kb, const DigFrag<NP>& cur, DigFrag<NP>& next) {
+            if (kb + ST - 2 < a.KB) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 3) * LOADS));
+            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+            pcm_ring_barrier();
+            if (kb + ST - 1 < a.KB) issue(kb + ST - 1);
+            const int nb = ((kb + 1) % ST) * (RPB * 64);
+            next.template load<0>(sa0 + nb, sb0 + nb);
+            markers(cur);
+            dig_mma<NP, 0, NP, 0, NP>(cur, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        f0.template load<0>(sa0, sb0);
+        for (int kb = 0; kb < a.KB; kb += 2) {
+            step(kb, f0, f1);
+            if (kb + 1 < a.KB) step(kb + 1, f1, f0);
+        }
+    } else {  // one set of operand registers, read in their own step
+        for (int kb = 0; kb < a.KB; ++kb) {
+            if (kb + ST - 2 < a.KB) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
+            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+            pcm_ring_barrier();
+            if (kb + ST - 1 < a.KB) issue(kb + ST - 1);
+            const int nb = (kb % ST) * (RPB * 64);
+            f0.template load<0>(sa0 + nb, sb0 + nb);
+            markers(f0);
+            dig_mma<NP, 0, NP, 0, NP>(f0, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();  // the last block is read: the ring is free
+
+    uint32_t* const vals = reinterpret_cast<uint32_t*>(stage);
+    row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
+    col_nar = (col_nar | (uint32_t)__shfl_xor((int)col_nar, 32)) & 0x80808080u;
+    if (lane < 32) {
+        if (wx == 0 && row_nar) rowv[wy * 32 + lane] = 1u;  // every wave of a row block saw the same rows
+        if (wy == 0) colv[wx * 32 + lane] = col_nar;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int lr = wy * 32 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+        uint32_t q[L];
+        dig_combine<NP>(acc, r, q);
+#pragma unroll
+        for (int l = 0; l < L; ++l) vals[l * (TR * TC) + lr * TC + wx * 32 + (lane & 31)] = q[l];
+    }
+    __syncthreads();
+    // a wave: 64 consecutive positions, every (4 / (TC / 64))-th row
+    constexpr int CH = TC / 64, STEP = 4 / CH;
+    const int col = (w % CH) * 64 + lane, first = w / CH;
+    const int n = tn * TC + col;
+    if (n >= a.P) return;
+    const int rows = a.MO - tm * TR < TR ? a.MO - tm * TR : TR;
+    const uint32_t cnar = colv[col];
+    const int img = n / hw_o, rem = n - img * hw_o;
+    const int64_t o = ((int64_t)img * a.MO + tm * TR) * hw_o + rem;
+    DigRound rd;
+    rd.fin = a.fin;
+    rd.fout = a.fout;
+    rd.at = at;
+    auto value = [&](int lr, uint32_t (&q)[L]) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) q[l] = vals[l * (TR * TC) + lr * TC + col];
+    };
+    auto is_nar = [&](int lr) { return (cnar | rowv[lr]) != 0; };
+    if (a.bias) {
+        if (rd.fout.n <= 8) dig_store_rows_bias<L, uint8_t, STEP>(first, rows, rd, (uint8_t*)a.out + o, hw_o, badd, value, is_nar);
+        else if (rd.fout.n <= 16) dig_store_rows_bias<L, uint16_t, STEP>(first, rows, rd, (uint16_t*)a.out + o, hw_o, badd, value, is_nar);
+        else dig_store_rows_bias<L, uint32_t, STEP>(first, rows, rd, (uint32_t*)a.out + o, hw_o, badd, value, is_nar);
+    } else {
+        if (rd.fout.n <= 8) dig_store_rows<L, uint8_t, STEP>(first, rows, rd, (uint8_t*)a.out + o, hw_o, value, is_nar);
+        else if (rd.fout.n <= 16) dig_store_rows<L, uint16_t, STEP>(first, rows, rd, (uint16_t*)a.out + o, hw_o, value, is_nar);
+        else dig_store_rows<L, uint32_t, STEP>(first, rows, rd, (uint32_t*)a.out + o, hw_o, value, is_nar);
+    }
+}
+
+template <int NP>
+inline hipError_t launch_dig_conv_product(hipStream_t stream, const DigConvArgs& a, int WY) {
+    const int tc = 32 * (4 / WY);
+    const dim3 grid((unsigned)(a.tiles_m * ((a.P + tc - 1) / tc)));
+    if (WY == 1) hipLaunchKernelGGL((dig_conv_kernel<NP, 1, 3>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((dig_conv_kernel<NP, 2, 4>), grid, dim3(256), 0, stream, a);
+    return hipGetLastError();
+}
+
+// in: x (forward) or dy (backward-data); workspace: [weight planes][planes of in][256 zeros][decision][scan]
+template <class F>
+inline hipError_t launch_dig_conv(hipStream_t stream, const DigConvPlan& p, const void* in, const void* w, const void* bias, void* out, int fout,
+                                  void* workspace) {
+    typedef typename Storage<F::N>::T T;
+    typedef DigFormat<F> D;
+    uint8_t* base = (uint8_t*)workspace;
+    uint4* Ad = (uint4*)base;
+    uint4* act = (uint4*)(base + p.w_bytes);
+    uint4* zero = (uint4*)(base + p.w_bytes + p.act_bytes);
+    DigInfo* info = (DigInfo*)(zero + 16);
+    void* stats = (void*)(zero + 32);
+    const int64_t pixels = (int64_t)p.NI * p.HI * p.WI;
+    const int HW = p.HI * p.WI;
+    const int64_t nx = pixels * p.CI, nw = (int64_t)p.WK * p.WC * p.R * p.S;
+    const DigStatJob sx{in, 1, nx, nx, 0}, sw{w, 1, nw, nw, 0};
+    hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sx, sw, stats);
+    PNN_CHECK_LAUNCH();
+    const unsigned wblocks = (unsigned)(((int64_t)p.KB * p.RBA * 64 + 255) / 256);
+    constexpr int PX = 4 / (int)sizeof(T);
+    if (HW % PX == 0 && ((uintptr_t)in & 3u) == 0) {
+        const unsigned ablocks = (unsigned)((pixels / PX * p.Cg + 255) / 256);
+        hipLaunchKernelGGL((dig_conv_digits_kernel<F, PX>), dim3(wblocks + ablocks), dim3(256), 0, stream, (const T*)in, HW, pixels, act, (const T*)w, p, Ad,
+                           zero, wblocks, stats, info);
+    } else {
+        const unsigned ablocks = (unsigned)((pixels * p.Cg + 255) / 256);
+        hipLaunchKernelGGL((dig_conv_digits_kernel<F, 1>), dim3(wblocks + ablocks), dim3(256), 0, stream, (const T*)in, HW, pixels, act, (const T*)w, p, Ad,
+                           zero, wblocks, stats, info);
+    }
+    PNN_CHECK_LAUNCH();
+    DigConvArgs a;
+    a.Ad = Ad; a.act = act; a.zero = zero; a.info = info;
+    a.RBA = p.RBA; a.KB = p.KB; a.K16 = p.K16; a.Cg = p.Cg;
+    a.HI = p.HI; a.WI = p.WI; a.HO = p.HO; a.WO = p.WO; a.S = p.S; a.offh = p.offh; a.offw = p.offw; a.sh = p.sh; a.sw = p.sw; a.MO = p.MO;
+    a.P = (int)p.P;
+    a.bias = bias; a.out = out;
+    a.fin = fmt_of_code(code_of<F>());
+    a.fout = fmt_of_code(fout);
+    a.tiles_m = p.RBA / p.WY;
+    if constexpr (D::NP1 == 4) {
+        a.np = 4;
+        const hipError_t e = launch_dig_conv_product<4>(stream, a, p.WY);
+        if (e != hipSuccess) return e;
+    }
+    a.np = D::NP2;
+    return launch_dig_conv_product<dig_conv_wide<F>()>(stream, a, p.WY);
+}
+
+// ---- backward-weight: dw[k][c][r][s] = sum over (n, oh, ow) of dy[n][k][oh][ow] x[n][c][oh sh + r - ph][ow sw + s - pw] ----
+
+struct DigConvBwPlan {
+    bool ok;
+    ConvGeom g;
+    int M, N, crs;             // outputs: K x CRS, or K x (CRS + 1) with the bias gradient as the last column
+    int NG;                    // groups of 16 images
+    int K16;                   // reduction length in 16s: OH OW NG
+    int WY, RBA, KB;           // waves along the rows, row blocks of dy's planes, k blocks (= splits * kb_per_split)
+    int tiles_m, tiles_n;
+    int splits, kb_per_split;
+    size_t a_bytes, x_bytes, ones_bytes, part_bytes;
+    // behind the planes and the blocks of ones: 256 bytes of zeros, 256 of decision, the scan's results, the partial sums
+    size_t part_off() const { return a_bytes + x_bytes + ones_bytes + 512 + DIG_STAT_BYTES; }
+    size_t total() const { return part_off() + part_bytes; }
+};
+
+template <class F>
+inline DigConvBwPlan dig_conv_bw_plan(const ConvGeom& g, bool with_bias) {
+    DigConvBwPlan p;
+    p.ok = false;
+    p.g = g;
+    if (!dig_conv_format<F>() || g.N <= 0 || g.C <= 0 || g.K <= 0) return p;
+    constexpr int slots = dig_conv_wide<F>(), L = dig_limbs<slots>();
+    const int64_t crs = (int64_t)g.C * g.R * g.S, P = (int64_t)g.N * g.OH * g.OW;
+    if (crs > 65536 || g.K > 65536 || P < 2048 || P >= ((int64_t)1 << 28) || g.K * crs * P < ((int64_t)1 << 22)) return p;
+    p.NG = (g.N + 15) / 16;
+    const int64_t k16 = (int64_t)g.OH * g.OW * p.NG;
+    if ((int64_t)g.C * g.H * g.W * p.NG * slots >= ((int64_t)1 << 30) || k16 >= ((int64_t)1 << 26) || g.H > 16384 || g.W > 16384) return p;
+    p.K16 = (int)k16;
+    p.M = g.K;
+    p.crs = (int)crs;
+    p.N = (int)crs + (with_bias ? 1 : 0);
+    p.WY = p.M > 32 ? 2 : 1;
+    const int tr = 32 * p.WY, tc = 32 * (4 / p.WY);
+    p.tiles_m = (p.M + tr - 1) / tr;
+    p.tiles_n = (p.N + tc - 1) / tc;
+    p.RBA = p.tiles_m * p.WY;
+    const int64_t kb_total = (k16 + 1) / 2, tiles = (int64_t)p.tiles_m * p.tiles_n;
+    int64_t splits = (512 + tiles - 1) / tiles;                    // about two workgroups per compute unit
+    if (splits > kb_total / 8) splits = kb_total / 8;              // at least 8 k blocks per slice
+    if (splits < (kb_total + 510) / 511) splits = (kb_total + 510) / 511;  // and at most what int32 sums hold
+    if (splits < 1) splits = 1;
+    const int64_t kbps = (kb_total + splits - 1) / splits;
+    splits = (kb_total + kbps - 1) / kbps;
+    if (splits > 65535) return p;
+    p.splits = (int)splits;
+    p.kb_per_split = (int)kbps;
+    p.KB = (int)(splits * kbps);
+    p.a_bytes = (size_t)p.KB * p.RBA * slots * 1024;
+    p.x_bytes = (size_t)g.C * g.H * g.W * p.NG * slots * 16;
+    p.ones_bytes = (size_t)p.NG * slots * 16;
+    if (p.a_bytes >= ((size_t)1 << 34)) return p;
+    p.part_bytes = ((size_t)p.splits * p.M * p.N * L + (size_t)p.splits * (p.M + p.N)) * 4;
+    p.ok = true;
+    return p;
+}
+
+// ablocks workgroups rewrite dy, the rest x (and the blocks of ones and zeros).
+//   dy: workgroup (row block rb, image group g, chunk of positions) keeps the patterns of 16 images x 32 rows x POS positions
+//       in LDS (read along the positions) and writes, per position and row, the planes of the 16 images.  Positions beyond
+//       OH OW (up to the padded reduction length 2 KB) are written as zeros.
+//   x:  one thread per (channel, PX consecutive pixels, image group); 16 loads a pixel-plane apart, coalesced along the pixels.
+template <class F, int NP, int PX, int POS>
+__device__ __forceinline__ void dig_conv_bw_planes(const typename Storage<F::N>::T* __restrict__ dy, const typename Storage<F::N>::T* __restrict__ x,
+                                                   const DigConvBwPlan& p, uint4* __restrict__ Ad, uint4* __restrict__ xb, uint4* __restrict__ ones,
+                                                   uint4* __restrict__ zero, unsigned ablocks, int chunks, const DigInfo& d, uint64_t* tab,
+                                                   typename Storage<F::N>::T (*tile)[32][POS + 4 / (int)sizeof(typename Storage<F::N>::T)]) {
+    typedef typename Storage<F::N>::T T;
+    typedef typename DigWord<NP>::T W;
+    constexpr int PW = 4 / (int)sizeof(T);  // positions per 32-bit word
+    const int t = threadIdx.x;
+    const bool rows = blockIdx.x < ablocks;
+    const DigLookup<F, NP> word{tab, rows ? d.base[1] : d.base[0]};
+    if constexpr (F::N == 8) tab[t] = dig_word<F, NP>((uint32_t)t, word.base);
+    const ConvGeom& g = p.g;
+    const int ohw = g.OH * g.OW;
+    if (rows) {
+        const int chunk = (int)(blockIdx.x % (unsigned)chunks);
+        const int gi = (int)((blockIdx.x / (unsigned)chunks) % (unsigned)p.NG);
+        const int rb = (int)(blockIdx.x / (unsigned)(chunks * p.NG));
+        // loads in batches of eight before their LDS stores, so that eight are in flight per thread
+        if (ohw % PW == 0 && ((uintptr_t)dy & 3u) == 0) {
+            constexpr int WPR = POS / PW, ITEMS = 16 * 32 * WPR;  // 32-bit words per row, in all
+#pragma unroll 1
+            for (int base = 0; base < ITEMS; base += 8 * 256) {
+                uint32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int item = base + u * 256 + t, pair = item / WPR, q = item % WPR;
+                    const int img = gi * 16 + (pair >> 5), row = rb * 32 + (pair & 31), pos = chunk * POS + q * PW;
+                    v[u] = (img < g.N && row < g.K && pos < ohw) ? *reinterpret_cast<const uint32_t*>(dy + ((int64_t)img * g.K + row) * ohw + pos) : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int item = base + u * 256 + t, pair = item / WPR, q = item % WPR;
+                    *reinterpret_cast<uint32_t*>(&tile[pair >> 5][pair & 31][q * PW]) = v[u];
+                }
+            }
+        } else {
+            constexpr int ITEMS = 16 * 32 * POS;
+#pragma unroll 1
+            for (int base = 0; base < ITEMS; base += 8 * 256) {
+                T v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int item = base + u * 256 + t, pair = item / POS, q = item % POS;
+                    const int img = gi * 16 + (pair >> 5), row = rb * 32 + (pair & 31), pos = chunk * POS + q;
+                    v[u] = (img < g.N && row < g.K && pos < ohw) ? dy[((int64_t)img * g.K + row) * ohw + pos] : (T)0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int item = base + u * 256 + t, pair = item / POS, q = item % POS;
+                    tile[pair >> 5][pair & 31][q] = v[u];
+                }
+            }
+        }
+        __syncthreads();
+        for (int item = t; item < POS * 32; item += 256) {
+            const int pl = item >> 5, rr = item & 31;
+            const int64_t k16 = (int64_t)(chunk * POS + pl) * p.NG + gi;
+            if (k16 >= 2 * (int64_t)p.KB) continue;
+            W wd[16];
+#pragma unroll
+            for (int b = 0; b < 16; ++b) wd[b] = word(tile[b][rr][pl]);
+            uint32_t dg[NP][4];
+            dig_planes_of<NP>(wd, dg);
+            const int kb = (int)(k16 >> 1), lane = (int)(k16 & 1) * 32 + rr;
+            uint4* out = Ad + ((int64_t)kb * p.RBA + rb) * (NP * 64) + lane;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) out[i * 64] = make_uint4(dg[i][0], dg[i][1], dg[i][2], dg[i][3]);
+        }
+        return;
+    }
+    __syncthreads();  // the table
+    const int64_t idx = (int64_t)(blockIdx.x - ablocks) * 256 + t;
+    if (idx < 16) zero[idx] = make_uint4(0, 0, 0, 0);  // what the product kernel reads for padding (no memset: graph capture)
+    if (idx < p.NG) {  // the column of ones, for the images the group really has
+        W wd[16];
+        const W one = word(F::NAR >> 1);
+#pragma unroll
+        for (int b = 0; b < 16; ++b) wd[b] = (int)idx * 16 + b < g.N ? one : (W)0;
+        uint32_t dg[NP][4];
+        dig_planes_of<NP>(wd, dg);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) ones[idx * NP + i] = make_uint4(dg[i][0], dg[i][1], dg[i][2], dg[i][3]);
+    }
+    const int64_t planes = (int64_t)g.C * g.H * g.W;  // pixels of all channels of one image
+    const int64_t groups = planes / PX;
+    if (idx >= groups * p.NG) return;
+    const int gi = (int)(idx / groups);
+    const int64_t pix = (idx - (int64_t)gi * groups) * PX;  // (c, h, w) as one index
+    const int nimg = g.N - gi * 16 < 16 ? g.N - gi * 16 : 16;
+    const T* q = x + (int64_t)gi * 16 * planes + pix;
+    uint32_t in[16];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        if (b >= nimg) in[b] = 0;
+        else if (PX > 1) in[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * planes);
+        else in[b] = q[(int64_t)b * planes];
+    }
+#pragma unroll
+    for (int px = 0; px < PX; ++px) {
+        W wd[16];
+#pragma unroll
+        for (int b = 0; b < 16; ++b) wd[b] = word((in[b] >> (8 * (int)sizeof(T) * px)) & (sizeof(T) == 1 ? 0xFFu : 0xFFFFu));
+        uint32_t dg[NP][4];
+        dig_planes_of<NP>(wd, dg);
+        uint4* out = xb + ((pix + px) * p.NG + gi) * NP;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) out[i] = make_uint4(dg[i][0], dg[i][1], dg[i][2], dg[i][3]);
+    }
+}
+
+template <class F>
+constexpr int dig_bw_positions() { return F::N == 8 ? 64 : 32; }
+
+template <class F, int PX>
+__global__ __launch_bounds__(256) void dig_conv_bw_digits_kernel(const typename Storage<F::N>::T* __restrict__ dy, const typename Storage<F::N>::T* __restrict__ x,
+                                                                 DigConvBwPlan p, uint4* __restrict__ Ad, uint4* __restrict__ xb, uint4* __restrict__ ones,
+                                                                 uint4* __restrict__ zero, unsigned ablocks, int chunks, const void* __restrict__ stats,
+                                                                 DigInfo* __restrict__ info) {
+    typedef DigFormat<F> D;
+    typedef typename Storage<F::N>::T T;
+    constexpr int POS = dig_bw_positions<F>();
+    __shared__ uint64_t tab[F::N == 8 ? 256 : 1];
+    __shared__ __attribute__((aligned(16))) T tile[16][32][POS + 4 / (int)sizeof(T)];
+    const DigInfo d = dig_read_decision<F>(stats, info, D::NP1 == 4, blockIdx.x == 0);
+    if (D::NP1 == 4 && d.np == 4) dig_conv_bw_planes<F, 4, PX, POS>(dy, x, p, Ad, xb, ones, zero, ablocks, chunks, d, tab, tile);
+    else dig_conv_bw_planes<F, dig_conv_wide<F>(), PX, POS>(dy, x, p, Ad, xb, ones, zero, ablocks, chunks, d, tab, tile);
+}
+
+struct DigConvBwArgs {
+    const uint4* Ad;      // dy's planes
+    const uint4* xb;      // x's planes, image-minor
+    const uint4* ones;    // per image group: the digits of 1 for the images it has
+    const uint4* zero;    // 256 bytes of zeros
+    const DigInfo* info;
+    int np, RBA, kb_per_split;
+    int NG, OH, OW, H, W, R, S, ph, pw, sh, sw;
+    int crs, M, N;
+    uint32_t* part;       // [slice][limb][M N]
+    uint32_t* rowflag;    // [slice][M]
+    uint32_t* colflag;    // [slice][N]
+    int tiles_m;
+    int splits;
+    void* dw;
+    void* dbias;
+    FmtRT fin, fout;
+    int qbits;
+};
+
+// Four waves as WY x (4 / WY), as in dig_conv_kernel; workgroup (tile, z) reduces slice z and leaves one integer per output.
+template <int NP, int WY, int ST>
+__global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_bw_kernel(DigConvBwArgs a) {
+    if (__builtin_amdgcn_readfirstlane(a.info->np) != a.np) return;
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
+    constexpr int WX = 4 / WY, NB = WX, NA = WY;
+    constexpr int RPB = (NA + NB) * NP;
+    constexpr int TR = 32 * WY, TC = 32 * WX;
+    static_assert(NP % 4 == 0, "copies spread evenly over the waves");
+    constexpr int ARUNS = NA * NP / 4, GRUNS = NB * NP / 4, LOADS = ARUNS + GRUNS;
+    __shared__ uint4 lds[ST * RPB * 64];
+    uint4* const stage = lds;
+
+    const int t = threadIdx.x;
+    const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wy = WY == 2 ? w >> 1 : 0, wx = WY == 2 ? (w & 1) : w;
+    const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
+    const int z = blockIdx.y;
+    const int kb0 = z * a.kb_per_split, nkb = a.kb_per_split;
+
+    const int64_t a_kb = (int64_t)a.RBA * NP * 64;
+    const uint4* asrc = a.Ad + kb0 * a_kb + ((int64_t)tm * NA * NP + w * ARUNS) * 64 + lane;
+    // x: wave w gathers GRUNS planes of column block w / (4 / NB); lane l serves column l % 32 of the block and the 16
+    // reduction indices (one pixel, one image group) of half l / 32
+    constexpr int WPB = 4 / NB;
+    const int cb = w / WPB, pl0 = (w % WPB) * GRUNS;
+    const int n = tn * TC + cb * 32 + (lane & 31);
+    int kind = 2, cbase = 0, dr = 0, ds = 0;  // kind 0: a column (c, r, s); 1: the column of ones; 2: beyond the columns
+    if (n < a.crs) {
+        const int rs = a.R * a.S;
+        const int c = n / rs, tp = n - c * rs;
+        const int r = tp / a.S, s = tp - r * a.S;
+        kind = 0;
+        cbase = c * a.H * a.W * a.NG * NP + pl0;
+        dr = r - a.ph;
+        ds = s - a.pw;
+    } else if (n < a.N) {
+        kind = 1;
+    }
+    // the reduction index of this lane's half, as (oh, ow, image group), stepped from k block to k block
+    int oh, ow, gi;
+    {
+        const int k16 = kb0 * 2 + (lane >> 5);
+        const int pos = k16 / a.NG;
+        gi = k16 - pos * a.NG;
+        oh = pos / a.OW;
+        ow = pos - oh * a.OW;
+    }
+    int issued = 0;
+    auto issue = [&]() {
+        uint4* buf = stage + (issued % ST) * (RPB * 64);
+#pragma unroll
+        for (int c = 0; c < ARUNS; ++c)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64),
+                                             (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
+        asrc += a_kb;
+        const uint4* s = a.zero;
+        if (oh < a.OH) {  // inside the reduction (its padded end reads zeros)
+            if (kind == 0) {
+                const int ih = oh * a.sh + dr, iw = ow * a.sw + ds;
+                if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W) s = a.xb + (cbase + ((ih * a.W + iw) * a.NG + gi) * NP);
+            } else if (kind == 1) {
+                s = a.ones + (gi * NP + pl0);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < GRUNS; ++c)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + c),
+                                             (__attribute__((address_space(3))) void*)(buf + (NA * NP + cb * NP + pl0 + c) * 64), 16, 0, 0);
+        gi += 2;  // the next k block: two reduction indices of 16 further
+        while (gi >= a.NG) {
+            gi -= a.NG;
+            if (++ow == a.OW) {
+                ow = 0;
+                ++oh;
+            }
+        }
+        ++issued;
+    };
+    const int a_nar = __builtin_amdgcn_readfirstlane(a.info->nar[1]), b_nar = __builtin_amdgcn_readfirstlane(a.info->nar[0]);
+    uint32_t row_nar = 0, col_nar = 0;
+#pragma unroll
+    for (int k = 0; k < ST - 1; ++k)
+        if (k < nkb) issue();
+    pm_v16i acc[NC];
+#pragma unroll
+    for (int s = 0; s < NC; ++s)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[s][r] = 0;
+    const uint4* const sa0 = stage + wy * NP * 64 + lane;
+    const uint4* const sb0 = stage + (NA + wx) * NP * 64 + lane;
+    DigFrag<NP> f0, f1;
+    auto markers = [&](const DigFrag<NP>& f) {
+        if (a_nar) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) row_nar |= pm_marker_bits((uint32_t)f.a[NP - 1][i]);
+        }
+        if (b_nar) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) col_nar |= pm_marker_bits((uint32_t)f.b[NP - 1][i]);
+        }
+    };
+    __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+    __syncthreads();
+    if constexpr (NP <= 4) {
+        auto step = [&](int kb, const DigFrag<NP>& cur, DigFrag<NP>& next) {
+            if (kb + ST - 2 < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 3) * LOADS));
+            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+            pcm_ring_barrier();
+            if (kb + ST - 1 < nkb) issue();
+            const int nb = ((kb + 1) % ST) * (RPB * 64);
+            next.template load<0>(sa0 + nb, sb0 + nb);
+            markers(cur);
+            dig_mma<NP, 0, NP, 0, NP>(cur, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        f0.template load<0>(sa0, sb0);
+        for (int kb = 0; kb < nkb; kb += 2) {
+            step(kb, f0, f1);
+            if (kb + 1 < nkb) step(kb + 1, f1, f0);
+        }
+    } else {  // one set of operand registers, read in their own step
+        for (int kb = 0; kb < nkb; ++kb) {
+            if (kb + ST - 2 < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
+            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+            pcm_ring_barrier();
+            if (kb + ST - 1 < nkb) issue();
+            const int nb = (kb % ST) * (RPB * 64);
+            f0.template load<0>(sa0 + nb, sb0 + nb);
+            markers(f0);
+            dig_mma<NP, 0, NP, 0, NP>(f0, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    // ---- this slice's integers and NaR flags ----
+    row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
+    col_nar = (col_nar | (uint32_t)__shfl_xor((int)col_nar, 32)) & 0x80808080u;
+    const int64_t MN = (int64_t)a.M * a.N;
+    const int nn = tn * TC + wx * 32 + (lane & 31), m0 = tm * TR + wy * 32;
+    // the first tile column stores the row flags of its tile row (the same in every column), the first tile row the column
+    // flags: every entry is written, so the workspace needs no clearing
+    if (lane < 32) {
+        if (tn == 0 && wx == 0 && m0 + lane < a.M) a.rowflag[(int64_t)z * a.M + m0 + lane] = row_nar;
+        if (tm == 0 && wy == 0 && nn < a.N) a.colflag[(int64_t)z * a.N + nn] = col_nar;
+    }
+    if (nn >= a.N) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int m = m0 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+        uint32_t q[L];
+        dig_combine<NP>(acc, r, q);
+        if (m < a.M) {
+#pragma unroll
+            for (int l = 0; l < L; ++l) a.part[((int64_t)z * L + l) * MN + (int64_t)m * a.N + nn] = q[l];
+        }
+    }
+}
+
+// Adds the slices (eight threads per output take every eighth), wraps to the quire's width (a long reduction can leave it),
+// rounds once, and routes the column of ones to the bias gradient.
+template <int NP>
+__global__ __launch_bounds__(256) void dig_conv_bw_merge_kernel(DigConvBwArgs a) {
+    constexpr int L = dig_limbs<NP>();
+    if (__builtin_amdgcn_readfirstlane(a.info->np) != a.np) return;
+    __shared__ uint32_t sum[L + 1][8][33];
+    const int64_t MN = (int64_t)a.M * a.N;
+    const int t = threadIdx.x, o = t & 31, zl = t >> 5;
+    const int64_t i = (int64_t)blockIdx.x * 32 + o;
+    const bool live = i < MN;
+    const int m = live ? (int)(i / a.N) : 0, n = live ? (int)(i - (int64_t)m * a.N) : 0;
+    uint32_t q[L], nar = 0;
+#pragma unroll
+    for (int l = 0; l < L; ++l) q[l] = 0;
+    if (live) {
+#pragma unroll 4
+        for (int z = zl; z < a.splits; z += 8) {
+            uint32_t p[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) p[l] = a.part[((int64_t)z * L + l) * MN + i];
+            quire_merge<L>(q, p);
+            nar |= a.rowflag[(int64_t)z * a.M + m] | a.colflag[(int64_t)z * a.N + n];
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l) sum[l][zl][o] = q[l];
+    sum[L][zl][o] = nar;
+    __syncthreads();
+    if (zl != 0 || !live) return;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) {
+        uint32_t p[L];
+#pragma unroll
+        for (int l = 0; l < L; ++l) p[l] = sum[l][k][o];
+        quire_merge<L>(q, p);
+        nar |= sum[L][k][o];
+    }
+    DigRound rd;
+    rd.fin = a.fin;
+    rd.fout = a.fout;
+    rd.at = a.info->base[0] + a.info->base[1];
+    const int bits = a.qbits - rd.at;
+    if (bits < 32 * L) dig_wrap<L>(q, bits);
+    const uint32_t v = dig_round<L>(q, rd, nar != 0, false, 0u);
+    if (n < a.crs) dig_store_pattern(a.dw, (int64_t)m * a.crs + n, rd.fout.n, v);
+    else dig_store_pattern(a.dbias, m, rd.fout.n, v);
+}
+
+template <int NP>
+inline hipError_t launch_dig_conv_bw_product(hipStream_t stream, DigConvBwArgs a, const DigConvBwPlan& p, uint8_t* part) {
+    constexpr int L = dig_limbs<NP>();
+    a.part = (uint32_t*)part;
+    a.rowflag = a.part + (size_t)p.splits * L * p.M * p.N;
+    a.colflag = a.rowflag + (size_t)p.splits * p.M;
+    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
+    if (p.WY == 1) hipLaunchKernelGGL((dig_conv_bw_kernel<NP, 1, 3>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((dig_conv_bw_kernel<NP, 2, 4>), grid, dim3(256), 0, stream, a);
+    PNN_CHECK_LAUNCH();
+    hipLaunchKernelGGL(dig_conv_bw_merge_kernel<NP>, dim3((unsigned)(((int64_t)p.M * p.N + 31) / 32)), dim3(256), 0, stream, a);
+    return hipGetLastError();
+}
+
+// workspace: [planes of dy][planes of x][blocks of ones][256 zeros][decision][scan][partial sums and flags of the slices]
+template <class F>
+inline hipError_t launch_dig_conv_bw(hipStream_t stream, const DigConvBwPlan& p, const void* dy, const void* x, void* dw, void* dbias, int fout,
+                                     void* workspace) {
+    typedef typename Storage<F::N>::T T;
+    typedef DigFormat<F> D;
+    uint8_t* base = (uint8_t*)workspace;
+    uint4* Ad = (uint4*)base;
+    uint4* xb = (uint4*)(base + p.a_bytes);
+    uint4* ones = (uint4*)(base + p.a_bytes + p.x_bytes);
+    uint4* zero = (uint4*)(base + p.a_bytes + p.x_bytes + p.ones_bytes);
+    DigInfo* info = (DigInfo*)(zero + 16);
+    void* stats = (void*)(zero + 32);
+    const ConvGeom& g = p.g;
+    const int64_t planes = (int64_t)g.C * g.H * g.W, nx = planes * g.N, ny = (int64_t)g.N * g.K * g.OH * g.OW;
+    const DigStatJob sx{x, 1, nx, nx, p.N > p.crs ? 1 : 0}, sy{dy, 1, ny, ny, 0};
+    hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sx, sy, stats);
+    PNN_CHECK_LAUNCH();
+    constexpr int POS = dig_bw_positions<F>(), PX = 4 / (int)sizeof(T);
+    const int posmax = (2 * p.KB + p.NG - 1) / p.NG;  // positions up to the padded end of the reduction
+    const int chunks = (posmax + POS - 1) / POS;
+    const unsigned ablocks = (unsigned)p.RBA * (unsigned)p.NG * (unsigned)chunks;
+    if (planes % PX == 0 && ((uintptr_t)x & 3u) == 0) {
+        const unsigned xblocks = (unsigned)((planes / PX * p.NG + 255) / 256);
+        hipLaunchKernelGGL((dig_conv_bw_digits_kernel<F, PX>), dim3(ablocks + xblocks), dim3(256), 0, stream, (const T*)dy, (const T*)x, p, Ad, xb, ones, zero,
+                           ablocks, chunks, stats, info);
+    } else {
+        const unsigned xblocks = (unsigned)((planes * p.NG + 255) / 256);
+        hipLaunchKernelGGL((dig_conv_bw_digits_kernel<F, 1>), dim3(ablocks + xblocks), dim3(256), 0, stream, (const T*)dy, (const T*)x, p, Ad, xb, ones, zero,
+                           ablocks, chunks, stats, info);
+    }
+    PNN_CHECK_LAUNCH();
+    DigConvBwArgs a;
+    a.Ad = Ad; a.xb = xb; a.ones = ones; a.zero = zero; a.info = info;
+    a.RBA = p.RBA; a.kb_per_split = p.kb_per_split;
+    a.NG = p.NG; a.OH = g.OH; a.OW = g.OW; a.H = g.H; a.W = g.W; a.R = g.R; a.S = g.S; a.ph = g.ph; a.pw = g.pw; a.sh = g.sh; a.sw = g.sw;
+    a.crs = p.crs; a.M = p.M; a.N = p.N;
+    a.tiles_m = p.tiles_m;
+    a.splits = p.splits;
+    a.dw = dw; a.dbias = dbias;
+    a.fin = fmt_of_code(code_of<F>());
+    a.fout = fmt_of_code(fout);
+    a.qbits = F::QBITS;
+    if constexpr (D::NP1 == 4) {
+        a.np = 4;
+        const hipError_t e = launch_dig_conv_bw_product<4>(stream, a, p, base + p.part_off());
+        if (e != hipSuccess) return e;
+    }
+    a.np = D::NP2;
+    return launch_dig_conv_bw_product<dig_conv_wide<F>()>(stream, a, p, base + p.part_off());
+}
+
+}  // namespace pnn

@@ -134,6 +134,7 @@ PNN_HD typename DigWord<NP>::T dig_word(uint32_t p, int base) {
 struct DigStatJob {
     const void* src;
     int64_t rows, cols, ld;  // a row-major matrix as stored
+    int with_one;            // the value one takes part as well (the column of ones of a bias gradient)
 };
 
 template <class F>
@@ -209,6 +210,7 @@ __global__ __launch_bounds__(1024) void dig_stat_kernel(DigStatJob job0, DigStat
             s.add(src[r * job.ld + (i - r * job.cols)]);
         }
     }
+    if (job.with_one) s.add(F::NAR >> 1);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1)
         s.merge((uint32_t)__shfl_xor((int)s.low, d), (uint32_t)__shfl_xor((int)s.high, d), (uint32_t)__shfl_xor((int)s.nar, d));
@@ -365,6 +367,20 @@ __device__ __forceinline__ void dig_combine(const pm_v16i (&acc)[2 * NP - 1], in
         if (l < W) carry += w[l < W ? l : 0];  // |w| < 2^56
         q[l] = (uint32_t)carry;
         carry >>= 32;
+    }
+}
+
+// Sign-extends the integer from bit `bits` - 1 (bits < 32 L): the wrap of a quire that a long reduction left.
+template <int L>
+PNN_HD void dig_wrap(uint32_t (&q)[L], int bits) {
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        const int top = bits - 1 - 32 * l;  // the sign bit, seen from this limb
+        if (top >= 0 && top < 31) {
+            q[l] = (uint32_t)((int32_t)(q[l] << (31 - top)) >> (31 - top));
+        } else if (top < 0) {
+            q[l] = l > 0 ? (uint32_t)((int32_t)q[l > 0 ? l - 1 : 0] >> 31) : 0u;
+        }
     }
 }
 

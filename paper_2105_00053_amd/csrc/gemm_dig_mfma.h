@@ -524,7 +524,7 @@ inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, co
     DigInfo* info = (DigInfo*)(mb + p.mb_bytes);
     void* stats = base + p.stat_off;
     *decision = info;
-    const DigStatJob sa{A, transA ? K : M, transA ? M : K, lda}, sb{B, transB ? N : K, transB ? K : N, ldb};
+    const DigStatJob sa{A, transA ? K : M, transA ? M : K, lda, 0}, sb{B, transB ? N : K, transB ? K : N, ldb, 0};
     hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sa, sb, stats);
     PNN_CHECK_LAUNCH();
     // op(A)[m,k] is A[m * lda + k] unless transA; op(B)[k,n] is B[k * ldb + n] unless transB
