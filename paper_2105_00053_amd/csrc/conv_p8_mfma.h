@@ -57,7 +57,7 @@ inline P8ConvMfmaPlan p8_conv_mfma_plan(int which, const ConvGeom& g) {
     p.KB = (p.K16 + 1) / 2;
     p.P = (int64_t)p.NI * p.HO * p.WO;
     const int64_t pin = (int64_t)p.NI * p.HI * p.WI;
-    if (2 * p.KB > PCM_MAXK16 || p.HI > 16384 || p.WI > 16384 || g.R > 4096 || g.S > 4096) return p;
+    if (2 * p.KB > PCM_MAXK16 || p.Cg > 256 || p.HI > 16384 || p.WI > 16384 || g.R > 4096 || g.S > 4096) return p;
     if (pin * p.Cg * 2 >= ((int64_t)1 << 30) || p.P >= ((int64_t)1 << 30) || p.P * p.MO >= ((int64_t)1 << 40)) return p;
     // worth the two rewriting launches: enough products, enough positions to fill the chip, enough rows to use a block
     const int64_t macs = p.P * p.MO * p.CI * g.R * g.S;
@@ -78,7 +78,9 @@ inline P8ConvMfmaPlan p8_conv_mfma_plan(int which, const ConvGeom& g) {
 //
 // Input tensor [NI][CI][HW] -> digit planes [NI * HW][Cg][2][16]; channels beyond CI are zeros.  One thread per channel
 // group and PX consecutive pixels (PX = 4 when HW is a multiple of 4 and the tensor is 4-byte aligned: one 32-bit load
-// per channel); consecutive threads take consecutive pixels, so every load is coalesced.
+// per channel); consecutive threads take consecutive pixels, so every load is coalesced, and the digits leave through LDS
+// in one contiguous stretch per workgroup (stored by the threads that make them, 32 bytes each at a stride of a pixel:
+// 55 us for 51 M elements, 2.8 TB/s; now 29 us, 5.3 TB/s).
 //
 // Weights [WK][WC][R][S] -> [KB][RBA][2][64][16] (and the 32 zero bytes behind the input planes) in the lane order of
 // the matrix instruction, reduction index 16 ((r S + s) Cg + cg) + channel.  Forward: row = output channel k,
@@ -88,9 +90,9 @@ template <int PX>
 __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __restrict__ src, int HW, int64_t pixels, uint8_t* __restrict__ act,
                                                              const uint8_t* __restrict__ w, P8ConvMfmaPlan p, uint8_t* __restrict__ wdst,
                                                              uint4* __restrict__ zero, unsigned wblocks) {
-    __shared__ int16_t tab[256];
+    __shared__ uint16_t tab[256];
     const int t = threadIdx.x;
-    tab[t] = t == 0x80 ? (int16_t)(PM_NAR_HI * 128) : (int16_t)Arith<P8>::stage((uint32_t)t);
+    tab[t] = pm_digits((uint32_t)t);
     __syncthreads();
     if (blockIdx.x < wblocks) {
         const int64_t idx = (int64_t)blockIdx.x * 256 + t;
@@ -114,10 +116,10 @@ __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __re
             for (int b = 0; b < 16; ++b) pat[b] = b < nch ? q[b * step] : 0u;  // all loads in flight together
 #pragma unroll
             for (int b = 0; b < 16; ++b) {
-                int v = tab[pat[b]];
+                uint32_t v = tab[pat[b]];
                 if (pat[b] == 0x80u && p.which != 0) v = 0;
-                hi[b >> 2] |= ((uint32_t)(v >> 7) & 0xFFu) << (8 * (b & 3));
-                lo[b >> 2] |= ((uint32_t)v & 0x7Fu) << (8 * (b & 3));
+                hi[b >> 2] |= (v >> 8) << (8 * (b & 3));
+                lo[b >> 2] |= (v & 0xFFu) << (8 * (b & 3));
             }
         }
         uint4* out = reinterpret_cast<uint4*>(wdst) + ((int64_t)(kb * p.RBA + rb) * 2) * 64 + lane;
@@ -125,33 +127,43 @@ __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __re
         out[64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
         return;
     }
-    const int64_t groups = pixels / PX;  // PX divides HW, hence pixels
-    const int64_t idx = (int64_t)(blockIdx.x - wblocks) * 256 + t;
-    if (idx >= groups * p.Cg) return;
-    const int cg = (int)(idx / groups);
-    const int64_t pix = (idx - (int64_t)cg * groups) * PX;
-    const int64_t img = pix / HW, hw = pix - img * HW;
-    const uint8_t* q = src + (img * p.CI + cg * 16) * (int64_t)HW + hw;
-    const int nch = p.CI - cg * 16 < 16 ? p.CI - cg * 16 : 16;
-    uint32_t word[16];
-#pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        if (b >= nch) word[b] = 0;
-        else if (PX == 4) word[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * HW);
-        else word[b] = q[(int64_t)b * HW];
-    }
-#pragma unroll
-    for (int px = 0; px < PX; ++px) {
-        uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
+    // the workgroup's pixels with all their channel groups are one contiguous stretch of the planes
+    extern __shared__ uint4 rows[];  // [pixel group][PX pixels x Cg groups x 2 digits, and one word so that rows fall on different banks]
+    const uint32_t QB = 256u / (uint32_t)p.Cg, cg = (uint32_t)t / QB, qi = (uint32_t)t - cg * QB;
+    const uint32_t group0 = (blockIdx.x - wblocks) * QB, groups = (uint32_t)(pixels / PX);  // PX divides HW, hence pixels
+    const uint32_t words = (uint32_t)(PX * 2) * p.Cg;
+    if (cg < (uint32_t)p.Cg && group0 + qi < groups) {
+        const uint32_t pix = (group0 + qi) * PX;
+        const uint32_t img = pix / (uint32_t)HW, hw = pix - img * (uint32_t)HW;
+        const uint8_t* q = src + ((int64_t)img * p.CI + cg * 16) * HW + hw;
+        const int nch = p.CI - (int)cg * 16 < 16 ? p.CI - (int)cg * 16 : 16;
+        uint32_t word[16];
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
-            const int v = tab[(word[b] >> (8 * px)) & 0xFFu];  // pattern 0 decodes to 0: channels beyond CI stay zero
-            hi[b >> 2] |= ((uint32_t)(v >> 7) & 0xFFu) << (8 * (b & 3));
-            lo[b >> 2] |= ((uint32_t)v & 0x7Fu) << (8 * (b & 3));
+            if (b >= nch) word[b] = 0;
+            else if (PX == 4) word[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * HW);
+            else word[b] = q[(int64_t)b * HW];
         }
-        uint4* out = reinterpret_cast<uint4*>(act) + ((pix + px) * p.Cg + cg) * 2;
-        out[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        out[1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        uint4* out = rows + qi * (words + 1) + cg * 2;
+#pragma unroll
+        for (int px = 0; px < PX; ++px) {
+            uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int b = 0; b < 16; ++b) {
+                const uint32_t v = tab[(word[b] >> (8 * px)) & 0xFFu];  // pattern 0 decodes to 0: channels beyond CI stay zero
+                hi[b >> 2] |= (v >> 8) << (8 * (b & 3));
+                lo[b >> 2] |= (v & 0xFFu) << (8 * (b & 3));
+            }
+            out[px * p.Cg * 2] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            out[px * p.Cg * 2 + 1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        }
+    }
+    __syncthreads();
+    const uint32_t ng = groups - group0 < QB ? groups - group0 : QB;
+    uint4* dst = reinterpret_cast<uint4*>(act) + (int64_t)group0 * words;
+    for (uint32_t o = t; o < ng * words; o += 256) {
+        const uint32_t r = o / words;
+        dst[o] = rows[o + r];
     }
 }
 
@@ -170,6 +182,10 @@ struct P8ConvMfmaArgs {
 // Four waves as WY x (4 / WY), a wave owns BI x BJ blocks of 32 x 32 outputs (rows: output channels, columns:
 // positions).  WY = 1 (all four waves side by side along the positions, 32 x 128 outputs) serves layers of at most 32
 // output channels, where a second row of waves would multiply and round nothing but padding.
+//
+// Bound by the matrix pipes' power and the copies that feed them: 256 images of 64 channels at 56 x 56, 3 x 3 to 64
+// channels (29.6 G products, 118 G int8 products), take 193 us, against 247 us with the ring and its table as two LDS
+// objects (which made every read of the ring wait for all copies) and one flag and bias read per output in the epilogue.
 template <int BI, int BJ, int WY>
 __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kernel(P8ConvMfmaArgs a) {
     constexpr int WX = 4 / WY;
@@ -178,8 +194,12 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
     constexpr int TR = 32 * BI * WY, TC = 32 * BJ * WX;
     // A ring of PCM_STAGES k blocks, copies running PCM_STAGES - 1 blocks ahead: a convolution's reduction is short
     // (tens of k blocks) and a block's matrix instructions take a fraction of a copy's latency, so depth hides it.
-    __shared__ uint4 stage[PCM_STAGES][(NA + NB) * 64];
-    __shared__ int2 ktab[PCM_MAXK16];  // per 16 reduction indices: offset of the tap and channel group in the planes, (dh, dw) packed
+    // One LDS object for the ring and the table behind it: beside a second object the compiler tells the two apart and waits
+    // for every outstanding copy in front of each read of the ring.
+    constexpr int BUF = (NA + NB) * 64;  // words of 16 bytes per block
+    __shared__ uint4 lds[PCM_STAGES * BUF + PCM_MAXK16 / 2];
+    uint4* const stage = lds;
+    int2* const ktab = reinterpret_cast<int2*>(lds + PCM_STAGES * BUF);  // per 16 reduction indices: offset of the tap and channel group in the planes, (dh, dw) packed
 
     const int t = threadIdx.x;
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -238,7 +258,7 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
     const uint4* zeroq = reinterpret_cast<const uint4*>(a.zero);
 
     auto issue = [&](int kb) {
-        uint4* sbuf = &stage[kb % PCM_STAGES][0];
+        uint4* sbuf = stage + (kb % PCM_STAGES) * BUF;
 #pragma unroll
         for (int c = 0; c < ARUNS; ++c)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64 + lane),
@@ -275,7 +295,7 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
         else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
         pcm_ring_barrier();  // everyone's copies of block kb are in LDS, and everyone has finished reading block kb - 1
         if (kb + PCM_STAGES - 1 < a.KB) issue(kb + PCM_STAGES - 1);  // into the buffer of block kb - 1
-        const uint4* sb = &stage[kb % PCM_STAGES][0];
+        const uint4* sb = stage + (kb % PCM_STAGES) * BUF;
         pm_v4i ah[BI], al[BI], bh[BJ], bl[BJ];
 #pragma unroll
         for (int i = 0; i < BI; ++i) {
@@ -307,7 +327,7 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
 
     // ---- the three sums into the quire, round once, store ----
     // Row flags (NaR weight or NaR bias in the channel) and the bias addends meet in LDS; column flags too.
-    uint32_t* rowv = reinterpret_cast<uint32_t*>(&stage[0][0]);
+    uint32_t* rowv = reinterpret_cast<uint32_t*>(stage);
     uint32_t* colv = rowv + TR;
     int32_t* rowb = reinterpret_cast<int32_t*>(colv + TC);
     row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
@@ -336,25 +356,36 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
     // (buffers 1 .. of the ring; buffer 0 holds the NaR flags) and leaves in 16-byte runs along the positions.
     const FmtRT fo = fmt_of_code(a.fout);
     const int esz = fo.n <= 8 ? 1 : (fo.n <= 16 ? 2 : 4);
-    uint8_t* tileb = reinterpret_cast<uint8_t*>(&stage[1][0]);
+    uint8_t* tileb = reinterpret_cast<uint8_t*>(stage + BUF);
     static_assert((PCM_STAGES - 1) * (NA + NB) * 1024 >= TR * TC * 4, "the rounded tile fits behind the NaR flags");
+    // flags and bias addends of four consecutive rows come in one read
+    const uint4* rowv4 = reinterpret_cast<const uint4*>(rowv);
+    const int4* rowb4 = reinterpret_cast<const int4*>(rowb);
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
         const int lc = (wx * BJ + j) * 32 + (lane & 31);
-        const bool cnar = colv[j * 32 + (lane & 31)] != 0;
+        const uint32_t cnar = colv[j * 32 + (lane & 31)];
 #pragma unroll
         for (int i = 0; i < BI; ++i) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int lr = i * 32 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
-                const uint32_t q = ((uint32_t)hh[i][j][r] << 14) + ((uint32_t)xx[i][j][r] << 7) + (uint32_t)ll[i][j][r] + (uint32_t)rowb[lr];
-                const bool nar = cnar || rowv[lr] != 0;
-                const int at = (wy * 32 * BI + lr) * TC + lc;
-                if (a.fout == 0) {
-                    tileb[at] = (uint8_t)(nar ? 0x80u : p8_round_quire((int32_t)q));
-                } else {
-                    const uint32_t q1[1] = {q};
-                    round_store<QuireAccum<P8>, 1>(q1, nar, a.fout, tileb, at);
+            for (int rq = 0; rq < 4; ++rq) {
+                const int lr0 = i * 32 + 8 * rq + 4 * (lane >> 5);
+                const uint4 fl = rowv4[lr0 >> 2];
+                const int4 ba = rowb4[lr0 >> 2];
+                const uint32_t flag[4] = {fl.x | cnar, fl.y | cnar, fl.z | cnar, fl.w | cnar};
+                const int32_t add[4] = {ba.x, ba.y, ba.z, ba.w};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int r = 4 * rq + u;
+                    const uint32_t q = ((uint32_t)hh[i][j][r] << 14) + ((uint32_t)xx[i][j][r] << 7) + (uint32_t)ll[i][j][r] + (uint32_t)add[u];
+                    const int at = (wy * 32 * BI + lr0 + u) * TC + lc;
+                    if (a.fout == 0) {
+                        const uint32_t v = p8_round_quire((int32_t)q);
+                        tileb[at] = (uint8_t)(flag[u] ? 0x80u : v);
+                    } else {
+                        const uint32_t q1[1] = {q};
+                        round_store<QuireAccum<P8>, 1>(q1, flag[u] != 0, a.fout, tileb, at);
+                    }
                 }
             }
         }
@@ -392,13 +423,14 @@ inline hipError_t launch_p8_conv_mfma(hipStream_t stream, const P8ConvMfmaPlan& 
     const int64_t pixels = (int64_t)p.NI * p.HI * p.WI;
     const int HW = p.HI * p.WI;
     const unsigned wblocks = (unsigned)(((int64_t)p.KB * p.RBA * 64 + 255) / 256);
+    const int64_t per = 256 / p.Cg;  // pixel groups per workgroup
     if (HW % 4 == 0 && ((uintptr_t)in & 3u) == 0) {
-        const unsigned ablocks = (unsigned)((pixels / 4 * p.Cg + 255) / 256);
-        hipLaunchKernelGGL(p8_conv_digits_kernel<4>, dim3(wblocks + ablocks), dim3(256), 0, stream, (const uint8_t*)in, HW, pixels, act,
+        const unsigned ablocks = (unsigned)((pixels / 4 + per - 1) / per);
+        hipLaunchKernelGGL(p8_conv_digits_kernel<4>, dim3(wblocks + ablocks), dim3(256), (size_t)per * (8 * p.Cg + 1) * 16, stream, (const uint8_t*)in, HW, pixels, act,
                            (const uint8_t*)w, p, Ad, reinterpret_cast<uint4*>(zero), wblocks);
     } else {
-        const unsigned ablocks = (unsigned)((pixels * p.Cg + 255) / 256);
-        hipLaunchKernelGGL(p8_conv_digits_kernel<1>, dim3(wblocks + ablocks), dim3(256), 0, stream, (const uint8_t*)in, HW, pixels, act,
+        const unsigned ablocks = (unsigned)((pixels + per - 1) / per);
+        hipLaunchKernelGGL(p8_conv_digits_kernel<1>, dim3(wblocks + ablocks), dim3(256), (size_t)per * (2 * p.Cg + 1) * 16, stream, (const uint8_t*)in, HW, pixels, act,
                            (const uint8_t*)w, p, Ad, reinterpret_cast<uint4*>(zero), wblocks);
     }
     PNN_CHECK_LAUNCH();
@@ -494,10 +526,10 @@ template <int PX>
 __global__ __launch_bounds__(256) void p8_conv_bw_digits_kernel(const uint8_t* __restrict__ dy, const uint8_t* __restrict__ x, P8ConvBwPlan p,
                                                                 uint8_t* __restrict__ Ad, uint8_t* __restrict__ xb, uint4* __restrict__ ones,
                                                                 uint4* __restrict__ zero, unsigned ablocks, int chunks) {
-    __shared__ int16_t tab[256];
+    __shared__ uint16_t tab[256];
     __shared__ __attribute__((aligned(16))) uint8_t tile[16][32][PCB_PITCH];
     const int t = threadIdx.x;
-    tab[t] = t == 0x80 ? (int16_t)(PM_NAR_HI * 128) : (int16_t)Arith<P8>::stage((uint32_t)t);
+    tab[t] = pm_digits((uint32_t)t);
     const ConvGeom& g = p.g;
     const int ohw = g.OH * g.OW;
     if (blockIdx.x < ablocks) {
@@ -548,9 +580,9 @@ __global__ __launch_bounds__(256) void p8_conv_bw_digits_kernel(const uint8_t* _
             uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
 #pragma unroll
             for (int b = 0; b < 16; ++b) {
-                const int v = tab[tile[b][rr][pl]];
-                hi[b >> 2] |= ((uint32_t)(v >> 7) & 0xFFu) << (8 * (b & 3));
-                lo[b >> 2] |= ((uint32_t)v & 0x7Fu) << (8 * (b & 3));
+                const uint32_t v = tab[tile[b][rr][pl]];
+                hi[b >> 2] |= (v >> 8) << (8 * (b & 3));
+                lo[b >> 2] |= (v & 0xFFu) << (8 * (b & 3));
             }
             const int kb = (int)(k16 >> 1), lane = (int)(k16 & 1) * 32 + rr;
             uint4* out = reinterpret_cast<uint4*>(Ad) + ((int64_t)(kb * p.RBA + rb) * 2) * 64 + lane;
@@ -589,9 +621,9 @@ __global__ __launch_bounds__(256) void p8_conv_bw_digits_kernel(const uint8_t* _
         uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
-            const int v = tab[(word[b] >> (8 * px)) & 0xFFu];
-            hi[b >> 2] |= ((uint32_t)(v >> 7) & 0xFFu) << (8 * (b & 3));
-            lo[b >> 2] |= ((uint32_t)v & 0x7Fu) << (8 * (b & 3));
+            const uint32_t v = tab[(word[b] >> (8 * px)) & 0xFFu];
+            hi[b >> 2] |= (v >> 8) << (8 * (b & 3));
+            lo[b >> 2] |= (v & 0xFFu) << (8 * (b & 3));
         }
         uint4* out = reinterpret_cast<uint4*>(xb) + ((pix + px) * p.NG + gi) * 2;
         out[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);

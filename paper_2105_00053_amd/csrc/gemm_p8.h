@@ -230,26 +230,25 @@ __global__ void p8_fill_zero_kernel(uint32_t* p, int64_t n) {
 
 // int32 quire (units of 2^-12) -> posit<8,0>, nearest, ties to even pattern, clamped to +-minpos / +-maxpos.
 // Straight-line code (an epilogue calls it for every output of a tile; branches per call cost more than they save):
-// with k = floor(log2 |value|), kk = k for k >= 0 and -k-1 otherwise, an arithmetic right shift by kk of "10" followed by
-// the fraction gives kk+1 ones, a zero and the fraction; for negative k the fraction is complemented before and the whole
-// word after the shift, which turns that head into kk+1 zeros and a one.  The eight fraction bits that the shifts can
-// push out are folded into bit 8 first, which always lies below the guard bit and is never pushed out itself.
+// the conversion to binary32 finds the leading bit and is exact up to 2^24, far beyond maxpos = 2^18 units, where only the
+// clamp matters.  With k = floor(log2 |value|), kk = k for k >= 0 and -k-1 otherwise, an arithmetic right shift by kk of
+// "10" followed by the fraction gives kk+1 ones, a zero and the fraction; for negative k the fraction is complemented
+// before and the whole word after the shift, which turns that head into kk+1 zeros and a one.  The 23 fraction bits stay
+// inside the word (2 + 6 + 23 bits), so nothing is lost before the rounding.
 PNN_HD uint32_t p8_round_quire(int32_t q) {
-    const uint32_t sm = (uint32_t)(q >> 31);  // all ones for a negative sum
-    const uint32_t mag = ((uint32_t)q ^ sm) - sm;
-    const int lz = clz32(mag);
-    const int k0 = 19 - lz;                              // floor(log2(mag)) - 12
-    const bool beyond = k0 >= 6 || k0 < -6;              // at or past maxpos / below minpos: the end pattern, no fraction
-    const int k = k0 > 6 ? 6 : (k0 < -6 ? -6 : k0);
-    const uint32_t frac = beyond ? 0u : ((mag << (lz & 31)) << 1);  // fraction bits at the top, leading one gone
+    const uint32_t bits = __builtin_bit_cast(uint32_t, (float)q);
+    const uint32_t sm = (uint32_t)((int32_t)bits >> 31);  // all ones for a negative sum
+    const uint32_t ab = bits & 0x7FFFFFFFu;
+    constexpr uint32_t LO = (127u + 6u) << 23, HI = (127u + 18u) << 23;  // minpos, maxpos: 2^6, 2^18 units
+    const uint32_t c = ab < LO ? LO : (ab > HI ? HI : ab);
+    const int k = (int)(c >> 23) - 139;                  // floor(log2(mag)) - 12
     const uint32_t sg = (uint32_t)(k >> 31);
     const uint32_t kk = (uint32_t)k ^ sg;
-    const uint32_t jam = (frac & 0xFFu) ? 0x100u : 0u;
-    const uint32_t w = 0x80000000u | (((frac | jam) ^ sg) >> 2);
-    const uint32_t x = (uint32_t)((int32_t)w >> kk) ^ sg;  // 7 kept bits, the guard bit, sticky bits
+    const uint32_t w = 0x80000000u | (((c << 9) ^ sg) >> 2);
+    const uint32_t x = (uint32_t)((int32_t)w >> kk) ^ sg;  // 7 kept bits, the guard bit, the rest of the fraction
     const uint32_t body = (x + 0x00FFFFFFu + ((x >> 25) & 1u)) >> 25;
     const uint32_t pat = ((body ^ sm) - sm) & 0xFFu;
-    return q == 0 ? 0u : pat;
+    return ab == 0 ? 0u : pat;
 }
 
 // PACKED: A and B point at operands rewritten by p8_pack_kernel (lda, ldb: their padded row counts),

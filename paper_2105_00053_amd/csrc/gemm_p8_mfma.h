@@ -2,7 +2,7 @@
 //
 // A decoded posit<8,0> is an integer v of at most 13 bits plus sign (units of minpos = 2^-6), and the quire is the
 // int32 sum of the products modulo 2^32.  Integer matrix instructions multiply int8 by int8 into int32 exactly, so v is
-// written in two base-128 digits, v = 128 hi + lo with hi = v >> 7 in [-32, 32] and lo = v & 127 in [0, 127], and
+// written in two base-128 digits that carry its sign, v = 128 hi + lo with hi in [-32, 32] and lo in [-127, 127], and
 //     a b = 2^14 (ah bh) + 2^7 (ah bl + al bh) + (al bl):
 // three int32 sums per output -- HH, X (both cross terms share it) and LL -- fed by four int8 products per posit
 // product, combined once after the reduction as (HH << 14) + (X << 7) + LL in 32-bit arithmetic.  Every step is exact
@@ -61,6 +61,16 @@ __device__ __forceinline__ void pcm_ring_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The two digits of a pattern, the high one in the upper byte: both carry the sign of the value, v = 128 hi + lo with
+// |lo| <= 127.  (With lo in 0 .. 127 every negative value has a high digit of -1 or below, all bits set: the high planes of
+// Gaussian data then toggle between 00 and FF, and the power that takes costs clock: 4096^3 250 us that way, 240 us now.)
+__device__ __forceinline__ uint16_t pm_digits(uint32_t pattern) {
+    if (pattern == 0x80u) return (uint16_t)((uint32_t)(PM_NAR_HI & 0xFF) << 8);
+    const int v = Arith<P8>::stage(pattern), m = v < 0 ? -v : v;
+    const int hi = v < 0 ? -(m >> 7) : m >> 7, lo = v < 0 ? -(m & 127) : m & 127;
+    return (uint16_t)(((uint32_t)(hi & 0xFF) << 8) | (uint32_t)(lo & 0xFF));
+}
+
 struct P8DigitJob {
     const uint8_t* src;
     int64_t s_r, s_k;   // element (row, k) at src[row * s_r + k * s_k]; one of the two is 1
@@ -73,9 +83,9 @@ struct P8DigitJob {
 // and eight row blocks: 512 lane slots of 16 bytes per digit, two per thread.
 template <int UNUSED = 0>
 __global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8DigitJob job1, unsigned blocks0) {
-    __shared__ int16_t tab[256];
+    __shared__ uint16_t tab[256];
     const int t = threadIdx.x;
-    tab[t] = t == 0x80 ? (int16_t)(PM_NAR_HI * 128) : (int16_t)Arith<P8>::stage((uint32_t)t);
+    tab[t] = pm_digits((uint32_t)t);
     __syncthreads();
     const bool first = blockIdx.x < blocks0;
     const P8DigitJob& job = first ? job0 : job1;
@@ -131,9 +141,9 @@ __global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8Digit
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
             const uint32_t pat = (w[b >> 2] >> (8 * (b & 3))) & 0xFFu;
-            const int v = tab[pat];  // -16384 for NaR: high digit -128, low digit 0
-            hi[b >> 2] |= ((uint32_t)(v >> 7) & 0xFFu) << (8 * (b & 3));
-            lo[b >> 2] |= ((uint32_t)v & 0x7Fu) << (8 * (b & 3));
+            const uint32_t v = tab[pat];
+            hi[b >> 2] |= (v >> 8) << (8 * (b & 3));
+            lo[b >> 2] |= (v & 0xFFu) << (8 * (b & 3));
         }
         uint4* out = reinterpret_cast<uint4*>(job.dst) + ((int64_t)(kb * job.RB + rb) * 2) * 64 + lane;
         out[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
