@@ -149,9 +149,12 @@ int launch_axpy(hipStream_t st, uint32_t alpha, int64_t n, const void* x, void* 
 
 // ---- large tensors, formats of at most 16 bits: binary64 arithmetic with LDS decode tables ----
 
-// Below this many elements the per-workgroup table set-up outweighs what the cheaper per-element work saves.
-constexpr int64_t AXPY_F64_MIN_16 = (int64_t)1 << 22;  // posit<16,1> tables: 128 KB per workgroup
-constexpr int64_t AXPY_F64_MIN_12 = (int64_t)1 << 19;  // 12-bit formats: a few KB
+// From this many elements on the cheaper work per element outweighs the tables that every workgroup sets up (both sides
+// measured, the narrowed copy included).  posit<16,1>, 128 KB of tables: 2^18 elements 7.6 us against 10.6 (where the
+// generic kernel needs a second launch for the last elements; without it they are equal), 2^21 7.3 against 15.4.  12-bit
+// formats, a few KB: 2^18 7.2 against 6.6, 2^19 7.4 against 9.6; the es = 1 pair 2^20 7.1 against 10.6.
+constexpr int64_t AXPY_F64_MIN_16 = (int64_t)1 << 19;
+constexpr int64_t AXPY_F64_MIN_12 = (int64_t)1 << 19;
 constexpr int64_t NARROW_STEP_MIN = (int64_t)1 << 20;
 
 inline int compute_units() {
@@ -163,9 +166,9 @@ inline int compute_units() {
     return cus;
 }
 
-// Launches the binary64 kernel on the first n - n % 8 elements; returns false (nothing launched) when it does not apply.
+// Launches the binary64 kernel; returns false (nothing launched) when it does not apply.
 template <class FX, class FY, class FC, bool COPY>
-bool launch_axpy_f64(hipStream_t st, uint32_t alpha, int64_t n, const void* x, void* y, void* yc, int64_t* done) {
+bool launch_axpy_f64(hipStream_t st, uint32_t alpha, int64_t n, const void* x, void* y, void* yc) {
     typedef typename Storage<FX::N>::T TX;
     typedef typename Storage<FY::N>::T TY;
     typedef typename Storage<FC::N>::T TC;
@@ -179,25 +182,26 @@ bool launch_axpy_f64(hipStream_t st, uint32_t alpha, int64_t n, const void* x, v
     const int64_t need = (nvec + THREADS - 1) / THREADS;
     if (blocks > need) blocks = need;
     hipLaunchKernelGGL((axpy_f64_kernel<FX, FY, FC, COPY, THREADS>), dim3((unsigned)blocks), dim3(THREADS), 0, st, (const TX*)x, (TY*)y,
-                       (TC*)yc, nvec, alpha);
-    *done = nvec * V;
+                       (TC*)yc, n, alpha);
     return true;
 }
 
 // Format triples the binary64 kernel is built for: the default mixed-precision set-up (16-bit optimizer, 8-bit
-// compute copy) and the paper's final one (posit(12,2) optimizer, posit(8,2) layers: Sec. 4, Table 4).
+// compute copy), the paper's final one (posit(12,2) optimizer, posit(8,2) layers: Sec. 4, Table 4) and its es = 1 neighbour.
 inline bool axpy_f64_dispatch(hipStream_t st, int fx, int fy, int fcopy, bool copy, uint32_t alpha, int64_t n, const void* x, void* y,
-                              void* yc, int64_t* done) {
+                              void* yc) {
 #define PNN_AXPY_F64(FX, FY, FC, CX, CY, CC)                                                                  \
     if (fx == CX && fy == CY) {                                                                               \
-        if (!copy) return launch_axpy_f64<FX, FY, FC, false>(st, alpha, n, x, y, nullptr, done);              \
-        if (fcopy == CC) return launch_axpy_f64<FX, FY, FC, true>(st, alpha, n, x, y, yc, done);              \
+        if (!copy) return launch_axpy_f64<FX, FY, FC, false>(st, alpha, n, x, y, nullptr);                    \
+        if (fcopy == CC) return launch_axpy_f64<FX, FY, FC, true>(st, alpha, n, x, y, yc);                    \
         return false;                                                                                         \
     }
     PNN_AXPY_F64(P16, P16, P8, PNN_POSIT16_1, PNN_POSIT16_1, PNN_POSIT8_0)
     PNN_AXPY_F64(P8, P16, P8, PNN_POSIT8_0, PNN_POSIT16_1, PNN_POSIT8_0)
     PNN_AXPY_F64(P12_2, P12_2, P8_2, PNN_POSIT12_2, PNN_POSIT12_2, PNN_POSIT8_2)
     PNN_AXPY_F64(P8_2, P12_2, P8_2, PNN_POSIT8_2, PNN_POSIT12_2, PNN_POSIT8_2)
+    PNN_AXPY_F64(P12_1, P12_1, P8_1, PNN_POSIT12_1, PNN_POSIT12_1, PNN_POSIT8_1)
+    PNN_AXPY_F64(P8_1, P12_1, P8_1, PNN_POSIT8_1, PNN_POSIT12_1, PNN_POSIT8_1)
 #undef PNN_AXPY_F64
     return false;
 }
@@ -374,18 +378,7 @@ extern "C" int posit_axpy(void* stream, int fx, int fy, uint32_t alpha_bits, int
     if (!x || !y) return PNN_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     discard_stale_hip_error();
-    {
-        int64_t done = 0;
-        if (axpy_f64_dispatch(st, fx, fy, fcopy, y_copy != nullptr, alpha_bits, n, x, y, y_copy, &done)) {
-            if (hipGetLastError() != hipSuccess) return PNN_EHIP;
-            if (done == n) return PNN_OK;
-            // the last n % 8 elements go through the generic path below
-            x = (const uint8_t*)x + done * elem_size(fx);
-            y = (uint8_t*)y + done * elem_size(fy);
-            if (y_copy) y_copy = (uint8_t*)y_copy + done * elem_size(fcopy);
-            n -= done;
-        }
-    }
+    if (axpy_f64_dispatch(st, fx, fy, fcopy, y_copy != nullptr, alpha_bits, n, x, y, y_copy)) return hip_status(hipGetLastError());
     if (!is_standard(fx) || !is_standard(fy) || (y_copy && !is_standard(fcopy))) {
         AxpyRT op;
         op.fx = fmt_of_code(fx);

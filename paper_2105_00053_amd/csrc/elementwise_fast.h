@@ -9,8 +9,11 @@
 // (s, err) IS the exact result.  The one rounding to posit<N,ES> needs the leading ~N bits of s and
 // "is anything nonzero below them", which err supplies when s itself was rounded.  Decoding is a
 // look-up: a table in LDS maps the magnitude pattern to the high word of its binary64 (built once
-// per workgroup with the field decoder of Eq. 2; 128 KB for posit<16,1>, so one 1024-thread
-// workgroup per compute unit walks the tensor in a grid-stride loop).
+// per workgroup; 128 KB for posit<16,1>, so one 1024-thread workgroup per compute unit walks the
+// tensor in a grid-stride loop).  Bound by memory, with the vector ALU close behind (about 50
+// instructions per element): 2^24 elements of posit<16,1> with a posit<8,0> copy take 28.8 us, 4.1 TB/s.
+// They took 38.1 us when the general field decoder built the tables (6 us a workgroup) and a second
+// launch did the last n % 8 elements.
 //
 // The narrowing conversion.  posit<16,1> -> posit<8,0> is a monotone step function of the pattern
 // (as a signed integer).  Inside an aligned block of 64 source patterns it takes at most two values,
@@ -39,14 +42,19 @@ PNN_HD uint32_t funnel_shr(uint32_t hi, uint32_t lo, int sh) {
 
 // High word of the binary64 that equals the posit with magnitude pattern `a` (0 .. 2^(N-1)); the low
 // word is zero because no format here has more than 20 fraction bits.  Zero gives 0.0, the NaR
-// pattern a quiet NaN: both then pass through the arithmetic as IEEE special values.
+// pattern a quiet NaN: both then pass through the arithmetic as IEEE special values.  No branches: a
+// workgroup decodes up to 32 K patterns into its table before it starts (the general field decoder took
+// 6 us for them).
 template <class F>
 PNN_HD uint32_t f64_hi_of_magnitude(uint32_t a) {
     static_assert(F::N <= 16 && F::FB <= 20, "the value must fit the high word of a binary64");
-    if (a == 0) return 0u;
-    if (a == F::NAR) return 0x7FF80000u;
-    const Real32 r = decode_fields32<F>(a);
-    return ((uint32_t)(r.scale + 1023) << 20) | (r.frac >> 12);
+    const uint32_t x = a << (33 - F::N);                    // regime on top; at least 17 zeros below the pattern
+    const uint32_t ones = (uint32_t)((int32_t)x >> 31);     // the regime is a run of ones
+    const uint32_t run = (uint32_t)clz32(x ^ ones);
+    const uint32_t k = (run ^ ~ones) + 1u + 2u * ones;      // run - 1 or -run
+    const uint32_t rest = (x << (run & 31u)) << 1;          // exponent, then fraction
+    const uint32_t hi = ((1023u + (k << F::ES)) << 20) + (rest >> (12 - F::ES));
+    return a == 0u ? 0u : (a == F::NAR ? 0x7FF80000u : hi);
 }
 
 // The same for a signed pattern.
@@ -161,8 +169,11 @@ template <class FS, class FD>
 PNN_HD uint32_t narrow_step_entry(uint32_t b) {
     static_assert(FS::N == 16 && FD::N == 8, "posit<16,es> to posit<8,es>");
     typedef Fmt<FD::N + 1, FD::ES> Mid;  // its odd patterns are the ties between neighbours of FD
+    // conversions of magnitude patterns: decode, round
+    auto narrow = [](uint32_t a) { return round_sum_to_body<FD>(f64_hi_of_magnitude<FS>(a), 0u, 0u); };
+    auto tie = [](uint32_t v) { return (int)round_sum_to_body<FS>(f64_hi_of_magnitude<Mid>(2u * v + 1u), 0u, 0u); };
     const uint32_t p0 = b << 6;
-    const uint32_t base = (uint32_t)PositToPosit<FS, FD>()(p0) & 0xFFu;
+    const uint32_t base = p0 == 0u ? 0u : (p0 == FS::NAR ? FD::NAR : ((p0 & FS::NAR) ? 0u - narrow((0u - p0) & FS::MASK) : narrow(p0))) & 0xFFu;
     const int sbase = (int)(int8_t)base;
     int t;  // first source pattern, as a signed integer, that converts to base + 1
     if (base == 0x7Fu) {
@@ -173,7 +184,7 @@ PNN_HD uint32_t narrow_step_entry(uint32_t b) {
         if (base == 0u) {
             t = 1;  // every positive value converts to at least minpos
         } else {
-            const int m = (int)PositToPosit<Mid, FS>()(2u * base + 1u);
+            const int m = tie(base);
             t = (base & 1u) ? m : m + 1;  // the tie itself goes to the even one of base, base + 1
         }
     } else {
@@ -181,7 +192,7 @@ PNN_HD uint32_t narrow_step_entry(uint32_t b) {
         if (v == 1) {
             t = 0;  // only zero converts to zero
         } else {
-            const int m = (int)PositToPosit<Mid, FS>()(2u * (uint32_t)(v - 1) + 1u);
+            const int m = tie((uint32_t)(v - 1));
             t = ((v - 1) & 1) == 0 ? -m : -m + 1;
         }
     }
@@ -240,10 +251,27 @@ template <class F>
 struct ValueTable {
     static constexpr bool SIGNED = F::N <= 12;
     static constexpr int ENTRIES = SIGNED ? (1 << F::N) : (1 << (F::N - 1)) + 1;
-    __device__ __forceinline__ static void fill(uint32_t* tab, int t, int threads) {
-        for (int a = t; a < ENTRIES; a += threads) {
-            if constexpr (SIGNED) tab[a] = f64_hi(f64_of_pattern<F>((uint32_t)a));
-            else tab[a] = f64_hi_of_magnitude<F>((uint32_t)a);
+    // A thread's entries of the large table are THREADS patterns apart, so that all but the first and the last know their
+    // regime before they know the thread: a constant and the thread's bits behind it.
+    template <int THREADS>
+    __device__ __forceinline__ static void fill(uint32_t* tab, int t) {
+        if constexpr (SIGNED) {
+            for (int a = t; a < ENTRIES; a += THREADS) tab[a] = f64_hi(f64_of_pattern<F>((uint32_t)a));
+        } else {
+            constexpr int STEPS = (ENTRIES - 1) / THREADS;
+            static_assert(STEPS >= 4 && STEPS * THREADS == ENTRIES - 1 && (THREADS & (THREADS - 1)) == 0, "whole steps, leading bits first");
+#pragma unroll
+            for (int j = 0; j < STEPS; ++j) {
+                const uint32_t a = (uint32_t)(j * THREADS);
+                if (j == 0 || j == STEPS - 1) {
+                    tab[a + t] = f64_hi_of_magnitude<F>(a + t);
+                } else {
+                    const uint32_t x = a << (33 - F::N);
+                    const int run = clz32(x ^ (uint32_t)((int32_t)x >> 31));
+                    tab[a + t] = f64_hi_of_magnitude<F>(a) + ((uint32_t)t << (22 + F::ES - F::N + run));
+                }
+            }
+            if (t == 0) tab[ENTRIES - 1] = f64_hi_of_magnitude<F>(F::NAR);
         }
     }
     __device__ __forceinline__ static uint32_t one(const uint32_t* tab, uint32_t p) {
@@ -305,7 +333,7 @@ struct CopyTable {
 template <class FX, class FY, class FC, bool COPY, int THREADS>
 __global__ __launch_bounds__(THREADS) void axpy_f64_kernel(const typename Storage<FX::N>::T* __restrict__ x,
                                                            typename Storage<FY::N>::T* __restrict__ y,
-                                                           typename Storage<FC::N>::T* __restrict__ yc, int64_t nvec, uint32_t alpha) {
+                                                           typename Storage<FC::N>::T* __restrict__ yc, int64_t n, uint32_t alpha) {
     typedef typename Storage<FX::N>::T TX;
     typedef typename Storage<FY::N>::T TY;
     typedef typename Storage<FC::N>::T TC;
@@ -316,15 +344,28 @@ __global__ __launch_bounds__(THREADS) void axpy_f64_kernel(const typename Storag
     __shared__ uint32_t tabX[SAME ? 1 : ValueTable<FX>::ENTRIES];
     __shared__ typename CopyTable<FY, FC>::Entry tabC[COPY ? CopyTable<FY, FC>::ENTRIES : 1];
     const int t = threadIdx.x;
-    ValueTable<FY>::fill(tabY, t, THREADS);
-    if constexpr (!SAME) ValueTable<FX>::fill(tabX, t, THREADS);
+    typedef Pack<uint32_t, XW> XV;
+    typedef Pack<uint32_t, 4> YV;
+    const int64_t nvec = n / 8, stride = (int64_t)gridDim.x * THREADS;
+    int64_t i = (int64_t)blockIdx.x * THREADS + t;
+    XV xa = {};
+    YV ya = {};
+    if (i < nvec) {  // in flight while the tables are built
+        xa = reinterpret_cast<const XV*>(x)[i];
+        ya = reinterpret_cast<const YV*>(y)[i];
+    }
+    ValueTable<FY>::template fill<THREADS>(tabY, t);
+    if constexpr (!SAME) ValueTable<FX>::template fill<THREADS>(tabX, t);
     if constexpr (COPY) CopyTable<FY, FC>::fill(tabC, t, THREADS);
     __syncthreads();
     const uint32_t* tx = SAME ? tabY : tabX;
     const double ad = f64_from_words(ValueTable<FY>::one(tabY, alpha), 0u);
-    const int64_t stride = (int64_t)gridDim.x * THREADS;
-    typedef Pack<uint32_t, XW> XV;
-    typedef Pack<uint32_t, 4> YV;
+    if (blockIdx.x == gridDim.x - 1 && t < (int)(n & 7)) {  // the last n % 8 elements, one per thread
+        const int64_t j = nvec * 8 + t;
+        const uint32_t r = axpy_f64<FY>(ad, f64_from_words(ValueTable<FX>::one(tx, x[j]), 0u), f64_from_words(ValueTable<FY>::one(tabY, y[j]), 0u));
+        y[j] = (TY)r;
+        if constexpr (COPY) yc[j] = (TC)CopyTable<FY, FC>::apply(tabC, r);
+    }
     // one step: the update of vector i from its already loaded operands
     auto step = [&](int64_t i, const XV& xv, const YV& yv) {
         uint32_t shi[8], pw[4];  // pw: the new patterns, two per word
@@ -375,10 +416,7 @@ __global__ __launch_bounds__(THREADS) void axpy_f64_kernel(const typename Storag
     };
     // Two vectors in flight per thread: the loads of one are issued before the other is computed (a thread's
     // vectors i, i + stride, ... never overlap another thread's, so loading ahead of the stores is safe).
-    int64_t i = (int64_t)blockIdx.x * THREADS + t;
     if (i >= nvec) return;
-    XV xa = reinterpret_cast<const XV*>(x)[i];
-    YV ya = reinterpret_cast<const YV*>(y)[i];
     for (;;) {
         const int64_t ib = i + stride;
         const bool more_b = ib < nvec;

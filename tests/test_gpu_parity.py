@@ -118,6 +118,21 @@ def test_axpy_large_tensors_take_the_binary64_kernel(fx, fy, fc, n):
             _assert_equal(to_np(res, fy), want, "axpy y")
 
 
+@pytest.mark.parametrize("fx,fy,fc", [("p16", "p16", "p8"), ("p8", "p16", "p8"), ("p12_1", "p12_1", "p8_1"), ("p8_1", "p12_1", "p8_1")])
+@pytest.mark.parametrize("tail", [0, 1, 7])
+def test_axpy_binary64_kernel_last_elements(fx, fy, fc, tail):
+    """The smallest size of the kernel with LDS decode tables: the last n % 8 elements are its last workgroup's."""
+    n = 2 ** 19 + tail
+    rng = np.random.default_rng(1900 + tail)
+    x, y = rand_patterns(rng, n, fx), rand_patterns(rng, n, fy)
+    alpha = int(rand_patterns(rng, 1, fy, 0, allow_nar=False)[0])
+    yd = to_dev(y)
+    res = pn.posit_axpy(alpha, to_dev(x), yd, fx, fy, fc)
+    want = oracle_axpy_chunked(alpha, x, y, fx, fy, fc)
+    _assert_equal(to_np(res[0], fy), want[0], "axpy y")
+    _assert_equal(to_np(res[1], fc), want[1], "axpy copy")
+
+
 def test_convert_posit16_to_posit8_large_takes_the_step_table_kernel():
     n = (1 << 21) + 11
     rng = np.random.default_rng(5)
