@@ -97,10 +97,22 @@ __device__ __forceinline__ void dig_load16(const T* q, int64_t step, int n, uint
     for (int b = 0; b < 16; ++b) pat[b] = b < n ? (uint32_t)q[b * step] : 0u;
 }
 
+// A wave's digits change hands in LDS before they are stored, so that a store instruction writes runs of the planes and not
+// 16 bytes in every 64 (NP planes) or more (posit(8,2), 4 M elements and fewer: 9.4 to 8.4 us on average).  Slot of plane j
+// of thread s: rows of NP slots, rotated so that sixteen threads reach sixteen different bank groups both ways.
+template <int NP>
+__device__ __forceinline__ int dig_xch(int s, int j) { return s * NP + (j ^ ((s >> (NP == 4 ? 2 : 1)) & (NP - 1))); }
+
+// LDS accesses of a wave complete in order: only the compiler has to keep them so.
+__device__ __forceinline__ void dig_wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <class F, int NP, int PX>
 __device__ __forceinline__ void dig_conv_planes(const typename Storage<F::N>::T* __restrict__ src, int HW, int64_t pixels, uint4* __restrict__ act,
                                                 const typename Storage<F::N>::T* __restrict__ w, const DigConvPlan& p, uint4* __restrict__ wdst,
-                                                uint4* __restrict__ zero, unsigned wblocks, const DigInfo& d, uint64_t* tab) {
+                                                uint4* __restrict__ zero, unsigned wblocks, const DigInfo& d, uint64_t* tab, uint4* xch) {
     typedef typename Storage<F::N>::T T;
     typedef typename DigWord<NP>::T W;
     const int t = threadIdx.x;
@@ -140,21 +152,25 @@ __device__ __forceinline__ void dig_conv_planes(const typename Storage<F::N>::T*
         for (int i = 0; i < NP; ++i) out[i * 64] = make_uint4(pl[i][0], pl[i][1], pl[i][2], pl[i][3]);
         return;
     }
-    const int64_t groups = pixels / PX;  // PX divides HW, hence pixels
-    const int64_t idx = (int64_t)(blockIdx.x - wblocks) * 256 + t;
-    if (idx >= groups * p.Cg) return;
-    const int cg = (int)(idx / groups);
-    const int64_t pix = (idx - (int64_t)cg * groups) * PX;
-    const int64_t img = pix / HW, hw = pix - img * HW;
-    const T* q = src + (img * p.CI + cg * 16) * (int64_t)HW + hw;
-    const int nch = p.CI - cg * 16 < 16 ? p.CI - cg * 16 : 16;
+    // channel groups run fastest over the threads, so a wave's digits are runs of Cg * NP * 16 bytes, PX pixels apart
+    const uint32_t total = (uint32_t)(pixels / PX) * (uint32_t)p.Cg;  // PX divides HW, hence pixels
+    const uint32_t first = (blockIdx.x - wblocks) * 256u + ((uint32_t)t & ~63u), idx = first + ((uint32_t)t & 63u);
     uint32_t in[16];  // PX patterns of one channel
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        if (b >= nch) in[b] = 0;
-        else if (PX > 1) in[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * HW);
-        else in[b] = q[(int64_t)b * HW];
+    for (int b = 0; b < 16; ++b) in[b] = 0;
+    if (idx < total) {
+        const uint32_t pg = idx / (uint32_t)p.Cg, cg = idx - pg * (uint32_t)p.Cg, pix = pg * PX;
+        const uint32_t img = pix / (uint32_t)HW, hw = pix - img * (uint32_t)HW;
+        const T* q = src + ((int64_t)img * p.CI + cg * 16) * (int64_t)HW + hw;
+        const int nch = p.CI - (int)cg * 16 < 16 ? p.CI - (int)cg * 16 : 16;
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            if (b >= nch) continue;
+            if (PX > 1) in[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * HW);
+            else in[b] = q[(int64_t)b * HW];
+        }
     }
+    uint4* const mine = xch + (t >> 6) * (64 * NP);
 #pragma unroll
     for (int px = 0; px < PX; ++px) {
         W wd[16];
@@ -162,9 +178,18 @@ __device__ __forceinline__ void dig_conv_planes(const typename Storage<F::N>::T*
         for (int b = 0; b < 16; ++b) wd[b] = word((in[b] >> (8 * (int)sizeof(T) * px)) & (sizeof(T) == 1 ? 0xFFu : 0xFFFFu));
         uint32_t pl[NP][4];
         dig_planes_of<NP>(wd, pl);
-        uint4* out = act + ((pix + px) * p.Cg + cg) * NP;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) out[i] = make_uint4(pl[i][0], pl[i][1], pl[i][2], pl[i][3]);
+        for (int i = 0; i < NP; ++i) mine[dig_xch<NP>(t & 63, i)] = make_uint4(pl[i][0], pl[i][1], pl[i][2], pl[i][3]);
+        dig_wave_fence();
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const uint32_t s = (uint32_t)(i * 64 + (t & 63)) / NP, j = (uint32_t)(t & 63) % NP;  // plane j of thread s of the wave
+            if (first + s < total) {
+                const uint32_t pg = (first + s) / (uint32_t)p.Cg, cg = first + s - pg * (uint32_t)p.Cg;
+                act[((int64_t)(pg * PX + px) * p.Cg + cg) * NP + j] = mine[dig_xch<NP>(s, j)];
+            }
+        }
+        dig_wave_fence();
     }
 }
 
@@ -179,8 +204,9 @@ __global__ __launch_bounds__(256) void dig_conv_digits_kernel(const typename Sto
     typedef DigFormat<F> D;
     __shared__ uint64_t tab[F::N == 8 ? 256 : 1];
     const DigInfo d = dig_read_decision<F>(stats, info, D::NP1 == 4, blockIdx.x == 0);
-    if (D::NP1 == 4 && d.np == 4) dig_conv_planes<F, 4, PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab);
-    else dig_conv_planes<F, dig_conv_wide<F>(), PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab);
+    __shared__ uint4 xch[256 * dig_conv_wide<F>()];
+    if (D::NP1 == 4 && d.np == 4) dig_conv_planes<F, 4, PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab, xch);
+    else dig_conv_planes<F, dig_conv_wide<F>(), PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab, xch);
 }
 
 struct DigConvArgs {
@@ -234,7 +260,10 @@ __device__ __forceinline__ void dig_store_rows_bias(int first, int rows, const D
 // Four waves as WY x (4 / WY), one block of 32 x 32 outputs each (rows: output channels, columns: positions).  WY = 1 (32 x
 // 128 outputs) serves layers of at most 32 output channels.  A ring of ST k blocks as in dig_gemm_kernel; operand registers
 // are read a step ahead.  A convolution's reduction is short, so prologue and rounding weigh as much as the matrix
-// instructions: all planes are multiplied.
+// instructions: four planes are all multiplied, and outputs of at most 16 bits are rounded through binary64 in registers
+// and stored from there (128 images of 32 channels at 32 x 32, posit(8,2), 3 x 3 to 32 channels: 31 us, with integers of 96
+// bits through LDS 36).  The kernel of eight planes is bound by the matrix pipes, so without NaR it multiplies only the
+// planes that hold digits: weights over most of the range of posit(8,2) 46 us, all 8 x 8 pairs 61.
 template <int NP, int WY, int ST>
 __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigConvArgs a) {
     if (__builtin_amdgcn_readfirstlane(a.info->np) != a.np) return;
@@ -315,6 +344,7 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigCon
 
     const int a_nar = __builtin_amdgcn_readfirstlane(a.info->nar[1]), b_nar = __builtin_amdgcn_readfirstlane(a.info->nar[0]);
     const int at = __builtin_amdgcn_readfirstlane(a.info->base[0] + a.info->base[1]);
+    const bool by_f64 = NP <= 4 && a.fout.n <= 16;
     __syncthreads();  // ktab
 #pragma unroll
     for (int k = 0; k < ST - 1; ++k)
@@ -326,14 +356,19 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigCon
         const int m = tm * TR + t;
         if (a.bias && m < a.MO) {
             const uint32_t bp = dig_load_pattern(a.bias, m, a.fin.n);
-            DigRound rd;
-            rd.fin = a.fin;
-            rd.at = 0;
-            const uint32_t none[3] = {0, 0, 0};
-            uint32_t u[4];
-            dig_add_bias<3>(none, rd, bp, u);
             nar = bp == a.fin.nar() ? 1u : 0u;
-            add = make_uint4(u[0], u[1], u[2], u[3]);
+            if (by_f64) {
+                const double v = nar ? 0.0 : dig_f64_of_pattern(bp, a.fin, 2 * a.fin.maxs() - at);
+                add = make_uint4(f64_lo(v), f64_hi(v), 0u, 0u);
+            } else {
+                DigRound rd;
+                rd.fin = a.fin;
+                rd.at = 0;
+                const uint32_t none[3] = {0, 0, 0};
+                uint32_t u[4];
+                dig_add_bias<3>(none, rd, bp, u);
+                add = make_uint4(u[0], u[1], u[2], u[3]);
+            }
         }
         rowv[t] = nar;
         badd[t] = add;
@@ -378,18 +413,23 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigCon
             step(kb, f0, f1);
             if (kb + 1 < a.KB) step(kb + 1, f1, f0);
         }
-    } else {  // one set of operand registers, read in their own step
-        for (int kb = 0; kb < a.KB; ++kb) {
-            if (kb + ST - 2 < a.KB) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
-            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-            pcm_ring_barrier();
-            if (kb + ST - 1 < a.KB) issue(kb + ST - 1);
-            const int nb = (kb % ST) * (RPB * 64);
-            f0.template load<0>(sa0 + nb, sb0 + nb);
-            markers(f0);
-            dig_mma<NP, 0, NP, 0, NP>(f0, acc);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    } else {  // one set of operand registers, read in their own step; the planes that hold anything
+        auto loop = [&](auto ta, auto tb) {
+            constexpr int TA = ta, TB = tb;
+            for (int kb = 0; kb < a.KB; ++kb) {
+                if (kb + ST - 2 < a.KB) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
+                else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+                pcm_ring_barrier();
+                if (kb + ST - 1 < a.KB) issue(kb + ST - 1);
+                const int nb = (kb % ST) * (RPB * 64);
+                f0.template load<0, TA, TB>(sa0 + nb, sb0 + nb);
+                if constexpr (TA == NP) markers(f0);
+                dig_mma<NP, 0, TA, 0, TB>(f0, acc);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        const int ua = __builtin_amdgcn_readfirstlane(a.info->used[1]), ub = __builtin_amdgcn_readfirstlane(a.info->used[0]);
+        dig_for_planes<NP>(a_nar || b_nar ? NP : ua, ub, loop);
     }
     __syncthreads();  // the last block is read: the ring is free
 
@@ -399,6 +439,52 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigCon
     if (lane < 32) {
         if (wx == 0 && row_nar) rowv[wy * 32 + lane] = 1u;  // every wave of a row block saw the same rows
         if (wy == 0) colv[wx * 32 + lane] = col_nar;
+    }
+    if constexpr (NP <= 4) {
+        if (by_f64) {  // rounded and stored where the matrix instruction leaves them: 16 rows of one position per lane
+            __syncthreads();
+            const int n = tn * TC + wx * 32 + (lane & 31);
+            if (n >= a.P) return;
+            const int img = n / hw_o, rem = n - img * hw_o;
+            const int64_t o = ((int64_t)img * a.MO + tm * TR) * hw_o + rem;
+            const int rows = a.MO - tm * TR;
+            const DigF64Round round(a.fout, 2 * a.fin.maxs() - at);
+            const uint32_t cnar = col_nar;
+            const uint32_t nar = a.fout.nar();
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                const int lr0 = wy * 32 + 8 * rq + 4 * (lane >> 5);
+                const uint4 fl = *reinterpret_cast<const uint4*>(rowv + lr0);
+                const uint32_t flag[4] = {fl.x | cnar, fl.y | cnar, fl.z | cnar, fl.w | cnar};
+                double s[4], e[4];
+                uint32_t v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    double hi, lo;
+                    DigF64<NP>::parts(acc, 4 * rq + u, hi, lo);
+                    dig_two_sum(hi, lo, s[u], e[u]);
+                }
+                if (a.bias) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint2 b = *reinterpret_cast<const uint2*>(badd + lr0 + u);
+                        dig_add_f64(s[u], e[u], f64_from_words(b.y, b.x));
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = flag[u] ? nar : round(s[u], e[u]);
+                if (a.fout.n <= 8) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (lr0 + u < rows) ((uint8_t*)a.out)[o + (int64_t)(lr0 + u) * hw_o] = (uint8_t)v[u];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (lr0 + u < rows) ((uint16_t*)a.out)[o + (int64_t)(lr0 + u) * hw_o] = (uint16_t)v[u];
+                }
+            }
+            return;
+        }
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -828,18 +914,23 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_bw_kernel(Dig
             step(kb, f0, f1);
             if (kb + 1 < nkb) step(kb + 1, f1, f0);
         }
-    } else {  // one set of operand registers, read in their own step
-        for (int kb = 0; kb < nkb; ++kb) {
-            if (kb + ST - 2 < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
-            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-            pcm_ring_barrier();
-            if (kb + ST - 1 < nkb) issue();
-            const int nb = (kb % ST) * (RPB * 64);
-            f0.template load<0>(sa0 + nb, sb0 + nb);
-            markers(f0);
-            dig_mma<NP, 0, NP, 0, NP>(f0, acc);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    } else {  // one set of operand registers, read in their own step; the planes that hold anything (see dig_conv_kernel)
+        auto loop = [&](auto ta, auto tb) {
+            constexpr int TA = ta, TB = tb;
+            for (int kb = 0; kb < nkb; ++kb) {
+                if (kb + ST - 2 < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
+                else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+                pcm_ring_barrier();
+                if (kb + ST - 1 < nkb) issue();
+                const int nb = (kb % ST) * (RPB * 64);
+                f0.template load<0, TA, TB>(sa0 + nb, sb0 + nb);
+                if constexpr (TA == NP) markers(f0);
+                dig_mma<NP, 0, TA, 0, TB>(f0, acc);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        const int ua = __builtin_amdgcn_readfirstlane(a.info->used[1]), ub = __builtin_amdgcn_readfirstlane(a.info->used[0]);
+        dig_for_planes<NP>(a_nar || b_nar ? NP : ua, ub, loop);
     }
 
     // ---- this slice's integers and NaR flags ----

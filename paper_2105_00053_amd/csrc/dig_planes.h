@@ -20,10 +20,16 @@
 // the top digit within [-64, 64], so -128 there marks NaR.
 #pragma once
 
+#include <type_traits>
+
+#include "elementwise_fast.h"
 #include "gemm_p8_mfma.h"
 #include "quire_gemm.h"
 
 namespace pnn {
+
+template <int V>
+using dig_int = std::integral_constant<int, V>;
 
 constexpr int DIG_MAXK = 16352;      // longest reduction of one set of int32 sums: 8 digit pairs * 2^14 * K < 2^31
 constexpr int DIG_STAT_WGS = 128;    // workgroups that scan one operand
@@ -40,6 +46,7 @@ struct DigInfo {
     int np;
     int base[2];
     int nar[2];
+    int used[2];  // planes 0 .. used - 1 hold all digits of the operand's values; the marker of NaR is in the top one
 };
 
 // Plane counts by format.  COVER: NP2 planes hold the whole format.  posit<32,2> has no narrow variant (NP1 = 0): six planes,
@@ -51,7 +58,7 @@ struct DigFormat {
     static constexpr bool COVER = FULL <= 8;
     static constexpr int NP2 = COVER ? FULL : 8;
     static constexpr int NP1 = !COVER ? 0 : NP2 <= 4 ? 3 : 4;
-    static constexpr bool BASE0 = COVER && NP2 > 4;  // the wide kernel counts its planes from minpos
+    static constexpr bool BASE0 = COVER && NP2 > 4;  // the wide kernel counts its planes from the lowest bit of the operand
 };
 
 template <int NP> struct DigWord { typedef uint64_t T; };
@@ -103,8 +110,9 @@ PNN_HD DigInfo dig_decide(const uint32_t (&low)[2], const uint32_t (&high)[2], c
     if (D::NP1 != 0 && narrow && fits(D::NP1)) r.np = D::NP1;
     else if (D::BASE0 || fits(D::NP2)) r.np = D::NP2;
     for (int o = 0; o < 2; ++o) {
-        r.base[o] = D::BASE0 && r.np != D::NP1 ? 0 : hi[o] + 1 - dig_capacity<F>(high[o], nar[o], r.np);
+        r.base[o] = D::BASE0 && r.np != D::NP1 ? lo[o] : hi[o] + 1 - dig_capacity<F>(high[o], nar[o], r.np);
         r.nar[o] = nar[o] ? 1 : 0;
+        r.used[o] = (hi[o] + 1 - r.base[o] + 9) / 8;  // |v| < 2^b takes ceil((b + 2) / 8) balanced digits at most
     }
     return r;
 }
@@ -298,16 +306,16 @@ __device__ __forceinline__ void dig_planes_of(const typename DigWord<NP>::T (&w)
 
 // ---- the inner step: one k block of 32, one 32 x 32 block of outputs per wave ----
 
-// Planes SP .. NP - 1 of the two blocks a wave multiplies in a step, as operand registers.
+// Planes SP .. TA - 1 and SP .. TB - 1 of the two blocks a wave multiplies in a step, as operand registers.
 template <int NP>
 struct DigFrag {
     pm_v4i a[NP], b[NP];
-    template <int SP>
+    template <int SP, int TA = NP, int TB = NP>
     __device__ __forceinline__ void load(const uint4* sa, const uint4* sb) {
 #pragma unroll
         for (int i = NP - 1; i >= SP; --i) {
-            b[i] = __builtin_bit_cast(pm_v4i, sb[i * 64]);
-            a[i] = __builtin_bit_cast(pm_v4i, sa[i * 64]);
+            if (i < TB) b[i] = __builtin_bit_cast(pm_v4i, sb[i * 64]);
+            if (i < TA) a[i] = __builtin_bit_cast(pm_v4i, sa[i * 64]);
         }
     }
 };
@@ -322,6 +330,23 @@ __device__ __forceinline__ void dig_mma(const DigFrag<NP>& f, pm_v16i (&acc)[2 *
             const int j = ((i - IF) & 1) ? JT - 1 - (jj - JF) : jj;
             acc[i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.a[i], f.b[j], acc[i + j], 0, 0, 0);
         }
+}
+
+// Calls loop(TA, TB) with the fewest planes that hold the operands' digits, four at least: 4 .. 7 each, or all NP of both.
+template <int NP, class Loop>
+__device__ __forceinline__ void dig_for_planes(int ua, int ub, const Loop& loop) {
+    static_assert(NP == 8, "eight slots");
+    auto second = [&](auto ta) {
+        if (ub <= 4) loop(ta, dig_int<4>());
+        else if (ub == 5) loop(ta, dig_int<5>());
+        else if (ub == 6) loop(ta, dig_int<6>());
+        else loop(ta, dig_int<7>());
+    };
+    if (ua > 7 || ub > 7) loop(dig_int<NP>(), dig_int<NP>());
+    else if (ua <= 4) second(dig_int<4>());
+    else if (ua == 5) second(dig_int<5>());
+    else if (ua == 6) second(dig_int<6>());
+    else second(dig_int<7>());
 }
 
 // The pairs of groups of which at least one lies below group g0 (ma, mb: the blocks' bits, uniform).
@@ -482,6 +507,97 @@ __device__ __forceinline__ uint32_t dig_round(const uint32_t (&q)[L], const DigR
     }
     return nar ? d.fout.nar() : res;
 }
+
+// ---- the same through binary64: up to four planes, formats of at most 16 bits ----
+//
+// The sums fall into two parts that are exact in binary64: a sum of s holds at most min(s + 1, 2 NP - 1 - s) digit pairs of
+// at most 2^14 each over at most 16352 indices, so that for four planes sums 0 .. 2 stay below 2^47 and sums 3 .. 6, in
+// units of 2^24, below 2^53 (with three planes: 0 and 1, 2 .. 4, less).  The parts' sum and its exact error round as in
+// elementwise_fast.h: about 50 instructions per output and no pass through LDS, where the integers' way takes over 100.
+
+// s + e = a + b exactly, s the rounded sum
+PNN_HD void dig_two_sum(double a, double b, double& s, double& e) {
+    s = a + b;
+    const double bb = s - a;
+    e = (a - (s - bb)) + (b - bb);
+}
+
+// (s, e) + b: s the new rounded sum, e with the sign of the exact error and less than a unit of s's last place.  If s + b
+// cancels (e1 = 0) the second sum is exact; otherwise u is below s1's last places, so r is a multiple of u's unit and v,
+// half of that at most, decides the sign only where r is zero.
+PNN_HD void dig_add_f64(double& s, double& e, double b) {
+    double s1, e1, u, v, r;
+    dig_two_sum(s, b, s1, e1);
+    dig_two_sum(e1, e, u, v);
+    dig_two_sum(s1, u, s, r);
+    e = r + v;
+}
+
+// value of a pattern (not NaR) times 2^up; formats of at most 16 bits
+PNN_HD double dig_f64_of_pattern(uint32_t p, const FmtRT& f, int up) {
+    if (p == 0) return 0.0;
+    bool neg;
+    int scale, nf;
+    uint32_t fr;
+    decode_core(p, f.n, f.es, neg, scale, fr, nf);
+    return f64_from_words(((uint32_t)(scale + up + 1023) << 20) | (fr >> 12) | (neg ? 0x80000000u : 0u), 0u);
+}
+
+// Constants of the rounding to a format of at most 16 bits, and the weight of the sums' unit (2^-qfrac).
+struct DigF64Round {
+    uint32_t minhi, maxhi, qf, himask, lomask, jam, half, mask;
+    int esh, n;
+    PNN_HD DigF64Round(const FmtRT& f, int qfrac) {
+        const int maxs = f.maxs(), hb = f.n - 12 + f.es;
+        minhi = (uint32_t)(1023 - maxs) << 20;
+        maxhi = (uint32_t)(1023 + maxs) << 20;
+        qf = (uint32_t)qfrac << 20;
+        himask = hb > 0 ? (1u << hb) - 1u : 0u;
+        lomask = hb >= 0 ? 0xFFFFFFFFu : 0xFFFFFFFFu >> -hb;
+        jam = 1u << f.n;
+        half = (1u << (32 - f.n)) - 1u;
+        mask = f.mask();
+        esh = 20 + f.es;
+        n = f.n;
+    }
+    // s + err, rounded once (round_sum_to_body explains the steps)
+    PNN_HD uint32_t operator()(double s, double err) const {
+        uint32_t hi = f64_hi(s);
+        const uint32_t lo = f64_lo(s), ehi = f64_hi(err);
+        const bool toward_zero = (ehi ^ (hi & 0x80000000u)) > 0x80000000u;
+        const uint32_t sm = (uint32_t)((int32_t)hi >> 31);
+        hi -= toward_zero && lo == 0u ? 1u : 0u;
+        const uint32_t ah0 = (hi & 0x7FFFFFFFu) - qf;
+        const uint32_t ah = ah0 < minhi ? minhi : (ah0 > maxhi ? maxhi : ah0);
+        const uint32_t h1 = ah - (1023u << 20);
+        const int k = (int32_t)h1 >> esh;
+        const uint32_t sg = (uint32_t)(k >> 31);
+        const uint32_t kk = (uint32_t)k ^ sg;
+        const uint32_t tail = funnel_shr(h1, lo, esh);
+        const uint32_t below = (h1 & himask) | (lo & lomask) | (ehi << 1);
+        const uint32_t w = funnel_shr(2u, (tail | (below != 0u ? jam : 0u)) ^ sg, 2);
+        const uint32_t x = (uint32_t)((int32_t)w >> kk) ^ sg;
+        const uint32_t lsb = (x >> (33 - n)) & 1u;
+        const uint32_t body = (x + half + lsb) >> (33 - n);
+        return s == 0.0 ? 0u : ((body ^ sm) - sm) & mask;
+    }
+};
+
+#if defined(__HIPCC__)
+template <int NP>
+struct DigF64 {
+    static_assert(NP == 3 || NP == 4, "parts that are exact in binary64");
+    static constexpr int NC = 2 * NP - 1, LOW = NP - 1;  // sums of the low part
+    static __device__ __forceinline__ void parts(const pm_v16i (&acc)[NC], int r, double& hi, double& lo) {
+        hi = (double)acc[LOW][r] * pow2d(8 * LOW);
+#pragma unroll
+        for (int s = LOW + 1; s < NC; ++s) hi = __builtin_fma((double)acc[s][r], pow2d(8 * s), hi);
+        lo = (double)acc[0][r];
+#pragma unroll
+        for (int s = 1; s < LOW; ++s) lo = __builtin_fma((double)acc[s][r], pow2d(8 * s), lo);
+    }
+};
+#endif
 
 __device__ __forceinline__ uint32_t dig_load_pattern(const void* p, int64_t i, int n) {
     return n <= 8 ? ((const uint8_t*)p)[i] : n <= 16 ? ((const uint16_t*)p)[i] : ((const uint32_t*)p)[i];

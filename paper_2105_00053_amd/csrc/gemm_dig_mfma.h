@@ -11,8 +11,6 @@
 // lowest plane its multiplication has to start from.
 #pragma once
 
-#include <type_traits>
-
 #include "dig_planes.h"
 
 namespace pnn {
@@ -150,8 +148,6 @@ struct DigGemmArgs {
     int M, N, tiles_m, tiles_n;
 };
 
-template <int V>
-using dig_int = std::integral_constant<int, V>;
 
 // Rounds and stores rows first, first + STEP, ... of one column, four in flight.
 template <int L, class T, int STEP, class Value, class IsNar>

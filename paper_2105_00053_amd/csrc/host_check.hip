@@ -496,6 +496,17 @@ int hostcheck_digits(int fmt, uint32_t lo, uint32_t hi, int nar, int narrow, int
     return -1;
 }
 
+// The same through binary64: the sums hi + lo + bias pattern of format `fin`, hi and lo integers in units of 2^-qfrac.
+void hostcheck_round_f64_parts(int qfrac, int fin, int fout, int64_t n, const double* hi, const double* lo, const uint32_t* bias, uint32_t* out) {
+    const DigF64Round round(fmt_of_code(fout), qfrac);
+    for (int64_t i = 0; i < n; ++i) {
+        double s, e;
+        dig_two_sum(hi[i], lo[i], s, e);
+        if (bias[i]) dig_add_f64(s, e, dig_f64_of_pattern(bias[i], fmt_of_code(fin), qfrac));
+        out[i] = round(s, e);
+    }
+}
+
 // The digit kernels' rounding of n integers of `limbs` (3, 4, 5) 32-bit limbs in units of 2^-qfrac.
 void hostcheck_round_limbs(int limbs, int qfrac, int fout, int64_t n, const uint32_t* q, uint32_t* out) {
     const FmtRT f = fmt_of_code(fout);

@@ -72,6 +72,33 @@ def test_three_passes(fmt, kind, geometry):
     _equal(to_np(only[0] if isinstance(only, tuple) else only, fmt), fast.conv2d_bwd_weight(dy, x, d, fmt, fmt), "backward-weight without bias gradient")
 
 
+@pytest.mark.parametrize("spans", [(22, 34), (34, 22), (38, 30), (30, 46), (46, 38), (46, 46), (56, 22)])
+@pytest.mark.parametrize("fmt,maxs", [("p8_2", 24), ("p10_1", 16), ("p12_1", 20), ("p16", 28)])
+def test_planes_that_hold_anything(fmt, maxs, spans):
+    """Operands whose values span so many powers of two: the wide kernel multiplies four to seven planes of each, or all
+    eight, without NaR; the spans lie at the bottom, in the middle and at the top of the format's range."""
+    d = GEOMETRIES[0 if spans[0] < 40 else 6]
+    desc, fm = _desc(d), MASTER[fmt]
+    oh, ow = fast.out_hw(d)
+    rng = np.random.default_rng(spans[0] * 64 + spans[1])
+
+    def tensor(shape, span, at):
+        low = -maxs + at * (2 * maxs - min(span, 2 * maxs))
+        v = np.exp2(low + rng.random(shape) * min(span, 2 * maxs)) * rng.choice([-1.0, 1.0], size=shape)
+        return fast.round_from_float(v.astype(np.float32), fmt)
+
+    x, w, dy = tensor((d["N"], d["C"], d["H"], d["W"]), spans[0], 0), tensor((d["K"], d["C"], d["R"], d["S"]), spans[1], 1), tensor((d["N"], d["K"], oh, ow), spans[1], 0.5)
+    bias = tensor((d["K"],), 2 * maxs, 0)
+    y = to_np(pn.posit_conv2d_fwd(to_dev(x), to_dev(w), desc, fmt, fmt, bias=to_dev(bias)), fmt)
+    _equal(y, fast.conv2d_fwd(x, w, d, fmt, fmt, bias=bias), "forward")
+    dx = to_np(pn.posit_conv2d_bwd_data(to_dev(dy), to_dev(w), desc, fmt, fmt), fmt)
+    _equal(dx, fast.conv2d_bwd_data(dy, w, d, fmt, fmt), "backward-data")
+    dw, db = pn.posit_conv2d_bwd_weight(to_dev(dy), to_dev(x), desc, fmt, fm, with_bias=True)
+    wdw, wdb = fast.conv2d_bwd_weight(dy, x, d, fmt, fm, with_bias=True)
+    _equal(to_np(dw, fm), wdw, "backward-weight")
+    _equal(to_np(db, fm), wdb, "bias gradient")
+
+
 @pytest.mark.parametrize("fmt", ["p8_1", "p16", "p12_1"])
 def test_weight_gradient_wraps_like_the_quire(fmt):
     """45056 products of maxpos leave a quire that guarantees 32767: it wraps modulo 2^bits, in the oracle and here."""

@@ -80,3 +80,40 @@ def test_rounding_of_the_sums(hc, limbs):  # noqa: F811
             L.hostcheck_round_limbs(limbs, qfrac, code, len(vals), _p(q), _p(got))
             for v, g in zip(vals, got.tolist()):
                 assert g == po.round_to_posit(Fraction(v) / Fraction(2) ** qfrac, f), (code, qfrac, v)
+
+
+@pytest.mark.parametrize("fmt,fout", [("p8_1", "p8_1"), ("p8_2", "p12_2"), ("p10_1", "p8_2"), ("p12_1", "p12_1"), ("p16", "p16"), ("p16", "p8")])
+def test_rounding_through_binary64(hc, fmt, fout):  # noqa: F811
+    """Both parts at every size they can have, and biases that cancel the sum, lie on its ties or far from it."""
+    L = _lib(hc)
+    L.hostcheck_round_f64_parts.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] + [ctypes.c_void_p] * 4
+    f, fo = po.FORMATS[fmt], po.FORMATS[fout]
+    rng = np.random.default_rng(64 + f.n + fo.n)
+    qmax = 2 * ((f.n - 2) << f.es)
+    for qfrac in (qmax, qmax - 7, qmax // 2, qmax // 4):
+        his, los, biases = [], [], []
+        for i in range(1500):
+            lo = int(rng.integers(0, 1 << int(rng.integers(1, 47)))) * (1 if i & 1 else -1)
+            hi = (int(rng.integers(0, 1 << int(rng.integers(1, 52)))) if i % 5 else 0) * (1 if i & 2 else -1) << 24
+            bias = int(rng.integers(0, 1 << f.n)) if i % 3 else 0
+            if bias == 1 << (f.n - 1):
+                bias = 0
+            b = Fraction(0) if bias == 0 else po.decode(bias, f) * Fraction(2) ** qfrac
+            if i % 4 == 1 and abs(b) < 1 << 74:  # the bias cancels all of the sum but a few units
+                hi = -(int(b) >> 24) << 24
+                lo = int(rng.integers(-3, 4))
+            if i % 4 == 2:  # a tie of the output format, give or take a unit
+                p = int(rng.integers(1, (1 << (fo.n - 1)) - 2))
+                t, u = (int(po.decode(v, fo) * Fraction(2) ** qfrac) for v in (p, p + 1))
+                hi, lo = ((t + u) // 2 >> 24) << 24, ((t + u) // 2 & 0xFFFFFF) + int(rng.integers(-1, 2))
+            if int(float(hi)) != hi or abs(hi) >= 1 << 76:
+                hi = 0
+            his.append(hi)
+            los.append(lo)
+            biases.append(bias)
+        got = np.zeros(len(his), dtype=np.uint32)
+        L.hostcheck_round_f64_parts(qfrac, CODE[fmt], CODE[fout], len(his), _p(np.array(his, dtype=np.float64)), _p(np.array(los, dtype=np.float64)),
+                              _p(np.array(biases, dtype=np.uint32)), _p(got))
+        for h, l, bias, g in zip(his, los, biases, got.tolist()):
+            b = Fraction(0) if bias == 0 else po.decode(bias, f)
+            assert g == po.round_to_posit(Fraction(h + l) / Fraction(2) ** qfrac + b, fo), (qfrac, h, l, bias)
