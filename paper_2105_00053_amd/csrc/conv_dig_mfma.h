@@ -728,20 +728,27 @@ __device__ __forceinline__ void dig_conv_bw_planes(const typename Storage<F::N>:
 #pragma unroll
         for (int i = 0; i < NP; ++i) ones[idx * NP + i] = make_uint4(dg[i][0], dg[i][1], dg[i][2], dg[i][3]);
     }
+    // as in dig_conv_planes: image groups run fastest over the threads, and a wave's digits change hands before the store
+    // (whole calls, posit(8,2): 128 x 32 x 32 x 32 to 32 channels 76 to 72 us, 256 x 64 x 28 x 28 to 64 228 to 223)
     const int64_t planes = (int64_t)g.C * g.H * g.W;  // pixels of all channels of one image
-    const int64_t groups = planes / PX;
-    if (idx >= groups * p.NG) return;
-    const int gi = (int)(idx / groups);
-    const int64_t pix = (idx - (int64_t)gi * groups) * PX;  // (c, h, w) as one index
-    const int nimg = g.N - gi * 16 < 16 ? g.N - gi * 16 : 16;
-    const T* q = x + (int64_t)gi * 16 * planes + pix;
+    const uint32_t NG = (uint32_t)p.NG, total = (uint32_t)(planes / PX) * NG;
+    const uint32_t first = (blockIdx.x - ablocks) * 256u + ((uint32_t)t & ~63u);
     uint32_t in[16];
 #pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        if (b >= nimg) in[b] = 0;
-        else if (PX > 1) in[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * planes);
-        else in[b] = q[(int64_t)b * planes];
+    for (int b = 0; b < 16; ++b) in[b] = 0;
+    if (idx < total) {
+        const uint32_t pg = (uint32_t)idx / NG, gi = (uint32_t)idx - pg * NG;
+        const int nimg = g.N - (int)gi * 16 < 16 ? g.N - (int)gi * 16 : 16;
+        const T* q = x + (int64_t)gi * 16 * planes + (int64_t)pg * PX;  // (c, h, w) as one index
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            if (b >= nimg) continue;
+            if (PX > 1) in[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * planes);
+            else in[b] = q[(int64_t)b * planes];
+        }
     }
+    static_assert(sizeof(T) * 16 * 32 * (POS + 4 / sizeof(T)) >= 256 * NP * 16, "the rows' tile has room for the exchange");
+    uint4* const mine = reinterpret_cast<uint4*>(&tile[0][0][0]) + (t >> 6) * (64 * NP);
 #pragma unroll
     for (int px = 0; px < PX; ++px) {
         W wd[16];
@@ -749,9 +756,18 @@ __device__ __forceinline__ void dig_conv_bw_planes(const typename Storage<F::N>:
         for (int b = 0; b < 16; ++b) wd[b] = word((in[b] >> (8 * (int)sizeof(T) * px)) & (sizeof(T) == 1 ? 0xFFu : 0xFFFFu));
         uint32_t dg[NP][4];
         dig_planes_of<NP>(wd, dg);
-        uint4* out = xb + ((pix + px) * p.NG + gi) * NP;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) out[i] = make_uint4(dg[i][0], dg[i][1], dg[i][2], dg[i][3]);
+        for (int i = 0; i < NP; ++i) mine[dig_xch<NP>(t & 63, i)] = make_uint4(dg[i][0], dg[i][1], dg[i][2], dg[i][3]);
+        dig_wave_fence();
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const uint32_t s = (uint32_t)(i * 64 + (t & 63)) / NP, j = (uint32_t)(t & 63) % NP;  // plane j of thread s of the wave
+            if (first + s < total) {
+                const uint32_t pg = (first + s) / NG, gi = first + s - pg * NG;
+                xb[((int64_t)(pg * PX + px) * NG + gi) * NP + j] = mine[dig_xch<NP>(s, j)];
+            }
+        }
+        dig_wave_fence();
     }
 }
 
