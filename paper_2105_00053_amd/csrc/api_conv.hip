@@ -127,6 +127,14 @@ GemmPlan conv_plan(const ConvDims& d) {
     return plan_split(d.M, d.N, d.K, 16 * ConvTile<F>::TM, 16 * ConvTile<F>::TN, Arith<F>::L);
 }
 
+// Weight gradients: the query does not know whether a bias gradient is wanted, and either plan may need more (without its
+// column there can be fewer tiles, hence more slices).  A plan that does not serve leaves its call to the older kernel.
+template <class Plan>
+size_t conv_bw_ws(const Plan& with_bias, const Plan& without, size_t older) {
+    const size_t a = with_bias.ok ? with_bias.total() : older, b = without.ok ? without.total() : older;
+    return a > b ? a : b;
+}
+
 template <class F>
 size_t conv_ws(int which, const ConvGeom& g) {
     const ConvDims d = conv_dims(which, g);
@@ -153,8 +161,7 @@ size_t conv_ws(int which, const ConvGeom& g) {
     }
     if constexpr (dig_conv_format<F>()) {
         if (which == 2) {
-            const DigConvBwPlan bp = dig_conv_bw_plan<F>(g, true);
-            if (bp.ok) b = bp.total();
+            b = conv_bw_ws(dig_conv_bw_plan<F>(g, true), dig_conv_bw_plan<F>(g, false), b);
         } else {
             const DigConvPlan dp = dig_conv_plan<F>(which, g);
             if (dp.ok) b = dp.total();

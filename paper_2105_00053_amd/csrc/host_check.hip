@@ -6,6 +6,9 @@
 #include "conv_p8.h"
 #include "api_common.h"
 #include "dig_planes.h"
+#include "conv_desc.h"
+#include "conv_p8_mfma.h"
+#include "conv_dig_mfma.h"
 #include "p16_window_arith.h"
 #include "noquire_arith.h"
 #include "loss_ops.h"
@@ -204,6 +207,18 @@ int host_digits(uint32_t lo, uint32_t hi, int nar, int narrow, int64_t n, const 
         }
         return host_digits_np<F, D::NP2>(d, n, p, digits, base);
     }
+}
+
+// Bytes that the weight gradient's matrix-core kernels take for this call; 0: they do not serve it.
+template <class F>
+size_t host_conv_bw_need(const ConvGeom& g, bool with_bias) {
+    if constexpr (dig_conv_format<F>()) {
+        const DigConvBwPlan p = dig_conv_bw_plan<F>(g, with_bias);
+        return p.ok ? p.total() : 0;
+    }
+    if (!(F::N == 8 && F::ES == 0) || !p8_conv_eligible(2, g)) return 0;
+    const P8ConvBwPlan p = p8_conv_bw_plan(g, with_bias);
+    return p.ok ? p.total() : 0;
 }
 
 template <int L>
@@ -512,5 +527,13 @@ void hostcheck_round_limbs(int limbs, int qfrac, int fout, int64_t n, const uint
     const FmtRT f = fmt_of_code(fout);
     for (int64_t i = 0; i < n; ++i)
         out[i] = limbs == 3 ? host_round<3>(q + 3 * i, qfrac, f) : limbs == 4 ? host_round<4>(q + 4 * i, qfrac, f) : host_round<5>(q + 5 * i, qfrac, f);
+}
+
+// Workspace that posit_conv2d_bwd_weight asks for with and without a bias gradient, as its plan has it (see host_conv_bw_need).
+size_t hostcheck_conv_bw_need(int fmt, const pnn_conv2d_desc* d, int with_bias) {
+    ConvGeom g;
+    if (!conv_geom(d, &g)) return 0;
+    PNN_DISPATCH_POSIT(fmt, return host_conv_bw_need<F>(g, with_bias != 0))
+    return 0;
 }
 }  // extern "C"

@@ -99,6 +99,21 @@ def test_planes_that_hold_anything(fmt, maxs, spans):
     _equal(to_np(db, fm), wdb, "bias gradient")
 
 
+@pytest.mark.parametrize("fmt,C,K", [("p8_1", 128, 4), ("p8_2", 64, 33), ("p10_1", 128, 4), ("p12_1", 128, 4), ("p16", 64, 33), ("p16", 128, 4)])
+def test_weight_gradient_with_whole_column_tiles(fmt, C, K):
+    """C R S a multiple of the column tile (64, or 128 for at most 32 output channels): without the bias column the product has
+    a tile less and the reduction more slices."""
+    d = dict(N=16, C=C, H=31, W=31, K=K, R=3, S=3, pad_h=1, pad_w=1)
+    rng = np.random.default_rng(C + K + BITS[fmt])
+    x, dy = _tensor(rng, (16, C, 31, 31), fmt, "gauss"), _tensor(rng, (16, K, 31, 31), fmt, "gauss", 1 / 16)
+    want, wdb = fast.conv2d_bwd_weight(dy, x, d, fmt, MASTER[fmt], with_bias=True)
+    only = pn.posit_conv2d_bwd_weight(to_dev(dy), to_dev(x), _desc(d), fmt, MASTER[fmt])
+    _equal(to_np(only[0] if isinstance(only, tuple) else only, MASTER[fmt]), want, "backward-weight without bias gradient")
+    dw, db = pn.posit_conv2d_bwd_weight(to_dev(dy), to_dev(x), _desc(d), fmt, MASTER[fmt], with_bias=True)
+    _equal(to_np(dw, MASTER[fmt]), want, "backward-weight")
+    _equal(to_np(db, MASTER[fmt]), wdb, "bias gradient")
+
+
 @pytest.mark.parametrize("fmt", ["p8_1", "p16", "p12_1"])
 def test_weight_gradient_wraps_like_the_quire(fmt):
     """45056 products of maxpos leave a quire that guarantees 32767: it wraps modulo 2^bits, in the oracle and here."""
