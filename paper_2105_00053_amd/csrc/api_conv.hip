@@ -148,10 +148,7 @@ size_t conv_ws(int which, const ConvGeom& g) {
         if (p8_pre_usable(which, g, &pp, &pplan)) b = p8_pre_ws_bytes(pp, pplan);
         const P8ConvMfmaPlan mp = p8_conv_mfma_plan(which, g);
         if (mp.ok) b = mp.total();
-        if (which == 2) {
-            const P8ConvBwPlan bp = p8_conv_bw_plan(g, true);
-            if (bp.ok) b = bp.total();
-        }
+        if (which == 2) b = conv_bw_ws(p8_conv_bw_plan(g, true), p8_conv_bw_plan(g, false), b);
     }
     if constexpr (is_b8<F>()) {
         if (p8_conv_eligible(which, g)) {

@@ -11,7 +11,7 @@ from oracle import fast
 from gpu_util import BITS, NP_DTYPE, mismatches, rand_patterns, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
-MASTER = {"p8_1": "p12_1", "p8_2": "p12_2", "p10_1": "p10_1", "p12_1": "p8_2", "p16": "p16"}
+MASTER = {"p8": "p16", "p8_1": "p12_1", "p8_2": "p12_2", "p10_1": "p10_1", "p12_1": "p8_2", "p16": "p16"}
 
 GEOMETRIES = [
     dict(N=33, C=17, H=15, W=13, K=33, R=3, S=3, pad_h=1, pad_w=1),
@@ -99,7 +99,7 @@ def test_planes_that_hold_anything(fmt, maxs, spans):
     _equal(to_np(db, fm), wdb, "bias gradient")
 
 
-@pytest.mark.parametrize("fmt,C,K", [("p8_1", 128, 4), ("p8_2", 64, 33), ("p10_1", 128, 4), ("p12_1", 128, 4), ("p16", 64, 33), ("p16", 128, 4)])
+@pytest.mark.parametrize("fmt,C,K", [("p8", 64, 6), ("p8", 64, 33), ("p8_1", 128, 4), ("p8_2", 64, 33), ("p10_1", 128, 4), ("p12_1", 128, 4), ("p16", 64, 33), ("p16", 128, 4)])
 def test_weight_gradient_with_whole_column_tiles(fmt, C, K):
     """C R S a multiple of the column tile (64, or 128 for at most 32 output channels): without the bias column the product has
     a tile less and the reduction more slices."""

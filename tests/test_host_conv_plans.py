@@ -34,7 +34,7 @@ def _bw_layers():
     return out
 
 
-@pytest.mark.parametrize("fmt", DIGIT_FORMATS)
+@pytest.mark.parametrize("fmt", ["p8"] + DIGIT_FORMATS)
 def test_weight_gradient_fits_the_queried_workspace(hc, fmt):  # noqa: F811
     L, served = binding.load(), 0
     for d in _bw_layers():
