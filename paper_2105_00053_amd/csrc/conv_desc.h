@@ -38,4 +38,15 @@ inline ConvDims conv_dims(int which, const ConvGeom& g) {
     return d;
 }
 
+// The gathering matrix-core kernels keep a tap's row and column offsets in 16 bits, stand -40000 and 0x7FFF rows for "no pixel"
+// and form addresses in 32 bits, those of taps in the border included.  Whether that holds where output (oh, ow) of image i
+// reads tap (r, s) at input (oh sh + r - offh, ow sw + s - offw), `unit` words per pixel; HI and WI are at most 16384.
+inline bool conv_gather_fits(int64_t NI, int64_t HI, int64_t WI, int64_t HO, int64_t WO, int64_t R, int64_t S, int64_t offh, int64_t offw, int64_t sh,
+                             int64_t sw, int64_t unit) {
+    const int64_t most = 16384, last_h = R - 1 - offh, last_w = S - 1 - offw;
+    if (offh > most || offw > most || last_h > most || last_w > most) return false;
+    const int64_t far = ((NI - 1) * HI + (HO - 1) * sh) * WI + (WO - 1) * sw, ahead = last_h * WI + last_w, behind = offh * WI + offw;
+    return (far + (ahead > 0 ? ahead : 0)) * unit < ((int64_t)1 << 31) && behind * unit < ((int64_t)1 << 31);
+}
+
 }  // namespace pnn

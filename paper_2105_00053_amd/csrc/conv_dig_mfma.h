@@ -17,6 +17,7 @@
 // eight are launched, the one decided on does the work.
 #pragma once
 
+#include "conv_desc.h"
 #include "gemm_dig_mfma.h"
 
 namespace pnn {
@@ -64,6 +65,7 @@ inline DigConvPlan dig_conv_plan(int which, const ConvGeom& g) {
     const int64_t pin = (int64_t)p.NI * p.HI * p.WI, k16 = (int64_t)g.R * g.S * p.Cg;
     if (k16 + 1 > DCM_MAXK16 || p.HI > 16384 || p.WI > 16384 || p.HO > 16384 || p.WO > 16384 || g.R > 4096 || g.S > 4096) return p;
     if (pin * p.Cg * slots >= ((int64_t)1 << 30) || p.P >= ((int64_t)1 << 30) || p.MO > 65536 || p.P * p.MO >= ((int64_t)1 << 40)) return p;
+    if (!conv_gather_fits(p.NI, p.HI, p.WI, p.HO, p.WO, g.R, g.S, p.offh, p.offw, g.sh, g.sw, p.Cg * slots)) return p;
     p.K16 = (int)k16;
     p.KB = (p.K16 + 1) / 2;
     // Four launches: below these sizes the byte-gather kernel of the 8-bit formats is faster forward (15 M products: 25 against

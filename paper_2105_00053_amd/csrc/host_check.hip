@@ -221,6 +221,26 @@ size_t host_conv_bw_need(const ConvGeom& g, bool with_bias) {
     return p.ok ? p.total() : 0;
 }
 
+// The gather of a forward (0) or backward-data (1) plan on the matrix cores: geometry of the gathered tensor and its taps, and
+// the digit words of a pixel.
+template <class Plan>
+int host_conv_gather(const Plan& p, int sh, int sw, int slots, int64_t* out) {
+    if (!p.ok) return 0;
+    const int64_t v[12] = {p.NI, p.HI, p.WI, p.HO, p.WO, p.R, p.S, p.offh, p.offw, sh, sw, (int64_t)p.Cg * slots};
+    for (int i = 0; i < 12; ++i) out[i] = v[i];
+    return 1;
+}
+
+template <class F>
+int host_conv_plan(int which, const ConvGeom& g, int64_t* out) {
+    if constexpr (dig_conv_format<F>()) {
+        const DigConvPlan p = dig_conv_plan<F>(which, g);
+        return host_conv_gather(p, g.sh, g.sw, dig_conv_wide<F>(), out);
+    }
+    if (!(F::N == 8 && F::ES == 0) || !p8_conv_eligible(which, g)) return 0;
+    return host_conv_gather(p8_conv_mfma_plan(which, g), g.sh, g.sw, 2, out);
+}
+
 template <int L>
 uint32_t host_round(const uint32_t* q, int qfrac, const FmtRT& f) {
     uint32_t l[L];
@@ -534,6 +554,14 @@ size_t hostcheck_conv_bw_need(int fmt, const pnn_conv2d_desc* d, int with_bias) 
     ConvGeom g;
     if (!conv_geom(d, &g)) return 0;
     PNN_DISPATCH_POSIT(fmt, return host_conv_bw_need<F>(g, with_bias != 0))
+    return 0;
+}
+
+// out: NI, HI, WI, HO, WO, R, S, offh, offw, sh, sw, words per pixel (see host_conv_gather).  Returns whether the plan serves.
+int hostcheck_conv_gather_plan(int fmt, int which, const pnn_conv2d_desc* d, int64_t* out) {
+    ConvGeom g;
+    if (!conv_geom(d, &g)) return 0;
+    PNN_DISPATCH_POSIT(fmt, return host_conv_plan<F>(which, g, out))
     return 0;
 }
 }  // extern "C"

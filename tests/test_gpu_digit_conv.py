@@ -72,6 +72,24 @@ def test_three_passes(fmt, kind, geometry):
     _equal(to_np(only[0] if isinstance(only, tuple) else only, fmt), fast.conv2d_bwd_weight(dy, x, d, fmt, fmt), "backward-weight without bias gradient")
 
 
+@pytest.mark.parametrize("pad", [16384, 16385, 40000, 49152])
+@pytest.mark.parametrize("fmt", ["p8_1", "p8_2", "p12_1", "p16"])
+def test_paddings_beyond_the_tensor(fmt, pad):
+    """Paddings of thousands of rows under a stride that lands one output row on the tensor: beyond 16 bits of offset the
+    general kernel serves."""
+    d = dict(N=64, C=16, H=7, W=9, K=128, R=3, S=3, pad_h=pad, pad_w=1, stride_h=pad // 2, stride_w=1)
+    rng = np.random.default_rng(pad + BITS[fmt])
+    x, w, dy = _tensor(rng, (64, 16, 7, 9), fmt, "gauss"), _tensor(rng, (128, 16, 3, 3), fmt, "gauss"), _tensor(rng, (64, 128) + fast.out_hw(d), fmt, "gauss")
+    bias = _tensor(rng, (128,), fmt, "gauss")
+    y = to_np(pn.posit_conv2d_fwd(to_dev(x), to_dev(w), _desc(d), fmt, fmt, bias=to_dev(bias)), fmt)
+    _equal(y, fast.conv2d_fwd(x, w, d, fmt, fmt, bias=bias), "forward")
+    assert len(np.unique(y[:, 0])) > 8  # some output row reads the tensor
+    dw, db = pn.posit_conv2d_bwd_weight(to_dev(dy), to_dev(x), _desc(d), fmt, fmt, with_bias=True)
+    wdw, wdb = fast.conv2d_bwd_weight(dy, x, d, fmt, fmt, with_bias=True)
+    _equal(to_np(dw, fmt), wdw, "backward-weight")
+    _equal(to_np(db, fmt), wdb, "bias gradient")
+
+
 @pytest.mark.parametrize("spans", [(22, 34), (34, 22), (38, 30), (30, 46), (46, 38), (46, 46), (56, 22)])
 @pytest.mark.parametrize("fmt,maxs", [("p8_2", 24), ("p10_1", 16), ("p12_1", 20), ("p16", 28)])
 def test_planes_that_hold_anything(fmt, maxs, spans):

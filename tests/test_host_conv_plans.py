@@ -44,3 +44,41 @@ def test_weight_gradient_fits_the_queried_workspace(hc, fmt):  # noqa: F811
             served += need > 0
             assert need <= query, (fmt, [getattr(d, f) for f, _ in d._fields_], with_bias)
     assert served > 300
+
+
+def _wide_paddings():
+    """Layers with paddings of thousands of rows or columns: strides that keep the output small, and stride 1."""
+    out = []
+    for pad in (1, 4000, 16383, 16385, 32767, 32769, 40000, 49151, 49152, 65535, 70001):
+        st = max(1, pad // 2)
+        for h, k in ((8, 128), (300, 128)):
+            out.append(binding.ConvDesc(64, 16, h, 8, k, 3, 3, pad, 1, st, 1))
+            out.append(binding.ConvDesc(64, 16, 8, h, k, 3, 3, 1, pad, 1, st))
+            out.append(binding.ConvDesc(1, 16, h, 8, 32, 3, 3, pad, 1, 1, 1))
+            out.append(binding.ConvDesc(1, 16, 8, h, 32, 3, 3, 1, pad, 1, 1))
+    out.append(binding.ConvDesc(1, 8, 16384, 1, 64, 3, 1, 65534, 0, 1, 1))  # in 16 bits this padding is two rows below the taps
+    out.append(binding.ConvDesc(2, 700, 1, 16000, 64, 1, 1, 8000, 0, 200, 1))
+    return out
+
+
+@pytest.mark.parametrize("which", [0, 1])
+@pytest.mark.parametrize("fmt", DIGIT_FORMATS)
+def test_gathers_stay_within_their_integers(hc, fmt, which):  # noqa: F811
+    """What the gathering kernels rely on: a tap's offsets survive 16 bits, the rows that stand for "no pixel" stay outside, and
+    every address, border included, fits 32 bits."""
+    out, served = (ctypes.c_int64 * 12)(), 0
+    hc.hostcheck_conv_gather_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    for d in _wide_paddings() + _bw_layers():
+        if not hc.hostcheck_conv_gather_plan(CODE[fmt], which, ctypes.byref(d), out):
+            continue
+        served += 1
+        NI, HI, WI, HO, WO, R, S, offh, offw, sh, sw, unit = out[:]
+        taps = [(-offh, R - 1 - offh), (-offw, S - 1 - offw)]
+        for lo, hi in taps:
+            assert -32768 <= lo and hi < 0x7FFF, (d.pad_h, d.pad_w)
+            assert -40000 + hi < 0
+        assert HI <= 0x7FFF
+        far = (((NI - 1) * HI + (HO - 1) * sh) * WI + (WO - 1) * sw) * unit
+        assert far + max(0, taps[0][1] * WI + taps[1][1]) * unit < 1 << 31
+        assert (taps[0][0] * WI + taps[1][0]) * unit > -(1 << 31)
+    assert served > 100
