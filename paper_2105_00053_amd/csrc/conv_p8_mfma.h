@@ -19,6 +19,7 @@
 // of this file.
 #pragma once
 
+#include "conv_desc.h"
 #include "gemm_p8_mfma.h"
 
 namespace pnn {
@@ -59,6 +60,7 @@ inline P8ConvMfmaPlan p8_conv_mfma_plan(int which, const ConvGeom& g) {
     const int64_t pin = (int64_t)p.NI * p.HI * p.WI;
     if (2 * p.KB > PCM_MAXK16 || p.Cg > 256 || p.HI > 16384 || p.WI > 16384 || g.R > 4096 || g.S > 4096) return p;
     if (pin * p.Cg * 2 >= ((int64_t)1 << 30) || p.P >= ((int64_t)1 << 30) || p.P * p.MO >= ((int64_t)1 << 40)) return p;
+    if (!conv_gather_fits(p.NI, p.HI, p.WI, p.HO, p.WO, g.R, g.S, p.offh, p.offw, 1, 1, p.Cg * 2)) return p;
     // worth the two rewriting launches: enough products, enough positions to fill the chip, enough rows to use a block
     const int64_t macs = p.P * p.MO * p.CI * g.R * g.S;
     if (macs < ((int64_t)1 << 24) || p.P < 8192 || p.MO < 4 || p.CI < 8) return p;

@@ -90,6 +90,17 @@ def test_paddings_beyond_the_tensor(fmt, pad):
     _equal(to_np(db, fmt), wdb, "bias gradient")
 
 
+@pytest.mark.parametrize("pad", [16384, 16385, 40000, 65534])
+def test_paddings_beyond_the_tensor_posit8_0(pad):
+    """The same for posit<8,0>, whose matrix-core kernels serve stride 1 only."""
+    d = dict(N=1, C=16, H=40, W=1, K=32, R=3, S=1, pad_h=pad, pad_w=0)
+    rng = np.random.default_rng(pad)
+    x, w = _tensor(rng, (1, 16, 40, 1), "p8", "gauss"), _tensor(rng, (32, 16, 3, 1), "p8", "gauss")
+    y = to_np(pn.posit_conv2d_fwd(to_dev(x), to_dev(w), _desc(d), "p8", "p8"), "p8")
+    _equal(y, fast.conv2d_fwd(x, w, d, "p8", "p8"), "forward")
+    assert len(np.unique(y)) > 32
+
+
 @pytest.mark.parametrize("spans", [(22, 34), (34, 22), (38, 30), (30, 46), (46, 38), (46, 46), (56, 22)])
 @pytest.mark.parametrize("fmt,maxs", [("p8_2", 24), ("p10_1", 16), ("p12_1", 20), ("p16", 28)])
 def test_planes_that_hold_anything(fmt, maxs, spans):

@@ -62,7 +62,7 @@ def _wide_paddings():
 
 
 @pytest.mark.parametrize("which", [0, 1])
-@pytest.mark.parametrize("fmt", DIGIT_FORMATS)
+@pytest.mark.parametrize("fmt", ["p8"] + DIGIT_FORMATS)
 def test_gathers_stay_within_their_integers(hc, fmt, which):  # noqa: F811
     """What the gathering kernels rely on: a tap's offsets survive 16 bits, the rows that stand for "no pixel" stay outside, and
     every address, border included, fits 32 bits."""
