@@ -87,7 +87,8 @@ typedef enum {
  * each, 2 bytes per element; for posit<8,1> / posit<8,2> products of 2^25 and more
  * (128 outputs each way, K from 256 to 8192) as up to four / eight; for posit<16,1>, posit<10,1> and posit<12,1> from
  * 96 x 96 outputs and K = 64 to 16352 on, and for posit<32,2> from 768 tiles of 16 x 16 outputs and K = 256 to 16352 on,
- * as up to eight; for posit<10,2> and posit<12,2>, and beyond those reductions, as doubles, 8 bytes per element). */
+ * as up to eight; for posit<10,2> and posit<12,2>, and beyond those reductions, as doubles, 8 bytes per element).  A
+ * posit<32,2> product of that size with a bias uses none of it and accepts NULL. */
 int posit_gemm(void* stream, int fin, int fout, int transA, int transB,
                int64_t M, int64_t N, int64_t K,
                const void* A, int64_t lda, const void* B, int64_t ldb,

@@ -101,14 +101,16 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
     typedef typename Storage<F::N>::T T;
     constexpr int TM = GemmTile<F>::TM, TN = GemmTile<F>::TN;
     const GemmPlan plan = gemm_plan<F>(M, N, K, limit);
-    if (plan.ws_bytes > 0 && (!ws || ws_bytes < plan.ws_bytes)) return PNN_EWORKSPACE;
+    // posit<32,2> with a bias: the LDS kernel, whose quire takes it at any scale and which needs no workspace
+    const bool use_dig = dig_gemm_fits<F>(M, N, K, limit) && (F::N != 32 || !bias);
+    const bool no_ws = F::N == 32 && bias && p32_lds_fits(M, N, K);
+    if (plan.ws_bytes > 0 && !no_ws && (!ws || ws_bytes < plan.ws_bytes)) return PNN_EWORKSPACE;
     RowMajorOut out;
     out.ld = ldc;
     hipError_t e;
     const int* served = nullptr;  // on the device: non-zero when the digit kernels did the work
     if constexpr (is_dig<F>()) {
-        // (posit<32,2> with a bias: the LDS kernel, whose quire takes it at any scale)
-        if (dig_gemm_fits<F>(M, N, K, limit) && (F::N != 32 || !bias)) {
+        if (use_dig) {
             const DigInfo* decision;
             e = launch_dig_gemm<F>(st, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, ws, &decision);
             if (e != hipSuccess || DigFormat<F>::COVER) return hip_status(e);

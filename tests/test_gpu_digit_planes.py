@@ -117,3 +117,18 @@ def test_static_scratch_gives_way_to_the_older_kernels():
     assert np.array_equal(got, same)
     want, _ = fast.gemm(np.ascontiguousarray(A[[0, M - 1]]), B, "p32", "p32")
     assert np.array_equal(got[[0, M - 1]], want)
+
+
+def test_posit32_with_bias_takes_no_workspace():
+    import torch
+    from paper_2105_00053_amd import binding
+    M, N, K = 450, 470, 256
+    rng = np.random.default_rng(32)
+    A, B, bias = _operand(rng, (M, K), "p32", "gauss"), _operand(rng, (K, N), "p32", "gauss"), _operand(rng, (N,), "p32", "gauss")
+    a, b, v, c = to_dev(A), to_dev(B), to_dev(bias), torch.zeros((M, N), dtype=torch.int32, device="cuda")
+    code, stream = binding.FORMAT_CODES["p32"], torch.cuda.current_stream().cuda_stream
+    call = binding.load().posit_gemm
+    assert call(stream, code, code, 0, 0, M, N, K, a.data_ptr(), K, b.data_ptr(), N, v.data_ptr(), c.data_ptr(), N, None, 0) == 0
+    want, _ = fast.gemm(A, B, "p32", "p32", bias=bias)
+    assert len(mismatches(to_np(c, "p32"), want)) == 0
+    assert call(stream, code, code, 0, 0, M, N, K, a.data_ptr(), K, b.data_ptr(), N, None, c.data_ptr(), N, None, 0) == 3
