@@ -107,7 +107,8 @@ size_t posit_gemm_workspace(int fin, int fout, int transA, int transB, int64_t M
  * so the call neither takes a workspace nor allocates or frees anything.  A problem whose
  * posit_gemm_workspace() exceeds PNN_GEMM_STATIC_SCRATCH_BYTES returns PNN_EWORKSPACE with nothing
  * launched (72 MiB covers the 4096^3 posit<8,0> product and every matrix product of the five
- * benchmark configurations).  The device that owns the pointers and the stream must be the
+ * benchmark configurations), except that posit<16,1>, (10,1), (12,1) and posit<32,2> products are
+ * then computed by a slower kernel where one needs no more than the array (posit<32,2>: always).  The device that owns the pointers and the stream must be the
  * current device.  Every call on a GPU uses that GPU's one array, which keeps the previous call's
  * contents (the kernels overwrite or clear what they read): calls that may overlap in time on one
  * GPU -- from different streams or threads -- race on it and must be serialised by the caller. */

@@ -33,7 +33,8 @@ constexpr bool is_b8() { return F::N == 8 && F::ES != 0; }
 template <class F>
 constexpr bool is_dig() { return F::N == 32 || (F::ES != 0 && DigFormat<F>::COVER); }
 
-// Products that go to the integer matrix cores as base-256 digit planes, where the workspace may have up to `limit` bytes.
+// Products that go to the integer matrix cores as base-256 digit planes, where the workspace may have up to `limit` bytes
+// (posit(8,1) and posit(8,2) do not give way to their older kernel: beyond the limit the call is refused).
 template <class F>
 inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
     if constexpr (!is_dig<F>()) return false;
@@ -46,7 +47,7 @@ inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
         } else if (M < 96 || N < 96 || K < 64) {
             return false;
         }
-        return dig_plan<F>(M, N, K).total <= limit;
+        return F::N == 8 || dig_plan<F>(M, N, K).total <= limit;
     }
 }
 
@@ -286,7 +287,7 @@ extern "C" int posit_gemm_static(void* stream, int fin, int fout, int transA, in
     bool launch;
     const int rc = gemm_check_args(fin, fout, transA, transB, M, N, K, A, lda, B, ldb, C, ldc, &launch);
     if (!launch) return rc;
-    // a kernel that wants more than the fixed array gives way to an older one that does not
+    // digit planes that want more than the fixed array give way to an older kernel that does not (see dig_gemm_fits)
     const size_t limit = PNN_GEMM_STATIC_SCRATCH_BYTES;
     size_t need = 0;
     PNN_DISPATCH_POSIT(fin, need = gemm_plan<F>(M, N, K, limit).ws_bytes)

@@ -28,3 +28,20 @@ def test_posit32_with_bias_needs_no_workspace():
     assert _gemm("p32", M, N, K, False, 0) == EWORKSPACE
     assert _gemm("p32", M, N, K, False, need - 1) == EWORKSPACE
     assert _gemm("p32", M, N, K, False, need) == EHIP
+
+
+def _static(fmt, M, N, K):
+    c = CODE[fmt]
+    return binding.load().posit_gemm_static(NULL, c, c, 0, 0, M, N, K, FAKE, K, FAKE, N, NULL, FAKE, N)
+
+
+@pytest.mark.parametrize("fmt", ["p8_1", "p8_2"])
+def test_static_scratch_refuses_what_exceeds_it(fmt):
+    assert binding.posit_gemm_workspace(fmt, fmt, 0, 0, 4096, 4096, 4096) > 72 << 20
+    assert _static(fmt, 4096, 4096, 4096) == EWORKSPACE
+    assert _static(fmt, 1024, 1024, 1024) == EHIP
+
+
+@pytest.mark.parametrize("fmt,M,N,K", [("p32", 4096, 4100, 1280), ("p32", 512, 512, 512), ("p16", 1024, 1024, 1024), ("p12_1", 1024, 1024, 1024)])
+def test_static_scratch_takes_what_an_older_kernel_can_do(fmt, M, N, K):
+    assert _static(fmt, M, N, K) == EHIP
