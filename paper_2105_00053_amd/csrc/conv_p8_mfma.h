@@ -58,12 +58,15 @@ inline P8ConvMfmaPlan p8_conv_mfma_plan(int which, const ConvGeom& g) {
     p.KB = (p.K16 + 1) / 2;
     p.P = (int64_t)p.NI * p.HO * p.WO;
     const int64_t pin = (int64_t)p.NI * p.HI * p.WI;
-    if (2 * p.KB > PCM_MAXK16 || p.Cg > 256 || p.HI > 16384 || p.WI > 16384 || g.R > 4096 || g.S > 4096) return p;
+    if (2 * p.KB > PCM_MAXK16 || p.HI > 16384 || p.WI > 16384 || g.R > 4096 || g.S > 4096) return p;
     if (pin * p.Cg * 2 >= ((int64_t)1 << 30) || p.P >= ((int64_t)1 << 30) || p.P * p.MO >= ((int64_t)1 << 40)) return p;
     if (!conv_gather_fits(p.NI, p.HI, p.WI, p.HO, p.WO, g.R, g.S, p.offh, p.offw, 1, 1, p.Cg * 2)) return p;
     // worth the two rewriting launches: enough products, enough positions to fill the chip, enough rows to use a block
     const int64_t macs = p.P * p.MO * p.CI * g.R * g.S;
     if (macs < ((int64_t)1 << 24) || p.P < 8192 || p.MO < 4 || p.CI < 8) return p;
+    // one block of output channels does not pay for rewriting more than 256 channel groups (43 images at 14 x 14, 1 x 1: 4112 to
+    // 64 channels 107 us on the gather kernel against 116 here, to 80 channels 175 against 118; 6400 to 16 111 against 169)
+    if (p.Cg > 256 && p.MO <= 64) return p;
     p.WY = p.MO > 32 ? 2 : 1;
     p.BI = (p.MO > 64 && ((p.MO + 127) / 128) * ((p.P + 63) / 64) >= 256) ? 2 : 1;  // 128-row tiles only if every compute unit still gets one
     const int64_t tiles_m = (p.MO + 32 * p.WY * p.BI - 1) / (32 * p.WY * p.BI);
@@ -80,15 +83,20 @@ inline P8ConvMfmaPlan p8_conv_mfma_plan(int which, const ConvGeom& g) {
 //
 // Input tensor [NI][CI][HW] -> digit planes [NI * HW][Cg][2][16]; channels beyond CI are zeros.  One thread per channel
 // group and PX consecutive pixels (PX = 4 when HW is a multiple of 4 and the tensor is 4-byte aligned: one 32-bit load
-// per channel); consecutive threads take consecutive pixels, so every load is coalesced, and the digits leave through LDS
-// in one contiguous stretch per workgroup (stored by the threads that make them, 32 bytes each at a stride of a pixel:
-// 55 us for 51 M elements, 2.8 TB/s; now 29 us, 5.3 TB/s).
+// per channel); consecutive threads take consecutive pixels, so every load is coalesced.  With up to PCM_STRETCH groups the
+// digits leave through LDS in one contiguous stretch per workgroup (stored by the threads that make them, 32 bytes each at a
+// stride of a pixel: 55 us for 51 M elements, 2.8 TB/s; now 29 us, 5.3 TB/s).  With more (DIRECT) a workgroup's stretch
+// would be a few pixels long and its loads as narrow, so a workgroup takes 256 pixel groups of one channel group instead
+// (whole calls, 1 x 1: 160 images of 1024 channels at 14 x 14 to 32 72 us in stretches, 60 direct; 43 of 3072 at 15 x 15 200
+// and 91; at 512 channels the two are equal).
 //
 // Weights [WK][WC][R][S] -> [KB][RBA][2][64][16] (and the 32 zero bytes behind the input planes) in the lane order of
 // the matrix instruction, reduction index 16 ((r S + s) Cg + cg) + channel.  Forward: row = output channel k,
 // channel = c.  Backward-data: row = c, channel = k, the tap taken at (R-1-r, S-1-s), NaR written as zero.  One
 // thread per (k block, row block, lane).
-template <int PX>
+constexpr int PCM_STRETCH = 32;
+
+template <int PX, bool DIRECT>
 __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __restrict__ src, int HW, int64_t pixels, uint8_t* __restrict__ act,
                                                              const uint8_t* __restrict__ w, P8ConvMfmaPlan p, uint8_t* __restrict__ wdst,
                                                              uint4* __restrict__ zero, unsigned wblocks) {
@@ -131,8 +139,11 @@ __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __re
     }
     // the workgroup's pixels with all their channel groups are one contiguous stretch of the planes
     extern __shared__ uint4 rows[];  // [pixel group][PX pixels x Cg groups x 2 digits, and one word so that rows fall on different banks]
-    const uint32_t QB = 256u / (uint32_t)p.Cg, cg = (uint32_t)t / QB, qi = (uint32_t)t - cg * QB;
-    const uint32_t group0 = (blockIdx.x - wblocks) * QB, groups = (uint32_t)(pixels / PX);  // PX divides HW, hence pixels
+    const uint32_t groups = (uint32_t)(pixels / PX);  // PX divides HW, hence pixels
+    const uint32_t rowsb = (groups + 255u) / 256u;    // DIRECT: workgroups per channel group
+    const uint32_t QB = DIRECT ? 256u : 256u / (uint32_t)p.Cg, blk = blockIdx.x - wblocks;
+    const uint32_t cg = DIRECT ? blk / rowsb : (uint32_t)t / QB, qi = DIRECT ? (uint32_t)t : (uint32_t)t - cg * QB;
+    const uint32_t group0 = (DIRECT ? blk - cg * rowsb : blk) * QB;
     const uint32_t words = (uint32_t)(PX * 2) * p.Cg;
     if (cg < (uint32_t)p.Cg && group0 + qi < groups) {
         const uint32_t pix = (group0 + qi) * PX;
@@ -146,7 +157,7 @@ __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __re
             else if (PX == 4) word[b] = *reinterpret_cast<const uint32_t*>(q + (int64_t)b * HW);
             else word[b] = q[(int64_t)b * HW];
         }
-        uint4* out = rows + qi * (words + 1) + cg * 2;
+        uint4* out = DIRECT ? reinterpret_cast<uint4*>(act) + (int64_t)(group0 + qi) * words + cg * 2 : rows + qi * (words + 1) + cg * 2;
 #pragma unroll
         for (int px = 0; px < PX; ++px) {
             uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
@@ -160,6 +171,7 @@ __global__ __launch_bounds__(256) void p8_conv_digits_kernel(const uint8_t* __re
             out[px * p.Cg * 2 + 1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
         }
     }
+    if (DIRECT) return;
     __syncthreads();
     const uint32_t ng = groups - group0 < QB ? groups - group0 : QB;
     uint4* dst = reinterpret_cast<uint4*>(act) + (int64_t)group0 * words;
@@ -425,16 +437,18 @@ inline hipError_t launch_p8_conv_mfma(hipStream_t stream, const P8ConvMfmaPlan& 
     const int64_t pixels = (int64_t)p.NI * p.HI * p.WI;
     const int HW = p.HI * p.WI;
     const unsigned wblocks = (unsigned)(((int64_t)p.KB * p.RBA * 64 + 255) / 256);
-    const int64_t per = 256 / p.Cg;  // pixel groups per workgroup
-    if (HW % 4 == 0 && ((uintptr_t)in & 3u) == 0) {
-        const unsigned ablocks = (unsigned)((pixels / 4 + per - 1) / per);
-        hipLaunchKernelGGL(p8_conv_digits_kernel<4>, dim3(wblocks + ablocks), dim3(256), (size_t)per * (8 * p.Cg + 1) * 16, stream, (const uint8_t*)in, HW, pixels, act,
-                           (const uint8_t*)w, p, Ad, reinterpret_cast<uint4*>(zero), wblocks);
-    } else {
-        const unsigned ablocks = (unsigned)((pixels + per - 1) / per);
-        hipLaunchKernelGGL(p8_conv_digits_kernel<1>, dim3(wblocks + ablocks), dim3(256), (size_t)per * (2 * p.Cg + 1) * 16, stream, (const uint8_t*)in, HW, pixels, act,
-                           (const uint8_t*)w, p, Ad, reinterpret_cast<uint4*>(zero), wblocks);
-    }
+    const bool direct = p.Cg > PCM_STRETCH, four = HW % 4 == 0 && ((uintptr_t)in & 3u) == 0;
+    const int64_t per = direct ? 256 : 256 / p.Cg, groups = four ? pixels / 4 : pixels;  // pixel groups per workgroup, in all
+    const unsigned ablocks = (unsigned)((groups + per - 1) / per * (direct ? p.Cg : 1));
+    const size_t lds = direct ? 0 : (size_t)per * ((four ? 8 : 2) * p.Cg + 1) * 16;
+#define PNN_LAUNCH_DIGITS(PX, DIRECT)                                                                                                              \
+    hipLaunchKernelGGL((p8_conv_digits_kernel<PX, DIRECT>), dim3(wblocks + ablocks), dim3(256), lds, stream, (const uint8_t*)in, HW, pixels, act, \
+                       (const uint8_t*)w, p, Ad, reinterpret_cast<uint4*>(zero), wblocks)
+    if (four && direct) PNN_LAUNCH_DIGITS(4, true);
+    else if (four) PNN_LAUNCH_DIGITS(4, false);
+    else if (direct) PNN_LAUNCH_DIGITS(1, true);
+    else PNN_LAUNCH_DIGITS(1, false);
+#undef PNN_LAUNCH_DIGITS
     PNN_CHECK_LAUNCH();
     P8ConvMfmaArgs a;
     a.Ad = Ad; a.act = act; a.zero = zero;

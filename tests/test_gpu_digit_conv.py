@@ -101,6 +101,21 @@ def test_paddings_beyond_the_tensor_posit8_0(pad):
     assert len(np.unique(y)) > 32
 
 
+@pytest.mark.parametrize("C,N,H,K", [(512, 37, 15, 5), (514, 43, 14, 5), (528, 37, 15, 5), (4096, 43, 14, 5), (4100, 43, 14, 64), (4100, 43, 14, 65),
+                                     (8192, 37, 15, 70)])
+def test_many_channels_posit8_0(C, N, H, K):
+    """Up to 32 groups of 16 input channels a workgroup writes the digits of a stretch of pixels, beyond of one group; 512 groups
+    are the most the kernel takes, beyond 256 with more than 64 outputs only."""
+    d = dict(N=N, C=C, H=H, W=H, K=K, R=1, S=1, pad_h=0, pad_w=0)
+    rng = np.random.default_rng(C + H)
+    x, w, bias = _tensor(rng, (N, C, H, H), "p8", "gauss"), _tensor(rng, (K, C, 1, 1), "p8", "gauss", 0.1), _tensor(rng, (K,), "p8", "gauss")
+    x[N - 1, C - 1, H - 1, H - 1] = 0x80
+    w[3, C - 2] = 0x80
+    y = to_np(pn.posit_conv2d_fwd(to_dev(x), to_dev(w), _desc(d), "p8", "p8", bias=to_dev(bias)), "p8")
+    images = np.array([0, N // 2, N - 1])
+    _equal(y[images], fast.conv2d_fwd(np.ascontiguousarray(x[images]), w, dict(d, N=3), "p8", "p8", bias=bias), "forward")
+
+
 @pytest.mark.parametrize("spans", [(22, 34), (34, 22), (38, 30), (30, 46), (46, 38), (46, 46), (56, 22)])
 @pytest.mark.parametrize("fmt,maxs", [("p8_2", 24), ("p10_1", 16), ("p12_1", 20), ("p16", 28)])
 def test_planes_that_hold_anything(fmt, maxs, spans):

@@ -82,3 +82,11 @@ def test_gathers_stay_within_their_integers(hc, fmt, which):  # noqa: F811
         assert far + max(0, taps[0][1] * WI + taps[1][1]) * unit < 1 << 31
         assert (taps[0][0] * WI + taps[1][0]) * unit > -(1 << 31)
     assert served > 100
+
+
+def test_posit8_0_layers_of_many_channels_stay_on_the_matrix_cores(hc):  # noqa: F811
+    out = (ctypes.c_int64 * 12)()
+    hc.hostcheck_conv_gather_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    served = lambda c, k: hc.hostcheck_conv_gather_plan(CODE["p8"], 0, ctypes.byref(binding.ConvDesc(43, c, 14, 14, k, 1, 1, 0, 0, 1, 1)), out)  # noqa: E731
+    assert served(4096, 16) and served(4097, 65) and served(8192, 256)
+    assert not served(4097, 64) and not served(8193, 256)
