@@ -47,7 +47,7 @@ inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
         } else if (M < 96 || N < 96 || K < 64) {
             return false;
         }
-        return F::N == 8 || dig_plan<F>(M, N, K).total <= limit;
+        return F::N == 8 || dig_plan<F>(M, N, K, limit).total <= limit;
     }
 }
 
@@ -56,7 +56,7 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
     if (dig_gemm_fits<F>(M, N, K, limit)) {
         GemmPlan p;
         p.splits = 1; p.k_per_split = K; p.ws_bytes = 0;
-        if constexpr (is_dig<F>()) p.ws_bytes = dig_plan<F>(M, N, K).total;
+        if constexpr (is_dig<F>()) p.ws_bytes = dig_plan<F>(M, N, K, limit).total;
         return p;
     }
     if constexpr (is_b8<F>()) {
@@ -113,7 +113,7 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
     if constexpr (is_dig<F>()) {
         if (use_dig) {
             const DigInfo* decision;
-            e = launch_dig_gemm<F>(st, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, ws, &decision);
+            e = launch_dig_gemm<F>(st, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, ws, limit, &decision);
             if (e != hipSuccess || DigFormat<F>::COVER) return hip_status(e);
             served = &decision->np;
         }

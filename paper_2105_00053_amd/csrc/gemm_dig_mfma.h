@@ -401,9 +401,8 @@ __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig
 // Adds the slices of every output, adds the bias, rounds once.  One output per thread; the slices' limbs are read along
 // the outputs.
 template <int NP>
-__global__ __launch_bounds__(256) void dig_merge_kernel(DigGemmArgs g) {
+__device__ __forceinline__ void dig_merge(const DigGemmArgs& g) {
     constexpr int L = dig_limbs<NP>();
-    if (__builtin_amdgcn_readfirstlane(g.info->np) != NP) return;
     const int64_t MN = (int64_t)g.M * g.N;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= MN) return;
@@ -427,29 +426,38 @@ __global__ __launch_bounds__(256) void dig_merge_kernel(DigGemmArgs g) {
     dig_store_pattern(g.C, (int64_t)m * g.ldc + n, rd.fout.n, dig_round<L>(q, rd, nar != 0, g.bias != nullptr, bp));
 }
 
+// One launch for the slices of either plane count: NPA planes' in a, NPB planes' in b.
+template <int NPA, int NPB>
+__global__ __launch_bounds__(256) void dig_merge_kernel(DigGemmArgs a, DigGemmArgs b) {
+    const int np = __builtin_amdgcn_readfirstlane(a.info->np);
+    if (np == NPA && a.splits > 1) dig_merge<NPA>(a);
+    if (NPB != NPA && np == NPB && b.splits > 1) dig_merge<NPB>(b);
+}
+
 // ---- host side ----
 
 struct DigPlan {
     int RBA, RBB, KB;
     bool narrow;               // there is a kernel of NP1 planes in the call
-    int splits, kb_per_split;  // of the kernel that cuts the reduction (NPS planes)
-    int kg;                    // groups of waves per workgroup in that kernel
-    size_t planes_bytes, ma_bytes, mb_bytes, stat_off, part_off, total;
+    int splits, kb_per_split;  // of the kernel of NPS planes
+    int wide_splits, wide_kb_per_split;  // of the one of NP2 planes behind a narrow one
+    int kg;                    // groups of waves per workgroup in the kernel of NPS planes
+    size_t planes_bytes, ma_bytes, mb_bytes, stat_off, part_off, wide_part_off, total;
 };
 
 // posit(8,1): three planes (22 bits) hold what its Gaussian tensors use, and five sums leave room for a third wave per SIMD;
 // below this size the second product kernel's launch costs more than that saves.
 constexpr int64_t DIG_P8_1_NARROW = (int64_t)1 << 31;
 
-// The kernel that may cut the reduction: that of four planes, or the only one.
+// The kernel that may always cut the reduction: that of four planes, or the only one.
 template <class F>
 constexpr int dig_nps() { return DigFormat<F>::NP1 == 4 ? 4 : DigFormat<F>::NP2; }
 
 // Room for 8 planes of both operands (posit(8,1): 4), the masks, 256 bytes for the decision, and what is not found inside
 // on top: the scan's results take a slot that no kernel of posit(8,2) uses (posit(8,1): the rest of the 256 bytes), the partial sums of a cut reduction the slots
-// that the narrow kernel leaves free if they fit there (posit(8,2): only then).
+// that the narrow kernel leaves free if they fit there (posit(8,2): only then).  limit: bytes of workspace there may be.
 template <class F>
-inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K) {
+inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
     typedef DigFormat<F> D;
     constexpr int slots = F::N == 8 && !D::BASE0 ? D::NP2 : 8, NPS = dig_nps<F>();
     static_assert(sizeof(DigInfo) <= 32 && 32 + 2 * DIG_STAT_WGS8 * 4 <= 256, "decision and packed scan results");
@@ -474,6 +482,7 @@ inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K) {
     }
     // Few tiles and a long reduction: slices, so that about 256 workgroups (one per compute unit) share it; each keeps at
     // least 16 k blocks, below which the merging launch costs more than it saves.
+    const size_t rest = p.total;  // where partial sums go that find no room among the planes
     p.narrow = D::NP1 != 0 && (D::NP1 == 4 || M * N * K >= DIG_P8_1_NARROW);
     p.splits = 1;
     p.kb_per_split = p.KB;
@@ -487,8 +496,26 @@ inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K) {
         p.kb_per_split = (int)((p.KB + s - 1) / s);
         p.splits = (p.KB + p.kb_per_split - 1) / p.kb_per_split;
         if (p.splits * per > p.planes_bytes - p.part_off) {
-            p.part_off = p.total;
+            p.part_off = rest;
             p.total += p.splits * per;
+        }
+    }
+    // The wide kernel takes four times as long per k block and holds one workgroup per compute unit: slices of at least 8 k
+    // blocks, where a merging launch is there anyway (all patterns of posit<16,1>, 96 x 97 x 4096: uncut 185 us, cut 39; 115 x 118 x 10332: 425 and 53).  posit(8,2)'s
+    // fixed workspace has no room for them.
+    p.wide_splits = 1;
+    p.wide_kb_per_split = p.KB;
+    p.wide_part_off = rest;
+    if (D::NP1 == 4 && F::N != 8 && p.splits > 1) {
+        int64_t w = 256 / tiles;
+        if (w > p.KB / 8) w = p.KB / 8;
+        if (w > 32) w = 32;
+        const int kbps = (int)((p.KB + w - 1) / w), slices = (p.KB + kbps - 1) / kbps;
+        const size_t total = rest + slices * (((size_t)M * N * dig_limbs<D::NP2>() + M + N) * 4);
+        if (total <= limit) {
+            p.wide_splits = slices;
+            p.wide_kb_per_split = kbps;
+            if (total > p.total) p.total = total;
         }
     }
     p.kg = NPS == 4 && tiles * p.splits <= 256 ? 2 : 1;
@@ -510,10 +537,10 @@ inline hipError_t launch_dig_whole(hipStream_t stream, const DigGemmArgs& g) {
 template <class F>
 inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, const void* A, int64_t lda, const void* B, int64_t ldb,
                                   const void* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace,
-                                  const DigInfo** decision) {
+                                  size_t limit, const DigInfo** decision) {
     typedef DigFormat<F> D;
     constexpr int NPS = dig_nps<F>();
-    const DigPlan p = dig_plan<F>(M, N, K);
+    const DigPlan p = dig_plan<F>(M, N, K, limit);
     uint8_t* base = (uint8_t*)workspace;
     uint8_t* ma = base + p.planes_bytes;
     uint8_t* mb = ma + p.ma_bytes;
@@ -536,14 +563,17 @@ inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, co
     g.fin = fmt_of_code(code_of<F>()); g.fout = fmt_of_code(fout); g.M = (int)M; g.N = (int)N;
     g.tiles_m = p.RBA / 2;
     g.tiles_n = p.RBB / 2;
-    g.splits = p.splits;
-    g.kb_per_split = p.kb_per_split;
-    g.part = g.rowflag = g.colflag = nullptr;
-    if (p.splits > 1) {
-        g.part = (uint32_t*)(base + p.part_off);
-        g.rowflag = g.part + (size_t)p.splits * dig_limbs<NPS>() * M * N;
-        g.colflag = g.rowflag + (size_t)p.splits * M;
-    }
+    auto slices = [&](int splits, int kb_per_split, size_t part_off, int limbs) {
+        g.splits = splits;
+        g.kb_per_split = kb_per_split;
+        g.part = g.rowflag = g.colflag = nullptr;
+        if (splits > 1) {
+            g.part = (uint32_t*)(base + part_off);
+            g.rowflag = g.part + (size_t)splits * limbs * M * N;
+            g.colflag = g.rowflag + (size_t)splits * M;
+        }
+    };
+    slices(p.splits, p.kb_per_split, p.part_off, dig_limbs<NPS>());
     hipError_t e;
     if constexpr (D::NP1 == 3) {
         if (p.narrow) {
@@ -554,14 +584,15 @@ inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, co
     if constexpr (NPS == 4) e = p.kg == 2 ? launch_dig_product<4, 2, 4>(stream, g, p.splits) : launch_dig_whole<4>(stream, g);
     else e = launch_dig_whole<NPS>(stream, g);
     if (e != hipSuccess) return e;
-    if (p.splits > 1) {
-        hipLaunchKernelGGL(dig_merge_kernel<NPS>, dim3((unsigned)((M * N + 255) / 256)), dim3(256), 0, stream, g);
-        PNN_CHECK_LAUNCH();
-    }
+    const DigGemmArgs first = g;
     if constexpr (D::NP1 == 4) {
-        g.splits = 1;
-        g.kb_per_split = p.KB;
+        slices(p.wide_splits, p.wide_kb_per_split, p.wide_part_off, dig_limbs<D::NP2>());
         e = launch_dig_whole<D::NP2>(stream, g);
+        if (e != hipSuccess) return e;
+    }
+    if (p.splits > 1) {
+        hipLaunchKernelGGL((dig_merge_kernel<NPS, D::NP2>), dim3((unsigned)((M * N + 255) / 256)), dim3(256), 0, stream, first, g);
+        PNN_CHECK_LAUNCH();
     }
     return e;
 }

@@ -9,6 +9,7 @@
 #include "conv_desc.h"
 #include "conv_p8_mfma.h"
 #include "conv_dig_mfma.h"
+#include "gemm_dig_mfma.h"
 #include "p16_window_arith.h"
 #include "noquire_arith.h"
 #include "loss_ops.h"
@@ -239,6 +240,21 @@ int host_conv_plan(int which, const ConvGeom& g, int64_t* out) {
     }
     if (!(F::N == 8 && F::ES == 0) || !p8_conv_eligible(which, g)) return 0;
     return host_conv_gather(p8_conv_mfma_plan(which, g), g.sh, g.sw, 2, out);
+}
+
+template <class F>
+int host_dig_plan(int64_t M, int64_t N, int64_t K, int64_t limit, int64_t* out) {
+    if constexpr (F::N == 8 && F::ES == 0) return 0;
+    else {
+        typedef DigFormat<F> D;
+        const DigPlan p = dig_plan<F>(M, N, K, limit < 0 ? SIZE_MAX : (size_t)limit);
+        const int64_t blocks = (int64_t)p.KB * (p.RBA + p.RBB), nps = dig_nps<F>();
+        const int64_t v[14] = {p.KB, p.splits, p.kb_per_split, (int64_t)p.part_off, ((int64_t)M * N * dig_limbs<dig_nps<F>()>() + M + N) * 4, blocks * nps * 1024,
+                               p.wide_splits, p.wide_kb_per_split, (int64_t)p.wide_part_off, ((int64_t)M * N * dig_limbs<D::NP2>() + M + N) * 4,
+                               blocks * D::NP2 * 1024, (int64_t)p.planes_bytes, (int64_t)(p.planes_bytes + p.ma_bytes + p.mb_bytes + 256), (int64_t)p.total};
+        for (int i = 0; i < 14; ++i) out[i] = v[i];
+        return 1;
+    }
 }
 
 template <int L>
@@ -562,6 +578,14 @@ int hostcheck_conv_gather_plan(int fmt, int which, const pnn_conv2d_desc* d, int
     ConvGeom g;
     if (!conv_geom(d, &g)) return 0;
     PNN_DISPATCH_POSIT(fmt, return host_conv_plan<F>(which, g, out))
+    return 0;
+}
+
+// The digit planes' plan of a matrix product (limit < 0: none).  out: k blocks; slices, k blocks per slice, offset and bytes per
+// slice of the partial sums and bytes of the planes of the kernel that always cuts; the same five of the wide kernel; room for
+// planes, end of the masks and the decision, total.
+int hostcheck_dig_plan(int fmt, int64_t M, int64_t N, int64_t K, int64_t limit, int64_t* out) {
+    PNN_DISPATCH_POSIT(fmt, return host_dig_plan<F>(M, N, K, limit, out))
     return 0;
 }
 }  // extern "C"

@@ -119,6 +119,24 @@ def test_static_scratch_gives_way_to_the_older_kernels():
     assert np.array_equal(got[[0, M - 1]], want)
 
 
+@pytest.mark.parametrize("fmt,fout,M,N,K,ta,tb", [("p16", "p16", 96, 97, 4097, 0, 1), ("p16", "p32", 130, 700, 1056, 1, 0), ("p16", "p8", 100, 97, 16352, 0, 0),
+                                                  ("p12_1", "p12_1", 162, 210, 3956, 0, 1), ("p10_1", "p16", 121, 319, 2993, 1, 1)])
+@pytest.mark.parametrize("bias,nar", [(False, False), (True, True)])
+def test_wide_windows_cut_into_slices(fmt, fout, M, N, K, ta, tb, bias, nar):
+    """Few tiles and a long reduction over operands that need all planes: the wide kernel's slices and their merge."""
+    rng = np.random.default_rng(M + N + K)
+    A, B = (rand_patterns(rng, s, fmt, special=0.01, allow_nar=False) for s in ((M, K), (K, N)))
+    if nar:
+        A[M - 1, K - 1] = A[3, 0] = B[K // 2, N - 1] = 1 << (BITS[fmt] - 1)
+    bv = _operand(rng, (N,), fmt, "uniform") if bias else None
+    Ain, Bin = (np.ascontiguousarray(A.T) if ta else A), (np.ascontiguousarray(B.T) if tb else B)
+    got = to_np(pn.posit_gemm(to_dev(Ain), to_dev(Bin), fmt, fout, trans_a=ta, trans_b=tb, bias=None if bv is None else to_dev(bv)), fout)
+    rows = np.array([0, 3, 31, 32, 63, 64, M - 1])
+    want, _ = fast.gemm(np.ascontiguousarray(A[rows]), B, fmt, fout, bias=bv)
+    bad = mismatches(got[rows], want)
+    assert len(bad) == 0, "%d outputs differ, first at %s" % (len(bad), bad[0])
+
+
 def test_posit32_with_bias_takes_no_workspace():
     import torch
     from paper_2105_00053_amd import binding

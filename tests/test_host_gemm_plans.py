@@ -7,10 +7,10 @@ import torch
 
 from paper_2105_00053_amd import binding
 
-from test_host_logic import CODE
+from test_host_logic import CODE, hc  # noqa: F401
 
 EWORKSPACE, EHIP = 3, 4
-pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="the accepted calls would be launched on addresses that do not exist")
+no_gpu = pytest.mark.skipif(torch.cuda.is_available(), reason="the accepted calls would be launched on addresses that do not exist")
 FAKE, NULL = ctypes.c_void_p(0x1000), ctypes.c_void_p(0)
 
 
@@ -19,6 +19,7 @@ def _gemm(fmt, M, N, K, bias, ws_bytes):
     return binding.load().posit_gemm(NULL, c, c, 0, 0, M, N, K, FAKE, K, FAKE, N, FAKE if bias else NULL, FAKE, N, FAKE if ws_bytes else NULL, ws_bytes)
 
 
+@no_gpu
 def test_posit32_with_bias_needs_no_workspace():
     """The kernel with the quire in LDS serves it; without bias the digit planes take what the query answers."""
     M, N, K = 512, 512, 512
@@ -35,6 +36,7 @@ def _static(fmt, M, N, K):
     return binding.load().posit_gemm_static(NULL, c, c, 0, 0, M, N, K, FAKE, K, FAKE, N, NULL, FAKE, N)
 
 
+@no_gpu
 @pytest.mark.parametrize("fmt", ["p8_1", "p8_2"])
 def test_static_scratch_refuses_what_exceeds_it(fmt):
     assert binding.posit_gemm_workspace(fmt, fmt, 0, 0, 4096, 4096, 4096) > 72 << 20
@@ -42,6 +44,31 @@ def test_static_scratch_refuses_what_exceeds_it(fmt):
     assert _static(fmt, 1024, 1024, 1024) == EHIP
 
 
+@no_gpu
 @pytest.mark.parametrize("fmt,M,N,K", [("p32", 4096, 4100, 1280), ("p32", 512, 512, 512), ("p16", 1024, 1024, 1024), ("p12_1", 1024, 1024, 1024)])
 def test_static_scratch_takes_what_an_older_kernel_can_do(fmt, M, N, K):
     assert _static(fmt, M, N, K) == EHIP
+
+
+@pytest.mark.parametrize("fmt", ["p8_1", "p8_2", "p10_1", "p12_1", "p16", "p32"])
+def test_slices_of_a_reduction_and_where_their_sums_go(hc, fmt):  # noqa: F811
+    """Every slice of either plane count has k blocks, the partial sums lie beside the planes and inside the workspace, and few
+    tiles with a long reduction are cut for both counts (posit(8,1) and (8,2): for the narrow one only)."""
+    out = (ctypes.c_int64 * 14)()
+    hc.hostcheck_dig_plan.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 4 + [ctypes.c_void_p]
+    for M, N, K in ((96, 96, 64), (96, 97, 4096), (100, 640, 1023), (115, 118, 10332), (97, 100, 16352), (787, 108, 4864), (300, 260, 1056), (512, 512, 512),
+                    (1024, 1024, 1024), (1000, 1537, 500), (96, 700, 1040), (384, 400, 8192)):
+        for limit in (-1, 72 << 20, 3 << 20):
+            assert hc.hostcheck_dig_plan(CODE[fmt], M, N, K, limit, out)
+            KB, s, kbps, off, per, planes, ws, wkbps, woff, wper, wplanes, room, rest, total = out[:]
+            for slices, k, at, size, used in ((s, kbps, off, per, planes), (ws, wkbps, woff, wper, wplanes)):
+                assert slices >= 1 and (slices - 1) * k < KB <= slices * k
+                if slices > 1:
+                    assert at % 16 == 0 and at >= used and at + slices * size <= total
+                    assert at + slices * size <= room or at >= rest
+            if fmt in ("p10_1", "p12_1", "p16"):
+                tiles = ((M + 63) // 64) * ((N + 63) // 64)
+                assert (s > 1) == (tiles <= 128 and KB >= 32)
+                if limit < 0:
+                    assert (ws > 1) == (s > 1)
+                assert ws == 1 or limit < 0 or total <= max(limit, rest + s * per)
