@@ -270,6 +270,26 @@ inline GemmPlan b8_conv_plan(int M, int N, int K) {
     return plan_split(M, N, K, tl.bm, tl.bn, Arith<F>::L, P8_KT);
 }
 
+// What a pass of a convolution takes on this kernel, in us, for choosing between it and the digit planes: the launches, one
+// slice's chain of k steps, the outputs, the workgroups, and the multiply-adds of whole tiles at the rate of their size.
+// Fitted to the three passes of 1965 layers of 2^22 to 2^31 multiply-adds, bias gradient included; off by 14 to 19 % (root
+// mean square).
+struct B8Cost { double one, cut, step, output, group, mac64, mac64x32, mac32, mac16; };
+
+template <class F>
+inline double b8_conv_us(bool weights, int M, int N, int K) {
+    static_assert(F::N == 8 && (F::ES == 1 || F::ES == 2), "posit(8,1) and posit(8,2)");
+    constexpr B8Cost COST[2][2] = {{{5, 5, 0.07, 6.7e-6, 0.0011, 9.2e-8, 1.29e-7, 7e-8, 3.8e-7}, {7, 19.4, 0.1, 0, 0.0108, 8.3e-8, 1e-7, 9.7e-8, 2e-7}},
+                                   {{4, 4, 0.08, 8.3e-6, 0.0017, 2.2e-7, 2.46e-7, 2e-7, 4.1e-7}, {7, 23.6, 0.15, 0, 0, 2.2e-7, 1.9e-7, 1.8e-7, 1e-7}}};
+    const B8Cost& c = COST[F::ES - 1][weights ? 1 : 0];
+    const B8Tile tl = b8_tile(M, N, K);
+    const GemmPlan plan = b8_conv_plan<F>(M, N, K);
+    const double tiles = (double)((M + tl.bm - 1) / tl.bm) * ((N + tl.bn - 1) / tl.bn);
+    const double mac = tl.bm == 64 ? (tl.bn == 64 ? c.mac64 : c.mac64x32) : tl.bm == 32 ? c.mac32 : c.mac16;
+    return (plan.splits > 1 ? c.cut : c.one) + c.step * (double)plan.k_per_split + c.output * M * N +
+           tiles * plan.splits * (c.group + mac * tl.bm * tl.bn * (double)plan.k_per_split);
+}
+
 // Launch on a problem built by p8_problem / p8_gemm_problem; merge_out maps the merged (Mw x Nw)
 // result to the output tensor.
 template <class F, class Out>

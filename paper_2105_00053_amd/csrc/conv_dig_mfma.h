@@ -17,6 +17,7 @@
 // eight are launched, the one decided on does the work.
 #pragma once
 
+#include "conv_b8.h"
 #include "conv_desc.h"
 #include "gemm_dig_mfma.h"
 
@@ -45,6 +46,20 @@ struct DigConvPlan {
     // behind the planes: 256 bytes of zeros, 256 of decision, the scan's results
     size_t total() const { return w_bytes + act_bytes + 512 + DIG_STAT_BYTES; }
 };
+
+// posit(8,1) and posit(8,2) have the byte-gather kernel beside this one: whether these four launches, fitted like b8_conv_us to
+// layers whose operands four planes hold (off by 8 to 19 %), take a tenth less at least.  Short reductions and one or two input
+// channels under a large filter stay there: posit(8,1) backward-data of 64 images of 16 channels at 16 x 16 to 16, 1 x 1,
+// 12.7 us there and 19.6 here; forward of 32 images of 1 channel at 32 x 32 to 32, 7 x 7, 20 and 36.  Weights over most of
+// the range of posit(8,2) take the wide kernel, at up to twice the time, hence a sixth there (one layer in eight is slower
+// here all the same).
+template <class F>
+inline bool dig_conv_pays(const DigConvPlan& p) {
+    const double groups = (double)(p.RBA / p.WY) * (double)((p.P + 32 * (4 / p.WY) - 1) / (32 * (4 / p.WY)));
+    const double waves = groups > 256 ? groups / 256 - 1 : 0, mb = (double)p.NI * p.HI * p.WI * p.Cg * 16 / (1 << 20);
+    const double here = F::ES == 1 ? 16.3 + 0.82 * p.KB * (1 + 0.5 * waves) + 4.05 * mb + 2.5 * waves : 19.1 + 0.77 * p.KB * (1 + 0.5 * waves) + 2.2 * mb + 2.6 * waves;
+    return b8_conv_us<F>(false, (int)p.P, p.MO, p.CI * p.R * p.S) >= (F::ES == 1 ? 1.1 : 1.2) * here;
+}
 
 template <class F>
 inline DigConvPlan dig_conv_plan(int which, const ConvGeom& g) {
@@ -76,6 +91,9 @@ inline DigConvPlan dig_conv_plan(int which, const ConvGeom& g) {
     p.RBA = (int)((p.MO + 32 * p.WY - 1) / (32 * p.WY)) * p.WY;
     p.w_bytes = (size_t)p.KB * p.RBA * slots * 1024;
     p.act_bytes = (size_t)pin * p.Cg * slots * 16;
+    if constexpr (F::N == 8) {
+        if (p8_conv_eligible(which, g) && !dig_conv_pays<F>(p)) return p;
+    }
     p.ok = true;
     return p;
 }
@@ -600,6 +618,19 @@ struct DigConvBwPlan {
     size_t total() const { return part_off() + part_bytes; }
 };
 
+// The same for the weight gradient, two launches and a merge: what is left to the byte-gather kernel are batches of one to three
+// images (padded to 16 here; posit(8,1), one image of 64 channels at 64 x 64 to 64, 3 x 3: 43 us there, 87 here) and much
+// input for few products (256 images of 128 channels at 56 x 56 to 32, 1 x 1: 381 and 626 us).  Without a bias gradient the other
+// path has a launch less.
+template <class F>
+inline bool dig_conv_bw_pays(const DigConvBwPlan& p, bool with_bias) {
+    const ConvGeom& g = p.g;
+    const double rows = (double)p.tiles_m * 32 * p.WY, cols = (double)p.tiles_n * 32 * (4 / p.WY), k = 16.0 * g.OH * g.OW * p.NG;
+    const double mb = ((double)g.C * g.H * g.W * p.NG * 16 + k * rows) / (1 << 20), more = mb > 24 ? mb - 24 : 0;
+    const double here = (F::ES == 1 ? 27.0 + 2.3 * mb : 30.5 + 1.14 * mb) + 2.2 * more + 1.84e-8 * k * rows * cols;
+    return b8_conv_us<F>(true, p.crs, g.K, g.N * g.OH * g.OW) - (with_bias ? 0.0 : 8.0) >= 1.1 * here;
+}
+
 template <class F>
 inline DigConvBwPlan dig_conv_bw_plan(const ConvGeom& g, bool with_bias) {
     DigConvBwPlan p;
@@ -637,6 +668,9 @@ inline DigConvBwPlan dig_conv_bw_plan(const ConvGeom& g, bool with_bias) {
     p.ones_bytes = (size_t)p.NG * slots * 16;
     if (p.a_bytes >= ((size_t)1 << 34)) return p;
     p.part_bytes = ((size_t)p.splits * p.M * p.N * L + (size_t)p.splits * (p.M + p.N)) * 4;
+    if constexpr (F::N == 8) {
+        if (p8_conv_eligible(2, g) && !dig_conv_bw_pays<F>(p, with_bias)) return p;
+    }
     p.ok = true;
     return p;
 }

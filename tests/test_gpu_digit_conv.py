@@ -21,6 +21,10 @@ GEOMETRIES = [
     dict(N=15, C=20, H=25, W=24, K=64, R=3, S=3, pad_h=1, pad_w=1, stride_h=2, stride_w=1),
     dict(N=64, C=6, H=14, W=14, K=16, R=5, S=5, pad_h=0, pad_w=0),
     dict(N=17, C=48, H=16, W=16, K=3, R=3, S=3, pad_h=3, pad_w=2),
+    dict(N=40, C=33, H=17, W=16, K=31, R=3, S=3, pad_h=1, pad_w=1),
+    dict(N=67, C=40, H=16, W=16, K=3, R=5, S=5, pad_h=2, pad_w=2),
+    dict(N=21, C=16, H=20, W=20, K=32, R=1, S=1, pad_h=0, pad_w=0),
+    dict(N=2, C=30, H=50, W=52, K=40, R=3, S=3, pad_h=1, pad_w=1),
 ]
 
 

@@ -90,3 +90,21 @@ def test_posit8_0_layers_of_many_channels_stay_on_the_matrix_cores(hc):  # noqa:
     served = lambda c, k: hc.hostcheck_conv_gather_plan(CODE["p8"], 0, ctypes.byref(binding.ConvDesc(43, c, 14, 14, k, 1, 1, 0, 0, 1, 1)), out)  # noqa: E731
     assert served(4096, 16) and served(4097, 65) and served(8192, 256)
     assert not served(4097, 64) and not served(8193, 256)
+
+
+@pytest.mark.parametrize("fmt,which,layer,served", [
+    ("p8_1", 1, (64, 16, 16, 16, 16, 1), False), ("p8_2", 1, (64, 32, 16, 16, 32, 1), False), ("p8_1", 0, (32, 1, 32, 32, 32, 7), False),
+    ("p8_2", 1, (32, 32, 16, 16, 1, 7), False), ("p8_1", 2, (1, 64, 64, 64, 64, 3), False), ("p8_1", 2, (130, 124, 53, 53, 24, 1), False),
+    ("p8_1", 1, (128, 32, 32, 32, 32, 3), True), ("p8_2", 0, (128, 3, 32, 32, 32, 3), True), ("p8_2", 1, (64, 16, 16, 16, 16, 3), True),
+    ("p8_1", 2, (128, 64, 16, 16, 64, 3), True), ("p8_2", 2, (2, 64, 64, 64, 64, 3), True), ("p16", 1, (64, 16, 16, 16, 16, 1), True)])
+def test_layers_that_stay_with_the_byte_gather_kernel(hc, fmt, which, layer, served):  # noqa: F811
+    """Both sides of the rule between the 8-bit formats' two kernels, at layers measured on both."""
+    n, c, h, w, k, r = layer
+    d = binding.ConvDesc(n, c, h, w, k, r, r, r // 2, r // 2, 1, 1)
+    if layer[0] == 130:
+        d.stride_h = d.stride_w = 2
+    if which == 2:
+        assert (_bw_need(hc, fmt, d, 1) > 0) == served
+    else:
+        hc.hostcheck_conv_gather_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+        assert bool(hc.hostcheck_conv_gather_plan(CODE[fmt], which, ctypes.byref(d), (ctypes.c_int64 * 12)())) == served
