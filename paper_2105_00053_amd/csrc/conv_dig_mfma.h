@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void dig_conv_digits_kernel(const typename Sto
                                                               DigInfo* __restrict__ info) {
     typedef DigFormat<F> D;
     __shared__ uint64_t tab[F::N == 8 ? 256 : 1];
-    const DigInfo d = dig_read_decision<F>(stats, info, D::NP1 == 4, blockIdx.x == 0);
+    const DigInfo d = dig_read_decision<F, false>(stats, info, D::NP1 == 4, blockIdx.x == 0);
     __shared__ uint4 xch[256 * dig_conv_wide<F>()];
     if (D::NP1 == 4 && d.np == 4) dig_conv_planes<F, 4, PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab, xch);
     else dig_conv_planes<F, dig_conv_wide<F>(), PX>(src, HW, pixels, act, w, p, wdst, zero, wblocks, d, tab, xch);
@@ -569,7 +569,7 @@ inline hipError_t launch_dig_conv(hipStream_t stream, const DigConvPlan& p, cons
     const int HW = p.HI * p.WI;
     const int64_t nx = pixels * p.CI, nw = (int64_t)p.WK * p.WC * p.R * p.S;
     const DigStatJob sx{in, 1, nx, nx, 0}, sw{w, 1, nw, nw, 0};
-    hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sx, sw, stats);
+    hipLaunchKernelGGL((dig_stat_kernel<F, false>), dim3((unsigned)dig_stat_wgs<false>(), 2), dim3(1024), 0, stream, sx, sw, stats);
     PNN_CHECK_LAUNCH();
     const unsigned wblocks = (unsigned)(((int64_t)p.KB * p.RBA * 64 + 255) / 256);
     constexpr int PX = 4 / (int)sizeof(T);
@@ -820,7 +820,7 @@ __global__ __launch_bounds__(256) void dig_conv_bw_digits_kernel(const typename 
     constexpr int POS = dig_bw_positions<F>();
     __shared__ uint64_t tab[F::N == 8 ? 256 : 1];
     __shared__ __attribute__((aligned(16))) T tile[16][32][POS + 4 / (int)sizeof(T)];
-    const DigInfo d = dig_read_decision<F>(stats, info, D::NP1 == 4, blockIdx.x == 0);
+    const DigInfo d = dig_read_decision<F, false>(stats, info, D::NP1 == 4, blockIdx.x == 0);
     if (D::NP1 == 4 && d.np == 4) dig_conv_bw_planes<F, 4, PX, POS>(dy, x, p, Ad, xb, ones, zero, ablocks, chunks, d, tab, tile);
     else dig_conv_bw_planes<F, dig_conv_wide<F>(), PX, POS>(dy, x, p, Ad, xb, ones, zero, ablocks, chunks, d, tab, tile);
 }
@@ -1088,7 +1088,7 @@ inline hipError_t launch_dig_conv_bw(hipStream_t stream, const DigConvBwPlan& p,
     const ConvGeom& g = p.g;
     const int64_t planes = (int64_t)g.C * g.H * g.W, nx = planes * g.N, ny = (int64_t)g.N * g.K * g.OH * g.OW;
     const DigStatJob sx{x, 1, nx, nx, p.N > p.crs ? 1 : 0}, sy{dy, 1, ny, ny, 0};
-    hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sx, sy, stats);
+    hipLaunchKernelGGL((dig_stat_kernel<F, false>), dim3((unsigned)dig_stat_wgs<false>(), 2), dim3(1024), 0, stream, sx, sy, stats);
     PNN_CHECK_LAUNCH();
     constexpr int POS = dig_bw_positions<F>(), PX = 4 / (int)sizeof(T);
     const int posmax = (2 * p.KB + p.NG - 1) / p.NG;  // positions up to the padded end of the reduction

@@ -164,23 +164,26 @@ struct DigScan {
     }
 };
 
-// posit(8,1) keeps what a workgroup saw in one word, so that the results of DIG_STAT_WGS8 workgroups fit beside the decision.
-constexpr int DIG_STAT_WGS8 = 28;
+// PACK: the matrix product of posit(8,1) keeps what a workgroup saw in 16 bits (smallest magnitude minus one, largest one, NaR),
+// so that the results of DIG_STAT_WGS8 workgroups fit beside the decision.  (With 28 workgroups, 32 bits each, convolutions
+// too, the scan of two 2048 x 2048 operands took 13.7 us, and the weight gradient of 256 images of 128 channels at 28 x 28 to
+// 128, 1 x 1, 224; now 177.)
+constexpr int DIG_STAT_WGS8 = 56;
 template <class F>
 constexpr bool dig_stat_packed() { return F::N == 8 && !DigFormat<F>::BASE0; }
-template <class F>
-constexpr int dig_stat_wgs() { return dig_stat_packed<F>() ? DIG_STAT_WGS8 : DIG_STAT_WGS; }
+template <bool PACK>
+constexpr int dig_stat_wgs() { return PACK ? DIG_STAT_WGS8 : DIG_STAT_WGS; }
 
 // Grid (dig_stat_wgs, 2), 1024 threads: workgroup (g, o) leaves what it saw of operand o in stats[o * wgs + g].  Bound by
 // memory: four 16-byte loads in flight per thread (one: 22 us for 2 x 16 MB, 1.5 TB/s).
-template <class F>
+template <class F, bool PACK>
 __global__ __launch_bounds__(1024) void dig_stat_kernel(DigStatJob job0, DigStatJob job1, void* __restrict__ stats) {
     typedef typename Storage<F::N>::T T;
     constexpr int V = 16 / (int)sizeof(T);
     const DigStatJob& job = blockIdx.y == 0 ? job0 : job1;
     const T* src = (const T*)job.src;
     const int t = threadIdx.x;
-    constexpr int WGS = dig_stat_wgs<F>();
+    constexpr int WGS = dig_stat_wgs<PACK>();
     const int64_t step = (int64_t)WGS * 1024, first = (int64_t)blockIdx.x * 1024 + t;
     DigScan<F> s;
     auto vec = [&](const uint4& v) {
@@ -229,24 +232,24 @@ __global__ __launch_bounds__(1024) void dig_stat_kernel(DigStatJob job0, DigStat
 #pragma unroll
         for (int i = 1; i < 16; ++i) s.merge(part[i].low, part[i].high, part[i].nar);
         const int at = blockIdx.y * WGS + blockIdx.x;
-        if constexpr (dig_stat_packed<F>()) ((uint32_t*)stats)[at] = (s.low < 0xFFu ? s.low : 0xFFu) | (s.high << 8) | (s.nar << 16);
+        if constexpr (PACK) ((uint16_t*)stats)[at] = (uint16_t)((s.low < 0xFFu ? s.low : 0xFFu) | (s.high << 8) | (s.nar << 15));
         else ((DigStat*)stats)[at] = DigStat{s.low, s.high, s.nar, 0};
     }
 }
 
 // Every workgroup (256 threads) of a digit launch reads the partial results and decides; the first one stores the decision
 // for the launches that follow.
-template <class F>
+template <class F, bool PACK>
 __device__ __forceinline__ DigInfo dig_read_decision(const void* __restrict__ stats, DigInfo* __restrict__ info, bool narrow, bool store) {
     static_assert(DIG_STAT_WGS == 128 && DIG_STAT_WGS8 <= 128, "two waves per operand");
-    constexpr int WGS = dig_stat_wgs<F>();
+    constexpr int WGS = dig_stat_wgs<PACK>();
     __shared__ DigStat wave[4];
     const int t = threadIdx.x, o = t >> 7, g = t & 127;
     DigScan<F> s;
     if (g < WGS) {
-        if constexpr (dig_stat_packed<F>()) {
-            const uint32_t v = ((const uint32_t*)stats)[o * WGS + g];
-            s.merge((v & 0xFFu) == 0xFFu ? 0xFFFFFFFFu : v & 0xFFu, (v >> 8) & 0xFFu, v >> 16);
+        if constexpr (PACK) {
+            const uint32_t v = ((const uint16_t*)stats)[o * WGS + g];
+            s.merge((v & 0xFFu) == 0xFFu ? 0xFFFFFFFFu : v & 0xFFu, (v >> 8) & 0x7Fu, v >> 15);
         } else {
             const DigStat v = ((const DigStat*)stats)[o * WGS + g];
             s.merge(v.low, v.high, v.nar);

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void dig_matrix_kernel(DigMatrixJob job0, DigM
             for (int b = 0; b < 16; ++b) dt[b] = v[b];
         }
     }
-    const DigInfo d = dig_read_decision<F>(stats, info, narrow != 0, blockIdx.x == 0);
+    const DigInfo d = dig_read_decision<F, dig_stat_packed<F>()>(stats, info, narrow != 0, blockIdx.x == 0);
     if (d.np == 0) return;
     __syncthreads();
     uint8_t* dst = first ? planes : planes + (int64_t)KB * job0.RB * d.np * 1024;
@@ -460,7 +460,7 @@ template <class F>
 inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
     typedef DigFormat<F> D;
     constexpr int slots = F::N == 8 && !D::BASE0 ? D::NP2 : 8, NPS = dig_nps<F>();
-    static_assert(sizeof(DigInfo) <= 32 && 32 + 2 * DIG_STAT_WGS8 * 4 <= 256, "decision and packed scan results");
+    static_assert(sizeof(DigInfo) <= 32 && 32 + 2 * DIG_STAT_WGS8 * 2 <= 256, "decision and packed scan results");
     DigPlan p;
     const int64_t tm = (M + 63) / 64, tn = (N + 63) / 64, tiles = tm * tn;
     p.RBA = (int)tm * 2;
@@ -548,7 +548,7 @@ inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, co
     void* stats = base + p.stat_off;
     *decision = info;
     const DigStatJob sa{A, transA ? K : M, transA ? M : K, lda, 0}, sb{B, transB ? N : K, transB ? K : N, ldb, 0};
-    hipLaunchKernelGGL(dig_stat_kernel<F>, dim3((unsigned)dig_stat_wgs<F>(), 2), dim3(1024), 0, stream, sa, sb, stats);
+    hipLaunchKernelGGL((dig_stat_kernel<F, dig_stat_packed<F>()>), dim3((unsigned)dig_stat_wgs<dig_stat_packed<F>()>(), 2), dim3(1024), 0, stream, sa, sb, stats);
     PNN_CHECK_LAUNCH();
     // op(A)[m,k] is A[m * lda + k] unless transA; op(B)[k,n] is B[k * ldb + n] unless transB
     const DigMatrixJob ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, ma, p.RBA};
