@@ -48,7 +48,7 @@ struct DigConvPlan {
 };
 
 // posit(8,1) and posit(8,2) have the byte-gather kernel beside this one: whether these four launches, fitted like b8_conv_us to
-// layers whose operands four planes hold (off by 8 to 19 %), take a tenth less at least.  Short reductions and one or two input
+// layers whose operands four planes hold (off by 8 to 19 %), take a twentieth less at least.  Short reductions and one or two input
 // channels under a large filter stay there: posit(8,1) backward-data of 64 images of 16 channels at 16 x 16 to 16, 1 x 1,
 // 12.7 us there and 19.6 here; forward of 32 images of 1 channel at 32 x 32 to 32, 7 x 7, 20 and 36.  Weights over most of
 // the range of posit(8,2) take the wide kernel, at up to twice the time, hence a sixth there (one layer in eight is slower
@@ -57,8 +57,8 @@ template <class F>
 inline bool dig_conv_pays(const DigConvPlan& p) {
     const double groups = (double)(p.RBA / p.WY) * (double)((p.P + 32 * (4 / p.WY) - 1) / (32 * (4 / p.WY)));
     const double waves = groups > 256 ? groups / 256 - 1 : 0, mb = (double)p.NI * p.HI * p.WI * p.Cg * 16 / (1 << 20);
-    const double here = F::ES == 1 ? 16.3 + 0.82 * p.KB * (1 + 0.5 * waves) + 4.05 * mb + 2.5 * waves : 19.1 + 0.77 * p.KB * (1 + 0.5 * waves) + 2.2 * mb + 2.6 * waves;
-    return b8_conv_us<F>(false, (int)p.P, p.MO, p.CI * p.R * p.S) >= (F::ES == 1 ? 1.1 : 1.2) * here;
+    const double here = F::ES == 1 ? 16.7 + 0.82 * p.KB * (1 + 0.5 * waves) + 2.2 * mb + 2.8 * waves : 19.1 + 0.77 * p.KB * (1 + 0.5 * waves) + 2.2 * mb + 2.6 * waves;
+    return b8_conv_us<F>(false, (int)p.P, p.MO, p.CI * p.R * p.S) >= (F::ES == 1 ? 1.05 : 1.2) * here;
 }
 
 template <class F>
@@ -620,15 +620,14 @@ struct DigConvBwPlan {
 
 // The same for the weight gradient, two launches and a merge: what is left to the byte-gather kernel are batches of one to three
 // images (padded to 16 here; posit(8,1), one image of 64 channels at 64 x 64 to 64, 3 x 3: 43 us there, 87 here) and much
-// input for few products (256 images of 128 channels at 56 x 56 to 32, 1 x 1: 381 and 626 us).  Without a bias gradient the other
-// path has a launch less.
+// input for few products.  Without a bias gradient the other path has a launch less.
 template <class F>
 inline bool dig_conv_bw_pays(const DigConvBwPlan& p, bool with_bias) {
     const ConvGeom& g = p.g;
     const double rows = (double)p.tiles_m * 32 * p.WY, cols = (double)p.tiles_n * 32 * (4 / p.WY), k = 16.0 * g.OH * g.OW * p.NG;
     const double mb = ((double)g.C * g.H * g.W * p.NG * 16 + k * rows) / (1 << 20), more = mb > 24 ? mb - 24 : 0;
-    const double here = (F::ES == 1 ? 27.0 + 2.3 * mb : 30.5 + 1.14 * mb) + 2.2 * more + 1.84e-8 * k * rows * cols;
-    return b8_conv_us<F>(true, p.crs, g.K, g.N * g.OH * g.OW) - (with_bias ? 0.0 : 8.0) >= 1.1 * here;
+    const double here = (F::ES == 1 ? 28.2 + 0.74 * mb : 30.5 + 1.14 * mb) + 1.1 * more + 1.88e-8 * k * rows * cols;
+    return b8_conv_us<F>(true, p.crs, g.K, g.N * g.OH * g.OW) - (with_bias ? 0.0 : 8.0) >= 1.15 * here;
 }
 
 template <class F>
