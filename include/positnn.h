@@ -158,7 +158,9 @@ int posit_conv2d_bwd_weight(void* stream, int fin, int fout, const pnn_conv2d_de
  * the tensors), or, from 2^26 multiply-adds on, as int8 digit planes (forward and backward-data: twice
  * the gathered tensor, channels padded to 16; backward-weight: twice x and twice dy, the batch padded
  * to 16); for posit(8,1), (8,2), (10,1), (12,1) and <16,1> from about 2^22 multiply-adds on as digit
- * planes likewise, four (posit(8,1)) or eight bytes per element.  The calls of one stream may share one workspace.  The answer
+ * planes likewise, four (posit(8,1)) or eight bytes per element whatever the data need, beside the partial sums of
+ * a weight gradient (posit(8,2), 256 images of 128 channels at 56 x 56 to 32, 1 x 1: 1.07 GB).  The calls of one
+ * stream may share one workspace.  The answer
  * depends on which, fin and desc (fout is accepted for the same reason as in posit_gemm_workspace). */
 size_t posit_conv2d_workspace(int which, int fin, int fout, const pnn_conv2d_desc* desc);
 

@@ -7,8 +7,8 @@
 // merge of a reduction cut into slices.
 //
 // Layout of the rewritten operands: [k block of 32][row block of 32][plane][lane][16 bytes] in the lane order of
-// v_mfma_i32_32x32x32_i8 (gemm_p8_mfma.h), and one byte per (k block, row block): the level of the block, that is the
-// lowest plane its multiplication has to start from.
+// v_mfma_i32_32x32x32_i8 (gemm_p8_mfma.h), and one byte per (k block, row block): bit g is set when group g of the planes
+// (DigGroups) holds a non-zero digit in the block.
 #pragma once
 
 #include "dig_planes.h"
