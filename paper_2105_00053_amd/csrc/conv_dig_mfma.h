@@ -381,13 +381,8 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigCon
                 const double v = nar ? 0.0 : dig_f64_of_pattern(bp, a.fin, 2 * a.fin.maxs() - at);
                 add = make_uint4(f64_lo(v), f64_hi(v), 0u, 0u);
             } else {
-                DigRound rd;
-                rd.fin = a.fin;
-                rd.at = 0;
-                const uint32_t none[3] = {0, 0, 0};
-                uint32_t u[4];
-                dig_add_bias<3>(none, rd, bp, u);
-                add = make_uint4(u[0], u[1], u[2], u[3]);
+                const unsigned __int128 v = (unsigned __int128)dig_bias_value(bp, a.fin);
+                add = make_uint4((uint32_t)v, (uint32_t)(v >> 32), (uint32_t)(v >> 64), (uint32_t)(v >> 96));
             }
         }
         rowv[t] = nar;

@@ -473,23 +473,27 @@ PNN_HD uint32_t dig_round_limbs(const uint32_t (&q)[L], int qfrac, const FmtRT& 
     return zero ? 0u : s ? (0u - body) & f.mask() : body;
 }
 
-// The integer of L limbs in units of minpos^2 * 2^at as a 128-bit quire (units of minpos^2), plus bias * 1.  Formats of at
+// bias * 1 in units of minpos^2 (zero for NaR, which the caller sees to); formats of at most 16 bits.
+PNN_HD __int128 dig_bias_value(uint32_t bias, const FmtRT& f) {
+    if (bias == 0 || bias == f.nar()) return 0;
+    bool neg;
+    int scale, nf;
+    uint32_t fr;
+    decode_core(bias, f.n, f.es, neg, scale, fr, nf);
+    const uint32_t sig = (1u << nf) | (nf ? fr >> (32 - nf) : 0u);
+    const __int128 v = (__int128)((unsigned __int128)sig << (scale - nf + 2 * f.maxs()));
+    return neg ? -v : v;
+}
+
+// The integer of L limbs in units of minpos^2 * 2^at as a 128-bit quire (units of minpos^2), plus a bias in its units.  Formats of at
 // most 16 bits, where the sums fit 128 bits: either at < 0 and the low bits are zero, or the shift stays within.
 template <int L>
-PNN_HD void dig_add_bias(const uint32_t (&q)[L], const DigRound& d, uint32_t bias, uint32_t (&out)[4]) {
+PNN_HD void dig_add_bias(const uint32_t (&q)[L], int at, __int128 bias, uint32_t (&out)[4]) {
     static_assert(L >= 3, "three limbs or more");
     const uint32_t top = L >= 4 ? q[L >= 4 ? 3 : 0] : (uint32_t)((int32_t)q[L - 1] >> 31);
     unsigned __int128 x = ((unsigned __int128)(((uint64_t)top << 32) | q[2]) << 64) | (((uint64_t)q[1] << 32) | q[0]);
-    x = d.at >= 0 ? x << d.at : (unsigned __int128)((__int128)x >> -d.at);
-    if (bias != 0 && bias != d.fin.nar()) {
-        bool neg;
-        int scale, nf;
-        uint32_t fr;
-        decode_core(bias, d.fin.n, d.fin.es, neg, scale, fr, nf);
-        const uint32_t sig = (1u << nf) | (nf ? fr >> (32 - nf) : 0u);
-        const unsigned __int128 v = (unsigned __int128)sig << (scale - nf + 2 * d.fin.maxs());
-        x = neg ? x - v : x + v;
-    }
+    x = at >= 0 ? x << at : (unsigned __int128)((__int128)x >> -at);
+    x += (unsigned __int128)bias;
 #pragma unroll
     for (int l = 0; l < 4; ++l) out[l] = (uint32_t)(x >> (32 * l));
 }
@@ -502,7 +506,7 @@ __device__ __forceinline__ uint32_t dig_round(const uint32_t (&q)[L], const DigR
     if (has_bias) {
         nar = nar || bias == d.fin.nar();
         uint32_t u[4];
-        dig_add_bias<L>(q, d, bias, u);
+        dig_add_bias<L>(q, d.at, dig_bias_value(bias, d.fin), u);
         const int qf = 2 * d.fin.maxs();
         res = d.fout.n <= 16 ? dig_round_limbs<4, false>(u, qf, d.fout) : dig_round_limbs<4, true>(u, qf, d.fout);
     } else {

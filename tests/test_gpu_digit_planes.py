@@ -74,6 +74,25 @@ def test_bias_nar_and_output_formats(fmt, fout, M, N, K, kinds, bias):
         assert (inner == 0).all()
 
 
+@pytest.mark.parametrize("fmt,fout,M,N,K", [("p16", "p16", 1030, 1100, 96), ("p12_1", "p16", 1030, 1100, 70), ("p10_1", "p10_1", 1030, 1100, 64),
+                                            ("p8_2", "p12_2", 1030, 1100, 258), ("p8_1", "p8_1", 1030, 1100, 258), ("p8_1", "p8_1", 2050, 2100, 512)])
+@pytest.mark.parametrize("up", [-10, -5, 0, 5, 12])
+def test_bias_at_every_weight_of_the_sums(fmt, fout, M, N, K, up):
+    """Uncut products whose sums' unit lies below minpos^2, between it and the unit of the biases, and above that; biases of all
+    patterns, in every other column the negative of a product in the column, which leaves sums near zero."""
+    rng = np.random.default_rng(M + K + up)
+    A, B = (fast.round_from_float((rng.standard_normal(s) * 2.0 ** up).astype(np.float32), fmt) for s in ((M, K), (K, N)))
+    bv = _operand(rng, (N,), fmt, "uniform")
+    part, _ = fast.gemm(np.ascontiguousarray(A[:1]), B, fmt, fmt)
+    bv[::2] = (-part[0, ::2].astype(np.int64)).astype(bv.dtype) & ((1 << BITS[fmt]) - 1)
+    bv[5] = 1 << (BITS[fmt] - 1)
+    got = to_np(pn.posit_gemm(to_dev(A), to_dev(B), fmt, fout, bias=to_dev(bv)), fout)
+    rows = np.array([0, 1, 31, 32, 63, 64, 500, M - 2, M - 1])
+    want, _ = fast.gemm(np.ascontiguousarray(A[rows]), B, fmt, fout, bias=bv)
+    assert len(mismatches(got[rows], want)) == 0
+    assert (got[:, 5] == 1 << (BITS[fout] - 1)).all()
+
+
 @pytest.mark.parametrize("fmt", ["p8_1", "p8_2", "p16", "p12_1", "p32"])
 @pytest.mark.parametrize("nar", [False, True])
 def test_windows_at_their_limits(fmt, nar):
