@@ -35,6 +35,10 @@ constexpr bool is_dig() { return F::N == 32 || (F::ES != 0 && DigFormat<F>::COVE
 
 // Products that go to the integer matrix cores as base-256 digit planes, where the workspace may have up to `limit` bytes
 // (posit(8,1) and posit(8,2) do not give way to their older kernel: beyond the limit the call is refused).
+// Timed against the kernels that served before, drawn products with and without bias: of 1400 of the 16-bit containers, 2^16 to
+// 2^31 multiply-adds, one was slower (860 x 286 x 112 with a bias, 28.6 us there, 30.6 here); of about 500
+// posit<32,2> without bias none; of 700 posit(8,1) with a bias, 2^25 to 2^34, 6 by 7 to 11 % (500 to 770 tiles, of which the
+// older kernel held three per compute unit, this one two), the mean 1.3 times as fast.
 template <class F>
 inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
     if constexpr (!is_dig<F>()) return false;
