@@ -47,18 +47,19 @@ struct DigConvPlan {
     size_t total() const { return w_bytes + act_bytes + 512 + DIG_STAT_BYTES; }
 };
 
-// posit(8,1) and posit(8,2) have the byte-gather kernel beside this one: whether these four launches, fitted like b8_conv_us to
-// layers whose operands four planes hold (off by 8 to 19 %), take a twentieth less at least.  Short reductions and one or two input
-// channels under a large filter stay there: posit(8,1) backward-data of 64 images of 16 channels at 16 x 16 to 16, 1 x 1,
-// 12.7 us there and 19.6 here; forward of 32 images of 1 channel at 32 x 32 to 32, 7 x 7, 20 and 36.  Weights over most of
-// the range of posit(8,2) take the wide kernel, at up to twice the time, hence a sixth there (one layer in eight is slower
-// here all the same).
+// posit(8,1) and posit(8,2) have the byte-gather kernel beside this one: whether these four launches pay, by an estimate fitted
+// like b8_conv_us to layers whose operands four planes hold (off by 8 to 19 %).  Short reductions and one or two input channels
+// under a large filter stay there: posit(8,1) backward-data of 64 images of 16 channels at 16 x 16 to 16, 1 x 1, 12.7 us there
+// and 19.6 here; forward of 32 images of 1 channel at 32 x 32 to 32, 7 x 7, 20 and 36.  The factors are those that lost least
+// over 2370 layers timed on both: 15 of 1675 backward-data passes more than 6 % slower than here, 27 than there (estimates
+// alike: 28 and 14; at 1.05 and 1.2: 78 and 8; posit(8,2), 24 images of 13 channels at 14 x 14 to 9, 5 x 5, 43 there and 26 here).  Weights over
+// most of the range of posit(8,2) take the wide kernel, at up to twice the time.
 template <class F>
 inline bool dig_conv_pays(const DigConvPlan& p) {
     const double groups = (double)(p.RBA / p.WY) * (double)((p.P + 32 * (4 / p.WY) - 1) / (32 * (4 / p.WY)));
     const double waves = groups > 256 ? groups / 256 - 1 : 0, mb = (double)p.NI * p.HI * p.WI * p.Cg * 16 / (1 << 20);
     const double here = F::ES == 1 ? 16.7 + 0.82 * p.KB * (1 + 0.5 * waves) + 2.2 * mb + 2.8 * waves : 19.1 + 0.77 * p.KB * (1 + 0.5 * waves) + 2.2 * mb + 2.6 * waves;
-    return b8_conv_us<F>(false, (int)p.P, p.MO, p.CI * p.R * p.S) >= (F::ES == 1 ? 1.05 : 1.2) * here;
+    return b8_conv_us<F>(false, (int)p.P, p.MO, p.CI * p.R * p.S) >= (p.which == 1 ? 0.95 : F::ES == 1 ? 1.0 : 1.1) * here;
 }
 
 template <class F>
