@@ -229,27 +229,31 @@ __global__ void p8_fill_zero_kernel(uint32_t* p, int64_t n) {
 }
 
 // int32 quire (units of 2^-12) -> posit<8,0>, nearest, ties to even pattern, clamped to +-minpos / +-maxpos.
-// Straight-line code (an epilogue calls it for every output of a tile; branches per call cost more than they save):
-// the conversion to binary32 finds the leading bit and is exact up to 2^24, far beyond maxpos = 2^18 units, where only the
-// clamp matters.  With k = floor(log2 |value|), kk = k for k >= 0 and -k-1 otherwise, an arithmetic right shift by kk of
-// "10" followed by the fraction gives kk+1 ones, a zero and the fraction; for negative k the fraction is complemented
-// before and the whole word after the shift, which turns that head into kk+1 zeros and a one.  The 23 fraction bits stay
-// inside the word (2 + 6 + 23 bits), so nothing is lost before the rounding.
-PNN_HD uint32_t p8_round_quire(int32_t q) {
-    const uint32_t bits = __builtin_bit_cast(uint32_t, (float)q);
-    const uint32_t sm = (uint32_t)((int32_t)bits >> 31);  // all ones for a negative sum
-    const uint32_t ab = bits & 0x7FFFFFFFu;
-    constexpr uint32_t LO = (127u + 6u) << 23, HI = (127u + 18u) << 23;  // minpos, maxpos: 2^6, 2^18 units
-    const uint32_t c = ab < LO ? LO : (ab > HI ? HI : ab);
-    const int k = (int)(c >> 23) - 139;                  // floor(log2(mag)) - 12
-    const uint32_t sg = (uint32_t)(k >> 31);
-    const uint32_t kk = (uint32_t)k ^ sg;
-    const uint32_t w = 0x80000000u | (((c << 9) ^ sg) >> 2);
-    const uint32_t x = (uint32_t)((int32_t)w >> kk) ^ sg;  // 7 kept bits, the guard bit, the rest of the fraction
-    const uint32_t body = (x + 0x00FFFFFFu + ((x >> 25) & 1u)) >> 25;
-    const uint32_t pat = ((body ^ sm) - sm) & 0xFFu;
-    return ab == 0 ? 0u : pat;
+// Straight-line code (an epilogue calls it for every output of a tile).  Without exponent bits the pattern, as a function
+// of the magnitude x, is piecewise linear: 64 x below one, and 128 - 2^(5-k) (2 - F) for x = 2^k (1 + F) from one on, so
+// rounding the encoding is rounding that number to an integer, ties to even.  The second piece is the binary32 number whose
+// bits are a constant minus the bits of x (that negates the exponent and turns 1 + F into 2 - F); it lies below the first for
+// x < 1 and x > 1 alike, so the median of both and 64 picks the right one.  Every step is exact for sums below 2^24 units;
+// from maxpos = 2^18 units on, and below minpos, only the clamp matters.  The pattern is the low byte of the result: the rounding is
+// that of adding 1.5 2^23, whose low bits then hold the integer in two's complement.
+PNN_HD float p8_med3(float a, float b, float c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_fmed3f(a, b, c);
+#else
+    return a < b ? (b < c ? b : a < c ? c : a) : (a < c ? a : b < c ? c : b);
+#endif
 }
+
+PNN_HD uint32_t p8_round_bits(float q) {
+    const float a = __builtin_fabsf(q);
+    const float steep = a * (1.0f / 64.0f);                                       // 64 x, x = q 2^-12
+    const uint32_t inv = ((260u + 12u) << 23) - __builtin_bit_cast(uint32_t, a > 1.0f ? a : 1.0f);  // 2^(5-k) (2 - F)
+    const float flat = 128.0f - __builtin_bit_cast(float, inv);
+    const float p = p8_med3(p8_med3(steep, flat, 64.0f), a < 1.0f ? a : 1.0f, 127.0f);  // a sum of 0 is an integer below 1 and stays 0
+    return __builtin_bit_cast(uint32_t, __builtin_copysignf(p, q) + 12582912.0f);
+}
+
+PNN_HD uint32_t p8_round_quire(int32_t q) { return p8_round_bits((float)q) & 0xFFu; }
 
 // PACKED: A and B point at operands rewritten by p8_pack_kernel (lda, ldb: their padded row counts),
 // rowflag_g / colflag_g at the NaR flags that kernel raised.
