@@ -6,6 +6,7 @@
 #include "api_common.h"
 #include "conv_p8.h"
 #include "gemm_p8_w4.h"
+#include "gemm_p8_f6.h"
 #include "gemm_p8_mfma.h"
 #include "gemm_dig_mfma.h"
 #include "conv_b8.h"
@@ -76,6 +77,11 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
         p.splits = 1; p.k_per_split = K; p.ws_bytes = 0;
         return p;
     }
+    if ((F::N == 8 && F::ES == 0) && p8_f6_fits(M, N, K, limit)) {  // digits for the 6-bit floating-point matrix cores, or planes as below
+        GemmPlan p;
+        p.splits = 1; p.k_per_split = K; p.ws_bytes = p8_f6_layout(M, N, K).total();
+        return p;
+    }
     if ((F::N == 8 && F::ES == 0) && p8_mfma_fits(M, N, K)) {  // digit planes of both operands for the integer matrix cores
         GemmPlan p;
         p.splits = 1; p.k_per_split = K; p.ws_bytes = p8_mfma_layout(M, N, K).total();
@@ -125,6 +131,9 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
     if ((F::N == 8 && F::ES == 0) && p8_small_gemm_fits(M, N, K))
         return hip_status(launch_p8_small_gemm(st, transA, transB, (const uint8_t*)A, lda, (const uint8_t*)B, ldb, (const uint8_t*)bias, C, ldc,
                                                fout, M, N, K));
+    if ((F::N == 8 && F::ES == 0) && p8_f6_fits(M, N, K, limit))
+        return hip_status(launch_p8_f6_gemm(st, transA, transB, (const uint8_t*)A, lda, (const uint8_t*)B, ldb, (const uint8_t*)bias, C, ldc, fout, M, N,
+                                            K, ws));
     if ((F::N == 8 && F::ES == 0) && p8_mfma_fits(M, N, K))
         return hip_status(launch_p8_mfma_gemm(st, transA, transB, (const uint8_t*)A, lda, (const uint8_t*)B, ldb, (const uint8_t*)bias, C, ldc, fout,
                                               M, N, K, ws));

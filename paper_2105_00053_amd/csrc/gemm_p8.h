@@ -255,6 +255,15 @@ PNN_HD uint32_t p8_round_bits(float q) {
 
 PNN_HD uint32_t p8_round_quire(int32_t q) { return p8_round_bits((float)q) & 0xFFu; }
 
+// The low bytes of four words
+PNN_HD uint32_t p8_pack4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0C0C0400u), __builtin_amdgcn_perm(b, a, 0x0C0C0400u), 0x05040100u);
+#else
+    return (a & 0xFFu) | ((b & 0xFFu) << 8) | ((c & 0xFFu) << 16) | (d << 24);
+#endif
+}
+
 // PACKED: A and B point at operands rewritten by p8_pack_kernel (lda, ldb: their padded row counts),
 // rowflag_g / colflag_g at the NaR flags that kernel raised.
 template <bool A_KFAST, bool B_KFAST, bool PACKED = false>

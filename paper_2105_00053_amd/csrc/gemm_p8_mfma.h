@@ -34,7 +34,7 @@ typedef int pm_v4i __attribute__((ext_vector_type(4)));
 typedef int pm_v16i __attribute__((ext_vector_type(16)));
 
 constexpr int PM_MIN_MN = 128;                   // smallest output extent each way
-constexpr int64_t PM_MIN_MNK = (int64_t)1 << 28;  // smallest product count
+constexpr int64_t PM_MIN_MNK = (int64_t)1 << 28;  // smallest product count (from PF_MIN_TILES tiles on: gemm_p8_f6.h)
 constexpr int PM_MIN_TILES = 81;                 // fewest 64 x 64 tiles: below, kernels that cut the reduction across workgroups win
 constexpr int PM_MIN_WGS = 512;                  // workgroups wanted before a larger tile is chosen
 constexpr int PM_MIN_KB_SPLIT = 16;              // fewest k blocks of 32 per slice
@@ -80,11 +80,17 @@ struct P8DigitJob {
 };
 
 // Both operands in one launch: the first blocks0 workgroups take job0, the rest job1.  A workgroup handles one k block
-// and eight row blocks: 512 lane slots of 16 bytes per digit, two per thread.
+// and eight row blocks: 512 lane slots of 16 bytes per digit, two per thread.  With flags (gemm_p8_f6.h) there is work only
+// if one of the nflags is set.
 template <int UNUSED = 0>
-__global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8DigitJob job1, unsigned blocks0) {
+__global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8DigitJob job1, unsigned blocks0, const uint32_t* __restrict__ flags, int nflags) {
     __shared__ uint16_t tab[256];
     const int t = threadIdx.x;
+    if (flags) {
+        uint32_t any = 0;
+        for (int i = t; i < nflags; i += 256) any |= flags[i];
+        if (!__syncthreads_or((int)any)) return;
+    }
     tab[t] = pm_digits((uint32_t)t);
     __syncthreads();
     const bool first = blockIdx.x < blocks0;
@@ -151,8 +157,22 @@ __global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8Digit
     }
 }
 
+// The tile of a workgroup.  XCD-aware order: consecutive workgroup ids go round-robin to the 8 XCDs, so give each XCD a contiguous
+// run of tiles, walked in bands of 8 tile-rows, column by column inside a band (neighbours share operand panels in L2)
+__device__ __forceinline__ void pm_tile(int id, int tiles_m, int tiles_n, int& tm, int& tn) {
+    const int nblk = tiles_m * tiles_n;
+    if ((nblk & 7) == 0) id = (id & 7) * (nblk >> 3) + (id >> 3);
+    const int band = id / (8 * tiles_n);
+    const int band_rows = (tiles_m - band * 8) < 8 ? (tiles_m - band * 8) : 8;
+    const int in_band = id - band * 8 * tiles_n;
+    tm = band * 8 + in_band % band_rows;
+    tn = in_band / band_rows;
+}
+
 // Ad / Bd: digit planes of p8_digits_kernel with RBA / RBB row blocks (multiples of 2 BI / 2 BJ) and KB k blocks (a
 // multiple of PM_KSTEP).  Four waves as 2 x 2; a wave owns BI x BJ blocks of 32 x 32 outputs, the workgroup 64 BI x 64 BJ.
+//
+// flags (gemm_p8_f6.h): one word per 128 x 128 outputs, flag_cols a row; outputs whose word is zero are done already.
 //
 // SPLIT: workgroup (tile, z) reduces the kb_per_split k blocks from z kb_per_split on and leaves its 32-bit sums and
 // its NaR flags in the workspace of a split reduction (ws: partial quires [z][M N], row flags [z][M], column flags
@@ -160,7 +180,8 @@ __global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8Digit
 template <int BI, int BJ, bool SPLIT = false>
 __global__ __launch_bounds__(256, (BI * BJ == 4 ? 2 : BI * BJ == 2 ? 3 : 4)) void p8_mfma_gemm_kernel(
     const uint8_t* __restrict__ Ad, const uint8_t* __restrict__ Bd, int RBA, int RBB, int KB, const uint8_t* __restrict__ bias, void* __restrict__ C,
-    int64_t ldc, int fout, int M, int N, int tiles_m, int tiles_n, int kb_per_split = 0, SplitWs ws = SplitWs{nullptr, nullptr, nullptr}) {
+    int64_t ldc, int fout, int M, int N, int tiles_m, int tiles_n, int kb_per_split = 0, SplitWs ws = SplitWs{nullptr, nullptr, nullptr},
+    const uint32_t* __restrict__ flags = nullptr, int flag_cols = 0) {
     constexpr int NA = 2 * BI * 2, NB = 2 * BJ * 2;  // runs of 1 KB (row block, digit) per k block and operand
     constexpr int TR = 64 * BI, TC = 64 * BJ;        // tile extents
     // [buffer][k block of the step][A runs, then B runs][lane]: 64 KB for 128 x 128 outputs
@@ -170,15 +191,9 @@ __global__ __launch_bounds__(256, (BI * BJ == 4 ? 2 : BI * BJ == 2 ? 3 : 4)) voi
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);  // the wave number, known to be uniform
     const int wy = w >> 1, wx = w & 1;
 
-    // XCD-aware order: consecutive workgroup ids go round-robin to the 8 XCDs, so give each XCD a contiguous run of
-    // tiles, walked in bands of 8 tile-rows, column by column inside a band (neighbours share operand panels in L2)
-    const int nblk = tiles_m * tiles_n;
-    int lid = blockIdx.x;
-    if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
-    const int band = lid / (8 * tiles_n);
-    const int band_rows = (tiles_m - band * 8) < 8 ? (tiles_m - band * 8) : 8;
-    const int in_band = lid - band * 8 * tiles_n;
-    const int tm = band * 8 + in_band % band_rows, tn = in_band / band_rows;
+    int tm, tn;
+    pm_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    if (flags && flags[(tm * TR / 128) * flag_cols + tn * TC / 128] == 0) return;
 
     // markers met in this lane's row of the row block / column of the column block this wave searches (its half of every k block)
     uint32_t row_nar = 0, col_nar = 0;
@@ -394,7 +409,8 @@ inline P8MfmaLayout p8_mfma_layout(int64_t M, int64_t N, int64_t K) {
 }
 
 inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
-                                      const uint8_t* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace) {
+                                      const uint8_t* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace,
+                                      const uint32_t* flags = nullptr, int nflags = 0, int flag_cols = 0) {
     const P8MfmaLayout l = p8_mfma_layout(M, N, K);
     uint8_t* base = (uint8_t*)workspace;
     uint8_t* Ad = base;
@@ -403,7 +419,7 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     P8DigitJob ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, Ad, l.RBA, l.KB};
     P8DigitJob jb{B, transB ? ldb : (int64_t)1, transB ? (int64_t)1 : ldb, (int)N, (int)K, Bd, l.RBB, l.KB};
     const unsigned blocks0 = (unsigned)((l.RBA + 7) / 8) * (unsigned)l.KB, blocks1 = (unsigned)((l.RBB + 7) / 8) * (unsigned)l.KB;
-    hipLaunchKernelGGL(p8_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0);
+    hipLaunchKernelGGL(p8_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, flags, nflags);
     PNN_CHECK_LAUNCH();
     const int tiles_m = l.RBA / (2 * l.BI), tiles_n = l.RBB / (2 * l.BJ);
     if (l.splits > 1) {
@@ -420,7 +436,7 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     const dim3 grid((unsigned)(tiles_m * tiles_n));
 #define PNN_PM_LAUNCH(bi, bj)                                                                                                                    \
     hipLaunchKernelGGL((p8_mfma_gemm_kernel<bi, bj>), grid, dim3(256), 0, stream, Ad, Bd, l.RBA, l.RBB, l.KB, bias, C, ldc, fout, (int)M, (int)N, \
-                       tiles_m, tiles_n, 0, SplitWs{nullptr, nullptr, nullptr})
+                       tiles_m, tiles_n, 0, SplitWs{nullptr, nullptr, nullptr}, flags, flag_cols)
     if (l.BI == 2 && l.BJ == 2) PNN_PM_LAUNCH(2, 2);
     else if (l.BI == 2) PNN_PM_LAUNCH(2, 1);
     else if (l.BJ == 2) PNN_PM_LAUNCH(1, 2);

@@ -7,6 +7,7 @@
 #include "api_common.h"
 #include "dig_planes.h"
 #include "conv_desc.h"
+#include "gemm_p8_f6.h"
 #include "conv_p8_mfma.h"
 #include "conv_dig_mfma.h"
 #include "gemm_dig_mfma.h"
@@ -462,6 +463,18 @@ int hostcheck_pw_dot(int64_t n, const uint32_t* a, const uint32_t* b, uint32_t* 
 // the epilogue rounding of the posit<8,0> kernels: 32-bit quire (units of minpos^2 = 2^-12) -> pattern
 int hostcheck_p8_round_quire(int64_t n, const int32_t* in, uint32_t* out) {
     for (int64_t i = 0; i < n; ++i) out[i] = p8_round_quire(in[i]);
+    return 0;
+}
+
+// the 6-bit digits of a posit<8,0> pattern: {flags, h, l, h^2 of the entry, l^2, value}; h and l as the codes read
+int hostcheck_p8_f6(uint32_t pattern, int32_t* out) {
+    const uint2 e = pf_entry(pattern);
+    out[0] = (int32_t)(e.x >> 30);
+    out[1] = pf_value(e.x & 63u);
+    out[2] = pf_value((e.x >> 16) & 63u);
+    out[3] = (int32_t)(e.y >> 16);
+    out[4] = (int32_t)(e.y & 0xFFFFu);
+    out[5] = pattern == 0x80u ? 0 : Arith<P8>::stage(pattern);
     return 0;
 }
 
