@@ -197,9 +197,8 @@ struct P8ConvMfmaArgs {
 // positions).  WY = 1 (all four waves side by side along the positions, 32 x 128 outputs) serves layers of at most 32
 // output channels, where a second row of waves would multiply and round nothing but padding.
 //
-// Bound by the matrix pipes' power and the copies that feed them: 256 images of 64 channels at 56 x 56, 3 x 3 to 64
-// channels (29.6 G products, 118 G int8 products), take 193 us, against 247 us with the ring and its table as two LDS
-// objects (which made every read of the ring wait for all copies) and one flag and bias read per output in the epilogue.
+// Bound by the copies and reads that feed the matrix pipes: 256 images of 64 channels at 56 x 56, 3 x 3 to 64 channels (29.6 G
+// products, 118 G int8 products) take 150 us, of which the matrix instructions alone would take 54.
 template <int BI, int BJ, int WY>
 __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kernel(P8ConvMfmaArgs a) {
     constexpr int WX = 4 / WY;
@@ -248,27 +247,33 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
     const int arun0 = (w * ARUNS) % NA;
     const int64_t a_kb = (int64_t)a.RBA * 2 * 64;
     const uint4* asrc = reinterpret_cast<const uint4*>(a.Ad) + (int64_t)tm * NA * 64 + arun0 * 64;
-    // Input: the k block's NB runs are (column block, digit) pairs.  With four column blocks in the tile wave w gathers
-    // both digits of column block w; with two, digit w % 2 of column block w / 2.  Lane l of a copy serves column
-    // l % 32 of the block and the 16 reduction indices of half l / 32.
+    // Input: of a column's k block four pieces of 16 bytes are gathered, (half of the 32 indices, digit), which lie together in
+    // the planes when both halves are channel groups of one tap.  Four lanes fetch one column's pieces, so that a copy touches
+    // 16 stretches of 64 bytes (a lane per column and one piece of it per copy touches 64 places: 256 images of 64 channels
+    // at 56 x 56, 3 x 3 to 64, 195 us a call that way and 179 now, backward-data 190 and 169).  With four column blocks in the tile wave w gathers column block w, 16 columns a copy; with two,
+    // half w % 2 of column block w / 2.  A copy lands in lane order, [column][piece], where reads of one piece would meet on a
+    // quarter of the banks: place s of column p holds piece s ^ (p / 4 % 4).
     constexpr bool HALF = WX * BJ == 2;
+    constexpr int COPIES = HALF ? 1 : 2;
     const int cb = HALF ? (w >> 1) : w;
     const int hw_o = a.HO * a.WO;
-    int oh, ow, base;
-    {
-        const int pos = tn * TC + cb * 32 + (lane & 31);
+    const int piece = (lane & 3) ^ (lane >> 4);  // column 16 c + lane / 4
+    int oh[COPIES], ow[COPIES], base[COPIES];
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) {
+        const int pos = tn * TC + cb * 32 + (HALF ? 16 * (w & 1) : 16 * c) + (lane >> 2);
         if (pos < a.P) {
             const int img = pos / hw_o, rem = pos - img * hw_o;
-            oh = rem / a.WO;
-            ow = rem - oh * a.WO;
-            base = ((img * a.HI + oh) * a.WI + ow) * a.Cg * 2;
+            oh[c] = rem / a.WO;
+            ow[c] = rem - oh[c] * a.WO;
+            base[c] = ((img * a.HI + oh[c]) * a.WI + ow[c]) * a.Cg * 2 + (piece & 1);
         } else {
-            oh = -40000;  // no tap brings this into the tensor
-            ow = 0;
-            base = 0;
+            oh[c] = -40000;  // no tap brings this into the tensor
+            ow[c] = 0;
+            base[c] = 0;
         }
     }
-    const uint4* actq = reinterpret_cast<const uint4*>(a.act) + (HALF ? (w & 1) : 0);
+    const uint4* actq = reinterpret_cast<const uint4*>(a.act);
     const uint4* zeroq = reinterpret_cast<const uint4*>(a.zero);
 
     auto issue = [&](int kb) {
@@ -278,22 +283,20 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64 + lane),
                                              (__attribute__((address_space(3))) void*)(sbuf + (arun0 + c) * 64), 16, 0, 0);
         asrc += a_kb;
-        const int2 e = ktab[kb * 2 + (lane >> 5)];
+        const int2 e = ktab[kb * 2 + (piece >> 1)];
         const int dh = (int)(short)(e.y & 0xFFFF), dw = e.y >> 16;
-        const int ih = oh + dh, iw = ow + dw;
-        const bool inside = (unsigned)ih < (unsigned)a.HI && (unsigned)iw < (unsigned)a.WI;
-        const uint4* s = inside ? actq + (base + e.x) : zeroq;
-        if (!HALF) {
-            uint4* d = sbuf + (NA + cb * 2) * 64;  // the same for every lane
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)s, (__attribute__((address_space(3))) void*)d, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + 1), (__attribute__((address_space(3))) void*)(d + 64),
-                                             16, 0, 0);
-        } else {
-            uint4* d = sbuf + (NA + cb * 2 + (w & 1)) * 64;
+#pragma unroll
+        for (int c = 0; c < COPIES; ++c) {
+            const int ih = oh[c] + dh, iw = ow[c] + dw;
+            const bool inside = (unsigned)ih < (unsigned)a.HI && (unsigned)iw < (unsigned)a.WI;
+            const uint4* s = inside ? actq + (base[c] + e.x) : zeroq;
+            uint4* d = sbuf + (NA + cb * 2 + (HALF ? (w & 1) : c)) * 64;  // the same for every lane
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)s, (__attribute__((address_space(3))) void*)d, 16, 0, 0);
         }
     };
-    constexpr int LOADS = ARUNS + (HALF ? 1 : 2);  // copies per wave and k block
+    constexpr int LOADS = ARUNS + COPIES;  // copies per wave and k block
+    // where this lane's operands lie in a column block: column lane % 32, half lane / 32
+    const int at_h = (lane & 31) * 4 + (((lane >> 5) * 2) ^ ((lane >> 2) & 3)), at_l = at_h ^ 1;
 
     // the blocks this wave searches for NaR markers: two waves that share blocks split them
     const int ia = BI == 2 ? wx : 0, jb = (BJ == 2 && WY == 2) ? wy : 0;
@@ -318,8 +321,8 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
         }
 #pragma unroll
         for (int j = 0; j < BJ; ++j) {
-            bh[j] = __builtin_bit_cast(pm_v4i, sb[(NA + (BJ * wx + j) * 2 + 0) * 64 + lane]);
-            bl[j] = __builtin_bit_cast(pm_v4i, sb[(NA + (BJ * wx + j) * 2 + 1) * 64 + lane]);
+            bh[j] = __builtin_bit_cast(pm_v4i, sb[(NA + (BJ * wx + j) * 2) * 64 + at_h]);
+            bl[j] = __builtin_bit_cast(pm_v4i, sb[(NA + (BJ * wx + j) * 2) * 64 + at_l]);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
