@@ -198,7 +198,7 @@ struct P8ConvMfmaArgs {
 // output channels, where a second row of waves would multiply and round nothing but padding.
 //
 // Bound by the copies and reads that feed the matrix pipes: 256 images of 64 channels at 56 x 56, 3 x 3 to 64 channels (29.6 G
-// products, 118 G int8 products) take 150 us, of which the matrix instructions alone would take 54.
+// products, 118 G int8 products) take 143 us, of which the matrix instructions alone would take 54.
 template <int BI, int BJ, int WY>
 __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kernel(P8ConvMfmaArgs a) {
     constexpr int WX = 4 / WY;
@@ -333,10 +333,10 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
         for (int i = 0; i < BI; ++i)
 #pragma unroll
             for (int j = 0; j < BJ; ++j) {
-                hh[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ah[i], bh[j], hh[i][j], 0, 0, 0);
-                xx[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ah[i], bl[j], xx[i][j], 0, 0, 0);
-                xx[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(al[i], bh[j], xx[i][j], 0, 0, 0);
-                ll[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(al[i], bl[j], ll[i][j], 0, 0, 0);
+                hh[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bh[j], ah[i], hh[i][j], 0, 0, 0);
+                xx[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bl[j], ah[i], xx[i][j], 0, 0, 0);
+                xx[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bh[j], al[i], xx[i][j], 0, 0, 0);
+                ll[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bl[j], al[i], ll[i][j], 0, 0, 0);
             }
         __builtin_amdgcn_sched_barrier(0);  // a block's reads and matrix instructions stay inside its own iteration
     }
@@ -368,45 +368,79 @@ __global__ __launch_bounds__(256, (BI * BJ == 2 ? 3 : 4)) void p8_conv_mfma_kern
     rowv += wy * 32 * BI;
     rowb += wy * 32 * BI;
     colv += wx * 32 * BJ;
-    // The matrix instruction leaves a lane with one position and 16 BI channels: stored from there, every store
-    // instruction would write 1 byte per lane, 32 bytes per channel row.  The rounded tile goes through LDS instead
-    // (buffers 1 .. of the ring; buffer 0 holds the NaR flags) and leaves in 16-byte runs along the positions.
-    const FmtRT fo = fmt_of_code(a.fout);
-    const int esz = fo.n <= 8 ? 1 : (fo.n <= 16 ? 2 : 4);
-    uint8_t* tileb = reinterpret_cast<uint8_t*>(stage + BUF);
-    static_assert((PCM_STAGES - 1) * (NA + NB) * 1024 >= TR * TC * 4, "the rounded tile fits behind the NaR flags");
-    // flags and bias addends of four consecutive rows come in one read
-    const uint4* rowv4 = reinterpret_cast<const uint4*>(rowv);
-    const int4* rowb4 = reinterpret_cast<const int4*>(rowb);
+    // The product is taken transposed: the matrix instruction leaves a lane with one channel and, in its registers, 16 of a
+    // block's 32 positions in runs of four.  Rounded to bytes and packed, two lanes that share a channel exchange halves, and each
+    // stores 16 consecutive positions.
+    if (a.fout == 0) {
+        const int half = lane >> 5, ch0 = tm * TR + wy * 32 * BI + (lane & 31);
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) {
-        const int lc = (wx * BJ + j) * 32 + (lane & 31);
-        const uint32_t cnar = colv[j * 32 + (lane & 31)];
+        for (int j = 0; j < BJ; ++j) {
+            const uint32_t cmask = (uint32_t)__ballot(colv[j * 32 + (lane & 31)] != 0);  // positions of the block that meet NaR
+            const int n0 = tn * TC + (wx * BJ + j) * 32 + 16 * half;
+            const int img = n0 / hw_o, rem = n0 - img * hw_o;
 #pragma unroll
-        for (int i = 0; i < BI; ++i) {
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const int lr0 = i * 32 + 8 * rq + 4 * (lane >> 5);
-                const uint4 fl = rowv4[lr0 >> 2];
-                const int4 ba = rowb4[lr0 >> 2];
-                const uint32_t flag[4] = {fl.x | cnar, fl.y | cnar, fl.z | cnar, fl.w | cnar};
-                const int32_t add[4] = {ba.x, ba.y, ba.z, ba.w};
+            for (int i = 0; i < BI; ++i) {
+                const uint32_t rnar = rowv[i * 32 + (lane & 31)];
+                const int32_t badd = rowb[i * 32 + (lane & 31)];
+                uint32_t d[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int r = 4 * rq + u;
-                    const uint32_t q = ((uint32_t)hh[i][j][r] << 14) + ((uint32_t)xx[i][j][r] << 7) + (uint32_t)ll[i][j][r] + (uint32_t)add[u];
-                    const int at = (wy * 32 * BI + lr0 + u) * TC + lc;
-                    if (a.fout == 0) {
-                        const uint32_t v = p8_round_quire((int32_t)q);
-                        tileb[at] = (uint8_t)(flag[u] ? 0x80u : v);
-                    } else {
-                        const uint32_t q1[1] = {q};
-                        round_store<QuireAccum<P8>, 1>(q1, flag[u] != 0, a.fout, tileb, at);
+                    uint32_t v[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int r = 4 * u + k;
+                        v[k] = p8_round_bits((float)(int32_t)(((uint32_t)hh[i][j][r] << 14) + ((uint32_t)xx[i][j][r] << 7) + (uint32_t)ll[i][j][r] + (uint32_t)badd));
+                    }
+                    d[u] = p8_pack4(v[0], v[1], v[2], v[3]);
+                }
+                if (cmask != 0 || __any(rnar != 0)) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t b4 = (cmask >> (8 * u + 4 * half)) & 15u;
+                        const uint32_t mk = rnar ? 0xFFFFFFFFu : (((b4 * 0x00204081u) & 0x01010101u) * 0xFFu);
+                        d[u] = (d[u] & ~mk) | (0x80808080u & mk);
+                    }
+                }
+                const auto s0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+                const uint32_t e[4] = {s0[0], s0[1], s1[0], s1[1]};
+                const int m = ch0 + 32 * i;
+                if (m >= a.MO || n0 >= a.P) continue;
+                uint8_t* dst = (uint8_t*)a.out + ((int64_t)img * a.MO + m) * hw_o + rem;
+                if (rem + 16 <= hw_o && n0 + 16 <= a.P) {
+                    __builtin_memcpy(dst, e, 16);  // any alignment
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 16; ++b) {
+                        // past the image's last position the next image's first channel row: a run of 16 may cover several images
+                        const int n = n0 + b, im = n / hw_o;
+                        if (n < a.P) ((uint8_t*)a.out)[((int64_t)im * a.MO + m) * hw_o + (n - im * hw_o)] = (uint8_t)(e[b >> 2] >> (8 * (b & 3)));
                     }
                 }
             }
         }
+        return;
     }
+    // Other output formats: the rounded tile goes through LDS (buffers 1 .. of the ring; buffer 0 holds the NaR flags) and
+    // leaves in 16-byte runs along the positions.
+    const FmtRT fo = fmt_of_code(a.fout);
+    const int esz = fo.n <= 8 ? 1 : (fo.n <= 16 ? 2 : 4);
+    uint8_t* tileb = reinterpret_cast<uint8_t*>(stage + BUF);
+    static_assert((PCM_STAGES - 1) * (NA + NB) * 1024 >= TR * TC * 4, "the rounded tile fits behind the NaR flags");
+#pragma unroll
+    for (int j = 0; j < BJ; ++j)
+#pragma unroll
+        for (int i = 0; i < BI; ++i) {
+            const int lr = i * 32 + (lane & 31);
+            const uint32_t rnar = rowv[lr];
+            const int32_t badd = rowb[lr];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int lc = j * 32 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+                const uint32_t q1[1] = {((uint32_t)hh[i][j][r] << 14) + ((uint32_t)xx[i][j][r] << 7) + (uint32_t)ll[i][j][r] + (uint32_t)badd};
+                round_store<QuireAccum<P8>, 1>(q1, (rnar | colv[lc]) != 0, a.fout, tileb, (wy * 32 * BI + lr) * TC + wx * 32 * BJ + lc);
+            }
+        }
     __syncthreads();
     const int per_run = 16 / esz;            // outputs per 16-byte run
     const int runs_per_row = TC / per_run;
