@@ -220,16 +220,18 @@ int conv_fwd(hipStream_t st, int fout, const ConvGeom& g, const void* x, const v
         st, a, b, out, d.M, d.N, d.K, bias, y, fout, ws, plan));
 }
 
-// The product kernels of this pass treat NaR weights as zeros; the outputs such a weight reaches are marked last.
+// The product kernels of this pass treat NaR weights as zeros; the outputs such a weight reaches are marked last, by the
+// digit-plane kernels themselves (*marked), behind the others by a launch of its own.
 template <class F>
-int conv_bwd_data_product(hipStream_t st, int fout, const ConvGeom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes) {
+int conv_bwd_data_product(hipStream_t st, int fout, const ConvGeom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, bool* marked) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(1, g);
     if constexpr (dig_conv_format<F>()) {
         const DigConvPlan dp = dig_conv_plan<F>(1, g);
         if (dp.ok) {  // integer matrix cores
             if (!ws || ws_bytes < dp.total()) return PNN_EWORKSPACE;
-            return hip_status(launch_dig_conv<F>(st, dp, dy, w, nullptr, dx, fout, ws));
+            *marked = true;
+            return hip_status(launch_dig_conv<F>(st, dp, dy, w, nullptr, dx, fout, ws, bwd_data_nar(w, code_of<F>(), fout, g)));
         }
     }
     if ((F::N == 8 && F::ES == 0) && p8_conv_eligible(1, g)) {
@@ -271,8 +273,9 @@ int conv_bwd_data_product(hipStream_t st, int fout, const ConvGeom& g, const voi
 
 template <class F>
 int conv_bwd_data(hipStream_t st, int fout, const ConvGeom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes) {
-    const int rc = conv_bwd_data_product<F>(st, fout, g, dy, w, dx, ws, ws_bytes);
-    if (rc != PNN_OK) return rc;
+    bool marked = false;
+    const int rc = conv_bwd_data_product<F>(st, fout, g, dy, w, dx, ws, ws_bytes, &marked);
+    if (rc != PNN_OK || marked) return rc;
     launch_bwd_data_nar_weights<F>(st, w, g, dx, fout);
     return hip_status(hipGetLastError());
 }

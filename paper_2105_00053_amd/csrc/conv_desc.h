@@ -49,4 +49,40 @@ inline bool conv_gather_fits(int64_t NI, int64_t HI, int64_t WI, int64_t HO, int
     return (far + (ahead > 0 ? ahead : 0)) * unit < ((int64_t)1 << 31) && behind * unit < ((int64_t)1 << 31);
 }
 
+// Backward-data on digit planes, NaR weights (see bwd_data_nar_weights_kernel, whose launch this replaces: 1.3 us of a call).
+// w: the weights, null where nothing is to be marked.  A workgroup marks its own tile, channels c0 .. c0 + TR - 1 and positions
+// p0 .. p0 + TC - 1, when everything that stores there has done so; it is called only if the weights hold NaR.
+struct BwdDataNar {
+    const void* w;  // [K][C][R][S]
+    int K, C, R, S, ph, pw, OH, OW, H, W, P;
+    FmtRT fin, fout;
+};
+
+template <int TR, int TC>
+__device__ __forceinline__ void bwd_data_nar_tile(const BwdDataNar& g, void* dx, int c0, int p0) {
+    const int rs = g.R * g.S, rows = g.C - c0 < TR ? g.C - c0 : TR;
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's own stores of the tile are done
+    __syncthreads();                // everyone's are
+    for (int64_t i = threadIdx.x; i < (int64_t)rows * g.K * rs; i += 256) {
+        const int tap = (int)(i % rs), k = (int)(i / rs % g.K), c = c0 + (int)(i / ((int64_t)rs * g.K));
+        const int64_t at = ((int64_t)k * g.C + c) * rs + tap;
+        const uint32_t v = g.fin.n <= 8 ? ((const uint8_t*)g.w)[at] : ((const uint16_t*)g.w)[at];
+        if (v != g.fin.nar()) continue;
+        const int r = tap / g.S, s = tap % g.S;
+        for (int p = p0; p < p0 + TC && p < g.P; ++p) {
+            const int n = p / (g.H * g.W), rem = p % (g.H * g.W);
+            const int oh = rem / g.W + g.ph - r, ow = rem % g.W + g.pw - s;  // unit stride
+            if (oh < 0 || oh >= g.OH || ow < 0 || ow >= g.OW) continue;
+            const int64_t o = ((int64_t)n * g.C + c) * g.H * g.W + rem;
+            if (g.fout.n <= 8) ((uint8_t*)dx)[o] = (uint8_t)g.fout.nar();
+            else if (g.fout.n <= 16) ((uint16_t*)dx)[o] = (uint16_t)g.fout.nar();
+            else ((uint32_t*)dx)[o] = g.fout.nar();
+        }
+    }
+}
+
+inline BwdDataNar bwd_data_nar(const void* w, int fin, int fout, const ConvGeom& g) {
+    return BwdDataNar{w, g.K, g.C, g.R, g.S, g.ph, g.pw, g.OH, g.OW, g.H, g.W, g.N * g.H * g.W, fmt_of_code(fin), fmt_of_code(fout)};
+}
+
 }  // namespace pnn

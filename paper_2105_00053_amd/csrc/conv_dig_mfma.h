@@ -242,6 +242,7 @@ struct DigConvArgs {
     void* out;
     FmtRT fin, fout;
     int tiles_m;
+    BwdDataNar nar;       // with weights only in the last launch of a backward-data call
 };
 
 // 128-bit quire from the sums' integer (units of minpos^2 2^at), for adding a bias: at < 0 drops zero bits, at >= 0 stays
@@ -286,8 +287,7 @@ __device__ __forceinline__ void dig_store_rows_bias(int first, int rows, const D
 // bits through LDS 36).  The kernel of eight planes is bound by the matrix pipes, so without NaR it multiplies only the
 // planes that hold digits: weights over most of the range of posit(8,2) 46 us, all 8 x 8 pairs 61.
 template <int NP, int WY, int ST>
-__global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigConvArgs a) {
-    if (__builtin_amdgcn_readfirstlane(a.info->np) != a.np) return;
+__device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
     constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
     constexpr int WX = 4 / WY, NB = WX;          // column blocks
     constexpr int NA = WY;                        // row blocks
@@ -540,6 +540,16 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigCon
     }
 }
 
+// The last launch of a backward-data call also marks what NaR weights reach, tile by tile: behind its own work, or, if another
+// launch did that, right away (100 images of 30 channels at 27 x 27 to 45, posit<16,1>: 57.6 us with a launch of its own, 56.6 so;
+// the posit<8,0> kernel, which has no spare launch, lost 1 to 4 % on large layers by it).
+template <int NP, int WY, int ST>
+__global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigConvArgs a) {
+    const bool mark = a.nar.w && __builtin_amdgcn_readfirstlane(a.info->nar[1]);
+    if (__builtin_amdgcn_readfirstlane(a.info->np) == a.np) dig_conv_tile<NP, WY, ST>(a);
+    if (mark) bwd_data_nar_tile<32 * WY, 32 * (4 / WY)>(a.nar, a.out, (int)(blockIdx.x % a.tiles_m) * 32 * WY, (int)(blockIdx.x / a.tiles_m) * 32 * (4 / WY));
+}
+
 template <int NP>
 inline hipError_t launch_dig_conv_product(hipStream_t stream, const DigConvArgs& a, int WY) {
     const int tc = 32 * (4 / WY);
@@ -552,7 +562,7 @@ inline hipError_t launch_dig_conv_product(hipStream_t stream, const DigConvArgs&
 // in: x (forward) or dy (backward-data); workspace: [weight planes][planes of in][256 zeros][decision][scan]
 template <class F>
 inline hipError_t launch_dig_conv(hipStream_t stream, const DigConvPlan& p, const void* in, const void* w, const void* bias, void* out, int fout,
-                                  void* workspace) {
+                                  void* workspace, const BwdDataNar& nar = BwdDataNar{}) {
     typedef typename Storage<F::N>::T T;
     typedef DigFormat<F> D;
     uint8_t* base = (uint8_t*)workspace;
@@ -588,12 +598,14 @@ inline hipError_t launch_dig_conv(hipStream_t stream, const DigConvPlan& p, cons
     a.fin = fmt_of_code(code_of<F>());
     a.fout = fmt_of_code(fout);
     a.tiles_m = p.RBA / p.WY;
+    a.nar = BwdDataNar{};
     if constexpr (D::NP1 == 4) {
         a.np = 4;
         const hipError_t e = launch_dig_conv_product<4>(stream, a, p.WY);
         if (e != hipSuccess) return e;
     }
     a.np = D::NP2;
+    a.nar = nar;
     return launch_dig_conv_product<dig_conv_wide<F>()>(stream, a, p.WY);
 }
 
