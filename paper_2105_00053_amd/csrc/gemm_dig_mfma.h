@@ -170,6 +170,58 @@ __device__ __forceinline__ void dig_store_rows(int first, int rows, const DigRou
     }
 }
 
+// Rounds and stores rows first, first + STEP, ... of column n of a tile that starts at row row0, the bias added where there is one.
+// value(row, limbs) gives the integer of the sums in units of minpos^2 2^at; cnar, row_flag(row): whether column or row meet NaR.
+template <int L, int STEP, class Value, class Flag>
+__device__ __forceinline__ void dig_round_column(const DigGemmArgs& g, int at, int row0, int n, int first, int rows, uint32_t cnar, const Value& value,
+                                                 const Flag& row_flag) {
+    DigRound rd;
+    rd.fin = g.fin;
+    rd.fout = g.fout;
+    rd.at = at;
+    auto is_nar = [&](int lr) { return (cnar | row_flag(lr)) != 0; };
+    auto store = [&](auto limbs, const auto& of) {
+        constexpr int W = limbs;
+        const int64_t base = (int64_t)row0 * g.ldc + n;
+        if (rd.fout.n <= 8) dig_store_rows<W, uint8_t, STEP>(first, rows, rd, (uint8_t*)g.C + base, g.ldc, of, is_nar);
+        else if (rd.fout.n <= 16) dig_store_rows<W, uint16_t, STEP>(first, rows, rd, (uint16_t*)g.C + base, g.ldc, of, is_nar);
+        else dig_store_rows<W, uint32_t, STEP>(first, rows, rd, (uint32_t*)g.C + base, g.ldc, of, is_nar);
+    };
+    if (g.bias) {
+        // The bias is decoded once per column, and the rows go four at a time as without it (decoded at every row, one row at
+        // a time: 784 x 2976 x 631 posit(8,1) 50 us, now 44).  A value is a multiple of 2^maxs minpos^2, so where the sums'
+        // unit is no larger and the bias fits their limbs it is added in that unit; else both are placed in 128 bits (46).
+        const uint32_t bp = dig_load_pattern(g.bias, n, rd.fin.n);
+        const __int128 bias = dig_bias_value(bp, rd.fin);
+        cnar |= bp == rd.fin.nar() ? 1u : 0u;
+        const int maxs = rd.fin.maxs();
+        if (L <= 4 && at <= maxs && 3 * maxs - at <= 32 * L - 3) {
+            const __int128 placed = at >= 0 ? bias >> at : (__int128)((unsigned __int128)bias << -at);
+            uint32_t bl[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) bl[l] = (uint32_t)(placed >> (l < 4 ? 32 * l : 127));
+            auto biased = [&](int lr, uint32_t (&u)[L]) {
+                uint32_t b[L];
+                value(lr, u);
+#pragma unroll
+                for (int l = 0; l < L; ++l) b[l] = bl[l];
+                quire_merge<L>(u, b);
+            };
+            store(dig_int<L>(), biased);
+            return;
+        }
+        auto biased = [&](int lr, uint32_t (&u)[4]) {
+            uint32_t q[L];
+            value(lr, q);
+            dig_add_bias<L>(q, at, bias, u);
+        };
+        rd.at = 0;
+        store(dig_int<4>(), biased);
+    } else {
+        store(dig_int<L>(), value);
+    }
+}
+
 // 64 x 64 outputs per workgroup: KG groups of four waves (2 x 2), a wave owns one block of 32 x 32 and its 2 NP - 1 sums
 // over the k blocks of its group (every KG-th).  The runs of a k block go straight into LDS, a ring of S blocks with copies
 // S - 1 blocks ahead.  The waves of a workgroup leave each barrier together and would all wait for their LDS reads
@@ -356,10 +408,6 @@ __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig
         if (tm == 0 && t < 64 && n < g.N) g.colflag[(int64_t)z * g.N + n] = cnar;
     }
     if (n >= g.N) return;
-    DigRound rd;
-    rd.fin = g.fin;
-    rd.fout = g.fout;
-    rd.at = at;
     auto value = [&](int lr, uint32_t (&q)[L]) {
 #pragma unroll
         for (int l = 0; l < L; ++l) q[l] = all[l * 4096 + lr * 64 + lane];
@@ -370,15 +418,7 @@ __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig
             quire_merge<L>(q, o);
         }
     };
-    auto is_nar = [&](int lr) { return (cnar | rowv[lr] | (KG == 2 ? rowv[(KG - 1) * 64 + lr] : 0u)) != 0; };
     const int rows = g.M - tm * 64 < 64 ? g.M - tm * 64 : 64;
-    auto store = [&](auto limbs, const auto& of) {
-        constexpr int W = limbs;
-        const int64_t first = (int64_t)tm * 64 * g.ldc + n;
-        if (rd.fout.n <= 8) dig_store_rows<W, uint8_t, 4 * KG>(wave, rows, rd, (uint8_t*)g.C + first, g.ldc, of, is_nar);
-        else if (rd.fout.n <= 16) dig_store_rows<W, uint16_t, 4 * KG>(wave, rows, rd, (uint16_t*)g.C + first, g.ldc, of, is_nar);
-        else dig_store_rows<W, uint32_t, 4 * KG>(wave, rows, rd, (uint32_t*)g.C + first, g.ldc, of, is_nar);
-    };
     if (sliced) {
         const int64_t MN = (int64_t)g.M * g.N;
 #pragma unroll 2
@@ -388,39 +428,105 @@ __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig
 #pragma unroll
             for (int l = 0; l < L; ++l) g.part[((int64_t)z * L + l) * MN + (int64_t)(tm * 64 + lr) * g.N + n] = q[l];
         }
-    } else if (g.bias) {
-        // The bias is decoded once per column, and the rows go four at a time as without it (decoded at every row, one row at
-        // a time: 784 x 2976 x 631 posit(8,1) 50 us, now 44).  A value is a multiple of 2^maxs minpos^2, so where the sums'
-        // unit is no larger and the bias fits their limbs it is added in that unit; else both are placed in 128 bits (46).
-        const uint32_t bp = dig_load_pattern(g.bias, n, rd.fin.n);
-        const __int128 bias = dig_bias_value(bp, rd.fin);
-        cnar |= bp == rd.fin.nar() ? 1u : 0u;
-        const int maxs = rd.fin.maxs();
-        if (L <= 4 && at <= maxs && 3 * maxs - at <= 32 * L - 3) {
-            const __int128 placed = at >= 0 ? bias >> at : (__int128)((unsigned __int128)bias << -at);
-            uint32_t bl[L];
-#pragma unroll
-            for (int l = 0; l < L; ++l) bl[l] = (uint32_t)(placed >> (l < 4 ? 32 * l : 127));
-            auto biased = [&](int lr, uint32_t (&u)[L]) {
-                uint32_t b[L];
-                value(lr, u);
-#pragma unroll
-                for (int l = 0; l < L; ++l) b[l] = bl[l];
-                quire_merge<L>(u, b);
-            };
-            store(dig_int<L>(), biased);
-            return;
-        }
-        auto biased = [&](int lr, uint32_t (&u)[4]) {
-            uint32_t q[L];
-            value(lr, q);
-            dig_add_bias<L>(q, at, bias, u);
-        };
-        rd.at = 0;
-        store(dig_int<4>(), biased);
-    } else {
-        store(dig_int<L>(), value);
+        return;
     }
+    dig_round_column<L, 4 * KG>(g, at, tm * 64, n, wave, rows, cnar, value, [&](int lr) { return rowv[lr] | (KG == 2 ? rowv[(KG - 1) * 64 + lr] : 0u); });
+}
+
+// Products of few tiles: 32 x 32 outputs per workgroup, whose KG waves share the reduction (wave kg the k blocks kg, kg + KG, ...).
+// No wave shares an operand with another, so the blocks go from memory straight to registers, two ahead, without LDS or a
+// barrier until the sums meet.  With 64 x 64 tiles such a product has a fraction of the chip's workgroups, each bound by its own
+// latency: the fill of the ring, a few steps, 16 outputs rounded per thread instead of four.
+template <int NP, int KG>
+__global__ __launch_bounds__(64 * KG, 2) void dig_gemm_small_kernel(DigGemmArgs g) {
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
+    if (__builtin_amdgcn_readfirstlane(g.info->np) != NP) return;
+    __shared__ uint32_t lds[KG * (L * 1024 + 64)];
+    const int t = threadIdx.x;
+    const int lane = t & 63, kg = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int tm = blockIdx.x % g.tiles_m, tn = blockIdx.x / g.tiles_m;
+    const int a_nar = __builtin_amdgcn_readfirstlane(g.info->nar[0]), b_nar = __builtin_amdgcn_readfirstlane(g.info->nar[1]);
+    const int at = __builtin_amdgcn_readfirstlane(g.info->base[0] + g.info->base[1]);
+    const uint4* sa = reinterpret_cast<const uint4*>(g.planes) + ((int64_t)kg * g.RBA + tm) * (NP * 64) + lane;
+    const uint4* sb = reinterpret_cast<const uint4*>(g.planes) + ((int64_t)g.KB * g.RBA + (int64_t)kg * g.RBB + tn) * (NP * 64) + lane;
+    const int64_t a_adv = (int64_t)KG * g.RBA * (NP * 64), b_adv = (int64_t)KG * g.RBB * (NP * 64);
+    pm_v16i acc[NC];
+#pragma unroll
+    for (int s = 0; s < NC; ++s)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[s][r] = 0;
+    uint32_t row_nar = 0, col_nar = 0;
+    const int n_steps = g.KB > kg ? (g.KB - kg + KG - 1) / KG : 0;
+    DigFrag<NP> f[3];
+    auto fetch = [&](int st, DigFrag<NP>& to) {
+        if (st < n_steps) {
+            to.template load<0>(sa, sb);
+            sa += a_adv;
+            sb += b_adv;
+        }
+    };
+    auto step = [&](int st, const DigFrag<NP>& cur, DigFrag<NP>& ahead) {
+        if (st >= n_steps) return;
+        fetch(st + 2, ahead);
+        if (a_nar) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) row_nar |= pm_marker_bits((uint32_t)cur.a[NP - 1][i]);
+        }
+        if (b_nar) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) col_nar |= pm_marker_bits((uint32_t)cur.b[NP - 1][i]);
+        }
+        dig_mma<NP, 0, NP, 0, NP>(cur, acc);
+    };
+    fetch(0, f[0]);
+    fetch(1, f[1]);
+    for (int st = 0; st < n_steps; st += 3) {
+        step(st, f[0], f[2]);
+        step(st + 1, f[1], f[0]);
+        step(st + 2, f[2], f[1]);
+    }
+    uint32_t* const rowv = lds + KG * L * 1024;  // [KG][32], then the columns'
+    uint32_t* const colv = rowv + KG * 32;
+    uint32_t* const vals = lds + kg * (L * 1024);
+    row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
+    col_nar = (col_nar | (uint32_t)__shfl_xor((int)col_nar, 32)) & 0x80808080u;
+    if (lane < 32) {
+        rowv[kg * 32 + lane] = row_nar;
+        colv[kg * 32 + lane] = col_nar;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int lr = (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+        uint32_t q[L];
+        dig_combine<NP>(acc, r, q);
+#pragma unroll
+        for (int l = 0; l < L; ++l) vals[l * 1024 + lr * 32 + (lane & 31)] = q[l];
+    }
+    __syncthreads();
+    const int col = t & 31, n = tn * 32 + col;
+    if (n >= g.N) return;
+    uint32_t cnar = 0;
+#pragma unroll
+    for (int k = 0; k < KG; ++k) cnar |= colv[k * 32 + col];
+    auto value = [&](int lr, uint32_t (&q)[L]) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) q[l] = lds[l * 1024 + (lr & 31) * 32 + col];
+#pragma unroll
+        for (int k = 1; k < KG; ++k) {
+            uint32_t o[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) o[l] = lds[(k * L + l) * 1024 + (lr & 31) * 32 + col];
+            quire_merge<L>(q, o);
+        }
+    };
+    auto row_flag = [&](int lr) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int k = 0; k < KG; ++k) v |= rowv[k * 32 + (lr & 31)];
+        return v;
+    };
+    const int rows = g.M - tm * 32 < 32 ? g.M - tm * 32 : 32;
+    dig_round_column<L, 2 * KG>(g, at, tm * 32, n, t >> 5, rows, cnar, value, row_flag);
 }
 
 // Adds the slices of every output, adds the bias, rounds once.  One output per thread; the slices' limbs are read along
@@ -467,12 +573,18 @@ struct DigPlan {
     int splits, kb_per_split;  // of the kernel of NPS planes
     int wide_splits, wide_kb_per_split;  // of the one of NP2 planes behind a narrow one
     int kg;                    // groups of waves per workgroup in the kernel of NPS planes
+    bool small;                // 32 x 32 tiles in the kernel of four planes
     size_t planes_bytes, ma_bytes, mb_bytes, stat_off, part_off, wide_part_off, total;
 };
 
 // posit(8,1): three planes (22 bits) hold what its Gaussian tensors use, and five sums leave room for a third wave per SIMD;
 // below this size the second product kernel's launch costs more than that saves.
 constexpr int64_t DIG_P8_1_NARROW = (int64_t)1 << 31;
+
+// Most tiles of 64 x 64 for which the kernel of four planes takes 32 x 32 (us a call, posit(12,1), 64 -> 32): 8 tiles, K = 586 22.3 ->
+// 17.2, 64 tiles, 512 21.2 -> 17.1, 96, 512 21.4 -> 19.5, 100, 640 23.2 -> 21.1; 144, 300 21.1 -> 21.9, 256, 1024 30.0 -> 34.8 (every
+// operand is read twice as often).  Eight waves are slower than four from 65 tiles on (two workgroups on some compute units).
+constexpr int DIG_SMALL_TILES = 112, DIG_SMALL_WAVES = 4;
 
 // The kernel that may always cut the reduction: that of four planes, or the only one.
 template <class F>
@@ -544,7 +656,16 @@ inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX
         }
     }
     p.kg = NPS == 4 && tiles * p.splits <= 256 ? 2 : 1;
+    p.small = NPS == 4 && p.splits == 1 && tiles <= DIG_SMALL_TILES;
     return p;
+}
+
+template <int NP, int KG>
+inline hipError_t launch_dig_small(hipStream_t stream, DigGemmArgs g) {
+    g.tiles_m = (g.M + 31) / 32;
+    g.tiles_n = (g.N + 31) / 32;
+    hipLaunchKernelGGL((dig_gemm_small_kernel<NP, KG>), dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(64 * KG), 0, stream, g);
+    return hipGetLastError();
 }
 
 template <int NP, int KG, int S>
@@ -606,7 +727,7 @@ inline hipError_t launch_dig_gemm(hipStream_t stream, int transA, int transB, co
             if (e != hipSuccess) return e;
         }
     }
-    if constexpr (NPS == 4) e = p.kg == 2 ? launch_dig_product<4, 2, 4>(stream, g, p.splits) : launch_dig_whole<4>(stream, g);
+    if constexpr (NPS == 4) e = p.small ? launch_dig_small<4, DIG_SMALL_WAVES>(stream, g) : p.kg == 2 ? launch_dig_product<4, 2, 4>(stream, g, p.splits) : launch_dig_whole<4>(stream, g);
     else e = launch_dig_whole<NPS>(stream, g);
     if (e != hipSuccess) return e;
     const DigGemmArgs first = g;

@@ -169,3 +169,33 @@ def test_posit32_with_bias_takes_no_workspace():
     want, _ = fast.gemm(A, B, "p32", "p32", bias=bias)
     assert len(mismatches(to_np(c, "p32"), want)) == 0
     assert call(stream, code, code, 0, 0, M, N, K, a.data_ptr(), K, b.data_ptr(), N, None, c.data_ptr(), N, None, 0) == 3
+
+
+@pytest.mark.parametrize("fmt,M,N,K,ta,tb,bias,fout", [
+    ("p16", 96, 96, 64, False, False, False, "p16"),       # two k blocks for four waves
+    ("p12_1", 97, 129, 65, True, False, True, "p12_1"),    # one row, column and index into the last tile and block
+    ("p10_1", 127, 96, 127, False, True, True, "p10_1"),   # four k blocks, the last one short
+    ("p16", 160, 161, 161, True, True, True, "p32"),       # six k blocks: waves with one and with two; wide output
+    ("p12_1", 300, 333, 991, False, False, False, "p8"),   # the longest reduction that is not cut: eight steps a wave
+    ("p16", 1024, 448, 96, False, True, False, "p16"),     # the last number of tiles that goes here, and the first beyond
+    ("p16", 1024, 449, 96, False, True, False, "p16"),
+    ("p8_2", 256, 270, 500, True, False, True, "p12_2"),
+])
+def test_few_tiles_of_32_by_32(fmt, M, N, K, ta, tb, bias, fout):
+    """The kernel whose waves share the reduction of one 32 x 32 tile: N(0, 1) operands with NaR in the first row, the last
+    column and in the bias; also data over the whole range, which it leaves to the kernel of more planes."""
+    rng = np.random.default_rng([23, M, N, K])
+    for kind in ("normal", "wide"):
+        A, B = (fast.round_from_float(rng.standard_normal(s).astype(np.float32), fmt) for s in ((M, K), (K, N)))
+        if kind == "wide":
+            A = rand_patterns(rng, (M, K), fmt, allow_nar=False)
+        nar = NP_DTYPE[fmt](1 << (BITS[fmt] - 1))
+        A[0, K - 1] = nar
+        B[K // 2, N - 1] = nar
+        b = None
+        if bias:
+            b = fast.round_from_float(rng.standard_normal(N).astype(np.float32), fmt)
+            b[1] = nar
+        C = pn.posit_gemm(to_dev(A.T if ta else A), to_dev(B.T if tb else B), fmt, fout, trans_a=ta, trans_b=tb, bias=None if b is None else to_dev(b))
+        want, _ = fast.gemm(A, B, fmt, fout, bias=b)
+        assert len(mismatches(to_np(C, fout), want)) == 0, kind
