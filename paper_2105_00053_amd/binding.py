@@ -5,6 +5,8 @@ HIP stream; every computation happens inside libpositnn_hip.so.  There is no
 CPU fallback: a missing library or a non-device tensor is an error.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -42,7 +44,7 @@ _lib = None
 
 def load():
     """Load the shared library (built by paper_2105_00053_amd.build); raises if it is missing."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -86,13 +88,48 @@ def load():
                  "posit_axpy_multi", "posit_unary", "posit_unary_bwd", "posit_cross_entropy", "posit_mse",
                  "posit_relu", "posit_relu_bwd", "posit_maxpool2d_fwd", "posit_maxpool2d_bwd", "posit_avgpool2d_fwd", "posit_avgpool2d_bwd"):
         getattr(L, name).restype = ci
-    _lib = L
+    native = _load_native()
+    native.init(*(ctypes.cast(getattr(L, name), vp).value for name in _NATIVE_ORDER))
+    _lib, _native = L, native
     return L
 
 
-# Argument marshalling is what a step of short kernels waits for (a launch takes 3 us of host time, a call through here took
-# 8.5 to 12.5, now 6 to 9): pointers and the stream go to ctypes as plain integers, and the stream handle is read without
-# building a torch.cuda.Stream object (2.7 us).
+# Argument marshalling is what a step of short kernels waits for: a launch takes 3 us of host time, a call through the Python code
+# here 6 to 9, one through csrc/binding_native.cpp 5 to 6
+# (the LeNet-5-shaped step of batch 64, about fifty calls: 377 us, now 272; a layer of 64 x 400 to 120 9.5 and 6.6).  So the calls of a training step go there first; it returns None for
+# whatever it does not take (a caller's workspace, unusual arguments, arguments that are wrong), which the Python code handles
+# or refuses.  There pointers and the stream go to ctypes as plain integers, and the stream handle is read without building a
+# torch.cuda.Stream object (2.7 us).
+_native = None
+_NATIVE_PATH = os.path.join(_HERE, "positnn_native.so")
+_NATIVE_ORDER = ("posit_gemm", "posit_gemm_workspace", "posit_conv2d_fwd", "posit_conv2d_bwd_data", "posit_conv2d_bwd_weight", "posit_conv2d_workspace",
+                 "posit_round", "posit_convert", "posit_relu", "posit_relu_bwd", "posit_maxpool2d_fwd", "posit_maxpool2d_bwd",
+                 "posit_avgpool2d_fwd", "posit_avgpool2d_bwd")
+
+
+def _load_native():
+    if not os.path.exists(_NATIVE_PATH):
+        raise PositError("positnn_native.so is not built: run `python -m paper_2105_00053_amd.build`")
+    loader = importlib.machinery.ExtensionFileLoader("positnn_native", _NATIVE_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("positnn_native", loader))
+    loader.exec_module(module)
+    return module
+
+
+def _ready():
+    """The current stream for a native call; None as long as library or device are not in use (the Python code judges the call)."""
+    if _native is None or _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
+        return None
+    return _raw_stream(_current_device())
+
+
+def _outputs(r):
+    """What a native call returned: the outputs, or a status."""
+    if r.__class__ is int:
+        _check(r)
+    return r
+
+
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None)
 
@@ -157,6 +194,11 @@ def posit_gemm_workspace(fin, fout, trans_a, trans_b, M, N, K):
 def posit_gemm(A, B, fin, fout, trans_a=False, trans_b=False, bias=None, out=None, workspace=None):
     """C = round_fout(op(A) @ op(B) (+ bias)), 2-D row-major device tensors of patterns."""
     fin, fout = _code(fin), _code(fout)
+    st = _ready()
+    if st is not None and workspace is None:
+        r = _native.gemm(st, fin, fout, int(trans_a), int(trans_b), A, B, bias, out)
+        if r is not None:
+            return _outputs(r)
     M, N, K, lda, ldb = _gemm_sizes(A, B, trans_a, trans_b, bias)
     if out is None:
         out = torch.empty((M, N), dtype=TORCH_DTYPE[fout], device=A.device)
@@ -198,6 +240,11 @@ def posit_conv2d_workspace(which, fin, fout, desc):
 
 def posit_conv2d_fwd(x, w, desc, fin, fout, bias=None, out=None, workspace=None):
     fin, fout = _code(fin), _code(fout)
+    st = _ready()
+    if st is not None and workspace is None and desc.__class__ is ConvDesc:
+        r = _native.conv(st, 0, fin, fout, ctypes.addressof(desc), 0, x, w, bias, out, None)
+        if r is not None:
+            return _outputs(r)
     oh, ow = conv_out_hw(desc)
     if out is None:
         out = torch.empty((desc.N, desc.K, oh, ow), dtype=TORCH_DTYPE[fout], device=x.device)
@@ -209,6 +256,11 @@ def posit_conv2d_fwd(x, w, desc, fin, fout, bias=None, out=None, workspace=None)
 
 def posit_conv2d_bwd_data(dy, w, desc, fin, fout, out=None, workspace=None):
     fin, fout = _code(fin), _code(fout)
+    st = _ready()
+    if st is not None and workspace is None and desc.__class__ is ConvDesc:
+        r = _native.conv(st, 1, fin, fout, ctypes.addressof(desc), 0, dy, w, None, out, None)
+        if r is not None:
+            return _outputs(r)
     if out is None:
         out = torch.empty((desc.N, desc.C, desc.H, desc.W), dtype=TORCH_DTYPE[fout], device=dy.device)
     wp, wbytes, _keep = _workspace(posit_conv2d_workspace(1, fin, fout, desc), dy.device, workspace)
@@ -219,6 +271,11 @@ def posit_conv2d_bwd_data(dy, w, desc, fin, fout, out=None, workspace=None):
 
 def posit_conv2d_bwd_weight(dy, x, desc, fin, fout, with_bias=False, out=None, out_bias=None, workspace=None):
     fin, fout = _code(fin), _code(fout)
+    st = _ready()
+    if st is not None and workspace is None and desc.__class__ is ConvDesc:
+        r = _native.conv(st, 2, fin, fout, ctypes.addressof(desc), 1 if with_bias else 0, dy, x, None, out, out_bias)
+        if r is not None:
+            return _outputs(r)
     if out is None:
         out = torch.empty((desc.K, desc.C, desc.R, desc.S), dtype=TORCH_DTYPE[fout], device=dy.device)
     if with_bias and out_bias is None:
@@ -338,6 +395,11 @@ def posit_mse(pred, target, f_pred, f_loss, f_grad, want_loss=True, want_grad=Tr
 def posit_round(src, fdst, out=None):
     """float32 / float64 device tensor -> tensor of posit patterns."""
     fdst = _code(fdst)
+    st = _ready()
+    if st is not None:
+        r = _native.round(st, fdst, src, out)
+        if r is not None:
+            return _outputs(r)
     fsrc = F32 if src.dtype == torch.float32 else F64 if src.dtype == torch.float64 else None
     if fsrc is None:
         raise PositError("posit_round takes float32 or float64")
@@ -350,6 +412,11 @@ def posit_round(src, fdst, out=None):
 def posit_convert(src, fsrc, fdst, out=None):
     """posit -> posit of another format, or posit -> float32 / float64."""
     fsrc, fdst = _code(fsrc), _code(fdst)
+    st = _ready()
+    if st is not None:
+        r = _native.convert(st, fsrc, fdst, src, out)
+        if r is not None:
+            return _outputs(r)
     if out is None:
         out = torch.empty(src.shape, dtype=TORCH_DTYPE[fdst], device=src.device)
     _check(load().posit_convert(_stream(), fsrc, fdst, src.numel(), _dev(src, fsrc, "src"), _dev(out, fdst, "dst")))
@@ -373,6 +440,11 @@ def posit_axpy(alpha_bits, x, y, fx, fy, fcopy=None, y_copy=None):
 
 def posit_relu(x, fmt, out=None):
     fmt = _code(fmt)
+    st = _ready()
+    if st is not None:
+        r = _native.relu(st, fmt, x, out)
+        if r is not None:
+            return _outputs(r)
     if out is None:
         out = torch.empty_like(x)
     _check(load().posit_relu(_stream(), fmt, x.numel(), _dev(x, fmt, "x"), _dev(out, fmt, "y")))
@@ -381,6 +453,11 @@ def posit_relu(x, fmt, out=None):
 
 def posit_relu_bwd(y_fwd, dy, fmt_y, fmt_d, out=None):
     fmt_y, fmt_d = _code(fmt_y), _code(fmt_d)
+    st = _ready()
+    if st is not None:
+        r = _native.relu_bwd(st, fmt_y, fmt_d, y_fwd, dy, out)
+        if r is not None:
+            return _outputs(r)
     if y_fwd.numel() != dy.numel():
         raise PositError("y_fwd and dy differ in size")
     if out is None:
@@ -399,6 +476,11 @@ def _planes(x):
 def posit_maxpool2d_fwd(x, fmt, kh=2, kw=2):
     """Returns (y, idx): idx is the uint8 window position of the first maximum."""
     fmt = _code(fmt)
+    st = _ready()
+    if st is not None:
+        r = _native.maxpool_fwd(st, fmt, kh, kw, x)
+        if r is not None:
+            return _outputs(r)
     planes, h, w = _planes(x)
     shape = tuple(x.shape[:-2]) + (h // kh, w // kw)
     y = torch.empty(shape, dtype=x.dtype, device=x.device)
@@ -409,6 +491,11 @@ def posit_maxpool2d_fwd(x, fmt, kh=2, kw=2):
 
 def posit_maxpool2d_bwd(dy, idx, fmt, kh=2, kw=2):
     fmt = _code(fmt)
+    st = _ready()
+    if st is not None:
+        r = _native.maxpool_bwd(st, fmt, kh, kw, dy, idx)
+        if r is not None:
+            return _outputs(r)
     planes, oh, ow = _planes(dy)
     shape = tuple(dy.shape[:-2]) + (oh * kh, ow * kw)
     dx = torch.empty(shape, dtype=dy.dtype, device=dy.device)
@@ -418,6 +505,11 @@ def posit_maxpool2d_bwd(dy, idx, fmt, kh=2, kw=2):
 
 def posit_avgpool2d_fwd(x, fin, fout, kh=2, kw=2):
     fin, fout = _code(fin), _code(fout)
+    st = _ready()
+    if st is not None:
+        r = _native.avgpool(st, 0, fin, fout, kh, kw, x)
+        if r is not None:
+            return _outputs(r)
     planes, h, w = _planes(x)
     y = torch.empty(tuple(x.shape[:-2]) + (h // kh, w // kw), dtype=TORCH_DTYPE[fout], device=x.device)
     _check(load().posit_avgpool2d_fwd(_stream(), fin, fout, planes, h, w, kh, kw, _dev(x, fin, "x"), _dev(y, fout, "y")))
@@ -426,6 +518,11 @@ def posit_avgpool2d_fwd(x, fin, fout, kh=2, kw=2):
 
 def posit_avgpool2d_bwd(dy, fin, fout, kh=2, kw=2):
     fin, fout = _code(fin), _code(fout)
+    st = _ready()
+    if st is not None:
+        r = _native.avgpool(st, 1, fin, fout, kh, kw, dy)
+        if r is not None:
+            return _outputs(r)
     planes, oh, ow = _planes(dy)
     dx = torch.empty(tuple(dy.shape[:-2]) + (oh * kh, ow * kw), dtype=TORCH_DTYPE[fout], device=dy.device)
     _check(load().posit_avgpool2d_bwd(_stream(), fin, fout, planes, oh * kh, ow * kw, kh, kw, _dev(dy, fin, "dy"), _dev(dx, fout, "dx")))

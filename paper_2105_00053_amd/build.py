@@ -20,6 +20,8 @@ RATES = os.path.join(HERE, "libpositnn_rates.so")  # instruction-issue microbenc
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
+NATIVE = os.path.join(HERE, "positnn_native.so")  # the binding's marshalling in C++ (csrc/binding_native.cpp)
+
 UNITS = ["api_elementwise.hip", "api_gemm.hip", "api_conv.hip", "api_glue.hip", "api_noquire.hip", "api_loss.hip"]
 # Floating-point model, stated rather than left to the compiler's default: the fp64 "buckets" that carry exact
 # sums rely on every operation being the IEEE one that is written -- (r + C) - C must round r, not fold to r, and a
@@ -45,17 +47,30 @@ def _compile(unit):
     return obj
 
 
+def _native_command():
+    """g++ line of the extension module: against torch's headers and libraries (those that `import torch` has loaded by then)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+            "-I" + os.path.join(root, "include"), "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding_native.cpp"),
+            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", NATIVE]
+
+
 def build(verbose=False):
     os.makedirs(OBJ, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(UNITS))) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(UNITS) + 1)) as ex:
+        native = ex.submit(_run, _native_command())
         objs = list(ex.map(_compile, UNITS))
+        native.result()
     _run([HIPCC, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", LIB] + objs)
     # host-only build of the scalar functions, for CPU unit tests
     _run([HIPCC, "-O2", "-std=c++17", "-fPIC", "-shared", "--cuda-host-only", "-x", "hip"] + FP_FLAGS + [
           "-Wno-unused-command-line-argument", os.path.join(CSRC, "host_check.hip"), "-o", HOSTCHECK])
     _run([HIPCC] + DEVICE_FLAGS + ["-shared", os.path.join(CSRC, "issue_rates.hip"), "-o", RATES])
     if verbose:
-        print("built", LIB, ",", HOSTCHECK, "and", RATES)
+        print("built", LIB, ",", HOSTCHECK, ",", NATIVE, "and", RATES)
     return LIB
 
 

@@ -1,0 +1,333 @@
+// The marshalling of the calls a training step is made of, in C++: what binding.py does for one of them in the interpreter
+// (checks, output and workspace allocation, the call through ctypes) took 6 to 9 us of host time, about twice the launch itself.
+//
+// Every function returns the outputs, or the library's status as an int when that is not zero, or None when it does not take
+// the call: anything unusual (other argument types, tensors that are no plain contiguous device tensors of the right element
+// size, sizes that do not match) is left to the Python code, which decides and raises as before.  The library's functions come
+// as addresses (init), so this object does not link against it.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+namespace {
+
+constexpr int F32 = 100, F64 = 101;
+enum Fn { GEMM, GEMM_WS, CONV_FWD, CONV_BWD_DATA, CONV_BWD_WEIGHT, CONV_WS, ROUND, CONVERT, RELU, RELU_BWD, MAXPOOL_FWD, MAXPOOL_BWD, AVGPOOL_FWD, AVGPOOL_BWD, COUNT };
+void* g_fn[COUNT];
+
+struct Desc {  // pnn_conv2d_desc
+    int64_t N, C, H, W, K, R, S, pad_h, pad_w, stride_h, stride_w;
+};
+
+// bytes per element of a format, 0 for none
+int elem_size(long f) {
+    switch (f) {
+        case 0: case 3: case 4: return 1;
+        case 1: case 5: case 6: case 7: case 8: return 2;
+        case 2: case F32: return 4;
+        case F64: return 8;
+        default: return 0;
+    }
+}
+
+at::ScalarType dtype_of(long f) {
+    switch (elem_size(f)) {
+        case 1: return at::kByte;
+        case 2: return at::kUInt16;
+        case 4: return f == F32 ? at::kFloat : at::kUInt32;
+        default: return at::kDouble;
+    }
+}
+
+bool dtype_fits(at::ScalarType t, int size) {
+    switch (size) {
+        case 1: return t == at::kByte || t == at::kChar;
+        case 2: return t == at::kUInt16 || t == at::kShort;
+        case 4: return t == at::kUInt32 || t == at::kInt || t == at::kFloat;
+        case 8: return t == at::kDouble || t == at::kLong || t == at::kUInt64;
+        default: return false;
+    }
+}
+
+// The tensor behind o if it is a plain contiguous device tensor of f's element size
+const at::Tensor* tensor(PyObject* o, long f) {
+    if (!THPVariable_CheckExact(o)) return nullptr;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || !t.is_contiguous() || !dtype_fits(t.scalar_type(), elem_size(f))) return nullptr;
+    return &t;
+}
+
+bool integer(PyObject* o, long* v) {
+    if (!PyLong_Check(o)) return false;
+    *v = PyLong_AsLong(o);
+    if (*v == -1 && PyErr_Occurred()) {
+        PyErr_Clear();
+        return false;
+    }
+    return true;
+}
+
+at::Tensor empty(at::IntArrayRef shape, at::ScalarType t, const at::Tensor& like) { return at::empty(shape, at::TensorOptions().dtype(t).device(like.device())); }
+
+// An output: the caller's tensor, or a new one.  False: the caller's does not fit.
+bool output(PyObject* o, long f, at::IntArrayRef shape, const at::Tensor& like, at::Tensor* out) {
+    if (o == Py_None) {
+        *out = empty(shape, dtype_of(f), like);
+        return true;
+    }
+    const at::Tensor* t = tensor(o, f);
+    if (!t) return false;
+    *out = *t;
+    return true;
+}
+
+PyObject* none() { Py_RETURN_NONE; }
+
+PyObject* result(int status, const at::Tensor& out) { return status ? PyLong_FromLong(status) : THPVariable_Wrap(out); }
+
+PyObject* result(int status, const at::Tensor& a, const at::Tensor& b) {
+    if (status) return PyLong_FromLong(status);
+    PyObject* x = THPVariable_Wrap(a);
+    PyObject* y = x ? THPVariable_Wrap(b) : nullptr;
+    PyObject* r = y ? PyTuple_Pack(2, x, y) : nullptr;
+    Py_XDECREF(x);
+    Py_XDECREF(y);
+    return r;
+}
+
+template <class F, class... A>
+int call(Fn which, A... args) {  // other Python threads may run meanwhile, as during a call through ctypes
+    int status;
+    Py_BEGIN_ALLOW_THREADS
+    status = reinterpret_cast<F>(g_fn[which])(args...);
+    Py_END_ALLOW_THREADS
+    return status;
+}
+
+// Arguments: nints leading integers (the first the stream), then objects.
+constexpr int MOST_INTS = 8;
+struct Args {
+    long i[MOST_INTS];
+    void* stream;
+    PyObject* const* o;
+};
+
+bool parse(PyObject* const* args, Py_ssize_t n, int nints, int nobjs, Args* a) {
+    if (n != nints + nobjs) return false;
+    for (int k = 0; k < nints; ++k)
+        if (!integer(args[k], &a->i[k])) return false;
+    a->stream = reinterpret_cast<void*>(a->i[0]);
+    a->o = args + nints;
+    return true;
+}
+
+// C++ exceptions (a functorch wrapper without storage, an allocation that fails) leave the call to the Python code, which meets
+// the same and raises.
+template <class B>
+PyObject* guarded(const B& body) {
+    try {
+        return body();
+    } catch (const std::exception&) {
+        return none();
+    }
+}
+
+typedef int (*gemm_t)(void*, int, int, int, int, int64_t, int64_t, int64_t, const void*, int64_t, const void*, int64_t, const void*, void*, int64_t, void*, size_t);
+typedef size_t (*gemm_ws_t)(int, int, int, int, int64_t, int64_t, int64_t);
+typedef int (*conv3_t)(void*, int, int, const Desc*, const void*, const void*, const void*, void*, void*, size_t);
+typedef int (*conv_bd_t)(void*, int, int, const Desc*, const void*, const void*, void*, void*, size_t);
+typedef int (*conv_bw_t)(void*, int, int, const Desc*, const void*, const void*, void*, void*, void*, size_t);
+typedef size_t (*conv_ws_t)(int, int, int, const Desc*);
+typedef int (*map_t)(void*, int, int, int64_t, const void*, void*);
+typedef int (*relu_t)(void*, int, int64_t, const void*, void*);
+typedef int (*relu_bwd_t)(void*, int, int, int64_t, const void*, const void*, void*);
+typedef int (*maxpool_t)(void*, int, int64_t, int64_t, int64_t, int64_t, int64_t, const void*, const void*, void*);
+typedef int (*avgpool_t)(void*, int, int, int64_t, int64_t, int64_t, int64_t, int64_t, const void*, void*);
+
+// gemm(stream, fin, fout, trans_a, trans_b, A, B, bias, out)
+PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 5, 4, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const int fin = (int)a.i[1], fout = (int)a.i[2], ta = a.i[3] != 0, tb = a.i[4] != 0;
+        const at::Tensor *A = tensor(a.o[0], fin), *B = tensor(a.o[1], fin), *bias = nullptr;
+        if (!A || !B || A->dim() != 2 || B->dim() != 2 || elem_size(fout) == 0) return none();
+        const int64_t lda = A->size(1), ldb = B->size(1);
+        const int64_t M = ta ? lda : A->size(0), K = ta ? A->size(0) : lda, N = tb ? B->size(0) : ldb;
+        if (K != (tb ? ldb : B->size(0))) return none();
+        if (a.o[2] != Py_None && (!(bias = tensor(a.o[2], fin)) || bias->numel() != N)) return none();
+        at::Tensor out, ws;
+        if (!output(a.o[3], fout, {M, N}, *A, &out) || out.dim() != 2) return none();
+        const size_t bytes = reinterpret_cast<gemm_ws_t>(g_fn[GEMM_WS])(fin, fout, ta, tb, M, N, K);
+        if (bytes) ws = empty({(int64_t)bytes}, at::kByte, *A);
+        return result(call<gemm_t>(GEMM, a.stream, fin, fout, ta, tb, M, N, K, (const void*)A->data_ptr(), lda, (const void*)B->data_ptr(), ldb,
+                                   (const void*)(bias ? bias->data_ptr() : nullptr), (void*)out.data_ptr(), out.size(1), bytes ? (void*)ws.data_ptr() : nullptr, bytes), out);
+    });
+}
+
+// conv(stream, which, fin, fout, desc, with_bias, first, second, bias, out, out_bias): first and second are x and w, dy and w, or dy and x
+PyObject* conv(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 6, 5, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const int which = (int)a.i[1], fin = (int)a.i[2], fout = (int)a.i[3];
+        const Desc* d = reinterpret_cast<const Desc*>(a.i[4]);
+        const bool with_bias = a.i[5] != 0;
+        const at::Tensor *x = tensor(a.o[0], fin), *w = tensor(a.o[1], fin), *bias = nullptr;
+        if (!x || !w || elem_size(fout) == 0) return none();
+        if (a.o[2] != Py_None && !(bias = tensor(a.o[2], fin))) return none();
+        const int64_t eh = d->H + 2 * d->pad_h - d->R, ew = d->W + 2 * d->pad_w - d->S;
+        if (eh < 0 || ew < 0 || d->stride_h <= 0 || d->stride_w <= 0) return none();
+        at::Tensor out, db, ws;
+        const bool ok = which == 0 ? output(a.o[3], fout, {d->N, d->K, eh / d->stride_h + 1, ew / d->stride_w + 1}, *x, &out)
+                                   : which == 1 ? output(a.o[3], fout, {d->N, d->C, d->H, d->W}, *x, &out) : output(a.o[3], fout, {d->K, d->C, d->R, d->S}, *x, &out);
+        if (!ok || (with_bias && !output(a.o[4], fout, {d->K}, *x, &db))) return none();
+        const size_t bytes = reinterpret_cast<conv_ws_t>(g_fn[CONV_WS])(which, fin, fout, d);
+        if (bytes) ws = empty({(int64_t)bytes}, at::kByte, *x);
+        const void *xp = x->data_ptr(), *wp = w->data_ptr();
+        void *op = out.data_ptr(), *sp = bytes ? ws.data_ptr() : nullptr;
+        if (which == 0) return result(call<conv3_t>(CONV_FWD, a.stream, fin, fout, d, xp, wp, (const void*)(bias ? bias->data_ptr() : nullptr), op, sp, bytes), out);
+        if (which == 1) return result(call<conv_bd_t>(CONV_BWD_DATA, a.stream, fin, fout, d, xp, wp, op, sp, bytes), out);
+        const int st = call<conv_bw_t>(CONV_BWD_WEIGHT, a.stream, fin, fout, d, xp, wp, op, with_bias ? (void*)db.data_ptr() : nullptr, sp, bytes);
+        return with_bias ? result(st, out, db) : result(st, out);
+    });
+}
+
+// round(stream, fdst, src, out), convert(stream, fsrc, fdst, src, out)
+PyObject* map_elements(Fn fn, void* stream, long fsrc, long fdst, const at::Tensor* src, PyObject* given) {
+    at::Tensor out;
+    if (!src || elem_size(fdst) == 0 || !output(given, fdst, src->sizes(), *src, &out)) return none();
+    return result(call<map_t>(fn, stream, (int)fsrc, (int)fdst, src->numel(), (const void*)src->data_ptr(), (void*)out.data_ptr()), out);
+}
+
+PyObject* round_to(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 2, 2, &a) || !THPVariable_CheckExact(a.o[0])) return none();
+    return guarded([&]() -> PyObject* {
+        const at::ScalarType t = THPVariable_Unpack(a.o[0]).scalar_type();
+        if (t != at::kFloat && t != at::kDouble) return none();
+        const long f = t == at::kFloat ? F32 : F64;
+        return map_elements(ROUND, a.stream, f, a.i[1], tensor(a.o[0], f), a.o[1]);
+    });
+}
+
+PyObject* convert(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 3, 2, &a)) return none();
+    return guarded([&]() -> PyObject* { return map_elements(CONVERT, a.stream, a.i[1], a.i[2], tensor(a.o[0], a.i[1]), a.o[1]); });
+}
+
+// relu(stream, fmt, x, out)
+PyObject* relu(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 2, 2, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const at::Tensor* x = tensor(a.o[0], a.i[1]);
+        const at::Tensor* given = a.o[1] == Py_None ? nullptr : tensor(a.o[1], a.i[1]);
+        if (!x || (a.o[1] != Py_None && !given)) return none();
+        const at::Tensor out = given ? *given : empty(x->sizes(), x->scalar_type(), *x);
+        return result(call<relu_t>(RELU, a.stream, (int)a.i[1], x->numel(), (const void*)x->data_ptr(), (void*)out.data_ptr()), out);
+    });
+}
+
+// relu_bwd(stream, fmt_y, fmt_d, y, dy, out)
+PyObject* relu_bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 3, 3, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const at::Tensor *y = tensor(a.o[0], a.i[1]), *dy = tensor(a.o[1], a.i[2]);
+        const at::Tensor* given = a.o[2] == Py_None ? nullptr : tensor(a.o[2], a.i[2]);
+        if (!y || !dy || y->numel() != dy->numel() || (a.o[2] != Py_None && !given)) return none();
+        const at::Tensor out = given ? *given : empty(dy->sizes(), dy->scalar_type(), *dy);
+        return result(call<relu_bwd_t>(RELU_BWD, a.stream, (int)a.i[1], (int)a.i[2], dy->numel(), (const void*)y->data_ptr(), (const void*)dy->data_ptr(),
+                                       (void*)out.data_ptr()), out);
+    });
+}
+
+// Leading extent and shape of a pooled tensor: [..., H, W] with the last two divided or multiplied
+struct Pool {
+    int64_t planes, h, w;
+    std::vector<int64_t> shape;
+    bool of(const at::Tensor* t, long kh, long kw, bool up) {
+        if (!t || t->dim() < 2 || kh <= 0 || kw <= 0) return false;
+        h = t->size(-2);
+        w = t->size(-1);
+        if (h * w == 0) return false;
+        planes = t->numel() / (h * w);
+        shape = t->sizes().vec();
+        shape[shape.size() - 2] = up ? h * kh : h / kh;
+        shape[shape.size() - 1] = up ? w * kw : w / kw;
+        return true;
+    }
+};
+
+// maxpool_fwd(stream, fmt, kh, kw, x), maxpool_bwd(stream, fmt, kh, kw, dy, idx)
+PyObject* maxpool_fwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 4, 1, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const at::Tensor* x = tensor(a.o[0], a.i[1]);
+        Pool p;
+        if (!p.of(x, a.i[2], a.i[3], false)) return none();
+        const at::Tensor y = empty(p.shape, x->scalar_type(), *x), idx = empty(p.shape, at::kByte, *x);
+        return result(call<maxpool_t>(MAXPOOL_FWD, a.stream, (int)a.i[1], p.planes, p.h, p.w, (int64_t)a.i[2], (int64_t)a.i[3], (const void*)x->data_ptr(),
+                                      (const void*)y.data_ptr(), (void*)idx.data_ptr()), y, idx);
+    });
+}
+
+PyObject* maxpool_bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 4, 2, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const at::Tensor *dy = tensor(a.o[0], a.i[1]), *idx = tensor(a.o[1], 0);
+        Pool p;
+        if (!idx || !p.of(dy, a.i[2], a.i[3], true)) return none();
+        const at::Tensor dx = empty(p.shape, dy->scalar_type(), *dy);
+        return result(call<maxpool_t>(MAXPOOL_BWD, a.stream, (int)a.i[1], p.planes, p.h * a.i[2], p.w * a.i[3], (int64_t)a.i[2], (int64_t)a.i[3],
+                                      (const void*)dy->data_ptr(), (const void*)idx->data_ptr(), (void*)dx.data_ptr()), dx);
+    });
+}
+
+// avgpool(stream, backward, fin, fout, kh, kw, x)
+PyObject* avgpool(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a;
+    if (!parse(args, n, 6, 1, &a)) return none();
+    return guarded([&]() -> PyObject* {
+        const bool back = a.i[1] != 0;
+        const long fin = a.i[2], fout = a.i[3], kh = a.i[4], kw = a.i[5];
+        const at::Tensor* x = tensor(a.o[0], fin);
+        Pool p;
+        if (elem_size(fout) == 0 || !p.of(x, kh, kw, back)) return none();
+        const at::Tensor y = empty(p.shape, dtype_of(fout), *x);
+        return result(call<avgpool_t>(back ? AVGPOOL_BWD : AVGPOOL_FWD, a.stream, (int)fin, (int)fout, p.planes, back ? p.h * kh : p.h, back ? p.w * kw : p.w, (int64_t)kh,
+                                      (int64_t)kw, (const void*)x->data_ptr(), (void*)y.data_ptr()), y);
+    });
+}
+
+// init(addresses): the library's functions in the order of Fn
+PyObject* init(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    if (n != COUNT) {
+        PyErr_SetString(PyExc_TypeError, "one address per function");
+        return nullptr;
+    }
+    for (int k = 0; k < COUNT; ++k) {
+        g_fn[k] = PyLong_AsVoidPtr(args[k]);
+        if (!g_fn[k]) {
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null address");
+            return nullptr;
+        }
+    }
+    Py_RETURN_NONE;
+}
+
+#define PNN_METHOD(name, fn) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(fn)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {PNN_METHOD("init", init), PNN_METHOD("gemm", gemm), PNN_METHOD("conv", conv), PNN_METHOD("round", round_to),
+                         PNN_METHOD("convert", convert), PNN_METHOD("relu", relu), PNN_METHOD("relu_bwd", relu_bwd), PNN_METHOD("maxpool_fwd", maxpool_fwd),
+                         PNN_METHOD("maxpool_bwd", maxpool_bwd), PNN_METHOD("avgpool", avgpool), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "positnn_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+extern "C" __attribute__((visibility("default"))) PyObject* PyInit_positnn_native() { return PyModule_Create(&module); }
