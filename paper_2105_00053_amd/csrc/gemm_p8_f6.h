@@ -16,8 +16,8 @@
 // chunk of 256 reduction indices and block of 32 rows, the largest sum of h^2 and of l^2 over a row; by Cauchy's inequality
 // the sums of a tile stay below  sum over chunks of  |ha||hb|  and  32 (|ha||lb| + |la||hb|) + |la||lb|.  N(0, 1) operands
 // with K = 4096 reach a third of 2^24.  A tile whose bound fails, or that meets one of the four patterns +-32, +-64 (no such
-// digits), raises its flag and is left to the int8 kernel of gemm_p8_mfma.h, launched behind this one, which multiplies the
-// flagged tiles and returns at once otherwise.
+// digits), raises its flag; the int8 kernel of gemm_p8_mfma.h, launched behind this
+// one, then takes the whole product, and returns at once (1.5 us a launch) if no tile did.
 #pragma once
 
 #include "gemm_p8_mfma.h"
@@ -226,7 +226,8 @@ struct P8F6Args {
     void* C;
     int64_t ldc;
     int fout, M, N, tiles_m, tiles_n;
-    uint32_t* flag;  // [tile]: the tile is left to the int8 kernel
+    uint32_t* flag;  // see pf_flag
+    uint4* mark;     // see pf_intact
 };
 
 // Operand registers of one block of 32 rows and 64 reduction indices.
@@ -344,7 +345,10 @@ __global__ __launch_bounds__(256, 2) void p8_f6_gemm_kernel(P8F6Args g) {
         bq += bound[2 * v + 1];
     }
     const bool left = !(bhh < PF_LIMIT / 16 && bq < PF_LIMIT);
-    if (t == 0) g.flag[tm * g.tiles_n + tn] = left ? 1u : 0u;
+    if (t == 0) {
+        g.flag[pf_flag(tm * g.tiles_n + tn)] = left ? 0u : PF_DONE;
+        if (blockIdx.x == 0) *g.mark = make_uint4(PF_DONE, PF_DONE, PF_DONE, PF_DONE);
+    }
     if (__builtin_amdgcn_readfirstlane(left)) {
         __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
         return;
@@ -500,12 +504,12 @@ __global__ __launch_bounds__(256, 2) void p8_f6_gemm_kernel(P8F6Args g) {
 struct P8F6Layout {
     int RBA, RBB, KB, chunks;
     int tiles_m, tiles_n;   // of 128 x 128 outputs
-    size_t a_bytes, b_bytes, sa_bytes, sb_bytes, flag_bytes, int8_bytes;
-    // the flags, and behind them these digits and their bounds or the int8 digits, which nothing needs at the same time
-    size_t total() const {
-        const size_t own = a_bytes + b_bytes + sa_bytes + sb_bytes;
-        return flag_bytes + (own > int8_bytes ? own : int8_bytes);
-    }
+    size_t a_bytes, b_bytes, sa_bytes, sb_bytes, int8_bytes;
+    // the int8 digits take the place of everything here where they are needed; flags and mark lie at their end, 2 KB per 256
+    // tiles and 2 KB
+    size_t flag_off() const { return int8_bytes - 2048 * ((size_t)(tiles_m * tiles_n + 255) / 256 + 1); }
+    size_t total() const { return int8_bytes; }
+    bool fits() const { return a_bytes + b_bytes + sa_bytes + sb_bytes <= flag_off(); }
 };
 
 inline P8F6Layout p8_f6_layout(int64_t M, int64_t N, int64_t K) {
@@ -520,28 +524,28 @@ inline P8F6Layout p8_f6_layout(int64_t M, int64_t N, int64_t K) {
     l.b_bytes = (size_t)l.KB * l.RBB * 3072;
     l.sa_bytes = (size_t)l.chunks * l.RBA * 16;
     l.sb_bytes = (size_t)l.chunks * l.RBB * 16;
-    l.flag_bytes = ((size_t)l.tiles_m * l.tiles_n * 4 + 15) / 16 * 16;
     l.int8_bytes = p8_mfma_layout(M, N, K).total();
     return l;
 }
 
 // Products that come here, where the workspace may have up to `limit` bytes.  Timed against the int8 kernel alone on N(0, 1)
 // operands (us, before -> now): 2048 x 2048 x 512 25.0 -> 24.2, x 4096 77.7 -> 57.4, 3072 x 3072 x 512 66 -> 36, 4096 x 4096 x 256
-// 60 -> 35, x 4096 240 -> 152, 8192 x 512 x 2048 52 -> 45; with half the tiles the chip is half empty and the two launches for
-// the tiles left weigh more: 1536^3 33.3 -> 36.4, 1024 x 2048 x 2048 34.6 -> 39.2.
+// 60 -> 35, x 4096 235 -> 153, 8192 x 512 x 2048 52 -> 45; with half the tiles the chip is half empty and the two launches
+// behind weigh more: 1536^3 33.3 -> 36.4, 1024 x 2048 x 2048 34.6 -> 39.2.
 inline bool p8_f6_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
-    return p8_mfma_fits(M, N, K) && K <= PF_MAX_K && ((M + 127) / 128) * ((N + 127) / 128) >= PF_MIN_TILES && p8_f6_layout(M, N, K).total() <= limit;
+    return p8_mfma_fits(M, N, K) && K <= PF_MAX_K && ((M + 127) / 128) * ((N + 127) / 128) >= PF_MIN_TILES && p8_f6_layout(M, N, K).total() <= limit &&
+           p8_f6_layout(M, N, K).fits();
 }
 
 inline hipError_t launch_p8_f6_gemm(hipStream_t stream, int transA, int transB, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                                     const uint8_t* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace) {
     const P8F6Layout l = p8_f6_layout(M, N, K);
-    uint32_t* flag = reinterpret_cast<uint32_t*>(workspace);
-    uint8_t* base = (uint8_t*)workspace + l.flag_bytes;
+    uint8_t* base = (uint8_t*)workspace;
     uint4* Ad = reinterpret_cast<uint4*>(base);
     uint4* Bd = reinterpret_cast<uint4*>(base + l.a_bytes);
     uint4* sa = reinterpret_cast<uint4*>(base + l.a_bytes + l.b_bytes);
     uint4* sb = reinterpret_cast<uint4*>(base + l.a_bytes + l.b_bytes + l.sa_bytes);
+    uint32_t* flag = reinterpret_cast<uint32_t*>(base + l.flag_off());
     // op(A)[m,k] is A[m * lda + k] unless transA; op(B)[k,n] is B[k * ldb + n] unless transB
     P8F6Job ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, Ad, sa, l.RBA, l.KB};
     P8F6Job jb{B, transB ? ldb : (int64_t)1, transB ? (int64_t)1 : ldb, (int)N, (int)K, Bd, sb, l.RBB, l.KB};
@@ -549,10 +553,10 @@ inline hipError_t launch_p8_f6_gemm(hipStream_t stream, int transA, int transB, 
     hipLaunchKernelGGL(p8_f6_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0);
     PNN_CHECK_LAUNCH();
     const int tiles = l.tiles_m * l.tiles_n;
-    P8F6Args a{Ad, Bd, sa, sb, l.RBA, l.RBB, l.KB, l.chunks, bias, C, ldc, fout, (int)M, (int)N, l.tiles_m, l.tiles_n, flag};
+    P8F6Args a{Ad, Bd, sa, sb, l.RBA, l.RBB, l.KB, l.chunks, bias, C, ldc, fout, (int)M, (int)N, l.tiles_m, l.tiles_n, flag, reinterpret_cast<uint4*>(base + l.int8_bytes - 16)};
     hipLaunchKernelGGL(p8_f6_gemm_kernel<0>, dim3((unsigned)tiles), dim3(256), 0, stream, a);
     PNN_CHECK_LAUNCH();
-    return launch_p8_mfma_gemm(stream, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, base, flag, tiles, l.tiles_n);
+    return launch_p8_mfma_gemm(stream, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, base, flag, tiles, a.mark);
 }
 
 }  // namespace pnn

@@ -71,6 +71,16 @@ __device__ __forceinline__ uint16_t pm_digits(uint32_t pattern) {
     return (uint16_t)(((uint32_t)(hi & 0xFF) << 8) | (uint32_t)(lo & 0xFF));
 }
 
+// Behind gemm_p8_f6.h the kernels of this file take the whole product if a tile is left, and return at once otherwise.  4096^3, us,
+// before that file and behind it: all patterns at random 291 and 319, N(0, 8^2) 251 and 274, N(0, 1) 235 and 153, N(0, 1) with one
+// +-64 (its row of tiles is left) 253 and 413.  What that file leaves here lies where this file's digits will, in places of low
+// digits, whose bytes are never -128: the last 16 bytes mark that they have not been written, and a flag word is PF_DONE for a
+// tile that needs nothing more.  A workgroup that reads the flags while another already writes digits over them can only find
+// more tiles left than there are, never fewer, so all agree to write.
+constexpr uint32_t PF_DONE = 0x80808080u;
+__device__ __forceinline__ bool pf_intact(const uint4* mark) { return mark->x == PF_DONE && mark->y == PF_DONE && mark->z == PF_DONE && mark->w == PF_DONE; }
+__device__ __forceinline__ int64_t pf_flag(int tile) { return (int64_t)(tile >> 8) * 512 + 256 + (tile & 255); }  // 1 KB of every 2
+
 struct P8DigitJob {
     const uint8_t* src;
     int64_t s_r, s_k;   // element (row, k) at src[row * s_r + k * s_k]; one of the two is 1
@@ -80,16 +90,15 @@ struct P8DigitJob {
 };
 
 // Both operands in one launch: the first blocks0 workgroups take job0, the rest job1.  A workgroup handles one k block
-// and eight row blocks: 512 lane slots of 16 bytes per digit, two per thread.  With flags (gemm_p8_f6.h) there is work only
-// if one of the nflags is set.
+// and eight row blocks: 512 lane slots of 16 bytes per digit, two per thread.
 template <int UNUSED = 0>
 __global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8DigitJob job1, unsigned blocks0, const uint32_t* __restrict__ flags, int nflags) {
     __shared__ uint16_t tab[256];
     const int t = threadIdx.x;
     if (flags) {
-        uint32_t any = 0;
-        for (int i = t; i < nflags; i += 256) any |= flags[i];
-        if (!__syncthreads_or((int)any)) return;
+        int left = 0;
+        for (int i = t; i < nflags; i += 256) left |= flags[pf_flag(i)] != PF_DONE;
+        if (!__syncthreads_or(left)) return;
     }
     tab[t] = pm_digits((uint32_t)t);
     __syncthreads();
@@ -172,8 +181,6 @@ __device__ __forceinline__ void pm_tile(int id, int tiles_m, int tiles_n, int& t
 // Ad / Bd: digit planes of p8_digits_kernel with RBA / RBB row blocks (multiples of 2 BI / 2 BJ) and KB k blocks (a
 // multiple of PM_KSTEP).  Four waves as 2 x 2; a wave owns BI x BJ blocks of 32 x 32 outputs, the workgroup 64 BI x 64 BJ.
 //
-// flags (gemm_p8_f6.h): one word per 128 x 128 outputs, flag_cols a row; outputs whose word is zero are done already.
-//
 // SPLIT: workgroup (tile, z) reduces the kb_per_split k blocks from z kb_per_split on and leaves its 32-bit sums and
 // its NaR flags in the workspace of a split reduction (ws: partial quires [z][M N], row flags [z][M], column flags
 // [z][N]); the merging launch adds, rounds and stores.  For products with few output tiles and a long reduction.
@@ -181,7 +188,8 @@ template <int BI, int BJ, bool SPLIT = false>
 __global__ __launch_bounds__(256, (BI * BJ == 4 ? 2 : BI * BJ == 2 ? 3 : 4)) void p8_mfma_gemm_kernel(
     const uint8_t* __restrict__ Ad, const uint8_t* __restrict__ Bd, int RBA, int RBB, int KB, const uint8_t* __restrict__ bias, void* __restrict__ C,
     int64_t ldc, int fout, int M, int N, int tiles_m, int tiles_n, int kb_per_split = 0, SplitWs ws = SplitWs{nullptr, nullptr, nullptr},
-    const uint32_t* __restrict__ flags = nullptr, int flag_cols = 0) {
+    const uint4* __restrict__ mark = nullptr) {
+    if (mark && pf_intact(mark)) return;
     constexpr int NA = 2 * BI * 2, NB = 2 * BJ * 2;  // runs of 1 KB (row block, digit) per k block and operand
     constexpr int TR = 64 * BI, TC = 64 * BJ;        // tile extents
     // [buffer][k block of the step][A runs, then B runs][lane]: 64 KB for 128 x 128 outputs
@@ -193,7 +201,6 @@ __global__ __launch_bounds__(256, (BI * BJ == 4 ? 2 : BI * BJ == 2 ? 3 : 4)) voi
 
     int tm, tn;
     pm_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    if (flags && flags[(tm * TR / 128) * flag_cols + tn * TC / 128] == 0) return;
 
     // markers met in this lane's row of the row block / column of the column block this wave searches (its half of every k block)
     uint32_t row_nar = 0, col_nar = 0;
@@ -410,7 +417,7 @@ inline P8MfmaLayout p8_mfma_layout(int64_t M, int64_t N, int64_t K) {
 
 inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                                       const uint8_t* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace,
-                                      const uint32_t* flags = nullptr, int nflags = 0, int flag_cols = 0) {
+                                      const uint32_t* flags = nullptr, int nflags = 0, const uint4* mark = nullptr) {
     const P8MfmaLayout l = p8_mfma_layout(M, N, K);
     uint8_t* base = (uint8_t*)workspace;
     uint8_t* Ad = base;
@@ -436,7 +443,7 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     const dim3 grid((unsigned)(tiles_m * tiles_n));
 #define PNN_PM_LAUNCH(bi, bj)                                                                                                                    \
     hipLaunchKernelGGL((p8_mfma_gemm_kernel<bi, bj>), grid, dim3(256), 0, stream, Ad, Bd, l.RBA, l.RBB, l.KB, bias, C, ldc, fout, (int)M, (int)N, \
-                       tiles_m, tiles_n, 0, SplitWs{nullptr, nullptr, nullptr}, flags, flag_cols)
+                       tiles_m, tiles_n, 0, SplitWs{nullptr, nullptr, nullptr}, mark)
     if (l.BI == 2 && l.BJ == 2) PNN_PM_LAUNCH(2, 2);
     else if (l.BI == 2) PNN_PM_LAUNCH(2, 1);
     else if (l.BJ == 2) PNN_PM_LAUNCH(1, 2);

@@ -1,4 +1,4 @@
-"""posit<8,0> products on the 6-bit floating-point matrix cores: digits, bounds, the tiles that go to the int8 kernel, edges."""
+"""posit<8,0> products on the 6-bit floating-point matrix cores: digits, bounds, the products that go to the int8 kernel, edges."""
 import ctypes
 
 import numpy as np
@@ -35,7 +35,7 @@ def test_digits_of_every_pattern():
 def _operands(kind, M, N, K):
     """Patterns of A (M x K) and B (K x N)."""
     rng = np.random.default_rng([17, M, N, K])
-    if kind == "patterns":  # whole range of the format: tiles with +-32 or +-64 (nearly all) are left to the int8 kernel
+    if kind == "patterns":  # whole range of the format: tiles with +-32 or +-64 (nearly all) are left
         A, B = (rng.integers(0, 256, s, dtype=np.uint8) for s in ((M, K), (K, N)))
         A[A == NAR] = 1
         B[B == NAR] = 255
@@ -46,6 +46,8 @@ def _operands(kind, M, N, K):
     A, B = (fast.round_from_float(rng.standard_normal(s).astype(np.float32), "p8") for s in ((M, K), (K, N)))
     if kind == "one sign":  # every product positive: the largest sums the bound admits for such data
         A, B = (np.where(x >= NAR, (256 - x.astype(np.int32)), x).astype(np.uint8) for x in (A, B))
+    elif kind == "some":
+        A[[5, 140, 1000], [0, K - 1, 7]] = 0x81, 0x7E, 0x7F
     elif kind == "special":  # NaR at the corners, one value without digits in a tile each of A and B
         A[0, 0] = A[M - 1, K - 1] = A[130, K // 2] = NAR
         B[0, 129] = B[K - 1, N - 1] = NAR
@@ -65,6 +67,8 @@ def _operands(kind, M, N, K):
     ("special", 2048, 2050, 448, True, True, False, "p16"),
     ("large", 2048, 2048, 1024, False, False, False, "p16"),
     ("patterns", 2048, 2048, 300, False, True, True, "p8"),
+    ("special", 2048, 2048, 2000, False, False, True, "p16"),   # a row and a column of tiles left
+    ("some", 2048, 2048, 700, True, False, True, "p8"),         # three rows of tiles left
     ("normal", 2048, 2048, 7168, False, False, False, "p8"),    # the longest reduction, and the first beyond it
     ("normal", 2048, 2048, 7169, False, False, False, "p8"),
 ])
