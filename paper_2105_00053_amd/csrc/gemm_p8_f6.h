@@ -12,12 +12,12 @@
 // digits, accumulators up to +-2^24); products of E2M3 numbers differ by a factor of at most 2^12, inside the window in which
 // it aligns its products (with E3M2 on both sides ratios of 2^14 fall out of that window).
 //
-// The bound is proved per output tile before the tile is multiplied: the launch that writes the digits leaves, for every
-// chunk of 256 reduction indices and block of 32 rows, the largest sum of h^2 and of l^2 over a row; by Cauchy's inequality
-// the sums of a tile stay below  sum over chunks of  |ha||hb|  and  32 (|ha||lb| + |la||hb|) + |la||lb|.  N(0, 1) operands
-// with K = 4096 reach a third of 2^24.  A tile whose bound fails, or that meets one of the four patterns +-32, +-64 (no such
-// digits), raises its flag; the int8 kernel of gemm_p8_mfma.h, launched behind this
-// one, then takes the whole product, and returns at once (1.5 us a launch) if no tile did.
+// The bound is proved for the whole product before anything is multiplied: the launch that writes the digits leaves, for every
+// chunk of 256 reduction indices and every 128 rows, the largest sum of h^2 and of l^2 over a row; by Cauchy's inequality the
+// sums stay below  sum over chunks of  |ha||hb|  and  32 (|ha||lb| + |la||hb|) + |la||lb|,  with the largest of each over all
+// rows.  N(0, 1) operands with K = 4096 reach a third of 2^24.  If the bound fails, or one of the four patterns +-32, +-64 (no
+// such digits) is met anywhere, every workgroup returns, and the int8 kernel of gemm_p8_mfma.h, launched behind this one, takes
+// the product; otherwise that one returns at once (1.5 us a launch).
 #pragma once
 
 #include "gemm_p8_mfma.h"
@@ -33,6 +33,8 @@ constexpr int PF_CHUNK = 4;          // k blocks of 64 per chunk of the bounds
 constexpr int PF_STAGES = 3;         // k blocks of 64 in LDS
 constexpr int PF_MAX_K = 7168;       // beyond, ordinary data come near the bound
 constexpr int PF_MIN_TILES = 256;    // fewest tiles of 128 x 128
+constexpr int PF_DECIDERS = 1024;    // workgroups that work out the bound: twice what the chip holds at once
+constexpr int PF_WRITERS = 8;        // of them, those that write it down (one per XCD; all of them: 12 us instead of 5 a refused launch)
 constexpr float PF_LIMIT = 16776000.0f;  // a little below 2^24: the bounds are worked out in binary32
 // scale operands (powers of two, bias 127) that turn E2M3 numbers, multiples of 2^-3, into integers: l, h, and h in units of l
 constexpr int PF_SCALE = 127 + 3, PF_SCALE_H32 = 127 + 3 + 5;
@@ -76,21 +78,25 @@ struct P8F6Job {
     int64_t s_r, s_k;   // element (row, k) at src[row * s_r + k * s_k]; one of the two is 1
     int rows, K;
     uint4* dst;         // [KB][RB][3][64]: per lane h[0-3]; h[4-5], l[0-1]; l[2-5] of its 32 codes of six bits each
-    uint4* stat;        // [chunk][RB]: {largest sum of h^2 over a row, of l^2, rows that hold NaR, whether a value has no digits}
-    int RB, KB;         // row blocks of 32 (a multiple of four), k blocks of 64
+    uint2* stat;        // [tile of 128 rows][chunk]: {largest sum of h^2 over a row, bit 31: a value has no digits; of l^2}
+    uint32_t* nar;      // [tile][chunk][4]: the rows of each row block that hold NaR
+    int RB, KB, chunks; // row blocks of 32 (a multiple of four), k blocks of 64
 };
 
 // Digits and bounds of both operands in one launch: the first blocks0 workgroups take job0, the rest job1.  A workgroup: four
 // row blocks, one per wave, and one chunk.  Bound by memory (a byte read and 1.5 written per element: 2 x 16.7 M elements take
-// 18.9 us, 4.4 TB/s), with about nine vector operations per element beside it.
+// 18.9 us, 4.4 TB/s), with about nine vector operations per element beside it.  A wave that has met a value without digits, which
+// refuses the product, writes no more of them.
 template <int UNUSED = 0>
-__global__ __launch_bounds__(256) void p8_f6_digits_kernel(P8F6Job job0, P8F6Job job1, unsigned blocks0) {
+__global__ __launch_bounds__(256) void p8_f6_digits_kernel(P8F6Job job0, P8F6Job job1, unsigned blocks0, uint32_t* verdict) {
     // One table of 256 entries and, for an operand stored reduction-index-major, one k block of 128 rows turned: rows of 72
     // bytes, 8-byte words exchanged by the row block so that neither side conflicts.
     constexpr int PITCH = 72;
     __shared__ __attribute__((aligned(16))) uint2 tab[256];
     __shared__ __attribute__((aligned(16))) uint8_t tile[128 * PITCH];
+    __shared__ uint2 best[4];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (blockIdx.x == 0 && t == 0) *verdict = PF_UNDECIDED;
     tab[t] = pf_entry((uint32_t)t);
     __syncthreads();
     const bool first = blockIdx.x < blocks0;
@@ -173,6 +179,7 @@ __global__ __launch_bounds__(256) void p8_f6_digits_kernel(P8F6Job job0, P8F6Job
 #pragma unroll
             for (int q = 0; q < 8; ++q) w[q] = raw[c][q];
         }
+        if (__any((int)flags < 0)) continue;
         uint32_t o[12];
 #pragma unroll
         for (int q = 0; q < 12; ++q) o[q] = 0;
@@ -213,21 +220,36 @@ __global__ __launch_bounds__(256) void p8_f6_digits_kernel(P8F6Job job0, P8F6Job
         ls = ls > lo ? ls : lo;
     }
     const uint64_t nar = __ballot((flags >> 30) & 1u), big = __ballot(flags >> 31);
-    if (lane == 0) job.stat[(int64_t)chunk * job.RB + rb] = make_uint4(hs, ls, (uint32_t)nar, big != 0 ? 1u : 0u);
+    const int64_t at = (int64_t)bx * job.chunks + chunk;
+    if (lane == 0) {
+        job.nar[at * 4 + wave] = (uint32_t)nar;
+        best[wave] = make_uint2(hs | (big != 0 ? 1u << 31 : 0u), ls);
+    }
+    __syncthreads();
+    if (t == 0) {
+        uint2 m = best[0];
+#pragma unroll
+        for (int v = 1; v < 4; ++v) {
+            m.x = m.x > best[v].x ? m.x : best[v].x;
+            m.y = m.y > best[v].y ? m.y : best[v].y;
+        }
+        job.stat[at] = m;
+    }
 }
 
 struct P8F6Args {
     const uint4* Ad;
     const uint4* Bd;
-    const uint4* sa;
-    const uint4* sb;
+    const uint2* sa;       // see P8F6Job
+    const uint2* sb;
+    const uint32_t* nar_a;
+    const uint32_t* nar_b;
     int RBA, RBB, KB, chunks;
     const uint8_t* bias;
     void* C;
     int64_t ldc;
     int fout, M, N, tiles_m, tiles_n;
-    uint32_t* flag;  // see pf_flag
-    uint4* mark;     // see pf_intact
+    uint32_t* verdict;     // see pf_done
 };
 
 // Operand registers of one block of 32 rows and 64 reduction indices.
@@ -263,9 +285,10 @@ __global__ __launch_bounds__(256, 2) void p8_f6_gemm_kernel(P8F6Args g) {
     constexpr int TR = 32 * NA, TC = 32 * NB;
     constexpr int S = PF_STAGES;                      // 72 KB of LDS for each of two workgroups
     // One LDS object (beside a second one the compiler waits for every copy in front of each read of the ring)
-    __shared__ uint4 lds[S * STAGE + W / 2 + (NA + NB + 3) / 4];
-    float* const bound = reinterpret_cast<float*>(lds + S * STAGE);              // [wave][2]
-    uint32_t* const nar = reinterpret_cast<uint32_t*>(lds + S * STAGE + W / 2);      // [NA + NB]: rows of each block that hold NaR
+    __shared__ uint4 lds[S * STAGE + (NA + NB + 3) / 4 + 1];
+    uint32_t* const nar = reinterpret_cast<uint32_t*>(lds + S * STAGE);  // [NA + NB]: rows of each block that hold NaR
+    uint32_t* const seen = nar + (NA + NB + 3) / 4 * 4;                      // the verdict as this workgroup found it
+    uint4* const most = lds + (S - 1) * STAGE;                              // [THREADS], in the buffer that nothing has been copied to yet
 
     const int t = threadIdx.x;
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -300,56 +323,87 @@ __global__ __launch_bounds__(256, 2) void p8_f6_gemm_kernel(P8F6Args g) {
         }
         ++next_kb;
     };
+    // ---- the bound, and the NaR rows of this tile ----
+    // The first workgroups all work out the bound from the same numbers, a lane per chunk and eight tiles of rows side by side; one
+    // that starts later looks whether they have refused by then (if it runs on all the same, the int8 kernel writes over what it
+    // leaves).
+    const bool decides = blockIdx.x < PF_DECIDERS;
+    const int c = t & 31;
+    static_assert((PF_MAX_K + 64 * PF_CHUNK - 1) / (64 * PF_CHUNK) <= 32, "a lane per chunk");
+    static_assert(NA == 4 && NB == 4, "a word of NaR rows per block");
+    if (t < NA + NB) nar[t] = 0;
+    const int cc = c < g.chunks ? c : g.chunks - 1;
+    const bool of_a = t < 32;
+    uint4 rows = make_uint4(0, 0, 0, 0);
+    if (t < 64) rows = *reinterpret_cast<const uint4*>(of_a ? g.nar_a + ((int64_t)tm * g.chunks + cc) * 4 : g.nar_b + ((int64_t)tn * g.chunks + cc) * 4);
+    struct Most {
+        uint2 a[4], b[4];
+    };
+    auto look = [&](Most& s, int i0) {  // past the end the last tile again
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + (t >> 5) + 8 * u;
+            s.a[u] = g.sa[(int64_t)(i < g.tiles_m ? i : g.tiles_m - 1) * g.chunks + cc];
+            s.b[u] = g.sb[(int64_t)(i < g.tiles_n ? i : g.tiles_n - 1) * g.chunks + cc];
+        }
+    };
+    uint4 m = make_uint4(0, 0, 0, 0);
+    auto take = [&](const Most& s) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            m.x = m.x > s.a[u].x ? m.x : s.a[u].x;
+            m.y = m.y > s.a[u].y ? m.y : s.a[u].y;
+            m.z = m.z > s.b[u].x ? m.z : s.b[u].x;
+            m.w = m.w > s.b[u].y ? m.w : s.b[u].y;
+        }
+    };
+    Most s0;
+    if (decides) look(s0, 0);
     issue(0);
     issue(1);
-
-    // ---- the bounds of this tile, and its NaR flags ----
-    if (t < NA + NB) nar[t] = 0;
-    __syncthreads();
-    float bhh = 0.0f, bq = 0.0f;
-    for (int c = t; c < g.chunks; c += THREADS) {
-        uint4 s[NA + NB];
-#pragma unroll
-        for (int b = 0; b < NA + NB; ++b) s[b] = b < NA ? g.sa[(int64_t)c * g.RBA + tm * NA + b] : g.sb[(int64_t)c * g.RBB + tn * NB + (b - NA)];
-        uint32_t ha = 0, la = 0, hb = 0, lb = 0, big = 0;
-#pragma unroll
-        for (int b = 0; b < NA + NB; ++b) {
-            uint32_t& hm = b < NA ? ha : hb;
-            uint32_t& lm = b < NA ? la : lb;
-            hm = hm > s[b].x ? hm : s[b].x;
-            lm = lm > s[b].y ? lm : s[b].y;
-            big |= s[b].w;
+    if (decides) {
+        take(s0);
+        for (int i = 32; i < g.tiles_m || i < g.tiles_n; i += 32) {
+            look(s0, i);
+            take(s0);
         }
-#pragma unroll
-        for (int b = 0; b < NA + NB; ++b)
-            if (s[b].z) atomicOr(&nar[b], s[b].z);
-        const float fha = __builtin_sqrtf((float)ha), fla = __builtin_sqrtf((float)la), fhb = __builtin_sqrtf((float)hb), flb = __builtin_sqrtf((float)lb);
-        bhh += fha * fhb + (big ? 1e30f : 0.0f);
-        bq += (float)PF_UNIT * (fha * flb + fla * fhb) + fla * flb;
-    }
-#pragma unroll
-    for (int d = 1; d < 64; d *= 2) {
-        bhh += __shfl_xor(bhh, d);
-        bq += __shfl_xor(bq, d);
-    }
-    if (lane == 0) {
-        bound[2 * w] = bhh;
-        bound[2 * w + 1] = bq;
+        most[t] = c < g.chunks ? m : make_uint4(0, 0, 0, 0);
+    } else if (t == 0) {
+        *seen = __hip_atomic_load(g.verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __builtin_amdgcn_s_waitcnt(pcm_vmcnt((S - 2) * (CA + CB)));  // block 0 has landed
     __syncthreads();
-    bhh = bq = 0.0f;
+    if (rows.x | rows.y | rows.z | rows.w) {
+        uint32_t* const to = nar + (of_a ? 0 : NA);
+        atomicOr(&to[0], rows.x);
+        atomicOr(&to[1], rows.y);
+        atomicOr(&to[2], rows.z);
+        atomicOr(&to[3], rows.w);
+    }
+    bool refused;
+    if (decides) {
+        m = make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int v = 0; v < W; ++v) {
-        bhh += bound[2 * v];
-        bq += bound[2 * v + 1];
+        for (int v = 0; v < THREADS / 32; ++v) {
+            const uint4 s = most[32 * v + c];
+            m.x = m.x > s.x ? m.x : s.x;
+            m.y = m.y > s.y ? m.y : s.y;
+            m.z = m.z > s.z ? m.z : s.z;
+            m.w = m.w > s.w ? m.w : s.w;
+        }
+        const float ha = __builtin_sqrtf((float)m.x), la = __builtin_sqrtf((float)m.y), hb = __builtin_sqrtf((float)m.z), lb = __builtin_sqrtf((float)m.w);
+        float bhh = ha * hb + ((m.x | m.z) >> 31 ? 1e30f : 0.0f), bq = (float)PF_UNIT * (ha * lb + la * hb) + la * lb;
+#pragma unroll
+        for (int d = 1; d < 32; d *= 2) {
+            bhh += __shfl_xor(bhh, d);
+            bq += __shfl_xor(bq, d);
+        }
+        refused = !(bhh < PF_LIMIT / 16 && bq < PF_LIMIT);
+        if (t == 0 && blockIdx.x < PF_WRITERS) __hip_atomic_store(g.verdict, refused ? PF_REFUSED : PF_DONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        refused = *seen == PF_REFUSED;
     }
-    const bool left = !(bhh < PF_LIMIT / 16 && bq < PF_LIMIT);
-    if (t == 0) {
-        g.flag[pf_flag(tm * g.tiles_n + tn)] = left ? 0u : PF_DONE;
-        if (blockIdx.x == 0) *g.mark = make_uint4(PF_DONE, PF_DONE, PF_DONE, PF_DONE);
-    }
-    if (__builtin_amdgcn_readfirstlane(left)) {
+    if (__builtin_amdgcn_readfirstlane(refused)) {
         __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
         return;
     }
@@ -504,12 +558,10 @@ __global__ __launch_bounds__(256, 2) void p8_f6_gemm_kernel(P8F6Args g) {
 struct P8F6Layout {
     int RBA, RBB, KB, chunks;
     int tiles_m, tiles_n;   // of 128 x 128 outputs
-    size_t a_bytes, b_bytes, sa_bytes, sb_bytes, int8_bytes;
-    // the int8 digits take the place of everything here where they are needed; flags and mark lie at their end, 2 KB per 256
-    // tiles and 2 KB
-    size_t flag_off() const { return int8_bytes - 2048 * ((size_t)(tiles_m * tiles_n + 255) / 256 + 1); }
+    size_t a_bytes, b_bytes, stat_bytes, nar_bytes, int8_bytes;
+    // the int8 digits take the place of everything here where they are needed; the verdict is the last word of it
     size_t total() const { return int8_bytes; }
-    bool fits() const { return a_bytes + b_bytes + sa_bytes + sb_bytes <= flag_off(); }
+    bool fits() const { return a_bytes + b_bytes + nar_bytes + stat_bytes <= int8_bytes - 16; }
 };
 
 inline P8F6Layout p8_f6_layout(int64_t M, int64_t N, int64_t K) {
@@ -522,8 +574,8 @@ inline P8F6Layout p8_f6_layout(int64_t M, int64_t N, int64_t K) {
     l.chunks = (l.KB + PF_CHUNK - 1) / PF_CHUNK;
     l.a_bytes = (size_t)l.KB * l.RBA * 3072;
     l.b_bytes = (size_t)l.KB * l.RBB * 3072;
-    l.sa_bytes = (size_t)l.chunks * l.RBA * 16;
-    l.sb_bytes = (size_t)l.chunks * l.RBB * 16;
+    l.nar_bytes = (size_t)l.chunks * (l.tiles_m + l.tiles_n) * 16;
+    l.stat_bytes = (size_t)l.chunks * (l.tiles_m + l.tiles_n) * 8;
     l.int8_bytes = p8_mfma_layout(M, N, K).total();
     return l;
 }
@@ -531,7 +583,10 @@ inline P8F6Layout p8_f6_layout(int64_t M, int64_t N, int64_t K) {
 // Products that come here, where the workspace may have up to `limit` bytes.  Timed against the int8 kernel alone on N(0, 1)
 // operands (us, before -> now): 2048 x 2048 x 512 25.0 -> 24.2, x 4096 77.7 -> 57.4, 3072 x 3072 x 512 66 -> 36, 4096 x 4096 x 256
 // 60 -> 35, x 4096 235 -> 153, 8192 x 512 x 2048 52 -> 45; with half the tiles the chip is half empty and the two launches
-// behind weigh more: 1536^3 33.3 -> 36.4, 1024 x 2048 x 2048 34.6 -> 39.2.
+// behind weigh more: 1536^3 33.3 -> 36.4, 1024 x 2048 x 2048 34.6 -> 39.2.  Refused operands pay for the digits and a launch that
+// returns (int8 kernel alone -> now, and in brackets when every tile decided for itself and the product was then taken again):
+// 4096^3 N(0, 1) with one +-64 236 -> 262 (392), N(0, 8^2) 248 -> 268 (271), all patterns at random 256 -> 273 (277); one +-64 at
+// 2048 x 2048 x 4096 76 -> 92 (130), 4096 x 4096 x 256 58 -> 72 (89), 8192 x 8192 x 2048 485 -> 509 (782).
 inline bool p8_f6_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
     return p8_mfma_fits(M, N, K) && K <= PF_MAX_K && ((M + 127) / 128) * ((N + 127) / 128) >= PF_MIN_TILES && p8_f6_layout(M, N, K).total() <= limit &&
            p8_f6_layout(M, N, K).fits();
@@ -543,20 +598,21 @@ inline hipError_t launch_p8_f6_gemm(hipStream_t stream, int transA, int transB, 
     uint8_t* base = (uint8_t*)workspace;
     uint4* Ad = reinterpret_cast<uint4*>(base);
     uint4* Bd = reinterpret_cast<uint4*>(base + l.a_bytes);
-    uint4* sa = reinterpret_cast<uint4*>(base + l.a_bytes + l.b_bytes);
-    uint4* sb = reinterpret_cast<uint4*>(base + l.a_bytes + l.b_bytes + l.sa_bytes);
-    uint32_t* flag = reinterpret_cast<uint32_t*>(base + l.flag_off());
+    uint32_t* nar_a = reinterpret_cast<uint32_t*>(base + l.a_bytes + l.b_bytes);
+    uint32_t* nar_b = nar_a + (size_t)l.chunks * l.tiles_m * 4;
+    uint2* sa = reinterpret_cast<uint2*>(base + l.a_bytes + l.b_bytes + l.nar_bytes);
+    uint2* sb = sa + (size_t)l.chunks * l.tiles_m;
+    uint32_t* verdict = reinterpret_cast<uint32_t*>(base + l.int8_bytes) - 1;
     // op(A)[m,k] is A[m * lda + k] unless transA; op(B)[k,n] is B[k * ldb + n] unless transB
-    P8F6Job ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, Ad, sa, l.RBA, l.KB};
-    P8F6Job jb{B, transB ? ldb : (int64_t)1, transB ? (int64_t)1 : ldb, (int)N, (int)K, Bd, sb, l.RBB, l.KB};
+    P8F6Job ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, Ad, sa, nar_a, l.RBA, l.KB, l.chunks};
+    P8F6Job jb{B, transB ? ldb : (int64_t)1, transB ? (int64_t)1 : ldb, (int)N, (int)K, Bd, sb, nar_b, l.RBB, l.KB, l.chunks};
     const unsigned blocks0 = (unsigned)l.tiles_m * (unsigned)l.chunks, blocks1 = (unsigned)l.tiles_n * (unsigned)l.chunks;
-    hipLaunchKernelGGL(p8_f6_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0);
+    hipLaunchKernelGGL(p8_f6_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, verdict);
     PNN_CHECK_LAUNCH();
-    const int tiles = l.tiles_m * l.tiles_n;
-    P8F6Args a{Ad, Bd, sa, sb, l.RBA, l.RBB, l.KB, l.chunks, bias, C, ldc, fout, (int)M, (int)N, l.tiles_m, l.tiles_n, flag, reinterpret_cast<uint4*>(base + l.int8_bytes - 16)};
-    hipLaunchKernelGGL(p8_f6_gemm_kernel<0>, dim3((unsigned)tiles), dim3(256), 0, stream, a);
+    P8F6Args a{Ad, Bd, sa, sb, nar_a, nar_b, l.RBA, l.RBB, l.KB, l.chunks, bias, C, ldc, fout, (int)M, (int)N, l.tiles_m, l.tiles_n, verdict};
+    hipLaunchKernelGGL(p8_f6_gemm_kernel<0>, dim3((unsigned)(l.tiles_m * l.tiles_n)), dim3(256), 0, stream, a);
     PNN_CHECK_LAUNCH();
-    return launch_p8_mfma_gemm(stream, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, base, flag, tiles, a.mark);
+    return launch_p8_mfma_gemm(stream, transA, transB, A, lda, B, ldb, bias, C, ldc, fout, M, N, K, base, verdict);
 }
 
 }  // namespace pnn

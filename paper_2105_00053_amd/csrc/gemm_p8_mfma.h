@@ -71,15 +71,11 @@ __device__ __forceinline__ uint16_t pm_digits(uint32_t pattern) {
     return (uint16_t)(((uint32_t)(hi & 0xFF) << 8) | (uint32_t)(lo & 0xFF));
 }
 
-// Behind gemm_p8_f6.h the kernels of this file take the whole product if a tile is left, and return at once otherwise.  4096^3, us,
-// before that file and behind it: all patterns at random 291 and 319, N(0, 8^2) 251 and 274, N(0, 1) 235 and 153, N(0, 1) with one
-// +-64 (its row of tiles is left) 253 and 413.  What that file leaves here lies where this file's digits will, in places of low
-// digits, whose bytes are never -128: the last 16 bytes mark that they have not been written, and a flag word is PF_DONE for a
-// tile that needs nothing more.  A workgroup that reads the flags while another already writes digits over them can only find
-// more tiles left than there are, never fewer, so all agree to write.
-constexpr uint32_t PF_DONE = 0x80808080u;
-__device__ __forceinline__ bool pf_intact(const uint4* mark) { return mark->x == PF_DONE && mark->y == PF_DONE && mark->z == PF_DONE && mark->w == PF_DONE; }
-__device__ __forceinline__ int64_t pf_flag(int tile) { return (int64_t)(tile >> 8) * 512 + 256 + (tile & 255); }  // 1 KB of every 2
+// Behind gemm_p8_f6.h the kernels of this file return at once if its verdict, one word, says that the product is done.  The word
+// lies where this file's digits will, in a place of low digits, whose bytes are never -128: it cannot turn into PF_DONE while
+// they are written, so workgroups that read it before and after agree.
+constexpr uint32_t PF_DONE = 0x80808080u, PF_REFUSED = 1u, PF_UNDECIDED = 0u;
+__device__ __forceinline__ bool pf_done(const uint32_t* verdict) { return verdict && __hip_atomic_load(verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == PF_DONE; }
 
 struct P8DigitJob {
     const uint8_t* src;
@@ -92,14 +88,10 @@ struct P8DigitJob {
 // Both operands in one launch: the first blocks0 workgroups take job0, the rest job1.  A workgroup handles one k block
 // and eight row blocks: 512 lane slots of 16 bytes per digit, two per thread.
 template <int UNUSED = 0>
-__global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8DigitJob job1, unsigned blocks0, const uint32_t* __restrict__ flags, int nflags) {
+__global__ __launch_bounds__(256) void p8_digits_kernel(P8DigitJob job0, P8DigitJob job1, unsigned blocks0, const uint32_t* verdict) {
     __shared__ uint16_t tab[256];
     const int t = threadIdx.x;
-    if (flags) {
-        int left = 0;
-        for (int i = t; i < nflags; i += 256) left |= flags[pf_flag(i)] != PF_DONE;
-        if (!__syncthreads_or(left)) return;
-    }
+    if (pf_done(verdict)) return;
     tab[t] = pm_digits((uint32_t)t);
     __syncthreads();
     const bool first = blockIdx.x < blocks0;
@@ -188,8 +180,8 @@ template <int BI, int BJ, bool SPLIT = false>
 __global__ __launch_bounds__(256, (BI * BJ == 4 ? 2 : BI * BJ == 2 ? 3 : 4)) void p8_mfma_gemm_kernel(
     const uint8_t* __restrict__ Ad, const uint8_t* __restrict__ Bd, int RBA, int RBB, int KB, const uint8_t* __restrict__ bias, void* __restrict__ C,
     int64_t ldc, int fout, int M, int N, int tiles_m, int tiles_n, int kb_per_split = 0, SplitWs ws = SplitWs{nullptr, nullptr, nullptr},
-    const uint4* __restrict__ mark = nullptr) {
-    if (mark && pf_intact(mark)) return;
+    const uint32_t* verdict = nullptr) {
+    if (pf_done(verdict)) return;
     constexpr int NA = 2 * BI * 2, NB = 2 * BJ * 2;  // runs of 1 KB (row block, digit) per k block and operand
     constexpr int TR = 64 * BI, TC = 64 * BJ;        // tile extents
     // [buffer][k block of the step][A runs, then B runs][lane]: 64 KB for 128 x 128 outputs
@@ -417,7 +409,7 @@ inline P8MfmaLayout p8_mfma_layout(int64_t M, int64_t N, int64_t K) {
 
 inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB, const uint8_t* A, int64_t lda, const uint8_t* B, int64_t ldb,
                                       const uint8_t* bias, void* C, int64_t ldc, int fout, int64_t M, int64_t N, int64_t K, void* workspace,
-                                      const uint32_t* flags = nullptr, int nflags = 0, const uint4* mark = nullptr) {
+                                      const uint32_t* verdict = nullptr) {
     const P8MfmaLayout l = p8_mfma_layout(M, N, K);
     uint8_t* base = (uint8_t*)workspace;
     uint8_t* Ad = base;
@@ -426,7 +418,7 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     P8DigitJob ja{A, transA ? (int64_t)1 : lda, transA ? lda : (int64_t)1, (int)M, (int)K, Ad, l.RBA, l.KB};
     P8DigitJob jb{B, transB ? ldb : (int64_t)1, transB ? (int64_t)1 : ldb, (int)N, (int)K, Bd, l.RBB, l.KB};
     const unsigned blocks0 = (unsigned)((l.RBA + 7) / 8) * (unsigned)l.KB, blocks1 = (unsigned)((l.RBB + 7) / 8) * (unsigned)l.KB;
-    hipLaunchKernelGGL(p8_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, flags, nflags);
+    hipLaunchKernelGGL(p8_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, verdict);
     PNN_CHECK_LAUNCH();
     const int tiles_m = l.RBA / (2 * l.BI), tiles_n = l.RBB / (2 * l.BJ);
     if (l.splits > 1) {
@@ -443,7 +435,7 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     const dim3 grid((unsigned)(tiles_m * tiles_n));
 #define PNN_PM_LAUNCH(bi, bj)                                                                                                                    \
     hipLaunchKernelGGL((p8_mfma_gemm_kernel<bi, bj>), grid, dim3(256), 0, stream, Ad, Bd, l.RBA, l.RBB, l.KB, bias, C, ldc, fout, (int)M, (int)N, \
-                       tiles_m, tiles_n, 0, SplitWs{nullptr, nullptr, nullptr}, mark)
+                       tiles_m, tiles_n, 0, SplitWs{nullptr, nullptr, nullptr}, verdict)
     if (l.BI == 2 && l.BJ == 2) PNN_PM_LAUNCH(2, 2);
     else if (l.BI == 2) PNN_PM_LAUNCH(2, 1);
     else if (l.BJ == 2) PNN_PM_LAUNCH(1, 2);
