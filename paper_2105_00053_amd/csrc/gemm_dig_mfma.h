@@ -585,10 +585,25 @@ constexpr int64_t DIG_P8_1_NARROW = (int64_t)1 << 31;
 // 17.2, 64 tiles, 512 21.2 -> 17.1, 96, 512 21.4 -> 19.5, 100, 640 23.2 -> 21.1; 144, 300 21.1 -> 21.9, 256, 1024 30.0 -> 34.8 (every
 // operand is read twice as often).  Eight waves are slower than four from 65 tiles on (two workgroups on some compute units).
 constexpr int DIG_SMALL_TILES = 112, DIG_SMALL_WAVES = 4;
+// posit(8,1), whose reduction is never cut and whose older kernel leaves empty planes out: with more than one workgroup per compute
+// unit only short reductions (us, 64 -> 32: 100 tiles, K = 512 18.7 -> 18.0, 1024 22.1 -> 23.6; 78, 640 20.3 -> 20.3, 8192 66 -> 94;
+// 110, 448 18.6 -> 17.9, 768 20.5 -> 21.3; 112, 320 17.0 -> 16.8, 448 17.5 -> 18.2, 1024 22.0 -> 25.2; 250 workgroups, 8192 63.7 -> 61.0).
+constexpr int DIG_SMALL_UNCUT_WGS = 256, DIG_SMALL_UNCUT_K = 320, DIG_SMALL_UNCUT_TILES = 110;
+constexpr int64_t DIG_SMALL_UNCUT_TILES_K = 55000;
 
 // The kernel that may always cut the reduction: that of four planes, or the only one.
 template <class F>
 constexpr int dig_nps() { return DigFormat<F>::NP1 == 4 ? 4 : DigFormat<F>::NP2; }
+
+template <class F>
+inline bool dig_small(int64_t M, int64_t N, int64_t K, int splits) {
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+    if (dig_nps<F>() != 4 || splits != 1) return false;
+    if (F::N == 8 && !DigFormat<F>::BASE0)
+        return ((M + 31) / 32) * ((N + 31) / 32) <= DIG_SMALL_UNCUT_WGS || (tiles <= DIG_SMALL_TILES && K <= DIG_SMALL_UNCUT_K) ||
+               (tiles <= DIG_SMALL_UNCUT_TILES && tiles * K <= DIG_SMALL_UNCUT_TILES_K);
+    return tiles <= DIG_SMALL_TILES;
+}
 
 // Room for 8 planes of both operands (posit(8,1): 4), the masks, 256 bytes for the decision, and what is not found inside
 // on top: the scan's results take a slot that no kernel of posit(8,2) uses (posit(8,1): the rest of the 256 bytes), the partial sums of a cut reduction the slots
@@ -656,7 +671,7 @@ inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX
         }
     }
     p.kg = NPS == 4 && tiles * p.splits <= 256 ? 2 : 1;
-    p.small = NPS == 4 && p.splits == 1 && tiles <= DIG_SMALL_TILES;
+    p.small = dig_small<F>(M, N, K, p.splits);
     return p;
 }
 

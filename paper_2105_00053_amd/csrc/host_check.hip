@@ -244,6 +244,12 @@ int host_conv_plan(int which, const ConvGeom& g, int64_t* out) {
 }
 
 template <class F>
+int host_dig_small(int64_t M, int64_t N, int64_t K) {
+    if constexpr (F::N != 32 && !(F::ES != 0 && DigFormat<F>::COVER)) return 0;
+    else return dig_plan<F>(M, N, K).small;
+}
+
+template <class F>
 int host_dig_plan(int64_t M, int64_t N, int64_t K, int64_t limit, int64_t* out) {
     if constexpr (F::N == 8 && F::ES == 0) return 0;
     else {
@@ -591,6 +597,12 @@ int hostcheck_conv_gather_plan(int fmt, int which, const pnn_conv2d_desc* d, int
     ConvGeom g;
     if (!conv_geom(d, &g)) return 0;
     PNN_DISPATCH_POSIT(fmt, return host_conv_plan<F>(which, g, out))
+    return 0;
+}
+
+// whether a product takes 32 x 32 tiles
+int hostcheck_dig_small(int fmt, int64_t M, int64_t N, int64_t K) {
+    PNN_DISPATCH_POSIT(fmt, return host_dig_small<F>(M, N, K))
     return 0;
 }
 

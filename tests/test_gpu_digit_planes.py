@@ -180,6 +180,9 @@ def test_posit32_with_bias_takes_no_workspace():
     ("p16", 1024, 448, 96, False, True, False, "p16"),     # the last number of tiles that goes here, and the first beyond
     ("p16", 1024, 449, 96, False, True, False, "p16"),
     ("p8_2", 256, 270, 500, True, False, True, "p12_2"),
+    ("p8_1", 256, 1024, 1023, False, True, True, "p8_1"),  # one workgroup per compute unit
+    ("p8_1", 640, 704, 500, True, False, False, "p12_1"),  # the longest reduction of that many tiles, and the first beyond
+    ("p8_1", 640, 704, 501, False, False, True, "p8_1"),
 ])
 def test_few_tiles_of_32_by_32(fmt, M, N, K, ta, tb, bias, fout):
     """The kernel whose waves share the reduction of one 32 x 32 tile: N(0, 1) operands with NaR in the first row, the last

@@ -34,6 +34,16 @@ def test_digits_of_every_pattern():
             assert abs(h) <= 48 and abs(l) <= 16 and (l == 0 or abs(v) < 256)
 
 
+def _digits():
+    """h and l of every pattern."""
+    L = ctypes.CDLL(build.HOSTCHECK)
+    out, h, l = np.zeros(6, dtype=np.int32), np.zeros(256, dtype=np.int64), np.zeros(256, dtype=np.int64)
+    for p in range(256):
+        L.hostcheck_p8_f6(ctypes.c_uint32(p), out.ctypes.data_as(ctypes.c_void_p))
+        h[p], l[p] = out[1:3]
+    return h, l
+
+
 def _operands(kind, M, N, K):
     """Patterns of A (M x K) and B (K x N)."""
     rng = np.random.default_rng([17, M, N, K])
@@ -46,7 +56,7 @@ def _operands(kind, M, N, K):
         A, B = (rng.choice(np.array([0x7C, 0x7D, 0x84, 0x83], np.uint8), s) for s in ((M, K), (K, N)))
         return A, B
     A, B = (fast.round_from_float(rng.standard_normal(s).astype(np.float32), "p8") for s in ((M, K), (K, N)))
-    if kind == "one sign":  # every product positive: the largest sums the bound admits for such data
+    if kind == "one sign":  # every product positive: the largest sums of such data
         A, B = (np.where(x >= NAR, (256 - x.astype(np.int32)), x).astype(np.uint8) for x in (A, B))
     elif kind == "some":
         A[[5, 140, 1000], [0, K - 1, 7]] = 0x81, 0x7E, 0x7F
@@ -86,6 +96,82 @@ def test_products_on_the_6_bit_matrix_cores(kind, M, N, K, ta, tb, bias, fout):
     rows = np.unique(np.concatenate([np.arange(4), np.arange(126, 134), [300], np.arange(M - 3, M), np.random.default_rng(1).integers(0, M, 16)]))
     want, _ = fast.gemm(np.ascontiguousarray(A[rows]), B, "p8", fout, bias=b)
     assert len(mismatches(to_np(C, fout)[rows], want)) == 0
+
+
+LIMIT = 16776000.0  # of the low sum's bound; the bound of the high one is a sixteenth
+
+
+def _bounds(A, B):
+    """The bounds the kernel works out: of the high sum and of the low one."""
+    h, l = _digits()
+    norms = [[np.sqrt(np.add.reduceat(d[X] ** 2, np.arange(0, X.shape[1], 256), axis=1).max(axis=0).astype(np.float64)) for d in (h, l)] for X in (A, B.T)]
+    (ha, la), (hb, lb) = norms
+    return (ha * hb).sum(), (32 * (ha * lb + la * hb) + la * lb).sum()
+
+
+def _at_the_bound(K):
+    """24 (h = 48) against 15/64 (l = 15): Cauchy's inequality is an equality, so the low sum itself comes up to the bound, in steps of
+    one unit (rows with 1/64 in places).  Every other row is negative; in half of the columns eight large entries bring the high
+    sum against it, to about three, so that its rounding sees the low units."""
+    rng = np.random.default_rng(11)
+    A, B = np.full((2048, K), 0x7D, np.uint8), np.full((K, 2048), 0x0F, np.uint8)
+    A[1::2] = 0x83
+    A[2::4][rng.random((512, K)) < 0.003] = 0x01
+    A[3::4][rng.random((512, K)) < 0.003] = 0xFF
+    for n in range(1, 2048, 2):
+        B[rng.choice(K, n // 2 % 7, replace=False), n] = 0x0E
+    large = np.array([0x83] * 6 + [0x84] + [0x100 - 0x76], np.uint8)  # -24, -16, -7
+    for n in range(2, 2048, 4):
+        B[rng.choice(K, 8, replace=False), n] = large
+        B[rng.choice(K, 8, replace=False), n + 1] = large
+    return A, B
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fout", ["p8", "p32"])
+def test_sums_at_the_bound_are_exact(fout):
+    A, B = _at_the_bound(720)
+    bhh, bq = _bounds(A, B)
+    assert bhh < LIMIT / 16 and 0.98 * 2 ** 24 < bq < LIMIT
+    rows = np.concatenate([np.arange(8), np.arange(1020, 1036)])
+    h, l = _digits()
+    ha, la, hb, lb = (X.astype(np.float64) for X in (h[A[rows]], l[A[rows]], h[B], l[B]))  # exact: integers far below 2^53
+    q = 32 * (ha @ lb + la @ hb) + la @ lb
+    assert np.abs(q).max() > 0.98 * 2 ** 24 and len(np.unique(q % 1536)) > 20  # at the bound, and not in steps of a cross product
+    workspace = torch.empty(pn.posit_gemm_workspace("p8", fout, False, False, 2048, 2048, 720), dtype=torch.uint8, device="cuda")
+    C = pn.posit_gemm(to_dev(A), to_dev(B), "p8", fout, workspace=workspace)
+    assert workspace[-4:].tolist() == [0x80] * 4  # the 6-bit kernel's verdict: done there
+    want, _ = fast.gemm(np.ascontiguousarray(A[rows]), B, "p8", fout)
+    assert len(np.unique(want.reshape(len(rows), -1, 4)[:, :, 2:])) > 20  # no saturation where the sums cancel
+    assert len(mismatches(to_np(C, fout)[rows], want)) == 0
+
+
+@pytest.mark.gpu
+def test_captured_product_follows_the_data_of_each_replay():
+    """One captured call on one workspace, its operands changed between replays: taken in 6 bits, refused by a value without digits,
+    by the bound, and taken again."""
+    M, N, K = 2176, 2050, 700
+    kinds = ["normal", "special", "normal", "large", "patterns", "normal"]
+    sets = [_operands(kind, M, N, K) for kind in kinds]
+    A, B = (to_dev(x) for x in sets[0])
+    out = torch.empty((M, N), dtype=torch.uint8, device="cuda")
+    workspace = torch.empty(pn.posit_gemm_workspace("p8", "p8", False, False, M, N, K), dtype=torch.uint8, device="cuda")
+    pn.posit_gemm(A, B, "p8", "p8", out=out, workspace=workspace)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pn.posit_gemm(A, B, "p8", "p8", out=out, workspace=workspace)
+    rows = np.concatenate([np.arange(4), np.arange(128, 132), [300], np.arange(M - 3, M)])
+    for kind, (a, b) in zip(kinds, sets):
+        A.copy_(to_dev(a))
+        B.copy_(to_dev(b))
+        out.fill_(0x55)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (workspace[-4:].tolist() == [0x80] * 4) == (kind == "normal")
+        want, _ = fast.gemm(np.ascontiguousarray(a[rows]), b, "p8", "p8")
+        assert len(mismatches(to_np(out, "p8")[rows], want)) == 0, kind
+        assert torch.equal(out, pn.posit_gemm(A, B, "p8", "p8")), kind
 
 
 @pytest.mark.gpu

@@ -72,3 +72,14 @@ def test_slices_of_a_reduction_and_where_their_sums_go(hc, fmt):  # noqa: F811
                 if limit < 0:
                     assert (ws > 1) == (s > 1)
                 assert ws == 1 or limit < 0 or total <= max(limit, rest + s * per)
+
+
+def test_which_products_take_32_by_32_tiles(hc):  # noqa: F811
+    """posit(8,1), whose reduction is never cut: beyond one workgroup per compute unit only short reductions.  The other formats by
+    their tiles, cut reductions aside."""
+    hc.hostcheck_dig_small.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3
+    for fmt, M, N, K, small in (("p8_1", 512, 512, 4096, 1), ("p8_1", 300, 800, 8192, 1), ("p8_1", 640, 704, 500, 1), ("p8_1", 640, 704, 501, 0),
+                                ("p8_1", 640, 640, 1024, 0), ("p8_1", 333, 777, 4096, 0), ("p8_1", 448, 1024, 320, 1), ("p8_1", 448, 1024, 321, 0), ("p8_1", 128, 3584, 2048, 0),
+                                ("p8_2", 640, 640, 1024, 1), ("p8_2", 640, 640, 2048, 0), ("p8_2", 640, 768, 300, 0), ("p12_1", 448, 1024, 768, 1),
+                                ("p12_1", 448, 1024, 1024, 0), ("p16", 513, 1024, 100, 0), ("p32", 512, 512, 512, 0)):
+        assert hc.hostcheck_dig_small(CODE[fmt], M, N, K) == small, (fmt, M, N, K)
