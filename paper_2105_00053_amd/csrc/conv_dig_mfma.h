@@ -352,10 +352,14 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64),
                                              (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
         asrc += a_kb;
-        const int2 e = ktab[kb * 2 + (lane >> 5)];
+        int2 e = ktab[kb * 2 + (lane >> 5)];
+        // (Both halves in one read: left to itself the compiler reads the offset only where the row is inside, behind a wait of its
+        // own; posit<16,1>, 77 images of 64 channels at 37 x 37, 3 x 3 to 20, forward 76.6 us and 74.5, 63 of 80 at 18 x 18, 5 x 5 to 55,
+        // backward-data 101.9 and 95.5.)
+        asm("" : "+v"(e.x), "+v"(e.y));
         const int dh = (int)(short)(e.y & 0xFFFF), dw = e.y >> 16;
         const int ih = oh + dh, iw = ow + dw;
-        const bool inside = (unsigned)ih < (unsigned)a.HI && (unsigned)iw < (unsigned)a.WI;
+        const bool inside = ((unsigned)ih < (unsigned)a.HI) & ((unsigned)iw < (unsigned)a.WI);
         const uint4* s = inside ? actq + (base + e.x) : zeroq;
 #pragma unroll
         for (int c = 0; c < GRUNS; ++c)
