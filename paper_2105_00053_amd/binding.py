@@ -8,6 +8,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -89,7 +90,8 @@ def load():
                  "posit_relu", "posit_relu_bwd", "posit_maxpool2d_fwd", "posit_maxpool2d_bwd", "posit_avgpool2d_fwd", "posit_avgpool2d_bwd"):
         getattr(L, name).restype = ci
     native = _load_native()
-    native.init(*(ctypes.cast(getattr(L, name), vp).value for name in _NATIVE_ORDER))
+    if native is not None:
+        native.init(*(ctypes.cast(getattr(L, name), vp).value for name in _NATIVE_ORDER))
     _lib, _native = L, native
     return L
 
@@ -108,12 +110,16 @@ _NATIVE_ORDER = ("posit_gemm", "posit_gemm_workspace", "posit_conv2d_fwd", "posi
 
 
 def _load_native():
-    if not os.path.exists(_NATIVE_PATH):
-        raise PositError("positnn_native.so is not built: run `python -m paper_2105_00053_amd.build`")
-    loader = importlib.machinery.ExtensionFileLoader("positnn_native", _NATIVE_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("positnn_native", loader))
-    loader.exec_module(module)
-    return module
+    """The extension module, or None with a warning: it is built for one interpreter and one torch, and the Python code serves
+    every call without it, more slowly."""
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("positnn_native", _NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("positnn_native", loader))
+        loader.exec_module(module)
+        return module
+    except ImportError as e:
+        warnings.warn("positnn_native.so is not in use, calls take longer: %s" % e, RuntimeWarning, stacklevel=3)
+        return None
 
 
 def _ready():

@@ -48,11 +48,16 @@ def _compile(unit):
 
 
 def _native_command():
-    """g++ line of the extension module: against torch's headers and libraries (those that `import torch` has loaded by then)."""
+    """g++ line of the extension module: against torch's headers and libraries (those that `import torch` has loaded by then).
+    None where the compiler or headers are not installed: the binding does without the module."""
+    import shutil
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
+    needed = [os.path.join(sysconfig.get_paths()["include"], "Python.h"), os.path.join(root, "include", "ATen", "ATen.h")]
+    if shutil.which("g++") is None or not all(os.path.exists(p) for p in needed):
+        return None
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
             "-I" + os.path.join(root, "include"), "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding_native.cpp"),
             "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", NATIVE]
@@ -61,16 +66,22 @@ def _native_command():
 def build(verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(UNITS) + 1)) as ex:
-        native = ex.submit(_run, _native_command())
+        command = _native_command()
+        native = ex.submit(_run, command) if command else None
         objs = list(ex.map(_compile, UNITS))
-        native.result()
+        if native:
+            native.result()
+        else:
+            sys.stderr.write("no g++, or no headers of Python or torch: positnn_native.so is left out\n")
+            if os.path.exists(NATIVE):
+                os.remove(NATIVE)  # built from other sources
     _run([HIPCC, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", LIB] + objs)
     # host-only build of the scalar functions, for CPU unit tests
     _run([HIPCC, "-O2", "-std=c++17", "-fPIC", "-shared", "--cuda-host-only", "-x", "hip"] + FP_FLAGS + [
           "-Wno-unused-command-line-argument", os.path.join(CSRC, "host_check.hip"), "-o", HOSTCHECK])
     _run([HIPCC] + DEVICE_FLAGS + ["-shared", os.path.join(CSRC, "issue_rates.hip"), "-o", RATES])
     if verbose:
-        print("built", LIB, ",", HOSTCHECK, ",", NATIVE, "and", RATES)
+        print("built", ", ".join(p for p in (LIB, HOSTCHECK, NATIVE, RATES) if os.path.exists(p)))
     return LIB
 
 
