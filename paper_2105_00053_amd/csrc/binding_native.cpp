@@ -151,9 +151,10 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Args a;
     if (!parse(args, n, 5, 4, &a)) return none();
     return guarded([&]() -> PyObject* {
+        if (elem_size(a.i[1]) == 0 || elem_size(a.i[2]) == 0) return none();  // before they are narrowed
         const int fin = (int)a.i[1], fout = (int)a.i[2], ta = a.i[3] != 0, tb = a.i[4] != 0;
         const at::Tensor *A = tensor(a.o[0], fin), *B = tensor(a.o[1], fin), *bias = nullptr;
-        if (!A || !B || A->dim() != 2 || B->dim() != 2 || elem_size(fout) == 0) return none();
+        if (!A || !B || A->dim() != 2 || B->dim() != 2) return none();
         const int64_t lda = A->size(1), ldb = B->size(1);
         const int64_t M = ta ? lda : A->size(0), K = ta ? A->size(0) : lda, N = tb ? B->size(0) : ldb;
         if (K != (tb ? ldb : B->size(0))) return none();
@@ -172,11 +173,12 @@ PyObject* conv(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Args a;
     if (!parse(args, n, 6, 5, &a)) return none();
     return guarded([&]() -> PyObject* {
+        if (elem_size(a.i[2]) == 0 || elem_size(a.i[3]) == 0) return none();  // before they are narrowed
         const int which = (int)a.i[1], fin = (int)a.i[2], fout = (int)a.i[3];
         const Desc* d = reinterpret_cast<const Desc*>(a.i[4]);
         const bool with_bias = a.i[5] != 0;
         const at::Tensor *x = tensor(a.o[0], fin), *w = tensor(a.o[1], fin), *bias = nullptr;
-        if (!x || !w || elem_size(fout) == 0) return none();
+        if (!x || !w) return none();
         if (a.o[2] != Py_None && !(bias = tensor(a.o[2], fin))) return none();
         const int64_t eh = d->H + 2 * d->pad_h - d->R, ew = d->W + 2 * d->pad_w - d->S;
         if (eh < 0 || ew < 0 || d->stride_h <= 0 || d->stride_w <= 0) return none();

@@ -46,6 +46,9 @@ def _calls():
         "element size": lambda: pn.posit_relu(x, "p16"),
         "pitch": lambda: pn.posit_gemm(x[:, ::2], w[:, ::2], "p8", "p8", trans_b=True),
         "format": lambda: pn.posit_gemm(x, w, 57, "p8", trans_b=True),
+        "format beyond 32 bits": lambda: pn.posit_gemm(x, w, 1 << 32, "p8", trans_b=True),
+        "output format beyond 32 bits": lambda: pn.posit_gemm(x, w, "p8", 1 << 32, trans_b=True),
+        "layer's format beyond 32 bits": lambda: pn.posit_conv2d_fwd(img, ker, d, "p8", 1 << 32, bias=kb),
         "format name": lambda: pn.posit_relu(x, "p9"),
         "source type": lambda: pn.posit_round(x, "p8"),
         "pool of a vector": lambda: pn.posit_maxpool2d_fwd(b, "p8"),
