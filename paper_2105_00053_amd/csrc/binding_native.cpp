@@ -71,16 +71,10 @@ bool integer(PyObject* o, long* v) {
 
 at::Tensor empty(at::IntArrayRef shape, at::ScalarType t, const at::Tensor& like) { return at::empty(shape, at::TensorOptions().dtype(t).device(like.device())); }
 
-// An output: the caller's tensor, or a new one.  False: the caller's does not fit.
-bool output(PyObject* o, long f, at::IntArrayRef shape, const at::Tensor& like, at::Tensor* out) {
-    if (o == Py_None) {
-        *out = empty(shape, dtype_of(f), like);
-        return true;
-    }
-    const at::Tensor* t = tensor(o, f);
-    if (!t) return false;
-    *out = *t;
-    return true;
+// An output the caller gave, or null for a new one.  False: it does not fit.
+bool given(PyObject* o, long f, const at::Tensor** out) {
+    *out = o == Py_None ? nullptr : tensor(o, f);
+    return o == Py_None || *out;
 }
 
 PyObject* none() { Py_RETURN_NONE; }
@@ -97,14 +91,19 @@ PyObject* result(int status, const at::Tensor& a, const at::Tensor& b) {
     return r;
 }
 
+// Allocations and the call itself run without the interpreter's lock, as torch.empty and a call through ctypes do: other Python
+// threads may run meanwhile, and the first allocation of a size can take long.  No Python object is touched inside.
+class Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+
+public:
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 template <class F, class... A>
-int call(Fn which, A... args) {  // other Python threads may run meanwhile, as during a call through ctypes
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = reinterpret_cast<F>(g_fn[which])(args...);
-    Py_END_ALLOW_THREADS
-    return status;
-}
+int call(Fn which, A... args) { return reinterpret_cast<F>(g_fn[which])(args...); }
 
 // Arguments: nints leading integers (the first the stream), then objects.
 constexpr int MOST_INTS = 8;
@@ -159,12 +158,19 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
         const int64_t M = ta ? lda : A->size(0), K = ta ? A->size(0) : lda, N = tb ? B->size(0) : ldb;
         if (K != (tb ? ldb : B->size(0))) return none();
         if (a.o[2] != Py_None && (!(bias = tensor(a.o[2], fin)) || bias->numel() != N)) return none();
+        const at::Tensor* to;
+        if (!given(a.o[3], fout, &to) || (to && to->dim() != 2)) return none();
         at::Tensor out, ws;
-        if (!output(a.o[3], fout, {M, N}, *A, &out) || out.dim() != 2) return none();
-        const size_t bytes = reinterpret_cast<gemm_ws_t>(g_fn[GEMM_WS])(fin, fout, ta, tb, M, N, K);
-        if (bytes) ws = empty({(int64_t)bytes}, at::kByte, *A);
-        return result(call<gemm_t>(GEMM, a.stream, fin, fout, ta, tb, M, N, K, (const void*)A->data_ptr(), lda, (const void*)B->data_ptr(), ldb,
-                                   (const void*)(bias ? bias->data_ptr() : nullptr), (void*)out.data_ptr(), out.size(1), bytes ? (void*)ws.data_ptr() : nullptr, bytes), out);
+        int status;
+        {
+            Unlocked here;
+            out = to ? *to : empty({M, N}, dtype_of(fout), *A);
+            const size_t bytes = reinterpret_cast<gemm_ws_t>(g_fn[GEMM_WS])(fin, fout, ta, tb, M, N, K);
+            if (bytes) ws = empty({(int64_t)bytes}, at::kByte, *A);
+            status = call<gemm_t>(GEMM, a.stream, fin, fout, ta, tb, M, N, K, (const void*)A->data_ptr(), lda, (const void*)B->data_ptr(), ldb,
+                                  (const void*)(bias ? bias->data_ptr() : nullptr), (void*)out.data_ptr(), out.size(1), bytes ? (void*)ws.data_ptr() : nullptr, bytes);
+        }
+        return result(status, out);
     });
 }
 
@@ -182,26 +188,42 @@ PyObject* conv(PyObject*, PyObject* const* args, Py_ssize_t n) {
         if (a.o[2] != Py_None && !(bias = tensor(a.o[2], fin))) return none();
         const int64_t eh = d->H + 2 * d->pad_h - d->R, ew = d->W + 2 * d->pad_w - d->S;
         if (eh < 0 || ew < 0 || d->stride_h <= 0 || d->stride_w <= 0) return none();
+        const at::Tensor *to, *to_bias = nullptr;
+        if (!given(a.o[3], fout, &to) || (with_bias && !given(a.o[4], fout, &to_bias))) return none();
         at::Tensor out, db, ws;
-        const bool ok = which == 0 ? output(a.o[3], fout, {d->N, d->K, eh / d->stride_h + 1, ew / d->stride_w + 1}, *x, &out)
-                                   : which == 1 ? output(a.o[3], fout, {d->N, d->C, d->H, d->W}, *x, &out) : output(a.o[3], fout, {d->K, d->C, d->R, d->S}, *x, &out);
-        if (!ok || (with_bias && !output(a.o[4], fout, {d->K}, *x, &db))) return none();
-        const size_t bytes = reinterpret_cast<conv_ws_t>(g_fn[CONV_WS])(which, fin, fout, d);
-        if (bytes) ws = empty({(int64_t)bytes}, at::kByte, *x);
-        const void *xp = x->data_ptr(), *wp = w->data_ptr();
-        void *op = out.data_ptr(), *sp = bytes ? ws.data_ptr() : nullptr;
-        if (which == 0) return result(call<conv3_t>(CONV_FWD, a.stream, fin, fout, d, xp, wp, (const void*)(bias ? bias->data_ptr() : nullptr), op, sp, bytes), out);
-        if (which == 1) return result(call<conv_bd_t>(CONV_BWD_DATA, a.stream, fin, fout, d, xp, wp, op, sp, bytes), out);
-        const int st = call<conv_bw_t>(CONV_BWD_WEIGHT, a.stream, fin, fout, d, xp, wp, op, with_bias ? (void*)db.data_ptr() : nullptr, sp, bytes);
-        return with_bias ? result(st, out, db) : result(st, out);
+        int status;
+        {
+            Unlocked here;
+            const at::ScalarType t = dtype_of(fout);
+            if (to) out = *to;
+            else if (which == 0) out = empty({d->N, d->K, eh / d->stride_h + 1, ew / d->stride_w + 1}, t, *x);
+            else if (which == 1) out = empty({d->N, d->C, d->H, d->W}, t, *x);
+            else out = empty({d->K, d->C, d->R, d->S}, t, *x);
+            if (with_bias) db = to_bias ? *to_bias : empty({d->K}, t, *x);
+            const size_t bytes = reinterpret_cast<conv_ws_t>(g_fn[CONV_WS])(which, fin, fout, d);
+            if (bytes) ws = empty({(int64_t)bytes}, at::kByte, *x);
+            const void *xp = x->data_ptr(), *wp = w->data_ptr();
+            void *op = out.data_ptr(), *sp = bytes ? ws.data_ptr() : nullptr;
+            if (which == 0) status = call<conv3_t>(CONV_FWD, a.stream, fin, fout, d, xp, wp, (const void*)(bias ? bias->data_ptr() : nullptr), op, sp, bytes);
+            else if (which == 1) status = call<conv_bd_t>(CONV_BWD_DATA, a.stream, fin, fout, d, xp, wp, op, sp, bytes);
+            else status = call<conv_bw_t>(CONV_BWD_WEIGHT, a.stream, fin, fout, d, xp, wp, op, with_bias ? (void*)db.data_ptr() : nullptr, sp, bytes);
+        }
+        return with_bias ? result(status, out, db) : result(status, out);
     });
 }
 
 // round(stream, fdst, src, out), convert(stream, fsrc, fdst, src, out)
-PyObject* map_elements(Fn fn, void* stream, long fsrc, long fdst, const at::Tensor* src, PyObject* given) {
+PyObject* map_elements(Fn fn, void* stream, long fsrc, long fdst, const at::Tensor* src, PyObject* dst) {
+    const at::Tensor* to;
+    if (!src || elem_size(fdst) == 0 || !given(dst, fdst, &to)) return none();
     at::Tensor out;
-    if (!src || elem_size(fdst) == 0 || !output(given, fdst, src->sizes(), *src, &out)) return none();
-    return result(call<map_t>(fn, stream, (int)fsrc, (int)fdst, src->numel(), (const void*)src->data_ptr(), (void*)out.data_ptr()), out);
+    int status;
+    {
+        Unlocked here;
+        out = to ? *to : empty(src->sizes(), dtype_of(fdst), *src);
+        status = call<map_t>(fn, stream, (int)fsrc, (int)fdst, src->numel(), (const void*)src->data_ptr(), (void*)out.data_ptr());
+    }
+    return result(status, out);
 }
 
 PyObject* round_to(PyObject*, PyObject* const* args, Py_ssize_t n) {
@@ -227,10 +249,16 @@ PyObject* relu(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!parse(args, n, 2, 2, &a)) return none();
     return guarded([&]() -> PyObject* {
         const at::Tensor* x = tensor(a.o[0], a.i[1]);
-        const at::Tensor* given = a.o[1] == Py_None ? nullptr : tensor(a.o[1], a.i[1]);
-        if (!x || (a.o[1] != Py_None && !given)) return none();
-        const at::Tensor out = given ? *given : empty(x->sizes(), x->scalar_type(), *x);
-        return result(call<relu_t>(RELU, a.stream, (int)a.i[1], x->numel(), (const void*)x->data_ptr(), (void*)out.data_ptr()), out);
+        const at::Tensor* to;
+        if (!x || !given(a.o[1], a.i[1], &to)) return none();
+        at::Tensor out;
+        int status;
+        {
+            Unlocked here;
+            out = to ? *to : empty(x->sizes(), x->scalar_type(), *x);
+            status = call<relu_t>(RELU, a.stream, (int)a.i[1], x->numel(), (const void*)x->data_ptr(), (void*)out.data_ptr());
+        }
+        return result(status, out);
     });
 }
 
@@ -240,11 +268,17 @@ PyObject* relu_bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!parse(args, n, 3, 3, &a)) return none();
     return guarded([&]() -> PyObject* {
         const at::Tensor *y = tensor(a.o[0], a.i[1]), *dy = tensor(a.o[1], a.i[2]);
-        const at::Tensor* given = a.o[2] == Py_None ? nullptr : tensor(a.o[2], a.i[2]);
-        if (!y || !dy || y->numel() != dy->numel() || (a.o[2] != Py_None && !given)) return none();
-        const at::Tensor out = given ? *given : empty(dy->sizes(), dy->scalar_type(), *dy);
-        return result(call<relu_bwd_t>(RELU_BWD, a.stream, (int)a.i[1], (int)a.i[2], dy->numel(), (const void*)y->data_ptr(), (const void*)dy->data_ptr(),
-                                       (void*)out.data_ptr()), out);
+        const at::Tensor* to;
+        if (!y || !dy || y->numel() != dy->numel() || !given(a.o[2], a.i[2], &to)) return none();
+        at::Tensor out;
+        int status;
+        {
+            Unlocked here;
+            out = to ? *to : empty(dy->sizes(), dy->scalar_type(), *dy);
+            status = call<relu_bwd_t>(RELU_BWD, a.stream, (int)a.i[1], (int)a.i[2], dy->numel(), (const void*)y->data_ptr(), (const void*)dy->data_ptr(),
+                                      (void*)out.data_ptr());
+        }
+        return result(status, out);
     });
 }
 
@@ -273,9 +307,16 @@ PyObject* maxpool_fwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
         const at::Tensor* x = tensor(a.o[0], a.i[1]);
         Pool p;
         if (!p.of(x, a.i[2], a.i[3], false)) return none();
-        const at::Tensor y = empty(p.shape, x->scalar_type(), *x), idx = empty(p.shape, at::kByte, *x);
-        return result(call<maxpool_t>(MAXPOOL_FWD, a.stream, (int)a.i[1], p.planes, p.h, p.w, (int64_t)a.i[2], (int64_t)a.i[3], (const void*)x->data_ptr(),
-                                      (const void*)y.data_ptr(), (void*)idx.data_ptr()), y, idx);
+        at::Tensor y, idx;
+        int status;
+        {
+            Unlocked here;
+            y = empty(p.shape, x->scalar_type(), *x);
+            idx = empty(p.shape, at::kByte, *x);
+            status = call<maxpool_t>(MAXPOOL_FWD, a.stream, (int)a.i[1], p.planes, p.h, p.w, (int64_t)a.i[2], (int64_t)a.i[3], (const void*)x->data_ptr(),
+                                     (const void*)y.data_ptr(), (void*)idx.data_ptr());
+        }
+        return result(status, y, idx);
     });
 }
 
@@ -286,9 +327,15 @@ PyObject* maxpool_bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
         const at::Tensor *dy = tensor(a.o[0], a.i[1]), *idx = tensor(a.o[1], 0);
         Pool p;
         if (!idx || !p.of(dy, a.i[2], a.i[3], true)) return none();
-        const at::Tensor dx = empty(p.shape, dy->scalar_type(), *dy);
-        return result(call<maxpool_t>(MAXPOOL_BWD, a.stream, (int)a.i[1], p.planes, p.h * a.i[2], p.w * a.i[3], (int64_t)a.i[2], (int64_t)a.i[3],
-                                      (const void*)dy->data_ptr(), (const void*)idx->data_ptr(), (void*)dx.data_ptr()), dx);
+        at::Tensor dx;
+        int status;
+        {
+            Unlocked here;
+            dx = empty(p.shape, dy->scalar_type(), *dy);
+            status = call<maxpool_t>(MAXPOOL_BWD, a.stream, (int)a.i[1], p.planes, p.h * a.i[2], p.w * a.i[3], (int64_t)a.i[2], (int64_t)a.i[3],
+                                     (const void*)dy->data_ptr(), (const void*)idx->data_ptr(), (void*)dx.data_ptr());
+        }
+        return result(status, dx);
     });
 }
 
@@ -302,9 +349,15 @@ PyObject* avgpool(PyObject*, PyObject* const* args, Py_ssize_t n) {
         const at::Tensor* x = tensor(a.o[0], fin);
         Pool p;
         if (elem_size(fout) == 0 || !p.of(x, kh, kw, back)) return none();
-        const at::Tensor y = empty(p.shape, dtype_of(fout), *x);
-        return result(call<avgpool_t>(back ? AVGPOOL_BWD : AVGPOOL_FWD, a.stream, (int)fin, (int)fout, p.planes, back ? p.h * kh : p.h, back ? p.w * kw : p.w, (int64_t)kh,
-                                      (int64_t)kw, (const void*)x->data_ptr(), (void*)y.data_ptr()), y);
+        at::Tensor y;
+        int status;
+        {
+            Unlocked here;
+            y = empty(p.shape, dtype_of(fout), *x);
+            status = call<avgpool_t>(back ? AVGPOOL_BWD : AVGPOOL_FWD, a.stream, (int)fin, (int)fout, p.planes, back ? p.h * kh : p.h, back ? p.w * kw : p.w, (int64_t)kh,
+                                     (int64_t)kw, (const void*)x->data_ptr(), (void*)y.data_ptr());
+        }
+        return result(status, y);
     });
 }
 

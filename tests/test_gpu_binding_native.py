@@ -1,5 +1,8 @@
 """The C++ marshalling of the binding against the Python code it stands in for: the same outputs bit for bit (types, shapes,
 given outputs), and the same errors, which the native code leaves to the Python code."""
+import threading
+import time
+
 import pytest
 import torch
 
@@ -65,14 +68,102 @@ def _outcome(call):
     return [(t.dtype, tuple(t.shape), t.cpu().view(torch.uint8).tolist() if t.numel() else []) for t in (r if isinstance(r, tuple) else (r,))]
 
 
+class _Recorder:
+    """The native module, noting for each call which function was asked and whether it took the call."""
+
+    def __init__(self, module):
+        self.module, self.asked = module, []
+
+    def __getattr__(self, name):
+        def function(*args):
+            r = getattr(self.module, name)(*args)
+            self.asked.append((name, r is not None))
+            return r
+        return function
+
+
+# the native functions that answer each call that succeeds (rounding makes some of the operands)
+TAKEN = {"gemm": "gemm", "gemm given": "gemm", "gemm workspace": "round round gemm", "fwd": "conv", "bwd_data": "conv", "bwd_weight": "conv",
+         "bwd_weight alone": "conv", "round": "round round", "convert": "convert convert", "relu": "relu relu", "relu_bwd": "round relu_bwd",
+         "maxpool": "maxpool_fwd round maxpool_bwd", "avgpool": "avgpool avgpool", "empty": "relu gemm"}
+
+
 def test_native_calls_do_what_the_python_code_does(monkeypatch):
     binding.load()
     calls = _calls()
-    taken = []
     for name, call in calls.items():
-        native = _outcome(call)
+        recorder = _Recorder(binding._native)
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_native", recorder)
+            native = _outcome(call)
         with monkeypatch.context() as m:
             m.setattr(binding, "_native", None)
             assert native == _outcome(call), name
-        taken.append(isinstance(native, list))
-    assert sum(taken) == 14  # the first fourteen run, the others raise
+        assert isinstance(native, list) == (name in TAKEN), name
+        if name in TAKEN:
+            assert recorder.asked == [(f, True) for f in TAKEN[name].split()], name
+        else:
+            assert all(not taken for _, taken in recorder.asked), name  # nothing, or left to the Python code
+
+
+def _longest_wait(call):
+    """Seconds that another Python thread stood still at most while call ran, the median of nine."""
+    waits = []
+    for _ in range(9):
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        started, stop, longest = threading.Event(), threading.Event(), [0.0]
+
+        def run():
+            last = time.perf_counter()
+            started.set()
+            while not stop.is_set():
+                now = time.perf_counter()
+                longest[0] = max(longest[0], now - last)
+                last = now
+
+        thread = threading.Thread(target=run)
+        thread.start()
+        started.wait()
+        time.sleep(0.02)
+        longest[0] = 0.0
+        call()
+        stop.set()
+        thread.join()
+        waits.append(longest[0])
+    return sorted(waits)[4]
+
+
+def test_other_threads_run_while_an_output_is_allocated(monkeypatch):
+    """8 GiB fresh from the driver take about half a millisecond, in which the interpreter's lock is free as it is for torch.empty."""
+    x = torch.zeros(1 << 30, dtype=torch.uint8, device="cuda")
+    convert = lambda: pn.posit_convert(x, "p8", "f64")
+    convert()
+    native = _longest_wait(convert)
+    monkeypatch.setattr(binding, "_native", None)
+    python = _longest_wait(convert)
+    assert native < 2 * python + 1e-4, (native, python)
+
+
+def test_native_calls_from_a_second_thread_on_its_own_stream():
+    """Each thread works on its own current stream; outputs and workspaces belong to it."""
+    a, b = _patterns((300, 256)), _patterns((256, 300), seed=2)
+    want = pn.posit_relu(pn.posit_gemm(a, b, "p8", "p8"), "p8")
+    torch.cuda.synchronize()
+    got = [[], []]
+
+    def run(out):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            assert binding._ready() == stream.cuda_stream
+            for _ in range(50):
+                out.append(pn.posit_relu(pn.posit_gemm(a, b, "p8", "p8"), "p8"))
+        stream.synchronize()
+
+    threads = [threading.Thread(target=run, args=(out,)) for out in got]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for out in got:
+        assert len(out) == 50 and all(torch.equal(t, want) for t in out)
