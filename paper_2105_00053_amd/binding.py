@@ -91,7 +91,8 @@ def load():
         getattr(L, name).restype = ci
     native = _load_native()
     if native is not None:
-        native.init(*(ctypes.cast(getattr(L, name), vp).value for name in _NATIVE_ORDER))
+        native.init(tuple((code, ELEM_SIZE[code], dtype, _SAME_SIZE[ELEM_SIZE[code]]) for code, dtype in TORCH_DTYPE.items()),
+                    *(ctypes.cast(getattr(L, name), vp).value for name in _NATIVE_ORDER))
     _lib, _native = L, native
     return L
 

@@ -9,53 +9,38 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/positnn.h"
 
 namespace {
 
-constexpr int F32 = 100, F64 = 101;
 enum Fn { GEMM, GEMM_WS, CONV_FWD, CONV_BWD_DATA, CONV_BWD_WEIGHT, CONV_WS, ROUND, CONVERT, RELU, RELU_BWD, MAXPOOL_FWD, MAXPOOL_BWD, AVGPOOL_FWD, AVGPOOL_BWD, COUNT };
 void* g_fn[COUNT];
 
-struct Desc {  // pnn_conv2d_desc
-    int64_t N, C, H, W, K, R, S, pad_h, pad_w, stride_h, stride_w;
+typedef pnn_conv2d_desc Desc;
+
+// The formats, as init() got them from binding.py: bytes per element (0: no such format), type of a new tensor, types taken
+struct Format {
+    int size;
+    at::ScalarType type;
+    uint64_t fits;
 };
+constexpr long FORMATS = 128;
+Format g_formats[FORMATS];
 
-// bytes per element of a format, 0 for none
-int elem_size(long f) {
-    switch (f) {
-        case 0: case 3: case 4: return 1;
-        case 1: case 5: case 6: case 7: case 8: return 2;
-        case 2: case F32: return 4;
-        case F64: return 8;
-        default: return 0;
-    }
-}
+int elem_size(long f) { return f < 0 || f >= FORMATS ? 0 : g_formats[f].size; }
 
-at::ScalarType dtype_of(long f) {
-    switch (elem_size(f)) {
-        case 1: return at::kByte;
-        case 2: return at::kUInt16;
-        case 4: return f == F32 ? at::kFloat : at::kUInt32;
-        default: return at::kDouble;
-    }
-}
+at::ScalarType dtype_of(long f) { return g_formats[f].type; }
 
-bool dtype_fits(at::ScalarType t, int size) {
-    switch (size) {
-        case 1: return t == at::kByte || t == at::kChar;
-        case 2: return t == at::kUInt16 || t == at::kShort;
-        case 4: return t == at::kUInt32 || t == at::kInt || t == at::kFloat;
-        case 8: return t == at::kDouble || t == at::kLong || t == at::kUInt64;
-        default: return false;
-    }
-}
+bool dtype_fits(at::ScalarType t, long f) { return elem_size(f) && (g_formats[f].fits >> (int)t & 1u); }
 
 // The tensor behind o if it is a plain contiguous device tensor of f's element size
 const at::Tensor* tensor(PyObject* o, long f) {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.is_cuda() || !t.is_contiguous() || !dtype_fits(t.scalar_type(), elem_size(f))) return nullptr;
+    if (!t.is_cuda() || !t.is_contiguous() || !dtype_fits(t.scalar_type(), f)) return nullptr;
     return &t;
 }
 
@@ -133,24 +118,25 @@ PyObject* guarded(const B& body) {
     }
 }
 
-typedef int (*gemm_t)(void*, int, int, int, int, int64_t, int64_t, int64_t, const void*, int64_t, const void*, int64_t, const void*, void*, int64_t, void*, size_t);
-typedef size_t (*gemm_ws_t)(int, int, int, int, int64_t, int64_t, int64_t);
-typedef int (*conv3_t)(void*, int, int, const Desc*, const void*, const void*, const void*, void*, void*, size_t);
-typedef int (*conv_bd_t)(void*, int, int, const Desc*, const void*, const void*, void*, void*, size_t);
-typedef int (*conv_bw_t)(void*, int, int, const Desc*, const void*, const void*, void*, void*, void*, size_t);
-typedef size_t (*conv_ws_t)(int, int, int, const Desc*);
-typedef int (*map_t)(void*, int, int, int64_t, const void*, void*);
-typedef int (*relu_t)(void*, int, int64_t, const void*, void*);
-typedef int (*relu_bwd_t)(void*, int, int, int64_t, const void*, const void*, void*);
-typedef int (*maxpool_t)(void*, int, int64_t, int64_t, int64_t, int64_t, int64_t, const void*, const void*, void*);
-typedef int (*avgpool_t)(void*, int, int, int64_t, int64_t, int64_t, int64_t, int64_t, const void*, void*);
+typedef decltype(&posit_gemm) gemm_t;
+typedef decltype(&posit_gemm_workspace) gemm_ws_t;
+typedef decltype(&posit_conv2d_fwd) conv3_t;
+typedef decltype(&posit_conv2d_bwd_data) conv_bd_t;
+typedef decltype(&posit_conv2d_bwd_weight) conv_bw_t;
+typedef decltype(&posit_conv2d_workspace) conv_ws_t;
+typedef decltype(&posit_round) map_t;
+typedef decltype(&posit_relu) relu_t;
+typedef decltype(&posit_relu_bwd) relu_bwd_t;
+typedef decltype(&posit_maxpool2d_fwd) maxpool_t;
+typedef decltype(&posit_maxpool2d_bwd) maxpool_bwd_t;
+typedef decltype(&posit_avgpool2d_fwd) avgpool_t;
 
 // gemm(stream, fin, fout, trans_a, trans_b, A, B, bias, out)
 PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Args a;
     if (!parse(args, n, 5, 4, &a)) return none();
     return guarded([&]() -> PyObject* {
-        if (elem_size(a.i[1]) == 0 || elem_size(a.i[2]) == 0) return none();  // before they are narrowed
+        if (!elem_size(a.i[1]) || !elem_size(a.i[2])) return none();  // before they are narrowed
         const int fin = (int)a.i[1], fout = (int)a.i[2], ta = a.i[3] != 0, tb = a.i[4] != 0;
         const at::Tensor *A = tensor(a.o[0], fin), *B = tensor(a.o[1], fin), *bias = nullptr;
         if (!A || !B || A->dim() != 2 || B->dim() != 2) return none();
@@ -179,7 +165,7 @@ PyObject* conv(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Args a;
     if (!parse(args, n, 6, 5, &a)) return none();
     return guarded([&]() -> PyObject* {
-        if (elem_size(a.i[2]) == 0 || elem_size(a.i[3]) == 0) return none();  // before they are narrowed
+        if (!elem_size(a.i[2]) || !elem_size(a.i[3])) return none();  // before they are narrowed
         const int which = (int)a.i[1], fin = (int)a.i[2], fout = (int)a.i[3];
         const Desc* d = reinterpret_cast<const Desc*>(a.i[4]);
         const bool with_bias = a.i[5] != 0;
@@ -232,7 +218,7 @@ PyObject* round_to(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         const at::ScalarType t = THPVariable_Unpack(a.o[0]).scalar_type();
         if (t != at::kFloat && t != at::kDouble) return none();
-        const long f = t == at::kFloat ? F32 : F64;
+        const long f = t == at::kFloat ? PNN_F32 : PNN_F64;
         return map_elements(ROUND, a.stream, f, a.i[1], tensor(a.o[0], f), a.o[1]);
     });
 }
@@ -314,7 +300,7 @@ PyObject* maxpool_fwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
             y = empty(p.shape, x->scalar_type(), *x);
             idx = empty(p.shape, at::kByte, *x);
             status = call<maxpool_t>(MAXPOOL_FWD, a.stream, (int)a.i[1], p.planes, p.h, p.w, (int64_t)a.i[2], (int64_t)a.i[3], (const void*)x->data_ptr(),
-                                     (const void*)y.data_ptr(), (void*)idx.data_ptr());
+                                     (void*)y.data_ptr(), (void*)idx.data_ptr());
         }
         return result(status, y, idx);
     });
@@ -324,7 +310,7 @@ PyObject* maxpool_bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Args a;
     if (!parse(args, n, 4, 2, &a)) return none();
     return guarded([&]() -> PyObject* {
-        const at::Tensor *dy = tensor(a.o[0], a.i[1]), *idx = tensor(a.o[1], 0);
+        const at::Tensor *dy = tensor(a.o[0], a.i[1]), *idx = tensor(a.o[1], PNN_POSIT8_0);
         Pool p;
         if (!idx || !p.of(dy, a.i[2], a.i[3], true)) return none();
         at::Tensor dx;
@@ -332,7 +318,7 @@ PyObject* maxpool_bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
         {
             Unlocked here;
             dx = empty(p.shape, dy->scalar_type(), *dy);
-            status = call<maxpool_t>(MAXPOOL_BWD, a.stream, (int)a.i[1], p.planes, p.h * a.i[2], p.w * a.i[3], (int64_t)a.i[2], (int64_t)a.i[3],
+            status = call<maxpool_bwd_t>(MAXPOOL_BWD, a.stream, (int)a.i[1], p.planes, p.h * a.i[2], p.w * a.i[3], (int64_t)a.i[2], (int64_t)a.i[3],
                                      (const void*)dy->data_ptr(), (const void*)idx->data_ptr(), (void*)dx.data_ptr());
         }
         return result(status, dx);
@@ -361,14 +347,35 @@ PyObject* avgpool(PyObject*, PyObject* const* args, Py_ssize_t n) {
     });
 }
 
-// init(addresses): the library's functions in the order of Fn
+// init(formats, address ...): formats as rows (code, bytes, dtype, dtypes taken), the library's functions in the order of Fn
 PyObject* init(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    if (n != COUNT) {
-        PyErr_SetString(PyExc_TypeError, "one address per function");
+    if (n != 1 + COUNT || !PyTuple_Check(args[0])) {
+        PyErr_SetString(PyExc_TypeError, "the formats and one address per function");
         return nullptr;
     }
+    for (Py_ssize_t k = 0; k < PyTuple_Size(args[0]); ++k) {
+        long code;
+        Format f;
+        PyObject *type, *taken;
+        if (!PyArg_ParseTuple(PyTuple_GetItem(args[0], k), "liO!O!", &code, &f.size, (PyTypeObject*)&THPDtypeType, &type, &PyTuple_Type, &taken)) return nullptr;
+        f.type = reinterpret_cast<THPDtype*>(type)->scalar_type;
+        f.fits = 0;
+        for (Py_ssize_t i = 0; i < PyTuple_Size(taken); ++i) {
+            PyObject* t = PyTuple_GetItem(taken, i);
+            if (!THPDtype_Check(t) || (int)reinterpret_cast<THPDtype*>(t)->scalar_type >= 64) {
+                PyErr_SetString(PyExc_TypeError, "a dtype");
+                return nullptr;
+            }
+            f.fits |= (uint64_t)1 << (int)reinterpret_cast<THPDtype*>(t)->scalar_type;
+        }
+        if (code < 0 || code >= FORMATS) {
+            PyErr_SetString(PyExc_ValueError, "format code");
+            return nullptr;
+        }
+        g_formats[code] = f;
+    }
     for (int k = 0; k < COUNT; ++k) {
-        g_fn[k] = PyLong_AsVoidPtr(args[k]);
+        g_fn[k] = PyLong_AsVoidPtr(args[1 + k]);
         if (!g_fn[k]) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null address");
             return nullptr;

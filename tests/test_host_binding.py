@@ -1,5 +1,6 @@
 """Loading the binding without a GPU."""
 import pytest
+import torch
 
 from paper_2105_00053_amd import binding
 
@@ -22,3 +23,15 @@ def test_the_library_loads_without_the_extension_module(unloaded, monkeypatch, t
     assert binding._native is None and binding._ready() is None
     assert binding.posit_gemm_workspace("p32", "p32", 0, 0, 512, 512, 512) > 0
     assert binding.load() is library
+
+
+def test_the_extension_module_knows_the_formats_of_the_python_code():
+    """It has no table of its own: rows that are no formats are refused."""
+    binding.load()
+    module = binding._load_native()
+    addresses = [1] * len(binding._NATIVE_ORDER)
+    for rows in (None, ((128, 1, torch.uint8, (torch.uint8,)),), ((0, 1, "uint8", (torch.uint8,)),), ((0, 1, torch.uint8, (1,)),), ((0, 1, torch.uint8),)):
+        with pytest.raises((TypeError, ValueError)):
+            module.init(rows, *addresses)
+    with pytest.raises(TypeError):
+        module.init((), *addresses[:-1])
