@@ -20,6 +20,8 @@ the path on that batch:
 on the launch stream.  The kernel forms every posit product exactly from four E2M3 x E2M3 products
 (two digits per operand, binary32 sums of integers below 2^24), so its bound is the 6-bit MFMA rate:
 achieved = 8 operations per posit MAC x M*N*K / time against the published 10.0 PFLOP/s.
+With --size, products that go to the int8 matrix cores (fewer than 256 tiles of 128 x 128, or
+K > 7168) are held against their 5.0 POP/s, four int8 products each; the smallest carry no roofline.
 The line also carries the posit MAC rate against the integer-VALU peak the metric names
 (one packed 16-bit dot-product lane-op = 2 MACs: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz x 2
 = 78.6 TMAC/s), which the previous, vector-ALU kernel was bound by.
@@ -37,7 +39,20 @@ if ROOT not in sys.path:
 
 PEAK_TMACS = 256 * 4 * 16 * 2.4e9 * 2 / 1e12  # 78.6 TMAC/s: integer vector ALU, packed 16-bit dot products
 PEAK_F6_TOPS = 10000.0                        # dense 6-bit floating-point MFMA, published
-F6_OPS_PER_POSIT_MAC = 8                      # four E2M3 multiply-accumulates: (32 ah + al)(32 bh + bl)
+PEAK_INT8_TOPS = 5000.0                       # dense int8 MFMA, published
+OPS_PER_POSIT_MAC = 8                         # four multiply-accumulates of digits: (32 ah + al)(32 bh + bl), in int8 128 for 32
+# HBM-side KiB per posit_gemm call at 4096^3 from two rocprofv3 --pmc passes (profiles/p8_gemm_4096_hbm_traffic.md):
+# FETCH_SIZE x 2.0 (copy-kernel scale) + WRITE_SIZE of the product and of the digit pass.
+GEMM_4096_TRAFFIC_KIB = (122369, 16490, 16583, 49176)  # (FETCH gemm, WRITE gemm, FETCH digit pass, WRITE digit pass)
+
+
+def gemm_kernel_of(size):
+    """Kernel, peak and unit of the posit<8,0> product of that size cubed, by the library's rule on sizes; None below 2^28 MACs."""
+    if (-(-size // 128)) ** 2 >= 256 and size <= 7168:
+        return "p8_f6_gemm_kernel", PEAK_F6_TOPS, "TFLOP/s (E2M3)"
+    if size ** 3 >= 2 ** 28:
+        return "p8_mfma_gemm_kernel", PEAK_INT8_TOPS, "TOP/s (int8)"
+    return None
 
 
 def _time_ms(torch, fn, reps, warm=2):
@@ -288,23 +303,32 @@ def main():
         "data": "synthetic",
         "config": {"workload": "posit<8,0> quire GEMM M=N=K=%d (benchmark config 5), step = round A,B + gemm + convert + axpy" % S,
                    "fin": "posit<8,0>", "fout": "posit<8,0>", "quire_bits": 32},
-        "roofline": {
+    }
+
+    kernel = gemm_kernel_of(S)
+    if kernel:
+        name, peak, unit = kernel
+        traffic, traffic_source = None, "not measured for this size"
+        if S == 4096 and GEMM_4096_TRAFFIC_KIB:
+            fg, wg, fd, wd = GEMM_4096_TRAFFIC_KIB
+            traffic = int((2.0 * (fg + fd) + wg + wd) * 1024)
+            traffic_source = "stored constant from profiles/p8_gemm_4096_hbm_traffic.md (two rocprofv3 --pmc runs), not measured by this run"
+        result["roofline"] = {
             "bound": "mfma",
-            "kernel": "p8_f6_gemm_kernel (with its digit pass: the posit_gemm call)",
-            "achieved": round(achieved * F6_OPS_PER_POSIT_MAC, 1),
-            "peak": PEAK_F6_TOPS,
-            "unit": "TFLOP/s (E2M3)",
-            "frac": round(achieved * F6_OPS_PER_POSIT_MAC / PEAK_F6_TOPS, 4),
+            "kernel": name + " (with its digit pass: the posit_gemm call)",
+            "achieved": round(achieved * OPS_PER_POSIT_MAC, 1),
+            "peak": peak,
+            "unit": unit,
+            "frac": round(achieved * OPS_PER_POSIT_MAC / peak, 4),
             "kernel_ms": round(gemm_ms, 4),
-            "f6_ops_per_posit_mac": F6_OPS_PER_POSIT_MAC,
+            "ops_per_posit_mac": OPS_PER_POSIT_MAC,
             "posit_TMAC_per_s": round(achieved, 3),
             "integer_valu_peak_TMAC_per_s": round(PEAK_TMACS, 1),
             "x_integer_valu_peak": round(achieved / PEAK_TMACS, 3),
             "algorithmic_bytes": 3 * S * S,
-            "traffic": None,
-            "traffic_source": "not measured for this kernel",
-        },
-    }
+            "traffic": traffic,
+            "traffic_source": traffic_source,
+        }
 
     if sustained:
         result["sustained"] = sustained

@@ -484,6 +484,9 @@ int hostcheck_p8_f6(uint32_t pattern, int32_t* out) {
     return 0;
 }
 
+// which matrix cores take a posit<8,0> product: 2 the 6-bit ones, 1 the int8 ones, 0 none
+int hostcheck_p8_product(int64_t M, int64_t N, int64_t K) { return p8_f6_fits(M, N, K, SIZE_MAX) ? 2 : p8_mfma_fits(M, N, K) ? 1 : 0; }
+
 // posit<16,1> -> posit<8,0> through the step table of the narrowing kernel
 int hostcheck_narrow_step(int64_t n, const uint64_t* in, uint64_t* out) {
     for (int64_t i = 0; i < n; ++i) {

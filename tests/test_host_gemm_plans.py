@@ -83,3 +83,12 @@ def test_which_products_take_32_by_32_tiles(hc):  # noqa: F811
                                 ("p8_2", 640, 640, 1024, 1), ("p8_2", 640, 640, 2048, 0), ("p8_2", 640, 768, 300, 0), ("p12_1", 448, 1024, 768, 1),
                                 ("p12_1", 448, 1024, 1024, 0), ("p16", 513, 1024, 100, 0), ("p32", 512, 512, 512, 0)):
         assert hc.hostcheck_dig_small(CODE[fmt], M, N, K) == small, (fmt, M, N, K)
+
+
+def test_benchmark_names_the_kernel_that_the_library_takes(hc):  # noqa: F811
+    import bench
+    hc.hostcheck_p8_product.argtypes = [ctypes.c_int64] * 3
+    names = {2: "p8_f6_gemm_kernel", 1: "p8_mfma_gemm_kernel"}
+    for size in (512, 645, 646, 1024, 1920, 1921, 2048, 4096, 7168, 7169, 8192):
+        kernel = bench.gemm_kernel_of(size)
+        assert (kernel and kernel[0]) == names.get(hc.hostcheck_p8_product(size, size, size)), size
