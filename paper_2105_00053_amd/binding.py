@@ -99,7 +99,7 @@ def load():
 
 # Argument marshalling is what a step of short kernels waits for: a launch takes 3 us of host time, a call through the Python code
 # here 6 to 9, one through csrc/binding_native.cpp 5 to 6
-# (the LeNet-5-shaped step of batch 64, about fifty calls: 377 us, now 272; a layer of 64 x 400 to 120 9.5 and 6.6).  So the calls of a training step go there first; it returns None for
+# (the LeNet-5-shaped step of batch 64, about fifty calls: 380 us, now 272 to 280; a layer of 64 x 400 to 120 9.8 and 6.3).  So the calls of a training step go there first; it returns None for
 # whatever it does not take (a caller's workspace, unusual arguments, arguments that are wrong), which the Python code handles
 # or refuses.  There pointers and the stream go to ctypes as plain integers, and the stream handle is read without building a
 # torch.cuda.Stream object (2.7 us).
