@@ -10,6 +10,7 @@
 #include "gemm_p8_mfma.h"
 #include "gemm_dig_mfma.h"
 #include "conv_b8.h"
+#include "direct_gemm.h"
 #include "gemm_bucket_pre.h"
 #include "gemm_p16_window.h"
 #include "gemm_p32_lds.h"
@@ -56,8 +57,50 @@ inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
     }
 }
 
+// us of a product on the kernel that takes it if the direct one does not, where that is a matrix-core kernel or, for (10,2) and
+// (12,2), the one with operands decoded once; fitted to products of 2^13 to 2^30 multiply-adds, off by 7 to 15 %.  Negative: another kernel.
+// From 2^29 on the matrix-core kernels with digits written once are the faster ones throughout: zero.
 template <class F>
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
+inline double prepared_us(int64_t M, int64_t N, int64_t K, size_t limit) {
+    const double g = (double)M * (double)N * (double)K / (1 << 30), k = 1e-3 * (double)K;
+    if (F::N == 8 && F::ES == 0) return p8_f6_fits(M, N, K, limit) ? 0 : p8_mfma_fits(M, N, K) ? (g < 0.5 ? 17 + 19 * g : 0) : -1;
+    if (dig_gemm_fits<F>(M, N, K, limit)) {
+        if (g >= 0.5) return 0;
+        if (F::N == 8) return F::ES == 1 ? 16 + 15.7 * g + 3.8 * k : 17.5 + 20 * g + 2.4 * k;
+        return 16.3 + 20 * g + 4 * k + 2.7 * (double)M * (double)N / (1 << 20);
+    }
+    if (bucket_pre_fits<F>(M, N, K)) return F::N == 10 ? 32 + 353 * g + 8 * k : 38 + 500 * g + 9 * k;
+    return -1;
+}
+
+// Products that go to the matrix cores straight from their patterns, in one launch.  Against the kernels that serve otherwise, 500
+// products of 8 to 4096 a side per format: faster by 1.6 (8 bits) and 4.6 to 6.3 times (10 to 16 bits) in the geometric mean, p16 48 x 368 x 340
+// 161 -> 8.4 us, posit<8,0> 850 x 160 x 1632 78 -> 9.7; what stays behind: estimates within a tenth of each other (8 bits with short table
+// entries: a fifth, strided operands cost them more), products of few outputs of the 8-bit formats (a thread group per output: 12 x 11 x 3737 7.8 us
+// there, 9.7 here) and reductions too short for a k block of 64 (1279 x 2486 x 11, p16, 52 and 57).
+template <class F>
+inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit) {
+    const DirectPlan none{DIRECT_NONE, 1, 0, 0};
+    if constexpr (F::N > 16) return none;
+    else {
+        if (K < 32 && M * N > ((int64_t)1 << 19)) return none;
+        if (F::N == 8) {
+            if (M * N < 2048 || (M * N < 4096 && K > 1024)) return none;
+            if (K < 32 && (F::ES == 2 || N < 32)) return none;
+        }
+        double us;
+        const DirectPlan p = direct_plan<F>(M, N, K, &us);
+        if (p.variant == DIRECT_NONE || p.ws_bytes > limit) return none;
+        const double prepared = prepared_us<F>(M, N, K, limit);
+        // other kernels: the vector ALU at some 10 TMAC/s and less
+        if (prepared < 0) return K <= 4096 || (double)M * (double)N * (double)K < 1e9 ? p : none;
+        return us < (F::N == 8 && F::ES < 2 ? 0.8 : 0.92) * prepared ? p : none;
+    }
+}
+
+// Cut of the kernels that serve where the direct one does not.
+template <class F>
+GemmPlan prepared_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
     if (dig_gemm_fits<F>(M, N, K, limit)) {
         GemmPlan p;
         p.splits = 1; p.k_per_split = K; p.ws_bytes = 0;
@@ -105,20 +148,33 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
     return plan_split(M, N, K, 16 * GemmTile<F>::TM, 16 * GemmTile<F>::TN, Arith<F>::L);
 }
 
+// What a call asks for: the query does not know the pitches, and operands beyond the direct kernel's offsets go to the others.
+template <class F>
+size_t gemm_workspace(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
+    const size_t a = prepared_plan<F>(M, N, K, limit).ws_bytes, b = direct_gemm_plan<F>(M, N, K, limit).ws_bytes;
+    return a > b ? a : b;
+}
+
 template <class F>
 int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, int64_t N, int64_t K,
                   const void* A, int64_t lda, const void* B, int64_t ldb, const void* bias, void* C, int64_t ldc,
                   void* ws, size_t ws_bytes, size_t limit) {
     typedef typename Storage<F::N>::T T;
     constexpr int TM = GemmTile<F>::TM, TN = GemmTile<F>::TN;
-    const GemmPlan plan = gemm_plan<F>(M, N, K, limit);
+    const GemmPlan plan = prepared_plan<F>(M, N, K, limit);
+    const size_t need = gemm_workspace<F>(M, N, K, limit);
     // posit<32,2> with a bias: the LDS kernel, whose quire takes it at any scale and which needs no workspace
     const bool use_dig = dig_gemm_fits<F>(M, N, K, limit) && (F::N != 32 || !bias);
     const bool no_ws = F::N == 32 && bias && p32_lds_fits(M, N, K);
-    if (plan.ws_bytes > 0 && !no_ws && (!ws || ws_bytes < plan.ws_bytes)) return PNN_EWORKSPACE;
+    if (need > 0 && !no_ws && (!ws || ws_bytes < need)) return PNN_EWORKSPACE;
     RowMajorOut out;
     out.ld = ldc;
     hipError_t e;
+    if constexpr (F::N <= 16) {
+        const DirectPlan direct = direct_gemm_plan<F>(M, N, K, limit);
+        if (direct.variant != DIRECT_NONE && direct_extent_fits(transA, transB, M, N, K, lda, ldb, sizeof(T)))
+            return hip_status(launch_direct_gemm<F>(st, direct, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, fout, ws));
+    }
     const int* served = nullptr;  // on the device: non-zero when the digit kernels did the work
     if constexpr (is_dig<F>()) {
         if (use_dig) {
@@ -232,7 +288,7 @@ using namespace pnn;
 extern "C" size_t posit_gemm_workspace(int fin, int fout, int transA, int transB, int64_t M, int64_t N, int64_t K) {
     (void)fout; (void)transA; (void)transB;
     if (!is_posit(fin) || M <= 0 || N <= 0 || K < 0) return 0;
-    PNN_DISPATCH_POSIT(fin, return gemm_plan<F>(M, N, K).ws_bytes)
+    PNN_DISPATCH_POSIT(fin, return gemm_workspace<F>(M, N, K))
     return 0;
 }
 
@@ -303,7 +359,7 @@ extern "C" int posit_gemm_static(void* stream, int fin, int fout, int transA, in
     // digit planes that want more than the fixed array give way to an older kernel that does not (see dig_gemm_fits)
     const size_t limit = PNN_GEMM_STATIC_SCRATCH_BYTES;
     size_t need = 0;
-    PNN_DISPATCH_POSIT(fin, need = gemm_plan<F>(M, N, K, limit).ws_bytes)
+    PNN_DISPATCH_POSIT(fin, need = gemm_workspace<F>(M, N, K, limit))
     if (need > PNN_GEMM_STATIC_SCRATCH_BYTES) return PNN_EWORKSPACE;  // beyond the fixed array: posit_gemm with a caller's workspace
     void* ws = nullptr;
     if (need > 0) {

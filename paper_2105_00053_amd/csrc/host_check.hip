@@ -6,6 +6,7 @@
 #include "conv_p8.h"
 #include "api_common.h"
 #include "dig_planes.h"
+#include "direct_mfma.h"
 #include "conv_desc.h"
 #include "gemm_p8_f6.h"
 #include "conv_p8_mfma.h"
@@ -269,6 +270,28 @@ uint32_t host_round(const uint32_t* q, int qfrac, const FmtRT& f) {
     uint32_t l[L];
     for (int i = 0; i < L; ++i) l[i] = q[i];
     return f.n <= 16 ? dig_round_limbs<L, false>(l, qfrac, f) : dig_round_limbs<L, true>(l, qfrac, f);
+}
+
+template <class F>
+int host_direct_digits(int64_t count, const uint32_t* patterns, uint32_t* words) {
+    if constexpr (F::N > 16) return 0;
+    else {
+        constexpr int ND = DirectFormat<F>::ND;
+        for (int64_t i = 0; i < count; ++i) {
+            uint32_t d[ND];
+            direct_digits<F>(patterns[i], d);
+            for (int h = 0; h < 3; ++h) words[3 * i + h] = h < ND ? d[h < ND ? h : 0] : 0u;
+        }
+        return DirectFormat<F>::NP;
+    }
+}
+
+template <class F>
+int host_direct_plan(int64_t M, int64_t N, int64_t K, int64_t* out) {
+    double us;
+    const DirectPlan p = direct_plan<F>(M, N, K, &us);
+    out[0] = p.variant; out[1] = p.splits; out[2] = p.k_per_split; out[3] = (int64_t)p.ws_bytes; out[4] = Arith<F>::L;
+    return p.variant != DIRECT_NONE;
 }
 
 extern "C" {
@@ -616,4 +639,16 @@ int hostcheck_dig_plan(int fmt, int64_t M, int64_t N, int64_t K, int64_t limit, 
     PNN_DISPATCH_POSIT(fmt, return host_dig_plan<F>(M, N, K, limit, out))
     return 0;
 }
+// Digits of patterns on the direct kernel, three words each; returns the number of planes (0: the format has none).
+int hostcheck_direct_digits(int fmt, int64_t count, const uint32_t* patterns, uint32_t* words) {
+    PNN_DISPATCH_POSIT(fmt, return host_direct_digits<F>(count, patterns, words))
+    return 0;
+}
+
+// variant, slices, reduction indices of a slice, workspace bytes, limbs of a partial quire
+int hostcheck_direct_plan(int fmt, int64_t M, int64_t N, int64_t K, int64_t* out) {
+    PNN_DISPATCH_POSIT(fmt, return host_direct_plan<F>(M, N, K, out))
+    return 0;
+}
+
 }  // extern "C"
