@@ -22,7 +22,7 @@ ARCH = "gfx950"
 
 NATIVE = os.path.join(HERE, "positnn_native.so")  # the binding's marshalling in C++ (csrc/binding_native.cpp)
 
-UNITS = ["api_elementwise.hip", "api_gemm.hip", "direct_gemm.hip", "api_conv.hip", "api_glue.hip", "api_noquire.hip", "api_loss.hip"]
+UNITS = ["api_elementwise.hip", "api_gemm.hip", "direct_gemm.hip", "direct_conv.hip", "api_conv.hip", "api_glue.hip", "api_noquire.hip", "api_loss.hip"]
 # Floating-point model, stated rather than left to the compiler's default: the fp64 "buckets" that carry exact
 # sums rely on every operation being the IEEE one that is written -- (r + C) - C must round r, not fold to r, and a
 # multiply-add is fused only where the source says fma().  So: no fast-math, no contraction across operations.

@@ -11,6 +11,7 @@
 #include "conv_p8_mfma.h"
 #include "conv_b8.h"
 #include "conv_dig_mfma.h"
+#include "direct_conv.h"
 
 namespace pnn {
 
@@ -168,7 +169,18 @@ size_t conv_ws(int which, const ConvGeom& g) {
         const size_t b2 = bias_grad_ws_bytes<F>(g.N, g.K, g.OH * g.OW);
         if (b2 > b) b = b2;
     }
+    for (int with_bias = 0; with_bias < (which == 2 ? 2 : 1); ++with_bias) {
+        const DirectConvPlan p = direct_conv_plan<F>(which, g, with_bias != 0);
+        if (p.cut.ws_bytes > b) b = p.cut.ws_bytes;
+    }
     return b;
+}
+
+// Whether a call brings what the query asks for: with less the kernels that serve otherwise take it, or refuse it.
+template <class F>
+bool has_ws(int which, const ConvGeom& g, const void* ws, size_t ws_bytes) {
+    const size_t need = conv_ws<F>(which, g);
+    return need == 0 || (ws && ws_bytes >= need);
 }
 
 template <class F>
@@ -176,6 +188,10 @@ int conv_fwd(hipStream_t st, int fout, const ConvGeom& g, const void* x, const v
              void* ws, size_t ws_bytes) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(0, g);
+    if constexpr (F::N <= 16) {
+        const DirectConvPlan p = direct_conv_plan<F>(0, g, false);
+        if (p.cut.variant != DIRECT_NONE && has_ws<F>(0, g, ws, ws_bytes)) return hip_status(launch_direct_conv<F>(st, p, g, x, w, bias, y, nullptr, fout, ws));
+    }
     if constexpr (dig_conv_format<F>()) {
         const DigConvPlan dp = dig_conv_plan<F>(0, g);
         if (dp.ok) {  // integer matrix cores
@@ -226,6 +242,10 @@ template <class F>
 int conv_bwd_data_product(hipStream_t st, int fout, const ConvGeom& g, const void* dy, const void* w, void* dx, void* ws, size_t ws_bytes, bool* marked) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(1, g);
+    if constexpr (F::N <= 16) {
+        const DirectConvPlan p = direct_conv_plan<F>(1, g, false);
+        if (p.cut.variant != DIRECT_NONE && has_ws<F>(1, g, ws, ws_bytes)) return hip_status(launch_direct_conv<F>(st, p, g, dy, w, nullptr, dx, nullptr, fout, ws));
+    }
     if constexpr (dig_conv_format<F>()) {
         const DigConvPlan dp = dig_conv_plan<F>(1, g);
         if (dp.ok) {  // integer matrix cores
@@ -285,6 +305,10 @@ int conv_bwd_weight(hipStream_t st, int fout, const ConvGeom& g, const void* dy,
                     void* ws, size_t ws_bytes) {
     typedef typename Storage<F::N>::T T;
     const ConvDims d = conv_dims(2, g);
+    if constexpr (F::N <= 16) {
+        const DirectConvPlan p = direct_conv_plan<F>(2, g, dbias != nullptr);  // the bias gradient rides along as a column of ones
+        if (p.cut.variant != DIRECT_NONE && has_ws<F>(2, g, ws, ws_bytes)) return hip_status(launch_direct_conv<F>(st, p, g, dy, x, nullptr, dw, dbias, fout, ws));
+    }
     if constexpr (dig_conv_format<F>()) {
         const DigConvBwPlan bp = dig_conv_bw_plan<F>(g, dbias != nullptr);
         if (bp.ok) {  // integer matrix cores, split reduction; the bias gradient rides along as a column of ones
