@@ -83,10 +83,10 @@ inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit
     const DirectPlan none{DIRECT_NONE, 1, 0, 0};
     if constexpr (F::N > 16) return none;
     else {
-        if (K < 32 && M * N > ((int64_t)1 << 19)) return none;
+        if (K < 16 && M * N > ((int64_t)1 << 19)) return none;
         if (F::N == 8) {
             if (M * N < 2048 || (M * N < 4096 && K > 1024)) return none;
-            if (K < 32 && (F::ES == 2 || N < 32)) return none;
+            if (K < 32 && M * N <= ((int64_t)1 << 19) && (F::ES == 2 || N < 32)) return none;
         }
         double us;
         const DirectPlan p = direct_plan<F>(M, N, K, &us);
@@ -162,17 +162,16 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
     typedef typename Storage<F::N>::T T;
     constexpr int TM = GemmTile<F>::TM, TN = GemmTile<F>::TN;
     const GemmPlan plan = prepared_plan<F>(M, N, K, limit);
-    const size_t need = gemm_workspace<F>(M, N, K, limit);
     // posit<32,2> with a bias: the LDS kernel, whose quire takes it at any scale and which needs no workspace
     const bool use_dig = dig_gemm_fits<F>(M, N, K, limit) && (F::N != 32 || !bias);
     const bool no_ws = F::N == 32 && bias && p32_lds_fits(M, N, K);
-    if (need > 0 && !no_ws && (!ws || ws_bytes < need)) return PNN_EWORKSPACE;
+    if (plan.ws_bytes > 0 && !no_ws && (!ws || ws_bytes < plan.ws_bytes)) return PNN_EWORKSPACE;
     RowMajorOut out;
     out.ld = ldc;
     hipError_t e;
     if constexpr (F::N <= 16) {
         const DirectPlan direct = direct_gemm_plan<F>(M, N, K, limit);
-        if (direct.variant != DIRECT_NONE && direct_extent_fits(transA, transB, M, N, K, lda, ldb, sizeof(T)))
+        if (direct.variant != DIRECT_NONE && (direct.ws_bytes == 0 || (ws && ws_bytes >= direct.ws_bytes)) && direct_extent_fits(transA, transB, M, N, K, lda, ldb, sizeof(T)))
             return hip_status(launch_direct_gemm<F>(st, direct, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, fout, ws));
     }
     const int* served = nullptr;  // on the device: non-zero when the digit kernels did the work
