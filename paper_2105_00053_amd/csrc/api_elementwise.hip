@@ -1,16 +1,23 @@
 // posit_round, posit_convert, posit_axpy: the bandwidth-bound entry points
 // (paper Fig. 2: tensor conversion, mixed-precision copies, SGD).  One thread
 // handles a short vector of consecutive elements so that the widest type moves
-// 16 bytes per access; a scalar kernel covers unaligned pointers and the tail.
+// 16 bytes per access; unaligned pointers and the tail go element by element.
 #include "api_common.h"
 #include "elementwise_fast.h"
 
 namespace pnn {
 
+// One launch: thread i < nvec a vector of V elements, the threads behind them one element each of what is left (all of them where a
+// pointer is not aligned, nvec = 0).  A launch of their own for the last elements cost 3 us of a call's 8 (posit<8,0> -> <16,1>, 892177
+// elements: 8.4 us; now 5.2; f32 -> posit<16,1>, 13400003: 19.1 and 17.3).
 template <class TS, class TD, int V, class Op>
-__global__ __launch_bounds__(256) void map_vec_kernel(const TS* __restrict__ src, TD* __restrict__ dst, int64_t nvec, Op op) {
+__global__ __launch_bounds__(256) void map_vec_kernel(const TS* __restrict__ src, TD* __restrict__ dst, int64_t nvec, int64_t n, Op op) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nvec) return;
+    if (i >= nvec) {
+        const int64_t e = i - nvec + nvec * V;
+        if (e < n) dst[e] = (TD)op((uint64_t)src[e]);
+        return;
+    }
     const Pack<TS, V> in = reinterpret_cast<const Pack<TS, V>*>(src)[i];
     Pack<TD, V> o;
 #pragma unroll
@@ -18,25 +25,22 @@ __global__ __launch_bounds__(256) void map_vec_kernel(const TS* __restrict__ src
     reinterpret_cast<Pack<TD, V>*>(dst)[i] = o;
 }
 
-template <class TS, class TD, class Op>
-__global__ __launch_bounds__(256) void map_scalar_kernel(const TS* __restrict__ src, TD* __restrict__ dst, int64_t begin, int64_t n, Op op) {
-    const int64_t i = begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    dst[i] = (TD)op((uint64_t)src[i]);
-}
-
 // 8-bit sources: the conversion is a function of 256 patterns, so each workgroup
 // evaluates it once into an LDS table and then only looks bytes up.  One thread
 // produces one 16-byte store (V = 16 / sizeof(TD) elements), so that both the
 // loads and the stores of a wavefront are contiguous.
 template <class TD, class Op>
-__global__ __launch_bounds__(256) void map_p8_table_kernel(const uint8_t* __restrict__ src, TD* __restrict__ dst, int64_t nvec, Op op) {
+__global__ __launch_bounds__(256) void map_p8_table_kernel(const uint8_t* __restrict__ src, TD* __restrict__ dst, int64_t nvec, int64_t n, Op op) {
     constexpr int V = 16 / sizeof(TD);
     __shared__ TD table[256];
     table[threadIdx.x] = (TD)op((uint64_t)threadIdx.x);
     __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nvec) return;
+    if (i >= nvec) {
+        const int64_t e = i - nvec + nvec * V;
+        if (e < n) dst[e] = table[src[e]];
+        return;
+    }
     const Pack<uint8_t, V> in = reinterpret_cast<const Pack<uint8_t, V>*>(src)[i];
     Pack<TD, V> o;
 #pragma unroll
@@ -44,27 +48,14 @@ __global__ __launch_bounds__(256) void map_p8_table_kernel(const uint8_t* __rest
     reinterpret_cast<Pack<TD, V>*>(dst)[i] = o;
 }
 
-template <class TS, class TD, class Op>
-int launch_map(hipStream_t st, const void* src, void* dst, int64_t n, Op op);
+inline unsigned map_blocks(int64_t nvec, int64_t n, int V) { return (unsigned)((nvec + (n - nvec * V) + 255) / 256); }
 
 template <class TD, class Op>
 int launch_map_p8(hipStream_t st, const void* src, void* dst, int64_t n, Op op) {
-    int64_t done = 0;
     constexpr int V = 16 / sizeof(TD);
-    if (aligned(src, V) && aligned(dst, 16)) {
-        const int64_t nvec = n / V;
-        if (nvec > 0) {
-            hipLaunchKernelGGL((map_p8_table_kernel<TD, Op>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st,
-                               (const uint8_t*)src, (TD*)dst, nvec, op);
-            done = nvec * V;
-            if (hipGetLastError() != hipSuccess) return PNN_EHIP;  // stop at the first failed launch
-        }
-    }
-    if (done < n) {
-        const int64_t rest = n - done;
-        hipLaunchKernelGGL((map_scalar_kernel<uint8_t, TD, Op>), dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, st,
-                           (const uint8_t*)src, (TD*)dst, done, n, op);
-    }
+    if (n <= 0) return PNN_OK;
+    const int64_t nvec = aligned(src, V) && aligned(dst, 16) ? n / V : 0;
+    hipLaunchKernelGGL((map_p8_table_kernel<TD, Op>), dim3(map_blocks(nvec, n, V)), dim3(256), 0, st, (const uint8_t*)src, (TD*)dst, nvec, n, op);
     return hip_status(hipGetLastError());
 }
 
@@ -72,29 +63,24 @@ template <class TS, class TD, class Op>
 int launch_map(hipStream_t st, const void* src, void* dst, int64_t n, Op op) {
     constexpr int WIDE = sizeof(TS) > sizeof(TD) ? sizeof(TS) : sizeof(TD);
     constexpr int V = 16 / WIDE;
-    int64_t done = 0;
-    if (aligned(src, sizeof(TS) * V) && aligned(dst, sizeof(TD) * V)) {
-        const int64_t nvec = n / V;
-        if (nvec > 0) {
-            hipLaunchKernelGGL((map_vec_kernel<TS, TD, V, Op>), dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st,
-                               (const TS*)src, (TD*)dst, nvec, op);
-            done = nvec * V;
-            if (hipGetLastError() != hipSuccess) return PNN_EHIP;  // stop at the first failed launch
-        }
-    }
-    if (done < n) {
-        const int64_t rest = n - done;
-        hipLaunchKernelGGL((map_scalar_kernel<TS, TD, Op>), dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, st,
-                           (const TS*)src, (TD*)dst, done, n, op);
-    }
+    if (n <= 0) return PNN_OK;
+    const int64_t nvec = aligned(src, sizeof(TS) * V) && aligned(dst, sizeof(TD) * V) ? n / V : 0;
+    hipLaunchKernelGGL((map_vec_kernel<TS, TD, V, Op>), dim3(map_blocks(nvec, n, V)), dim3(256), 0, st, (const TS*)src, (TD*)dst, nvec, n, op);
     return hip_status(hipGetLastError());
 }
 
 template <class TX, class TY, class TC, int V, class Op, class Cp>
 __global__ __launch_bounds__(256) void axpy_vec_kernel(const TX* __restrict__ x, TY* __restrict__ y, TC* __restrict__ yc,
-                                                       int64_t nvec, Op op, Cp cp) {
+                                                       int64_t nvec, int64_t n, Op op, Cp cp) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nvec) return;
+    if (i >= nvec) {  // as in map_vec_kernel
+        const int64_t e = i - nvec + nvec * V;
+        if (e >= n) return;
+        const uint32_t r = op((uint32_t)x[e], (uint32_t)y[e]);
+        y[e] = (TY)r;
+        if (yc) yc[e] = (TC)cp((uint64_t)r);
+        return;
+    }
     const Pack<TX, V> xv = reinterpret_cast<const Pack<TX, V>*>(x)[i];
     Pack<TY, V> yv = reinterpret_cast<Pack<TY, V>*>(y)[i];
 #pragma unroll
@@ -108,16 +94,6 @@ __global__ __launch_bounds__(256) void axpy_vec_kernel(const TX* __restrict__ x,
     }
 }
 
-template <class TX, class TY, class TC, class Op, class Cp>
-__global__ __launch_bounds__(256) void axpy_scalar_kernel(const TX* __restrict__ x, TY* __restrict__ y, TC* __restrict__ yc,
-                                                          int64_t begin, int64_t n, Op op, Cp cp) {
-    const int64_t i = begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t r = op((uint32_t)x[i], (uint32_t)y[i]);
-    y[i] = (TY)r;
-    if (yc) yc[i] = (TC)cp((uint64_t)r);
-}
-
 template <class FX, class FY, class FC>
 int launch_axpy(hipStream_t st, uint32_t alpha, int64_t n, const void* x, void* y, void* yc) {
     typedef typename Storage<FX::N>::T TX;
@@ -129,21 +105,11 @@ int launch_axpy(hipStream_t st, uint32_t alpha, int64_t n, const void* x, void* 
     Axpy<FX, FY> op;
     op.alpha = alpha;
     PositToPosit<FY, FC> cp;
-    int64_t done = 0;
-    if (aligned(x, sizeof(TX) * V) && aligned(y, sizeof(TY) * V) && (!yc || aligned(yc, sizeof(TC) * V))) {
-        const int64_t nvec = n / V;
-        if (nvec > 0) {
-            hipLaunchKernelGGL((axpy_vec_kernel<TX, TY, TC, V, Axpy<FX, FY>, PositToPosit<FY, FC>>),
-                               dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st, (const TX*)x, (TY*)y, (TC*)yc, nvec, op, cp);
-            done = nvec * V;
-            if (hipGetLastError() != hipSuccess) return PNN_EHIP;  // stop at the first failed launch
-        }
-    }
-    if (done < n) {
-        const int64_t rest = n - done;
-        hipLaunchKernelGGL((axpy_scalar_kernel<TX, TY, TC, Axpy<FX, FY>, PositToPosit<FY, FC>>),
-                           dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, st, (const TX*)x, (TY*)y, (TC*)yc, done, n, op, cp);
-    }
+    if (n <= 0) return PNN_OK;
+    const bool ok = aligned(x, sizeof(TX) * V) && aligned(y, sizeof(TY) * V) && (!yc || aligned(yc, sizeof(TC) * V));
+    const int64_t nvec = ok ? n / V : 0;
+    hipLaunchKernelGGL((axpy_vec_kernel<TX, TY, TC, V, Axpy<FX, FY>, PositToPosit<FY, FC>>), dim3(map_blocks(nvec, n, V)), dim3(256), 0, st, (const TX*)x,
+                       (TY*)y, (TC*)yc, nvec, n, op, cp);
     return hip_status(hipGetLastError());
 }
 
@@ -241,16 +207,12 @@ int convert_from(hipStream_t st, int dst, int64_t n, const void* s, void* d) {
         return PNN_EINVAL;
     }
     if (FS::N == 16 && dst == PNN_POSIT8_0 && n >= NARROW_STEP_MIN && aligned(s, 16) && aligned(d, 8)) {
-        // step-table kernel on whole vectors of 8, the generic kernel on what is left
         const int64_t nvec = n / 8;
         int64_t blocks = (nvec + 255) / 256;
         const int64_t cap = (int64_t)compute_units() * 8;
         if (blocks > cap) blocks = cap;
-        hipLaunchKernelGGL((narrow_step_kernel<P16, P8>), dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)s, (uint8_t*)d, nvec);
-        if (hipGetLastError() != hipSuccess) return PNN_EHIP;
-        const int64_t done = nvec * 8;
-        if (done == n) return PNN_OK;
-        return launch_map<TS, uint8_t>(st, (const TS*)s + done, (uint8_t*)d + done, n - done, PositToPosit<FS, P8>());
+        hipLaunchKernelGGL((narrow_step_kernel<P16, P8>), dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)s, (uint8_t*)d, nvec, n);
+        return hip_status(hipGetLastError());
     }
     switch (dst) {
         case PNN_POSIT8_0: return launch_map<TS, uint8_t>(st, s, d, n, PositToPosit<FS, P8>());
@@ -325,9 +287,34 @@ inline MapRT make_map(int src, int dst) {
     return m;
 }
 
+// Formats outside Table 1.  Rounding and the narrowing copies of mixed-precision training with the formats as constants, 8-bit sources through
+// the table, the rest with formats known at run time.  13.4 M elements, us: posit(10,2) to (8,2) 36.9 with formats known at run time, 19.4 as constants; f32 to
+// (8,2) 32.9 and 15.9; (8,2) to (12,2) 36.9, through the table 8.5.
 inline int launch_map_rt(hipStream_t st, int src, int dst, int64_t n, const void* s, void* d) {
-    hipLaunchKernelGGL(map_rt_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, s, d, (int)elem_size(src), (int)elem_size(dst), n,
-                       make_map(src, dst));
+    if (src == PNN_F32) {
+        switch (dst) {
+            case PNN_POSIT8_1: return launch_map<uint32_t, uint8_t>(st, s, d, n, RoundF32<P8_1>());
+            case PNN_POSIT8_2: return launch_map<uint32_t, uint8_t>(st, s, d, n, RoundF32<P8_2>());
+            case PNN_POSIT10_1: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P10_1>());
+            case PNN_POSIT10_2: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P10_2>());
+            case PNN_POSIT12_1: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P12_1>());
+            case PNN_POSIT12_2: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P12_2>());
+        }
+    }
+    if (src == PNN_POSIT12_2 && dst == PNN_POSIT8_2) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P12_2, P8_2>());
+    if (src == PNN_POSIT10_2 && dst == PNN_POSIT8_2) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P10_2, P8_2>());
+    if (src == PNN_POSIT12_1 && dst == PNN_POSIT8_1) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P12_1, P8_1>());
+    if (src == PNN_POSIT10_1 && dst == PNN_POSIT8_1) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P10_1, P8_1>());
+    const MapRT op = make_map(src, dst);
+    if (elem_size(src) == 1) {
+        switch (elem_size(dst)) {
+            case 1: return launch_map_p8<uint8_t>(st, s, d, n, op);
+            case 2: return launch_map_p8<uint16_t>(st, s, d, n, op);
+            case 4: return launch_map_p8<uint32_t>(st, s, d, n, op);
+            default: return launch_map_p8<uint64_t>(st, s, d, n, op);
+        }
+    }
+    hipLaunchKernelGGL(map_rt_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, s, d, (int)elem_size(src), (int)elem_size(dst), n, op);
     return hip_status(hipGetLastError());
 }
 

@@ -214,9 +214,9 @@ struct alignas(sizeof(T) * V) Pack {
     T v[V];
 };
 
-// dst[i] = round_FD(src[i]) for posit<16,1> -> posit<8,0>; 8 elements per thread and step.
+// dst[i] = round_FD(src[i]) for posit<16,1> -> posit<8,0>; 8 elements per thread and step, the last n - 8 nvec by the first workgroup.
 template <class FS, class FD>
-__global__ __launch_bounds__(256) void narrow_step_kernel(const uint16_t* __restrict__ src, uint8_t* __restrict__ dst, int64_t nvec) {
+__global__ __launch_bounds__(256) void narrow_step_kernel(const uint16_t* __restrict__ src, uint8_t* __restrict__ dst, int64_t nvec, int64_t n) {
     __shared__ uint16_t tab[1024];
     for (int b = threadIdx.x; b < 1024; b += 256) tab[b] = (uint16_t)narrow_step_entry<FS, FD>((uint32_t)b);
     __syncthreads();
@@ -232,6 +232,8 @@ __global__ __launch_bounds__(256) void narrow_step_kernel(const uint16_t* __rest
         }
         reinterpret_cast<uint2*>(dst)[i] = make_uint2(o[0], o[1]);
     }
+    const int64_t e = nvec * 8 + threadIdx.x;
+    if (blockIdx.x == 0 && e < n) dst[e] = (uint8_t)narrow_step_apply(tab[src[e] >> 6], src[e]);
 }
 
 typedef short pnn_short2 __attribute__((ext_vector_type(2)));
