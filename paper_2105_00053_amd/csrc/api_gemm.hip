@@ -98,6 +98,15 @@ inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit
     }
 }
 
+// posit<32,2> below the tiles from which the digit planes and the LDS kernel serve: in one launch on the matrix cores, the window of bits taken by each
+// workgroup for itself.  Against the general kernel, us: 8 x 8 x 4 19.9 and 8.3, 64 x 64 x 256 215 and 9.6, 432 x 432 x 2048 803 and 95; operands
+// that span more than the window, 64 x 64 x 1024 220 and 90, x 2048 224 and 176, 16 x 16 x 4000 235 and 345 (N(0, 1): 55), hence the end of the
+// reduction; 432 x 432 x 16, three rounds of workgroups, 20.5 and 23.  Where the other two serve they are faster: 500 x 500 x 500 35 and 45.
+inline bool p32_direct_fits(int64_t M, int64_t N, int64_t K) {
+    const int64_t tiles = ((M + 15) / 16) * ((N + 15) / 16);
+    return K >= 1 && K <= 2048 && M <= 16384 && N <= 16384 && tiles < (K < 32 ? 512 : 768);
+}
+
 // Cut of the kernels that serve where the direct one does not.
 template <class F>
 GemmPlan prepared_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX) {
@@ -173,6 +182,10 @@ int gemm_dispatch(hipStream_t st, int fout, int transA, int transB, int64_t M, i
         const DirectPlan direct = direct_gemm_plan<F>(M, N, K, limit);
         if (direct.variant != DIRECT_NONE && (direct.ws_bytes == 0 || (ws && ws_bytes >= direct.ws_bytes)) && direct_extent_fits(transA, transB, M, N, K, lda, ldb, sizeof(T)))
             return hip_status(launch_direct_gemm<F>(st, direct, transA, transB, M, N, K, A, lda, B, ldb, bias, C, ldc, fout, ws));
+    }
+    if constexpr (F::N == 32) {
+        if (p32_direct_fits(M, N, K) && !bias && direct_extent_fits(transA, transB, M, N, K, lda, ldb, sizeof(T)))
+            return hip_status(launch_direct_p32(st, transA, transB, M, N, K, A, lda, B, ldb, C, ldc, fout));
     }
     const int* served = nullptr;  // on the device: non-zero when the digit kernels did the work
     if constexpr (is_dig<F>()) {

@@ -83,6 +83,10 @@ inline bool direct_extent_fits(int transA, int transB, int64_t M, int64_t N, int
     return a <= most / (lda > 0 ? lda : 1) && b <= most / (ldb > 0 ? ldb : 1);
 }
 
+// posit<32,2> without a bias
+hipError_t launch_direct_p32(hipStream_t st, int transA, int transB, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
+                             void* C, int64_t ldc, int fout);
+
 template <class F>
 hipError_t launch_direct_gemm(hipStream_t st, const DirectPlan& p, int transA, int transB, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
                               const void* B, int64_t ldb, const void* bias, void* C, int64_t ldc, int fout, void* workspace);

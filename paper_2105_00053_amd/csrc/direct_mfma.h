@@ -40,6 +40,13 @@ struct DirectFormat {
     static constexpr int NW = (NC + 3) / 4;        // 64-bit words of four sums
     static constexpr bool TABLE = F::N <= 12;      // digits looked up in LDS
     static constexpr int TW = ND == 3 ? 4 : ND;    // words of an entry
+    static constexpr int L = Arith<F>::L;          // limbs of an output
+};
+// posit<32,2>: the 62 bits that eight planes hold, from the lowest bit of the workgroup's operands up (direct_p32_kernel)
+template <>
+struct DirectFormat<P32> {
+    static constexpr int NP = 8, ND = 2, NC = 15, NW = 4, TW = 2, L = 5;
+    static constexpr bool TABLE = false;
 };
 
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -55,9 +62,9 @@ inline int direct_run(uint32_t y) {
 }
 #endif
 
-// The magnitude of a pattern (NaR: F::NAR) as an integer in units of minpos, lowest word first; zero and NaR: zero.
+// The magnitude of a pattern (NaR: F::NAR) as an integer in units of minpos 2^base, lowest word first; zero and NaR: zero.
 template <class F>
-PNN_HD void direct_magnitude(uint32_t mag, uint32_t (&m)[DirectFormat<F>::ND]) {
+PNN_HD void direct_magnitude(uint32_t mag, uint32_t (&m)[DirectFormat<F>::ND], int base = 0) {
     constexpr int ND = DirectFormat<F>::ND;
     const uint32_t y = mag << (33 - F::N);  // first regime bit in bit 31; NaR: nothing left
     const int c = (int)y >> 31;
@@ -66,7 +73,7 @@ PNN_HD void direct_magnitude(uint32_t mag, uint32_t (&m)[DirectFormat<F>::ND]) {
     const uint32_t sig = ((z << F::ES) & 0x7FFFFFFFu) | ((y < 1u ? y : 1u) << 31);
     const int e = F::ES ? (int)((z >> (31 - F::ES)) & ((1u << F::ES) - 1u)) : 0;
     const int k = (run ^ ~c) + 2 * c + 1;   // run - 1 for ones, -run for zeros
-    const int h = k * (1 << F::ES) + e + F::MAXS;  // where the leading bit belongs
+    const int h = k * (1 << F::ES) + e + F::MAXS - base;  // where the leading bit belongs
     if constexpr (ND == 1) {
         m[0] = sig >> ((31 - h) & 31);
     } else if constexpr (ND == 2) {
@@ -94,10 +101,10 @@ PNN_HD void direct_balance(const uint32_t (&m)[ND], uint32_t sg, uint32_t (&d)[N
 }
 
 template <class F>
-PNN_HD void direct_digits(uint32_t p, uint32_t (&d)[DirectFormat<F>::ND]) {
+PNN_HD void direct_digits(uint32_t p, uint32_t (&d)[DirectFormat<F>::ND], int base = 0) {
     const int s = (int)(p << (32 - F::N)) >> (32 - F::N);
     uint32_t m[DirectFormat<F>::ND];
-    direct_magnitude<F>((uint32_t)(s < 0 ? -s : s), m);
+    direct_magnitude<F>(s < 0 ? 0u - (uint32_t)s : (uint32_t)s, m, base);
     direct_balance(m, (uint32_t)(s >> 31), d);
 }
 
@@ -135,6 +142,7 @@ struct DirectMatrix {
     typedef uint32_t Row;
     __device__ __forceinline__ Row row(int r) const { return (uint32_t)(r < rows ? r : rows - 1) * s_r; }
     __device__ __forceinline__ const T* at(uint32_t bytes) const { return (const T*)((const char*)p + bytes); }
+    __device__ __forceinline__ T one(Row r, int k) const { return *at(r + (uint32_t)k * s_k); }
     __device__ __forceinline__ void fetch(Row r, int k0, int kend, DirectRaw<T>& raw) const {
         if (s_k == sizeof(T) && k0 + 16 <= kend) {
             __builtin_memcpy(raw.w, at(r + (uint32_t)k0 * (uint32_t)sizeof(T)), 16 * sizeof(T));  // any alignment
@@ -157,12 +165,13 @@ struct DirectFrag {
     typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
     dm_v4i pl[D::NP];
     // nar: whether a NaR was among the patterns, as is_nar() reads it
-    static constexpr uint32_t NO_NAR = F::N == 8 ? 0u : 0xFFFFFFFFu;
-    __device__ static __forceinline__ bool is_nar(uint32_t nar) { return F::N == 8 ? nar != 0 : (nar & 0xFFFFu) == 0 || nar >> 16 == 0; }
-    __device__ __forceinline__ void convert(const Raw& raw, const Entry* tab, uint32_t& nar) {
+    static constexpr uint32_t NO_NAR = F::N == 8 || F::N == 32 ? 0u : 0xFFFFFFFFu;
+    __device__ static __forceinline__ bool is_nar(uint32_t nar) { return F::N == 8 || F::N == 32 ? nar != 0 : (nar & 0xFFFFu) == 0 || nar >> 16 == 0; }
+    __device__ __forceinline__ void convert(const Raw& raw, const Entry* tab, uint32_t& nar, int base = 0) {
 #pragma unroll
         for (int i = 0; i < 16 / Raw::PER; ++i) {
             if constexpr (F::N == 8) nar |= nar_bytes(raw.w[i]);
+            else if constexpr (F::N == 32) nar |= raw.w[i] == F::NAR ? 1u : 0u;
             else nar = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, nar),
                                                                               __builtin_bit_cast(u16x2, (raw.w[i] & (F::MASK * 0x10001u)) ^ (F::NAR * 0x10001u))));
         }
@@ -183,7 +192,7 @@ struct DirectFrag {
                         for (int h = 0; h < D::ND; ++h) d[e][h] = v[h];
                     }
                 } else {
-                    direct_digits<F>(p, d[e]);
+                    direct_digits<F>(p, d[e], base);
                 }
             }
 #pragma unroll
@@ -264,9 +273,10 @@ struct DirectLds {
 // Outputs of a workgroup from the sums in LDS: combined, rounded and stored, or left for the merge of the slices.
 template <class F, class Out, int TR, int TC, int THREADS>
 __device__ __forceinline__ void direct_finish(const DirectLds<F, TR, TC>& s, const Out& out, int m0, int n0, int M, int N,
-                                              const typename Storage<F::N>::T* __restrict__ bias, void* __restrict__ C, int fout, const SplitWs& ws) {
+                                              const typename Storage<F::N>::T* __restrict__ bias, void* __restrict__ C, int fout, const SplitWs& ws, int at = 0) {
     typedef DirectFormat<F> D;
-    constexpr int OUTS = TR * TC, L = Arith<F>::L, RB = TC / 16;
+    constexpr int OUTS = TR * TC, L = D::L, RB = TC / 16;
+    const int qfrac = F::QFRAC - at;  // the sums count units of minpos^2 2^at
     const int t = threadIdx.x;
     const bool sliced = gridDim.z > 1;
     const int64_t z = blockIdx.z;
@@ -290,15 +300,17 @@ __device__ __forceinline__ void direct_finish(const DirectLds<F, TR, TC>& s, con
             continue;
         }
         bool nar = (s.rown[lr] | s.coln[lc]) != 0;
-        if (bias) {
-            const uint32_t bp = bias[n];
-            if (bp == F::NAR) nar = true;
-            else Arith<F>::add_value(q, Arith<F>::stage(bp));
+        if constexpr (F::N <= 16) {
+            if (bias) {
+                const uint32_t bp = bias[n];
+                if (bp == F::NAR) nar = true;
+                else Arith<F>::add_value(q, Arith<F>::stage(bp));
+            }
         }
-        const uint32_t v = fo.n <= 16 ? dig_round_limbs<L, false>(q, F::QFRAC, fo) : dig_round_limbs<L, true>(q, F::QFRAC, fo);
-        int64_t at;
-        void* dst = merge_dest(out, C, m, n, at);
-        dig_store_pattern(dst, at, fo.n, nar ? fo.nar() : v);
+        const uint32_t v = fo.n <= 16 ? dig_round_limbs<L, false>(q, qfrac, fo) : dig_round_limbs<L, true>(q, qfrac, fo);
+        int64_t index;
+        void* dst = merge_dest(out, C, m, n, index);
+        dig_store_pattern(dst, index, fo.n, nar ? fo.nar() : v);
     }
     if (sliced) {
         // as in quire_gemm_kernel: the first tile column stores the row flags, the first tile row the column flags, all of them
@@ -413,6 +425,129 @@ __global__ __launch_bounds__(256 * KG) void direct_shared_kernel(OpA opa, OpB op
     lds.add(acc, f, lane);
     __syncthreads();
     direct_finish<F, Out, TR, TC, THREADS>(lds, out, m0, n0, M, N, bias, C, fout, ws);
+}
+
+// posit<32,2>, 16 x 16 outputs, eight waves that share the reduction.  Which 62 bits of the format's 241 the planes hold is decided
+// by the workgroup from its own rows and columns: a first pass over them takes the smallest and the largest magnitude (the weight of a
+// pattern's last bit never falls when the magnitude grows).  Rows or columns that span more go to 512-bit quires in LDS as in
+// p32_lds_gemm_kernel, two threads to an output.  N(0, 1), us a call with the general kernel and with this one: 64 x 128 x 400
+// 333 and 12, 79 x 1024 x 96 85 and 16.4, 64 x 192 x 1248 269 and 21; with 2 % of the patterns from the whole range 329 and 40, 86 and 25, 271 and 110.
+template <class Op>
+__global__ __launch_bounds__(512) void direct_p32_kernel(Op opa, Op opb, int M, int N, int K, void* __restrict__ C, int64_t ldc, int fout, int tiles_n) {
+    typedef P32 F;
+    typedef DirectFormat<F> D;
+    typedef Arith<F> AR;
+    constexpr int KG = 8, THREADS = 64 * KG, T = 16, LIMBS = 18;
+    __shared__ DirectLds<F, T, T> lds;
+    __shared__ unsigned long long quire[LIMBS][T * T];
+    __shared__ AR::Elem stage[2][T][T];
+    __shared__ uint32_t low[2], high[2];  // smallest magnitude minus one (all ones: none), largest
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int m0 = (int)(blockIdx.x / (unsigned)tiles_n) * T, n0 = (int)(blockIdx.x % (unsigned)tiles_n) * T;
+    const int nkb = (K + 63) / 64;
+    const typename Op::Row ra = opa.row(m0 + (lane & 15)), rb = opb.row(n0 + (lane & 15));
+    lds.template clear<THREADS>(t);
+    if (t < 2) {
+        low[t] = 0xFFFFFFFFu;
+        high[t] = 0;
+    }
+    __syncthreads();
+    uint32_t na = 0, nb = 0, lo[2] = {0xFFFFFFFFu, 0xFFFFFFFFu}, hi[2] = {0u, 0u};
+    auto scan = [&](const DirectRaw<uint32_t>& raw, uint32_t& l, uint32_t& h) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t p = raw.w[i], m = (int)p < 0 ? 0u - p : p;  // NaR stays
+            l = m - 1u < l ? m - 1u : l;
+            h = (m & 0x7FFFFFFFu) > h ? (m & 0x7FFFFFFFu) : h;
+        }
+    };
+    for (int kb = w; kb < nkb; kb += KG) {
+        const int k0 = kb * 64 + 16 * (lane >> 4);
+        DirectRaw<uint32_t> fa, fb;
+        opb.fetch(rb, k0, K, fb);
+        opa.fetch(ra, k0, K, fa);
+        scan(fa, lo[0], hi[0]);
+        scan(fb, lo[1], hi[1]);
+    }
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            const uint32_t l = (uint32_t)__shfl_xor((int)lo[o], d), h = (uint32_t)__shfl_xor((int)hi[o], d);
+            lo[o] = l < lo[o] ? l : lo[o];
+            hi[o] = h > hi[o] ? h : hi[o];
+        }
+        if (lane == 0) {
+            atomicMin(&low[o], lo[o]);
+            atomicMax(&high[o], hi[o]);
+        }
+    }
+    __syncthreads();
+    int base[2];
+    bool fits = true;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        const uint32_t h = __builtin_amdgcn_readfirstlane(high[o]), l = __builtin_amdgcn_readfirstlane(low[o]) + 1u;
+        base[o] = h ? dig_low_bit<F>(l) : 0;
+        fits = fits && (h == 0 || dig_high_bit<F>(h) + 1 - base[o] <= 62);
+    }
+    if (fits) {
+        dm_v4i acc[D::NC];
+#pragma unroll
+        for (int s = 0; s < D::NC; ++s) acc[s] = dm_v4i{0, 0, 0, 0};
+        for (int kb = w; kb < nkb; kb += KG) {
+            const int k0 = kb * 64 + 16 * (lane >> 4);
+            DirectRaw<uint32_t> fa, fb;
+            opb.fetch(rb, k0, K, fb);
+            opa.fetch(ra, k0, K, fa);
+            DirectFrag<F> a, b;
+            b.convert(fb, lds.tab, nb, base[1]);
+            a.convert(fa, lds.tab, na, base[0]);
+            direct_mma<F>(a.pl, b.pl, acc);
+        }
+        if (w < nkb) {
+            if (na) lds.rown[lane & 15] = 1;
+            if (nb) lds.coln[lane & 15] = 1;
+            lds.add(acc, 0, lane);
+        }
+        __syncthreads();
+        direct_finish<F, RowMajorOut, T, T, THREADS>(lds, RowMajorOut{ldc}, m0, n0, M, N, nullptr, C, fout, SplitWs{nullptr, nullptr, nullptr}, base[0] + base[1]);
+        return;
+    }
+    for (int i = t; i < LIMBS * T * T; i += THREADS) (&quire[0][0])[i] = 0;
+    const int o = t & 255, half = t >> 8, r = o >> 4, c = o & 15;  // output (r, c); staging: element (k = r, row = c) of operand `half`
+    const Op& op = half ? opb : opa;
+    const typename Op::Row row = op.row((half ? n0 : m0) + c);
+    for (int k0 = 0; k0 < K; k0 += T) {
+        const uint32_t p = k0 + r < K ? op.one(row, k0 + r) : 0u;
+        __syncthreads();  // the slice before has been read; the quires are clear
+        if (p == F::NAR) (half ? lds.coln : lds.rown)[c] = 1;
+        stage[half][r][c] = AR::stage(p);
+        __syncthreads();
+#pragma unroll 2
+        for (int kk = half; kk < T; kk += 2) {
+            const AR::Elem a = stage[0][kk][r], b = stage[1][kk][c];
+            const int64_t P = (int64_t)(int32_t)a.x * (int64_t)(int32_t)b.x;
+            const int s = (int)(a.y + b.y), idx = s >> 5, off = s & 31;
+            const uint64_t word = (uint64_t)P << off;
+            const int64_t w2 = (P >> 32) >> (32 - off);
+            unsigned long long* at = &quire[idx][o];
+            __hip_atomic_fetch_add(at, (unsigned long long)(uint32_t)word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_add(at + T * T, (unsigned long long)(uint32_t)(word >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_add(at + 2 * T * T, (unsigned long long)w2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    __syncthreads();
+    if (half || m0 + r >= M || n0 + c >= N) return;
+    uint32_t limbs[16];
+    int64_t carry = 0;
+#pragma unroll
+    for (int l = 0; l < 16; ++l) {
+        const int64_t v = (int64_t)quire[l][o] + carry;
+        limbs[l] = (uint32_t)v;
+        carry = v >> 32;
+    }
+    round_store<QuireAccum<F>, 16>(limbs, (lds.rown[r] | lds.coln[c]) != 0, fout, C, (int64_t)(m0 + r) * ldc + n0 + c);
 }
 
 // ---- host side ----

@@ -104,3 +104,23 @@ def test_operand_beyond_two_gigabytes():
     assert L.posit_gemm(ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), 0, 0, 0, 0, M, N, K, ptr(Ad), ld, ptr(Bd), N, None, ptr(C), N, None, 0) == 0
     want, _ = fast.gemm(A, B, "p8", "p8")
     assert len(mismatches(to_np(C, "p8"), want)) == 0
+
+
+@pytest.mark.parametrize("order", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("size", [(1, 1, 1), (16, 16, 64), (17, 33, 65), (50, 47, 511), (15, 100, 513), (33, 20, 2048), (300, 500, 40)])
+@pytest.mark.parametrize("values", ["window", "range", "zero"])
+def test_p32(values, size, order):
+    """posit<32,2>: tiles whose operands the planes hold, tiles that span more (both kinds in one call with "range"), and zeros."""
+    rng = np.random.default_rng(sum(size))
+    M, N, K = size
+    ta, tb = map(bool, order)
+    A, B = (fast.round_from_float(rng.standard_normal(s).astype(np.float32), "p32") if values != "zero" else np.zeros(s, np.uint32)
+            for s in ((K, M) if ta else (M, K), (N, K) if tb else (K, N)))
+    if values == "range":
+        A[(slice(None), 0) if ta else 0] = rand_patterns(rng, (K,), "p32", allow_nar=False)
+        A[-1, -1], B[0, 0] = 1, 0x7FFFFFFF
+        B[-1, -1] = 0x80000000
+    for fout in ("p32", "p16", "p8"):
+        want, _ = fast.gemm(A, B, "p32", fout, trans_a=ta, trans_b=tb)
+        got = to_np(pn.posit_gemm(to_dev(A), to_dev(B), "p32", fout, trans_a=ta, trans_b=tb), fout)
+        assert len(mismatches(got, want)) == 0, fout
