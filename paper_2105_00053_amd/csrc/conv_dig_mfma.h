@@ -279,40 +279,51 @@ __device__ __forceinline__ void dig_store_rows_bias(int first, int rows, const D
     }
 }
 
-// Four waves as WY x (4 / WY), one block of 32 x 32 outputs each (rows: output channels, columns: positions).  WY = 1 (32 x
-// 128 outputs) serves layers of at most 32 output channels.  A ring of ST k blocks as in dig_gemm_kernel; operand registers
-// are read a step ahead.  A convolution's reduction is short, so prologue and rounding weigh as much as the matrix
-// instructions: four planes are all multiplied, and outputs of at most 16 bits are rounded through binary64 in registers
-// and stored from there (128 images of 32 channels at 32 x 32, posit(8,2), 3 x 3 to 32 channels: 31 us, with integers of 96
-// bits through LDS 36).  The kernel of eight planes is bound by the matrix pipes, so without NaR it multiplies only the
-// planes that hold digits: weights over most of the range of posit(8,2) 46 us, all 8 x 8 pairs 61.
-template <int NP, int WY, int ST>
-__device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
-    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
-    constexpr int WX = 4 / WY, NB = WX;          // column blocks
-    constexpr int NA = WY;                        // row blocks
+// Four waves: 32 x 64 outputs (WY = 1: layers of at most 32 output channels) or 64 x 32 (rows: output channels, columns: positions).
+template <int WY>
+struct DigConvShape {
+    static constexpr int NA = WY, NB = 2 / WY;  // row and column blocks of 32
+    static constexpr int TR = 32 * NA, TC = 32 * NB;
+};
+
+// A wave owns 16 x 32 outputs, two blocks of v_mfma_i32_16x16x64_i8 whose 2 NP - 1 sums take 56 registers for four planes and 120 for
+// eight, so that three and two workgroups share a CU (with blocks of 32 x 32 outputs two and one, and twice the outputs in a workgroup:
+// a last round of workgroups twice as long).  A step takes a pair of k blocks of 32: a lane's 16 reduction indices come from block l / 32 of it.
+// Four planes: a ring of two pairs, the next one copied while a pair is multiplied.  Eight planes: room for one pair, whose 24 operand
+// quads go to registers before the next pair's copies start; the other workgroup multiplies meanwhile.
+// Prologue and rounding weigh as much as the matrix instructions of a short reduction: four planes are all multiplied, and outputs of at most 16 bits
+// are rounded through binary64 in registers and stored from there (128 images of 32 channels at 32 x 32, posit(8,2), 3 x 3 to 32 channels: 31 us, with
+// integers of 96 bits through LDS 36).  Eight planes without NaR: only the planes that hold digits (weights over most of the range of posit(8,2) 46 us, all 8 x 8
+// pairs 61).  us a call, 32 x 32 -> now: posit<16,1> backward-data of 100 images of 30 channels at 27 x 27 to 45, 3 x 3, 54.9 and 45.9; forward of 46 of 48 at
+// 22 x 22 to 39, 5 x 5, stride 2, 49.0 and 34.0.  An odd last block (dig_single_mma; beside a block of
+// zeros before): posit(12,1) backward-data of 10 of 48 at 43 x 43 to 24, 3 x 3, 25.0 and 23.6.
+template <int NP, int WY>
+__device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int tn) {
+    typedef DigConvShape<WY> Sh;
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), NA = Sh::NA, NB = Sh::NB, TR = Sh::TR, TC = Sh::TC, WAVES = 4, THREADS = 256;
+    constexpr int PAIRS = NP <= 4 ? 2 : 1;        // held in LDS
     constexpr int RPB = (NA + NB) * NP;           // runs of 1 KB per k block
-    constexpr int TR = 32 * WY, TC = 32 * WX;
-    static_assert(NP % 4 == 0, "copies spread evenly over the waves");
-    constexpr int ARUNS = NA * NP / 4;            // weight runs copied by a wave
-    constexpr int GRUNS = NB * NP / 4;            // gathered runs: planes of one column block
-    constexpr int LOADS = ARUNS + GRUNS;
-    constexpr int RING = ST * RPB * 64, KTAB = DCM_MAXK16 / 2;  // words of 16 bytes
-    // one LDS object (see dig_gemm_kernel): ring, (tap, channel group) table, NaR flags, bias addends
-    __shared__ uint4 lds[RING + KTAB + (TR + TC) / 4 + TR];
+    static_assert((NA * NP) % WAVES == 0 && (NB * NP) % WAVES == 0 && WAVES % NB == 0, "copies spread evenly over the waves");
+    constexpr int ARUNS = NA * NP / WAVES;        // weight runs copied by a wave
+    constexpr int GRUNS = NB * NP / WAVES;        // gathered runs: planes of one column block
+    constexpr int RING = 2 * PAIRS * RPB * 64, KTAB = DCM_MAXK16 / 2;  // words of 16 bytes
+    // one LDS object (see dig_gemm_kernel): the ring and the (tap, channel group) table; 52 KB, three workgroups to a CU.  Behind the
+    // loop the outputs' integers, the bias addends and the NaR flags take the ring.
+    __shared__ uint4 lds[RING + KTAB];
     uint4* const stage = lds;
     int2* const ktab = reinterpret_cast<int2*>(lds + RING);
-    uint32_t* const rowv = reinterpret_cast<uint32_t*>(lds + RING + KTAB);
+    constexpr int VALS = L * TR * TC / 4;
+    uint4* const badd = stage + VALS;
+    uint32_t* const rowv = reinterpret_cast<uint32_t*>(badd + TR);
     uint32_t* const colv = rowv + TR;
-    uint4* const badd = lds + RING + KTAB + (TR + TC) / 4;
-    static_assert(L * TR * TC * 4 <= RING * 16, "the outputs' integers pass through the ring");
+    static_assert(VALS + TR + (TR + TC) / 4 <= RING, "room in the ring");
 
     const int t = threadIdx.x;
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wy = WY == 2 ? w >> 1 : 0, wx = WY == 2 ? (w & 1) : w;
-    const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
+    const int wr = w % (2 * NA), wc = w / (2 * NA);  // block of 16 rows, block of 32 columns
+    const int pairs = (a.KB + 1) / 2;
 
-    for (int k = t; k < 2 * a.KB; k += 256) {
+    for (int k = t; k < 4 * pairs; k += THREADS) {
         int2 e = make_int2(0, 0x7FFF);  // beyond the reduction: a row offset no pixel has
         if (k < a.K16) {
             const int tap = k / a.Cg, cg = k - tap * a.Cg;
@@ -325,11 +336,11 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
     }
 
     // weights: wave w copies ARUNS of the k block's NA NP runs, wave-uniform addresses
-    const uint4* asrc = a.Ad + ((int64_t)tm * NA * NP + w * ARUNS) * 64 + lane;
+    const uint4* const asrc = a.Ad + ((int64_t)tm * NA * NP + w * ARUNS) * 64 + lane;
     const int64_t a_kb = (int64_t)a.RBA * NP * 64;
-    // gathered tensor: wave w takes GRUNS planes of column block w / (4 / NB); lane l of a copy serves column l % 32 of the
+    // gathered tensor: wave w takes GRUNS planes of column block w / (WAVES / NB); lane l of a copy serves column l % 32 of the
     // block and the 16 reduction indices of half l / 32
-    constexpr int WPB = 4 / NB;  // waves per column block
+    constexpr int WPB = WAVES / NB;  // waves per column block
     const int cb = w / WPB, pl0 = (w % WPB) * GRUNS;
     const int hw_o = a.HO * a.WO;
     int oh = -40000, ow = 0, base = 0;  // beyond the positions: no tap brings this into the tensor
@@ -345,143 +356,139 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
     }
     const uint4* const actq = a.act + pl0;
     const uint4* const zeroq = a.zero;
-    auto issue = [&](int kb) {
-        uint4* buf = stage + (kb % ST) * (RPB * 64);
+    auto issue = [&](int p) {  // the two k blocks of pair p, or the last one
+        const uint4* src[2];
 #pragma unroll
-        for (int c = 0; c < ARUNS; ++c)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64),
-                                             (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
-        asrc += a_kb;
-        int2 e = ktab[kb * 2 + (lane >> 5)];
-        // (Both halves in one read: left to itself the compiler reads the offset only where the row is inside, behind a wait of its
-        // own; posit<16,1>, 77 images of 64 channels at 37 x 37, 3 x 3 to 20, forward 76.6 us and 74.5, 63 of 80 at 18 x 18, 5 x 5 to 55,
-        // backward-data 101.9 and 95.5.)
-        asm("" : "+v"(e.x), "+v"(e.y));
-        const int dh = (int)(short)(e.y & 0xFFFF), dw = e.y >> 16;
-        const int ih = oh + dh, iw = ow + dw;
-        const bool inside = ((unsigned)ih < (unsigned)a.HI) & ((unsigned)iw < (unsigned)a.WI);
-        const uint4* s = inside ? actq + (base + e.x) : zeroq;
+        for (int h = 0; h < 2; ++h) {
+            int2 e = ktab[p * 4 + 2 * h + (lane >> 5)];
+            // (Both halves in one read: left to itself the compiler reads the offset only where the row is inside, behind a wait of its
+            // own; posit<16,1>, 77 images of 64 channels at 37 x 37, 3 x 3 to 20, forward 76.6 us and 74.5, 63 of 80 at 18 x 18, 5 x 5 to 55,
+            // backward-data 101.9 and 95.5.)
+            asm("" : "+v"(e.x), "+v"(e.y));
+            const int dh = (int)(short)(e.y & 0xFFFF), dw = e.y >> 16;
+            const int ih = oh + dh, iw = ow + dw;
+            const bool inside = ((unsigned)ih < (unsigned)a.HI) & ((unsigned)iw < (unsigned)a.WI);
+            src[h] = inside ? actq + (base + e.x) : zeroq;
+        }
 #pragma unroll
-        for (int c = 0; c < GRUNS; ++c)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + c),
-                                             (__attribute__((address_space(3))) void*)(buf + (NA * NP + cb * NP + pl0 + c) * 64), 16, 0, 0);
+        for (int h = 0; h < 2; ++h) {
+            const int kb = 2 * p + h;
+            if (kb >= a.KB) break;
+            uint4* buf = stage + (kb & (2 * PAIRS - 1)) * (RPB * 64);
+            const uint4* as = asrc + (int64_t)kb * a_kb;
+#pragma unroll
+            for (int c = 0; c < ARUNS; ++c)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(as + c * 64),
+                                                 (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
+#pragma unroll
+            for (int c = 0; c < GRUNS; ++c)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[h] + c),
+                                                 (__attribute__((address_space(3))) void*)(buf + (NA * NP + cb * NP + pl0 + c) * 64), 16, 0, 0);
+        }
     };
 
     const int a_nar = __builtin_amdgcn_readfirstlane(a.info->nar[1]), b_nar = __builtin_amdgcn_readfirstlane(a.info->nar[0]);
     const int at = __builtin_amdgcn_readfirstlane(a.info->base[0] + a.info->base[1]);
     const bool by_f64 = NP <= 4 && a.fout.n <= 16;
     __syncthreads();  // ktab
-#pragma unroll
-    for (int k = 0; k < ST - 1; ++k)
-        if (k < a.KB) issue(k);
-    // bias addends and row flags while the first blocks come in
-    if (t < TR) {
-        uint32_t nar = 0;
-        uint4 add = make_uint4(0, 0, 0, 0);
-        const int m = tm * TR + t;
-        if (a.bias && m < a.MO) {
-            const uint32_t bp = dig_load_pattern(a.bias, m, a.fin.n);
-            nar = bp == a.fin.nar() ? 1u : 0u;
-            if (by_f64) {
-                const double v = nar ? 0.0 : dig_f64_of_pattern(bp, a.fin, 2 * a.fin.maxs() - at);
-                add = make_uint4(f64_lo(v), f64_hi(v), 0u, 0u);
-            } else {
-                const unsigned __int128 v = (unsigned __int128)dig_bias_value(bp, a.fin);
-                add = make_uint4((uint32_t)v, (uint32_t)(v >> 32), (uint32_t)(v >> 64), (uint32_t)(v >> 96));
-            }
+    issue(0);
+    // the bias while the first blocks come in
+    uint32_t bias_nar = 0;
+    uint4 bias_add = make_uint4(0, 0, 0, 0);
+    if (a.bias && t < TR && tm * TR + t < a.MO) {
+        const uint32_t bp = dig_load_pattern(a.bias, tm * TR + t, a.fin.n);
+        bias_nar = bp == a.fin.nar() ? 1u : 0u;
+        if (by_f64) {
+            const double v = bias_nar ? 0.0 : dig_f64_of_pattern(bp, a.fin, 2 * a.fin.maxs() - at);
+            bias_add = make_uint4(f64_lo(v), f64_hi(v), 0u, 0u);
+        } else {
+            const unsigned __int128 v = (unsigned __int128)dig_bias_value(bp, a.fin);
+            bias_add = make_uint4((uint32_t)v, (uint32_t)(v >> 32), (uint32_t)(v >> 64), (uint32_t)(v >> 96));
         }
-        rowv[t] = nar;
-        badd[t] = add;
     }
 
-    pm_v16i acc[NC];
+    dig_v4i acc[2][NC];
 #pragma unroll
-    for (int s = 0; s < NC; ++s)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[s][r] = 0;
-    uint32_t row_nar = 0, col_nar = 0;
-    const uint4* const sa0 = stage + wy * NP * 64 + lane;
-    const uint4* const sb0 = stage + (NA + wx) * NP * 64 + lane;
-    DigFrag<NP> f0, f1;
-    auto markers = [&](const DigFrag<NP>& f) {
-        if (a_nar) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) row_nar |= pm_marker_bits((uint32_t)f.a[NP - 1][i]);
-        }
-        if (b_nar) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) col_nar |= pm_marker_bits((uint32_t)f.b[NP - 1][i]);
+        for (int s = 0; s < NC; ++s) acc[h][s] = dig_v4i{0, 0, 0, 0};
+    uint32_t row_nar = 0, col_nar[2] = {0, 0};
+    // lane l of a fragment: row or column l % 16 of its block, reduction indices 16 ((l / 16) % 2) .. of k block l / 32 of the pair
+    const uint4* const lane0 = stage + (lane >> 5) * (RPB * 64) + ((lane >> 4) & 1) * 32 + (lane & 15);
+    const uint4* const sa0 = lane0 + (wr >> 1) * NP * 64 + (wr & 1) * 16;
+    const uint4* const sb0 = lane0 + (NA + wc) * NP * 64;
+    auto loop = [&](auto ta, auto tb) {
+        constexpr int TA = ta, TB = tb;
+        for (int p = 0; p < a.KB / 2; ++p) {
+            // This wave's copies of pair p have landed; behind the barrier everyone's have, and everyone's reads of the pair before have
+            // been consumed, so its half of the ring takes the next.
+            __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+            pcm_ring_barrier();
+            if (PAIRS == 2 && p + 1 < pairs) issue(p + 1);
+            const int half = (p & (PAIRS - 1)) * (2 * RPB * 64);
+            DigPair<NP> f;
+            f.template load<0, TA, TB>(sa0 + half, sb0 + half);
+            if (PAIRS == 1 && p + 1 < pairs) {
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): read; behind the barrier everyone has
+                pcm_ring_barrier();
+                issue(p + 1);
+            }
+            if (TA == NP && TB == NP) dig_pair_markers<NP>(a_nar, b_nar, f, row_nar, col_nar);
+            dig_pair_mma<NP, 0, TA, 0, TB>(f, acc);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-    __syncthreads();
     if constexpr (NP <= 4) {
-        // one step: block kb is in cur; see dig_gemm_kernel for what the waits and the barrier stand for
-        auto step = [&](int kb, const DigFrag<NP>& cur, DigFrag<NP>& next) {
-            if (kb + ST - 2 < a.KB) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 3) * LOADS));
-            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-            pcm_ring_barrier();
-            if (kb + ST - 1 < a.KB) issue(kb + ST - 1);
-            const int nb = ((kb + 1) % ST) * (RPB * 64);
-            next.template load<0>(sa0 + nb, sb0 + nb);
-            markers(cur);
-            dig_mma<NP, 0, NP, 0, NP>(cur, acc);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        f0.template load<0>(sa0, sb0);
-        for (int kb = 0; kb < a.KB; kb += 2) {
-            step(kb, f0, f1);
-            if (kb + 1 < a.KB) step(kb + 1, f1, f0);
-        }
-    } else {  // one set of operand registers, read in their own step; the planes that hold anything
-        auto loop = [&](auto ta, auto tb) {
-            constexpr int TA = ta, TB = tb;
-            for (int kb = 0; kb < a.KB; ++kb) {
-                if (kb + ST - 2 < a.KB) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
-                else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-                pcm_ring_barrier();
-                if (kb + ST - 1 < a.KB) issue(kb + ST - 1);
-                const int nb = (kb % ST) * (RPB * 64);
-                f0.template load<0, TA, TB>(sa0 + nb, sb0 + nb);
-                if constexpr (TA == NP) markers(f0);
-                dig_mma<NP, 0, TA, 0, TB>(f0, acc);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
+        loop(dig_int<NP>(), dig_int<NP>());
+    } else {  // the planes that hold anything
         const int ua = __builtin_amdgcn_readfirstlane(a.info->used[1]), ub = __builtin_amdgcn_readfirstlane(a.info->used[0]);
         dig_for_planes<NP>(a_nar || b_nar ? NP : ua, ub, loop);
     }
-    __syncthreads();  // the last block is read: the ring is free
+    if (a.KB & 1) {
+        __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+        pcm_ring_barrier();
+        const int at = ((pairs - 1) & (PAIRS - 1)) * (2 * RPB * 64) - (lane >> 5) * (RPB * 64);
+        dig_single_mma<NP>(sa0 + at, sb0 + at, lane, a_nar, b_nar, row_nar, col_nar, acc);
+    }
+    __syncthreads();  // the last pair is read: the ring is free
+    if (t < TR) {
+        rowv[t] = bias_nar;
+        badd[t] = bias_add;
+    }
+    if (a_nar) __syncthreads();  // the flags of the rows come on top
 
     uint32_t* const vals = reinterpret_cast<uint32_t*>(stage);
-    row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
-    col_nar = (col_nar | (uint32_t)__shfl_xor((int)col_nar, 32)) & 0x80808080u;
-    if (lane < 32) {
-        if (wx == 0 && row_nar) rowv[wy * 32 + lane] = 1u;  // every wave of a row block saw the same rows
-        if (wy == 0) colv[wx * 32 + lane] = col_nar;
+    row_nar = dig_pair_across(row_nar);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) col_nar[h] = dig_pair_across(col_nar[h]);
+    if (lane < 16) {
+        if (wc == 0 && row_nar) rowv[wr * 16 + lane] = 1u;  // every wave of a row block saw the same rows
+        if (wr == 0) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) colv[wc * 32 + 16 * h + lane] = col_nar[h];
+        }
     }
     if constexpr (NP <= 4) {
-        if (by_f64) {  // rounded and stored where the matrix instruction leaves them: 16 rows of one position per lane
+        if (by_f64) {  // rounded and stored where the matrix instruction leaves them: four rows of one position per lane and block
             __syncthreads();
-            const int n = tn * TC + wx * 32 + (lane & 31);
-            if (n >= a.P) return;
-            const int img = n / hw_o, rem = n - img * hw_o;
-            const int64_t o = ((int64_t)img * a.MO + tm * TR) * hw_o + rem;
-            const int rows = a.MO - tm * TR;
+            const int rows = a.MO - tm * TR, lr0 = wr * 16 + 4 * (lane >> 4);
             const DigF64Round round(a.fout, 2 * a.fin.maxs() - at);
-            const uint32_t cnar = col_nar;
             const uint32_t nar = a.fout.nar();
+            const uint4 fl = *reinterpret_cast<const uint4*>(rowv + lr0);
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const int lr0 = wy * 32 + 8 * rq + 4 * (lane >> 5);
-                const uint4 fl = *reinterpret_cast<const uint4*>(rowv + lr0);
-                const uint32_t flag[4] = {fl.x | cnar, fl.y | cnar, fl.z | cnar, fl.w | cnar};
+            for (int h = 0; h < 2; ++h) {
+                const int n = tn * TC + wc * 32 + 16 * h + (lane & 15);
+                if (n >= a.P) continue;
+                const int img = n / hw_o, rem = n - img * hw_o;
+                const int64_t o = ((int64_t)img * a.MO + tm * TR) * hw_o + rem;
+                const uint32_t flag[4] = {fl.x | col_nar[h], fl.y | col_nar[h], fl.z | col_nar[h], fl.w | col_nar[h]};
                 double s[4], e[4];
                 uint32_t v[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     double hi, lo;
-                    DigF64<NP>::parts(acc, 4 * rq + u, hi, lo);
+                    DigF64<NP>::parts(acc[h], u, hi, lo);
                     dig_two_sum(hi, lo, s[u], e[u]);
                 }
                 if (a.bias) {
@@ -507,17 +514,19 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
         }
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int lr = wy * 32 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
-        uint32_t q[L];
-        dig_combine<NP>(acc, r, q);
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int l = 0; l < L; ++l) vals[l * (TR * TC) + lr * TC + wx * 32 + (lane & 31)] = q[l];
-    }
+        for (int r = 0; r < 4; ++r) {
+            const int lr = wr * 16 + 4 * (lane >> 4) + r;
+            uint32_t q[L];
+            dig_combine<NP>(acc[h], r, q);
+#pragma unroll
+            for (int l = 0; l < L; ++l) vals[l * (TR * TC) + lr * TC + wc * 32 + 16 * h + (lane & 15)] = q[l];
+        }
     __syncthreads();
-    // a wave: 64 consecutive positions, every (4 / (TC / 64))-th row
-    constexpr int CH = TC / 64, STEP = 4 / CH;
-    const int col = (w % CH) * 64 + lane, first = w / CH;
+    // neighbouring threads: neighbouring positions, every STEP-th row
+    constexpr int STEP = THREADS / TC;
+    const int col = t % TC, first = t / TC;
     const int n = tn * TC + col;
     if (n >= a.P) return;
     const int rows = a.MO - tm * TR < TR ? a.MO - tm * TR : TR;
@@ -529,10 +538,11 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
     rd.fout = a.fout;
     rd.at = at;
     auto value = [&](int lr, uint32_t (&q)[L]) {
+        lr = lr < TR ? lr : TR - 1;  // asked for beyond the rows, not stored
 #pragma unroll
         for (int l = 0; l < L; ++l) q[l] = vals[l * (TR * TC) + lr * TC + col];
     };
-    auto is_nar = [&](int lr) { return (cnar | rowv[lr]) != 0; };
+    auto is_nar = [&](int lr) { return (cnar | rowv[lr < TR ? lr : TR - 1]) != 0; };
     if (a.bias) {
         if (rd.fout.n <= 8) dig_store_rows_bias<L, uint8_t, STEP>(first, rows, rd, (uint8_t*)a.out + o, hw_o, badd, value, is_nar);
         else if (rd.fout.n <= 16) dig_store_rows_bias<L, uint16_t, STEP>(first, rows, rd, (uint16_t*)a.out + o, hw_o, badd, value, is_nar);
@@ -547,20 +557,26 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a) {
 // The last launch of a backward-data call also marks what NaR weights reach, tile by tile: behind its own work, or, if another
 // launch did that, right away (100 images of 30 channels at 27 x 27 to 45, posit<16,1>: 57.6 us with a launch of its own, 56.6 so;
 // the posit<8,0> kernel, which has no spare launch, lost 1 to 4 % on large layers by it).
-template <int NP, int WY, int ST>
-__global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_kernel(DigConvArgs a) {
+template <int NP, int WY>
+__global__ __launch_bounds__(256, (NP <= 4 ? 3 : 2)) void dig_conv_kernel(DigConvArgs a) {
+    typedef DigConvShape<WY> Sh;
     const bool mark = a.nar.w && __builtin_amdgcn_readfirstlane(a.info->nar[1]);
-    if (__builtin_amdgcn_readfirstlane(a.info->np) == a.np) dig_conv_tile<NP, WY, ST>(a);
-    if (mark) bwd_data_nar_tile<32 * WY, 32 * (4 / WY)>(a.nar, a.out, (int)(blockIdx.x % a.tiles_m) * 32 * WY, (int)(blockIdx.x / a.tiles_m) * 32 * (4 / WY));
+    // a position's row tiles and the positions that share its taps on one XCD; nothing is shared by a single row of 1 x 1 tiles
+    const int tile = a.tiles_m > 1 || a.K16 > a.Cg ? dig_xcd_order((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x, tm = tile % a.tiles_m, tn = tile / a.tiles_m;
+    if (__builtin_amdgcn_readfirstlane(a.info->np) == a.np) dig_conv_tile<NP, WY>(a, tm, tn);
+    if (mark) bwd_data_nar_tile<Sh::TR, Sh::TC>(a.nar, a.out, tm * Sh::TR, tn * Sh::TC);
+}
+
+template <int NP, int WY>
+inline hipError_t launch_dig_conv_shape(hipStream_t stream, const DigConvArgs& a) {
+    typedef DigConvShape<WY> Sh;
+    hipLaunchKernelGGL((dig_conv_kernel<NP, WY>), dim3((unsigned)(a.tiles_m * ((a.P + Sh::TC - 1) / Sh::TC))), dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 template <int NP>
 inline hipError_t launch_dig_conv_product(hipStream_t stream, const DigConvArgs& a, int WY) {
-    const int tc = 32 * (4 / WY);
-    const dim3 grid((unsigned)(a.tiles_m * ((a.P + tc - 1) / tc)));
-    if (WY == 1) hipLaunchKernelGGL((dig_conv_kernel<NP, 1, 3>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((dig_conv_kernel<NP, 2, 4>), grid, dim3(256), 0, stream, a);
-    return hipGetLastError();
+    return WY == 1 ? launch_dig_conv_shape<NP, 1>(stream, a) : launch_dig_conv_shape<NP, 2>(stream, a);
 }
 
 // in: x (forward) or dy (backward-data); workspace: [weight planes][planes of in][256 zeros][decision][scan]
@@ -856,24 +872,26 @@ struct DigConvBwArgs {
     int qbits;
 };
 
-// Four waves as WY x (4 / WY), as in dig_conv_kernel; workgroup (tile, z) reduces slice z and leaves one integer per output.
-template <int NP, int WY, int ST>
-__global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_bw_kernel(DigConvBwArgs a) {
+// Blocks, fragments and the step of two k blocks as in dig_conv_tile, one pair of them in LDS; workgroup (tile, z) reduces slice z and leaves
+// one integer per output.  us a call, 32 x 32 -> now: posit(8,2),
+// 128 images of 64 channels at 16 x 16 to 64, 3 x 3, 58.2 and 46.3; posit<16,1>, 48 of 58 at 48 x 48 to 7, 5 x 5, 147 and 112.
+template <int NP, int WY>
+__global__ __launch_bounds__(256, (NP <= 4 ? 4 : 2)) void dig_conv_bw_kernel(DigConvBwArgs a) {
     if (__builtin_amdgcn_readfirstlane(a.info->np) != a.np) return;
-    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
-    constexpr int WX = 4 / WY, NB = WX, NA = WY;
+    typedef DigConvShape<WY> Sh;
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), NA = Sh::NA, NB = Sh::NB, TR = Sh::TR, TC = Sh::TC;
     constexpr int RPB = (NA + NB) * NP;
-    constexpr int TR = 32 * WY, TC = 32 * WX;
-    static_assert(NP % 4 == 0, "copies spread evenly over the waves");
-    constexpr int ARUNS = NA * NP / 4, GRUNS = NB * NP / 4, LOADS = ARUNS + GRUNS;
-    __shared__ uint4 lds[ST * RPB * 64];
+    static_assert((NA * NP) % 4 == 0 && (NB * NP) % 4 == 0, "copies spread evenly over the waves");
+    constexpr int ARUNS = NA * NP / 4, GRUNS = NB * NP / 4;
+    __shared__ uint4 lds[2 * RPB * 64];
     uint4* const stage = lds;
 
     const int t = threadIdx.x;
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wy = WY == 2 ? w >> 1 : 0, wx = WY == 2 ? (w & 1) : w;
-    const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
-    const int z = blockIdx.y;
+    const int wr = w % (2 * NA), wc = w / (2 * NA);  // block of 16 rows, block of 32 columns
+    // the tiles of a slice next to each other: they share its blocks
+    const int id = dig_xcd_order((int)(blockIdx.x + blockIdx.y * gridDim.x), (int)(gridDim.x * gridDim.y));
+    const int z = id / (int)gridDim.x, tile = id - z * (int)gridDim.x, tm = tile % a.tiles_m, tn = tile / a.tiles_m;
     const int kb0 = z * a.kb_per_split, nkb = a.kb_per_split;
 
     const int64_t a_kb = (int64_t)a.RBA * NP * 64;
@@ -904,118 +922,110 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 2 : 1)) void dig_conv_bw_kernel(Dig
         oh = pos / a.OW;
         ow = pos - oh * a.OW;
     }
-    int issued = 0;
-    auto issue = [&]() {
-        uint4* buf = stage + (issued % ST) * (RPB * 64);
+    auto issue = [&](int p) {  // the two k blocks of pair p, or the slice's last one
 #pragma unroll
-        for (int c = 0; c < ARUNS; ++c)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(asrc + c * 64),
-                                             (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
-        asrc += a_kb;
-        const uint4* s = a.zero;
-        if (oh < a.OH) {  // inside the reduction (its padded end reads zeros)
-            if (kind == 0) {
-                const int ih = oh * a.sh + dr, iw = ow * a.sw + ds;
-                if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W) s = a.xb + (cbase + ((ih * a.W + iw) * a.NG + gi) * NP);
-            } else if (kind == 1) {
-                s = a.ones + (gi * NP + pl0);
+        for (int h = 0; h < 2; ++h) {
+            if (2 * p + h >= nkb) break;
+            uint4* buf = stage + h * (RPB * 64);
+            const uint4* as = asrc + (int64_t)(2 * p + h) * a_kb;
+#pragma unroll
+            for (int c = 0; c < ARUNS; ++c)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(as + c * 64),
+                                                 (__attribute__((address_space(3))) void*)(buf + (w * ARUNS + c) * 64), 16, 0, 0);
+            const uint4* s = a.zero;
+            if (oh < a.OH) {  // inside the reduction (its padded end reads zeros)
+                if (kind == 0) {
+                    const int ih = oh * a.sh + dr, iw = ow * a.sw + ds;
+                    if ((unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W) s = a.xb + (cbase + ((ih * a.W + iw) * a.NG + gi) * NP);
+                } else if (kind == 1) {
+                    s = a.ones + (gi * NP + pl0);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < GRUNS; ++c)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + c),
+                                                 (__attribute__((address_space(3))) void*)(buf + (NA * NP + cb * NP + pl0 + c) * 64), 16, 0, 0);
+            gi += 2;  // the next k block: two reduction indices of 16 further
+            while (gi >= a.NG) {
+                gi -= a.NG;
+                if (++ow == a.OW) {
+                    ow = 0;
+                    ++oh;
+                }
             }
         }
-#pragma unroll
-        for (int c = 0; c < GRUNS; ++c)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + c),
-                                             (__attribute__((address_space(3))) void*)(buf + (NA * NP + cb * NP + pl0 + c) * 64), 16, 0, 0);
-        gi += 2;  // the next k block: two reduction indices of 16 further
-        while (gi >= a.NG) {
-            gi -= a.NG;
-            if (++ow == a.OW) {
-                ow = 0;
-                ++oh;
-            }
-        }
-        ++issued;
     };
     const int a_nar = __builtin_amdgcn_readfirstlane(a.info->nar[1]), b_nar = __builtin_amdgcn_readfirstlane(a.info->nar[0]);
-    uint32_t row_nar = 0, col_nar = 0;
+    issue(0);
+    dig_v4i acc[2][NC];
 #pragma unroll
-    for (int k = 0; k < ST - 1; ++k)
-        if (k < nkb) issue();
-    pm_v16i acc[NC];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int s = 0; s < NC; ++s)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[s][r] = 0;
-    const uint4* const sa0 = stage + wy * NP * 64 + lane;
-    const uint4* const sb0 = stage + (NA + wx) * NP * 64 + lane;
-    DigFrag<NP> f0, f1;
-    auto markers = [&](const DigFrag<NP>& f) {
-        if (a_nar) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) row_nar |= pm_marker_bits((uint32_t)f.a[NP - 1][i]);
-        }
-        if (b_nar) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) col_nar |= pm_marker_bits((uint32_t)f.b[NP - 1][i]);
+        for (int s = 0; s < NC; ++s) acc[h][s] = dig_v4i{0, 0, 0, 0};
+    uint32_t row_nar = 0, col_nar[2] = {0, 0};
+    const uint4* const lane0 = stage + (lane >> 5) * (RPB * 64) + ((lane >> 4) & 1) * 32 + (lane & 15);
+    const uint4* const sa0 = lane0 + (wr >> 1) * NP * 64 + (wr & 1) * 16;
+    const uint4* const sb0 = lane0 + (NA + wc) * NP * 64;
+    const int pairs = (nkb + 1) / 2;
+    auto loop = [&](auto ta, auto tb) {
+        constexpr int TA = ta, TB = tb;
+        for (int p = 0; p < nkb / 2; ++p) {
+            __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));  // see dig_conv_tile
+            pcm_ring_barrier();
+            DigPair<NP> f;
+            f.template load<0, TA, TB>(sa0, sb0);
+            if (p + 1 < pairs) {
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+                pcm_ring_barrier();
+                issue(p + 1);
+            }
+            if (TA == NP && TB == NP) dig_pair_markers<NP>(a_nar, b_nar, f, row_nar, col_nar);
+            dig_pair_mma<NP, 0, TA, 0, TB>(f, acc);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-    __syncthreads();
     if constexpr (NP <= 4) {
-        auto step = [&](int kb, const DigFrag<NP>& cur, DigFrag<NP>& next) {
-            if (kb + ST - 2 < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 3) * LOADS));
-            else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-            pcm_ring_barrier();
-            if (kb + ST - 1 < nkb) issue();
-            const int nb = ((kb + 1) % ST) * (RPB * 64);
-            next.template load<0>(sa0 + nb, sb0 + nb);
-            markers(cur);
-            dig_mma<NP, 0, NP, 0, NP>(cur, acc);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        f0.template load<0>(sa0, sb0);
-        for (int kb = 0; kb < nkb; kb += 2) {
-            step(kb, f0, f1);
-            if (kb + 1 < nkb) step(kb + 1, f1, f0);
-        }
-    } else {  // one set of operand registers, read in their own step; the planes that hold anything (see dig_conv_kernel)
-        auto loop = [&](auto ta, auto tb) {
-            constexpr int TA = ta, TB = tb;
-            for (int kb = 0; kb < nkb; ++kb) {
-                if (kb + ST - 2 < nkb) __builtin_amdgcn_s_waitcnt(pcm_vmcnt((ST - 2) * LOADS));
-                else __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
-                pcm_ring_barrier();
-                if (kb + ST - 1 < nkb) issue();
-                const int nb = (kb % ST) * (RPB * 64);
-                f0.template load<0, TA, TB>(sa0 + nb, sb0 + nb);
-                if constexpr (TA == NP) markers(f0);
-                dig_mma<NP, 0, TA, 0, TB>(f0, acc);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
+        loop(dig_int<NP>(), dig_int<NP>());
+    } else {  // the planes that hold anything
         const int ua = __builtin_amdgcn_readfirstlane(a.info->used[1]), ub = __builtin_amdgcn_readfirstlane(a.info->used[0]);
         dig_for_planes<NP>(a_nar || b_nar ? NP : ua, ub, loop);
     }
+    if (nkb & 1) {
+        __builtin_amdgcn_s_waitcnt(pcm_vmcnt(0));
+        pcm_ring_barrier();
+        const int at = -(lane >> 5) * (RPB * 64);
+        dig_single_mma<NP>(sa0 + at, sb0 + at, lane, a_nar, b_nar, row_nar, col_nar, acc);
+    }
 
     // ---- this slice's integers and NaR flags ----
-    row_nar = (row_nar | (uint32_t)__shfl_xor((int)row_nar, 32)) & 0x80808080u;
-    col_nar = (col_nar | (uint32_t)__shfl_xor((int)col_nar, 32)) & 0x80808080u;
+    row_nar = dig_pair_across(row_nar);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) col_nar[h] = dig_pair_across(col_nar[h]);
     const int64_t MN = (int64_t)a.M * a.N;
-    const int nn = tn * TC + wx * 32 + (lane & 31), m0 = tm * TR + wy * 32;
+    const int n0 = tn * TC + wc * 32 + (lane & 15), m0 = tm * TR + wr * 16;
     // the first tile column stores the row flags of its tile row (the same in every column), the first tile row the column
     // flags: every entry is written, so the workspace needs no clearing
-    if (lane < 32) {
-        if (tn == 0 && wx == 0 && m0 + lane < a.M) a.rowflag[(int64_t)z * a.M + m0 + lane] = row_nar;
-        if (tm == 0 && wy == 0 && nn < a.N) a.colflag[(int64_t)z * a.N + nn] = col_nar;
+    if (lane < 16) {
+        if (tn == 0 && wc == 0 && m0 + lane < a.M) a.rowflag[(int64_t)z * a.M + m0 + lane] = row_nar;
+        if (tm == 0 && wr == 0) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (n0 + 16 * h < a.N) a.colflag[(int64_t)z * a.N + n0 + 16 * h] = col_nar[h];
+        }
     }
-    if (nn >= a.N) return;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = m0 + (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
-        uint32_t q[L];
-        dig_combine<NP>(acc, r, q);
-        if (m < a.M) {
+    for (int h = 0; h < 2; ++h) {
+        const int nn = n0 + 16 * h;
 #pragma unroll
-            for (int l = 0; l < L; ++l) a.part[((int64_t)z * L + l) * MN + (int64_t)m * a.N + nn] = q[l];
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + 4 * (lane >> 4) + r;
+            uint32_t q[L];
+            dig_combine<NP>(acc[h], r, q);
+            if (m < a.M && nn < a.N) {
+#pragma unroll
+                for (int l = 0; l < L; ++l) a.part[((int64_t)z * L + l) * MN + (int64_t)m * a.N + nn] = q[l];
+            }
         }
     }
 }
@@ -1075,9 +1085,10 @@ inline hipError_t launch_dig_conv_bw_product(hipStream_t stream, DigConvBwArgs a
     a.part = (uint32_t*)part;
     a.rowflag = a.part + (size_t)p.splits * L * p.M * p.N;
     a.colflag = a.rowflag + (size_t)p.splits * p.M;
-    const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
-    if (p.WY == 1) hipLaunchKernelGGL((dig_conv_bw_kernel<NP, 1, 3>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((dig_conv_bw_kernel<NP, 2, 4>), grid, dim3(256), 0, stream, a);
+    const int tc = p.WY == 1 ? DigConvShape<1>::TC : DigConvShape<2>::TC;
+    const dim3 grid((unsigned)(p.tiles_m * ((p.N + tc - 1) / tc)), (unsigned)p.splits);
+    if (p.WY == 1) hipLaunchKernelGGL((dig_conv_bw_kernel<NP, 1>), grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((dig_conv_bw_kernel<NP, 2>), grid, dim3(256), 0, stream, a);
     PNN_CHECK_LAUNCH();
     hipLaunchKernelGGL(dig_conv_bw_merge_kernel<NP>, dim3((unsigned)(((int64_t)p.M * p.N + 31) / 32)), dim3(256), 0, stream, a);
     return hipGetLastError();

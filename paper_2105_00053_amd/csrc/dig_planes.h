@@ -367,6 +367,123 @@ __device__ __forceinline__ void dig_mma_below(int g0, uint32_t ma, uint32_t mb, 
     }
 }
 
+// Workgroup `id` of `total` in an order that gives each of the eight XCDs, which take workgroups in turn, a contiguous run, so that
+// neighbours share an L2.
+__device__ __forceinline__ int dig_xcd_order(int id, int total) {
+    const int q = id & 7, each = total >> 3, more = total & 7;
+    return q * each + (q < more ? q : more) + (id >> 3);
+}
+
+// ---- the step of two k blocks: 16 rows and 32 columns per wave, v_mfma_i32_16x16x64_i8 ----
+
+typedef int dig_v4i __attribute__((ext_vector_type(4)));
+
+// Lane l holds row or column l % 16 and 16 reduction indices: half (l / 16) % 2 of k block l / 32 of the pair.
+template <int NP>
+struct DigPair {
+    dig_v4i a[NP], b[2][NP];
+    template <int SP, int TA = NP, int TB = NP>
+    __device__ __forceinline__ void load(const uint4* sa, const uint4* sb) {
+#pragma unroll
+        for (int i = TA - 1; i >= SP; --i) a[i] = __builtin_bit_cast(dig_v4i, sa[i * 64]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = TB - 1; j >= SP; --j) b[h][j] = __builtin_bit_cast(dig_v4i, sb[j * 64 + 16 * h]);
+    }
+};
+
+template <int NP, int IF, int IT, int JF, int JT>
+__device__ __forceinline__ void dig_pair_mma(const DigPair<NP>& f, dig_v4i (&acc)[2][2 * NP - 1]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = IF; i < IT; ++i)
+#pragma unroll
+            for (int jj = JF; jj < JT; ++jj) {
+                const int j = ((i - IF) & 1) ? JT - 1 - (jj - JF) : jj;  // the order keeps a sum from following itself
+                acc[h][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f.a[i], f.b[h][j], acc[h][i + j], 0, 0, 0);
+            }
+}
+
+// As dig_mma_below
+template <int NP, int GA, int GB>
+__device__ __forceinline__ void dig_pair_below(int g0, uint32_t ma, uint32_t mb, const DigPair<NP>& f, dig_v4i (&acc)[2][2 * NP - 1]) {
+    typedef DigGroups<NP> D;
+    if constexpr (GA < D::G) {
+        if constexpr (GB < D::G) {
+            if ((GA < g0 || GB < g0) && (ma & (1u << GA)) && (mb & (1u << GB)))
+                dig_pair_mma<NP, D::start(GA), D::start(GA + 1), D::start(GB), D::start(GB + 1)>(f, acc);
+            dig_pair_below<NP, GA, GB + 1>(g0, ma, mb, f, acc);
+        } else {
+            dig_pair_below<NP, GA + 1, 0>(g0, ma, mb, f, acc);
+        }
+    }
+}
+
+// NaR markers of the top planes
+template <int NP>
+__device__ __forceinline__ void dig_pair_markers(int a_nar, int b_nar, const DigPair<NP>& f, uint32_t& row_nar, uint32_t (&col_nar)[2]) {
+    if (a_nar) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) row_nar |= pm_marker_bits((uint32_t)f.a[NP - 1][q]);
+    }
+    if (b_nar) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) col_nar[h] |= pm_marker_bits((uint32_t)f.b[h][NP - 1][q]);
+    }
+}
+
+// A single k block: lanes below 32 take plane 2 m of the rows and plane j of the columns, the lanes above planes 2 m + 1 and j - 1, the
+// same 32 indices: both products belong to sum 2 m + j.  NP (NP + 1) / 2 instructions for NP^2 products of half a pair's length, where a block of zeros
+// beside it would take NP^2.  sa, sb: the block as lanes below 32 read it.
+template <int NP>
+__device__ __forceinline__ void dig_single_mma(const uint4* sa, const uint4* sb, int lane, int a_nar, int b_nar, uint32_t& row_nar, uint32_t (&col_nar)[2],
+                                               dig_v4i (&acc)[2][2 * NP - 1]) {
+    constexpr int MA = (NP + 1) / 2;
+    const int hi = lane >> 5;
+    const dig_v4i none = {0, 0, 0, 0};
+    dig_v4i a[MA];
+#pragma unroll
+    for (int m = 0; m < MA; ++m) {
+        const bool last = 2 * m + 1 == NP;  // no plane for the lanes above
+        const dig_v4i v = __builtin_bit_cast(dig_v4i, sa[(2 * m + (last ? 0 : hi)) * 64]);
+        a[m] = last && hi ? none : v;
+    }
+    if (a_nar && hi == ((NP - 1) & 1)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) row_nar |= pm_marker_bits((uint32_t)a[MA - 1][q]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        dig_v4i b[NP + 1];
+#pragma unroll
+        for (int j = 0; j <= NP; ++j) {
+            const bool out = j == 0 ? hi != 0 : j == NP ? hi == 0 : false;
+            const dig_v4i v = __builtin_bit_cast(dig_v4i, sb[(j == 0 ? 0 : j == NP ? NP - 1 : j - hi) * 64 + 16 * h]);
+            b[j] = out ? none : v;
+        }
+        if (b_nar && hi) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) col_nar[h] |= pm_marker_bits((uint32_t)b[NP][q]);
+        }
+#pragma unroll
+        for (int m = 0; m < MA; ++m)
+#pragma unroll
+            for (int j = 0; j <= NP; ++j)
+                if (2 * m + j <= 2 * NP - 2) acc[h][2 * m + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[m], b[j], acc[h][2 * m + j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Marker bits of a row or column: of the four lanes that hold its reduction indices
+__device__ __forceinline__ uint32_t dig_pair_across(uint32_t v) {
+    v |= (uint32_t)__shfl_xor((int)v, 16);
+    return (v | (uint32_t)__shfl_xor((int)v, 32)) & 0x80808080u;
+}
+
 // ---- the sums as one integer ----
 
 // Limbs that hold sum_s acc[s] 256^s: 2 NP - 2 bytes above int32 sums, and a sign.
@@ -375,8 +492,8 @@ constexpr int dig_limbs() { return (8 * (2 * NP - 2) + 33 + 31) / 32; }
 
 // Four sums at a time into 64 bits by 32 x 32 + 64 multiply-adds (the powers of 256 are hidden from the compiler, which
 // would make pairs of shifts and adds of them), then the words with carries.
-template <int NP>
-__device__ __forceinline__ void dig_combine(const pm_v16i (&acc)[2 * NP - 1], int r, uint32_t (&q)[dig_limbs<NP>()]) {
+template <int NP, class V>
+__device__ __forceinline__ void dig_combine(const V (&acc)[2 * NP - 1], int r, uint32_t (&q)[dig_limbs<NP>()]) {
     constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), W = (NC + 3) / 4;
     int c8 = 1 << 8, c16 = 1 << 16, c24 = 1 << 24;
     asm("" : "+s"(c8), "+s"(c16), "+s"(c24));
@@ -595,7 +712,8 @@ template <int NP>
 struct DigF64 {
     static_assert(NP == 3 || NP == 4, "parts that are exact in binary64");
     static constexpr int NC = 2 * NP - 1, LOW = NP - 1;  // sums of the low part
-    static __device__ __forceinline__ void parts(const pm_v16i (&acc)[NC], int r, double& hi, double& lo) {
+    template <class V>
+    static __device__ __forceinline__ void parts(const V (&acc)[NC], int r, double& hi, double& lo) {
         hi = (double)acc[LOW][r] * pow2d(8 * LOW);
 #pragma unroll
         for (int s = LOW + 1; s < NC; ++s) hi = __builtin_fma((double)acc[s][r], pow2d(8 * s), hi);

@@ -227,9 +227,9 @@ __device__ __forceinline__ void dig_round_column(const DigGemmArgs& g, int at, i
 // S - 1 blocks ahead.  The waves of a workgroup leave each barrier together and would all wait for their LDS reads
 // together, so the operand registers of a step are read during the step before (two sets).  What a step costs beside its
 // matrix instructions is scalar code, hence the straight-line loop over a fixed set of planes (DigGroups).  Registers decide
-// how many waves a SIMD holds: 5 sums three, 7 sums two, more one.
+// how many waves a SIMD holds: 5 sums three, 7 sums two; for more see dig_gemm_pair_kernel.
 template <int NP, int KG, int S>
-__global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig_gemm_kernel(DigGemmArgs g) {
+__global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : 2)) void dig_gemm_kernel(DigGemmArgs g) {
     typedef DigGroups<NP> D;
     constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
     constexpr int RPB = 4 * NP;  // runs of 1 KB per k block: two row blocks and two column blocks of NP planes
@@ -431,6 +431,219 @@ __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : NP == 4 ? 2 : 1)) void dig
         return;
     }
     dig_round_column<L, 4 * KG>(g, at, tm * 64, n, wave, rows, cnar, value, [&](int lr) { return rowv[lr] | (KG == 2 ? rowv[(KG - 1) * 64 + lr] : 0u); });
+}
+
+// 64 x 32 outputs per workgroup, a wave 16 x 32 of them, whose 2 NP - 1 sums (120 registers for eight planes, 56 for four) leave room for a second
+// workgroup on the CU, four with four planes.  LDS holds one pair of k blocks; its operands go to registers before the next pair's copies start, and the
+// other workgroups multiply meanwhile.  Blocks of 32 x 32 outputs per wave left one wave to a SIMD with eight planes, which waited for every barrier, LDS read
+// and rounding alone.  us a call, 1 % of extremes, 32 x 32 -> now: posit<16,1> 1024^3 65.5 and 58.7, 971 x 1044 x 976 111 and 81, 4096^3 2697 and 2145,
+// posit(8,2) 512 x 512 x 8192 274 and 172; posit<32,2>, N(0, 1), 1024^3 52.7 and 47.5.
+template <int NP>
+__global__ __launch_bounds__(256, (NP <= 4 ? 4 : 2)) void dig_gemm_pair_kernel(DigGemmArgs g) {
+    typedef DigGroups<NP> D;
+    constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), TR = 64, TC = 32;
+    constexpr int RPB = 3 * NP;  // runs of 1 KB per k block: two row blocks and a column block of NP planes
+    constexpr int MAXP = (DIG_MAXK / 32 + 2) / 2;
+    if (__builtin_amdgcn_readfirstlane(g.info->np) != NP) return;
+    // one LDS object (see dig_gemm_kernel)
+    constexpr int VALS = L * TR * TC / 4, RING = 2 * RPB * 64 > VALS ? 2 * RPB * 64 : VALS;  // words of 16 bytes
+    constexpr int MASKW = (3 * MAXP + 15) / 16, LISTW = (2 * MAXP + 15) / 16;
+    __shared__ uint4 lds[RING + MASKW + (TR + TC) / 4 + 1 + LISTW];
+    uint4* const stage = lds;
+    uint8_t* const masks = reinterpret_cast<uint8_t*>(lds + RING);     // [3][MAXP]: the tile's row blocks 0, 1 and its column block, by pairs
+    uint32_t* const rowv = reinterpret_cast<uint32_t*>(lds + RING + MASKW);
+    uint32_t* const colv = rowv + TR;
+    uint32_t* const present = colv + TC;                               // pairs that hold anything in groups 0 and 1; entries of the list
+    uint16_t* const list = reinterpret_cast<uint16_t*>(present + 4);   // pairs that hold anything below the main loop's planes
+
+    const int t = threadIdx.x;
+    const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    // XCD-aware order, as in gemm_p8_mfma.h: each XCD a contiguous run of tiles, walked in bands of 8 tile-rows
+    const int nblk = g.tiles_m * g.tiles_n;
+    int lid = blockIdx.x;
+    if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+    const int band = lid / (8 * g.tiles_n);
+    const int band_rows = (g.tiles_m - band * 8) < 8 ? (g.tiles_m - band * 8) : 8;
+    const int in_band = lid - band * 8 * g.tiles_n;
+    const int tm = band * 8 + in_band % band_rows, tn = in_band / band_rows;
+    const int z = blockIdx.y;
+    const int kb0 = z * g.kb_per_split;
+    const int nkb = (kb0 + g.kb_per_split < g.KB ? kb0 + g.kb_per_split : g.KB) - kb0;
+    const int whole = nkb / 2;  // pairs; an odd block behind them is multiplied in all its planes
+
+    const uint4* const pa = reinterpret_cast<const uint4*>(g.planes) + ((int64_t)kb0 * g.RBA + tm * 2) * (NP * 64) + lane;
+    const uint4* const pb = reinterpret_cast<const uint4*>(g.planes) + ((int64_t)g.KB * g.RBA + (int64_t)kb0 * g.RBB + tn) * (NP * 64) + lane;
+    // wave w copies planes SP + w, SP + w + 4 of the three blocks
+    typedef __attribute__((address_space(3))) uint4 LdsQuad;
+    LdsQuad* const ring = (LdsQuad*)lds;
+    auto issue = [&](auto sp, int p) {
+        constexpr int SP = sp;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = 2 * p + h;
+            if (k >= nkb) break;
+            const uint4* const ka = pa + (int64_t)k * g.RBA * (NP * 64);
+            const uint4* const kb = pb + (int64_t)k * g.RBB * (NP * 64);
+#pragma unroll
+            for (int i = 0; i < (NP - SP + 3) / 4; ++i) {
+                const int c = SP + w + 4 * i;
+                if (c >= NP) continue;
+#pragma unroll
+                for (int b = 0; b < 3; ++b)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b < 2 ? ka + (b * NP + c) * 64 : kb + c * 64),
+                                                     (__attribute__((address_space(3))) void*)(ring + (h * RPB + b * NP + c) * 64), 16, 0, 0);
+            }
+        }
+    };
+    issue(dig_int<0>(), 0);
+    if (t < 3) present[t] = 0;
+    const int a_nar = __builtin_amdgcn_readfirstlane(g.info->nar[0]), b_nar = __builtin_amdgcn_readfirstlane(g.info->nar[1]);
+    const int at = __builtin_amdgcn_readfirstlane(g.info->base[0] + g.info->base[1]);
+    __syncthreads();
+    for (int p = t; p < whole; p += 256) {
+        uint32_t any = 0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            uint32_t m = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int64_t k = kb0 + 2 * p + h;
+                m |= b < 2 ? g.ma[k * g.RBA + tm * 2 + b] : g.mb[k * g.RBB + tn];
+            }
+            masks[b * MAXP + p] = (uint8_t)m;
+            any |= m;
+        }
+        if (any & 1u) atomicAdd(&present[0], 1u);
+        if (any & 2u) atomicAdd(&present[1], 1u);
+    }
+    __syncthreads();
+    // The straight-line loop starts at the first group that more than a quarter of the pairs use (see dig_gemm_kernel); of five and six planes half of them
+    // (1024^3, N(0, 1) with extremes, (10,1) 41.5 and 38.6 us, (12,1) 48.0 and 47.2; posit(8,2) with four planes, 4096 x 4096 x 1024, 155 and 171; posit<32,2> 4096^3 1667 and 2252).
+    constexpr uint32_t SHARE = NP == 5 || NP == 6 ? 2 : 4;
+    const uint32_t p0 = __builtin_amdgcn_readfirstlane(present[0]), p1 = __builtin_amdgcn_readfirstlane(present[1]);
+    const int g0 = SHARE * p0 > (uint32_t)whole ? 0 : SHARE * p1 > (uint32_t)whole ? 1 : 2;
+    const uint32_t below = (1u << g0) - 1u;
+    for (int p = t; p < whole; p += 256)
+        if ((masks[p] | masks[MAXP + p] | masks[2 * MAXP + p]) & below) list[atomicAdd(&present[2], 1u)] = (uint16_t)p;
+
+    dig_v4i acc[2][NC];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < NC; ++s) acc[h][s] = dig_v4i{0, 0, 0, 0};
+    uint32_t row_nar = 0, col_nar[2] = {0, 0};
+    const uint4* const lane0 = stage + (lane >> 5) * (RPB * 64) + ((lane >> 4) & 1) * 32 + (lane & 15);
+    const uint4* const sa0 = lane0 + (w >> 1) * NP * 64 + (w & 1) * 16;
+    const uint4* const sb0 = lane0 + 2 * NP * 64;
+    // This wave's copies are in LDS; behind the barrier everyone's are.
+    auto landed = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0), lgkmcnt(0)
+        pcm_ring_barrier();
+    };
+    // Everyone has read the pair: LDS takes the next one.
+    auto taken = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        pcm_ring_barrier();
+    };
+    auto loop = [&](auto sp) {
+        constexpr int SP = sp;
+#pragma unroll 1
+        for (int p = 0; p < whole; ++p) {
+            DigPair<NP> f;
+            landed();
+            f.template load<SP>(sa0, sb0);
+            if (p + 1 < whole) {
+                taken();
+                issue(sp, p + 1);
+            } else if (nkb & 1) {
+                taken();
+                issue(dig_int<0>(), p + 1);
+            }
+            dig_pair_markers<NP>(a_nar, b_nar, f, row_nar, col_nar);
+            dig_pair_mma<NP, SP, NP, SP, NP>(f, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (g0 == 0) loop(dig_int<0>());
+    else if (g0 == 1) loop(dig_int<D::start(1)>());
+    else loop(dig_int<D::start(2)>());
+    if (nkb & 1) {
+        landed();
+        const int to = -(lane >> 5) * (RPB * 64);
+        dig_single_mma<NP>(sa0 + to, sb0 + to, lane, a_nar, b_nar, row_nar, col_nar, acc);
+    }
+    __syncthreads();
+    // the pairs with anything below once more, the planes left out only
+    const int extra = __builtin_amdgcn_readfirstlane((int)present[2]);
+    if (extra > 0) issue(dig_int<0>(), __builtin_amdgcn_readfirstlane((int)list[0]));
+#pragma unroll 1
+    for (int e = 0; e < extra; ++e) {
+        const int p = list[e];
+        const uint32_t ma = __builtin_amdgcn_readfirstlane((uint32_t)masks[(w >> 1) * MAXP + p]), mb = __builtin_amdgcn_readfirstlane((uint32_t)masks[2 * MAXP + p]);
+        DigPair<NP> f;
+        landed();
+        f.template load<0>(sa0, sb0);
+        if (e + 1 < extra) {
+            const int next = __builtin_amdgcn_readfirstlane((int)list[e + 1]);
+            taken();
+            issue(dig_int<0>(), next);
+        }
+        dig_pair_below<NP, 0, 0>(g0, ma, mb, f, acc);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+
+    // ---- NaR flags, and the sums as one integer per output, to LDS; then rounded and stored (or left for the merge) ----
+    uint32_t* const vals = reinterpret_cast<uint32_t*>(stage);
+    row_nar = dig_pair_across(row_nar);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) col_nar[h] = dig_pair_across(col_nar[h]);
+    if (lane < 16) {
+        rowv[w * 16 + lane] = row_nar;
+        if (w == 0) {  // the four waves saw the same columns
+#pragma unroll
+            for (int h = 0; h < 2; ++h) colv[16 * h + lane] = col_nar[h];
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int lr = w * 16 + 4 * (lane >> 4) + r;
+            uint32_t q[L];
+            dig_combine<NP>(acc[h], r, q);
+#pragma unroll
+            for (int l = 0; l < L; ++l) vals[l * (TR * TC) + lr * TC + 16 * h + (lane & 15)] = q[l];
+        }
+    __syncthreads();
+    constexpr int STEP = 256 / TC;
+    const bool sliced = gridDim.y > 1;
+    const int col = t % TC, first = t / TC, n = tn * TC + col;
+    const uint32_t cnar = colv[col];
+    if (sliced) {
+        // the first tile column stores the row flags of its tile row, the first tile row the column flags: all of them
+        if (tn == 0 && t < TR && tm * TR + t < g.M) g.rowflag[(int64_t)z * g.M + tm * TR + t] = rowv[t];
+        if (tm == 0 && t < TC && n < g.N) g.colflag[(int64_t)z * g.N + n] = cnar;
+    }
+    if (n >= g.N) return;
+    auto value = [&](int lr, uint32_t (&q)[L]) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) q[l] = vals[l * (TR * TC) + lr * TC + col];
+    };
+    const int rows = g.M - tm * TR < TR ? g.M - tm * TR : TR;
+    if (sliced) {
+        const int64_t MN = (int64_t)g.M * g.N;
+#pragma unroll 2
+        for (int lr = first; lr < rows; lr += STEP) {
+            uint32_t q[L];
+            value(lr, q);
+#pragma unroll
+            for (int l = 0; l < L; ++l) g.part[((int64_t)z * L + l) * MN + (int64_t)(tm * TR + lr) * g.N + n] = q[l];
+        }
+        return;
+    }
+    dig_round_column<L, STEP>(g, at, tm * TR, n, first, rows, cnar, value, [&](int lr) { return rowv[lr]; });
 }
 
 // Products of few tiles: 32 x 32 outputs per workgroup, whose KG waves share the reduction (wave kg the k blocks kg, kg + KG, ...).
@@ -652,7 +865,7 @@ inline DigPlan dig_plan(int64_t M, int64_t N, int64_t K, size_t limit = SIZE_MAX
             p.total += p.splits * per;
         }
     }
-    // The wide kernel takes four times as long per k block and holds one workgroup per compute unit: slices of at least 8 k
+    // The wide kernel takes four times as long per k block and two workgroups of half a tile fill a compute unit: slices of at least 8 k
     // blocks, where a merging launch is there anyway (all patterns of posit<16,1>, 96 x 97 x 4096: uncut 185 us, cut 39; 115 x 118 x 10332: 425 and 53).  posit(8,2)'s
     // fixed workspace has no room for them.
     p.wide_splits = 1;
@@ -689,10 +902,20 @@ inline hipError_t launch_dig_product(hipStream_t stream, const DigGemmArgs& g, i
     return hipGetLastError();
 }
 
-// One group of waves, a ring of four blocks (64 KB and two workgroups per compute unit for four planes).
+// One group of waves per tile.  Four planes: dig_gemm_pair_kernel from the sizes on that fill the chip without cutting (us, dig_gemm_kernel and it: posit<16,1>
+// 1500 x 700 x 2000 58.5 and 48.7, posit(8,2) 4096^3 508 and 478, (12,1) 3000 x 3000 x 300 68.7 and 62.1), but posit<16,1> beyond 2^35 multiply-adds, whose
+// Gaussian operands reach the lowest plane in many pairs and few blocks (4096 x 4096 x 1024 200 and 195, 4096^3 652 and 680); three planes: dig_gemm_kernel
+// (posit(8,1) 2500 x 1200 x 900 42.4 and 47.3).
 template <int NP>
-inline hipError_t launch_dig_whole(hipStream_t stream, const DigGemmArgs& g) {
-    return launch_dig_product<NP, 1, 4>(stream, g, g.splits);
+inline hipError_t launch_dig_whole(hipStream_t stream, DigGemmArgs g) {
+    if constexpr (NP <= 4) {
+        if (NP == 3 || (g.fin.n == 16 && (double)g.M * g.N * g.KB * 32 > (double)((int64_t)1 << 35))) return launch_dig_product<NP, 1, 4>(stream, g, g.splits);
+    }
+    if constexpr (NP >= 4) {
+        g.tiles_n = (g.N + 31) / 32;
+        hipLaunchKernelGGL(dig_gemm_pair_kernel<NP>, dim3((unsigned)(g.tiles_m * g.tiles_n), (unsigned)g.splits), dim3(256), 0, stream, g);
+    }
+    return hipGetLastError();
 }
 
 template <class F>
