@@ -105,9 +105,17 @@ def backward_and_update(net, tape, dy, alpha=None, grads=None):
     pending = []
     for kind, li, aux, saved in reversed(tape):
         if kind == "fc":
-            dw = pn.posit_gemm(dy, saved, fc, fm, trans_a=True)
-            ones = torch.full((dy.shape[0], 1), net.one, dtype=dy.dtype, device=dy.device)
-            db = pn.posit_gemm(dy, ones, fc, fm, trans_a=True).reshape(-1)
+            (n, cout), cin = dy.shape, saved.shape[1]
+            if cout * cin <= 1 << 16 and n * cout * cin <= 1 << 22:
+                # as the weight gradient of a 1 x 1 filter over images of one pixel, with the bias gradient as its column of ones: one call
+                # instead of two products and a tensor of ones; beyond, the product has the faster kernels
+                dw, db = pn.posit_conv2d_bwd_weight(dy.reshape(n, cout, 1, 1), saved.reshape(n, cin, 1, 1),
+                                                    pn.ConvDesc(n, cin, 1, 1, cout, 1, 1, 0, 0, 1, 1), fc, fm, with_bias=True)
+                dw = dw.reshape(cout, cin)
+            else:
+                dw = pn.posit_gemm(dy, saved, fc, fm, trans_a=True)
+                ones = torch.full((n, 1), net.one, dtype=dy.dtype, device=dy.device)
+                db = pn.posit_gemm(dy, ones, fc, fm, trans_a=True).reshape(-1)
             dx = pn.posit_gemm(dy, net.w8[li], fc, fc)
             _update(net, li, dw, db, alpha, grads, pending)
             dy = dx
