@@ -101,10 +101,11 @@ inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit
 // posit<32,2> below the tiles from which the digit planes and the LDS kernel serve: in one launch on the matrix cores, the window of bits taken by each
 // workgroup for itself.  Against the general kernel, us: 8 x 8 x 4 19.9 and 8.3, 64 x 64 x 256 215 and 9.6, 432 x 432 x 2048 803 and 95; operands
 // that span more than the window, 64 x 64 x 1024 220 and 90, x 2048 224 and 176, 16 x 16 x 4000 235 and 345 (N(0, 1): 55), hence the end of the
-// reduction; 432 x 432 x 16, three rounds of workgroups, 20.5 and 23.  Where the other two serve they are faster: 500 x 500 x 500 35 and 45.
+// reduction below 256 tiles; from there on the general kernel is full: 256 x 256 x 11904 1469 and 174 (1466 and 1070), 350 x 260 x 3000 579 and 92 (579
+// and 565).  432 x 432 x 16, three rounds of workgroups, 20.5 and 23.  Where the other two serve they are faster: 500 x 500 x 500 35 and 45.
 inline bool p32_direct_fits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + 15) / 16) * ((N + 15) / 16);
-    return K >= 1 && K <= 2048 && M <= 16384 && N <= 16384 && tiles < (K < 32 ? 512 : 768);
+    return K >= 1 && K <= (tiles < 256 ? 2048 : DIRECT_MAXK) && M <= 16384 && N <= 16384 && tiles < (K < 32 ? 512 : 768);
 }
 
 // Cut of the kernels that serve where the direct one does not.

@@ -107,7 +107,7 @@ def test_operand_beyond_two_gigabytes():
 
 
 @pytest.mark.parametrize("order", [(0, 0), (0, 1), (1, 0), (1, 1)])
-@pytest.mark.parametrize("size", [(1, 1, 1), (16, 16, 64), (17, 33, 65), (50, 47, 511), (15, 100, 513), (33, 20, 2048), (300, 500, 40)])
+@pytest.mark.parametrize("size", [(1, 1, 1), (16, 16, 64), (17, 33, 65), (50, 47, 511), (15, 100, 513), (33, 20, 2048), (300, 500, 40), (256, 251, 2049)])
 @pytest.mark.parametrize("values", ["window", "range", "zero"])
 def test_p32(values, size, order):
     """posit<32,2>: tiles whose operands the planes hold, tiles that span more (both kinds in one call with "range"), and zeros."""
