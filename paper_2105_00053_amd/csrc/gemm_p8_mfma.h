@@ -350,6 +350,94 @@ __global__ __launch_bounds__(256, (BI * BJ == 4 ? 2 : BI * BJ == 2 ? 3 : 4)) voi
     }
 }
 
+// Products of few tiles: 32 x 32 outputs per workgroup, whose KG waves share the reduction (wave kg the k blocks kg, kg + KG, ...), operands from
+// memory straight to registers, two blocks ahead, no barrier until the sums meet.  us a call, 64 x 64 in slices or whole -> now:
+// 512 x 512 x 2048 18.8 and 12.0, 640 x 640 x 8192 71.7 and 35.6, 260 x 816 x 3602 26.6 and 22.1, 1024^3 19.2 and 16.2, 1024 x 1024 x 4096 40.5 and 32.8.
+template <int KG>
+__global__ __launch_bounds__(64 * KG, 4) void p8_mfma_small_kernel(const uint8_t* __restrict__ Ad, const uint8_t* __restrict__ Bd, int RBA, int RBB, int KB,
+                                                                   const uint8_t* __restrict__ bias, void* __restrict__ C, int64_t ldc, int fout, int M, int N,
+                                                                   int tiles_m, int tiles_n) {
+    __shared__ uint32_t vals[KG][1024];
+    __shared__ uint32_t rown[32], coln[32];
+    const int t = threadIdx.x;
+    const int lane = t & 63, kg = __builtin_amdgcn_readfirstlane(t >> 6);
+    int tm, tn;
+    pm_tile(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    if (t < 32) rown[t] = coln[t] = 0;
+    const uint4* sa = reinterpret_cast<const uint4*>(Ad) + ((int64_t)kg * RBA + tm) * 128 + lane;
+    const uint4* sb = reinterpret_cast<const uint4*>(Bd) + ((int64_t)kg * RBB + tn) * 128 + lane;
+    const int64_t a_adv = (int64_t)KG * RBA * 128, b_adv = (int64_t)KG * RBB * 128;
+    const int steps = KB > kg ? (KB - kg + KG - 1) / KG : 0;
+    struct Frag { pm_v4i ah, al, bh, bl; } f[3];
+    auto fetch = [&](int st, Frag& to) {
+        if (st >= steps) return;
+        to.ah = __builtin_bit_cast(pm_v4i, sa[0]);
+        to.al = __builtin_bit_cast(pm_v4i, sa[64]);
+        to.bh = __builtin_bit_cast(pm_v4i, sb[0]);
+        to.bl = __builtin_bit_cast(pm_v4i, sb[64]);
+        sa += a_adv;
+        sb += b_adv;
+    };
+    pm_v16i hh, xx, ll;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) hh[r] = xx[r] = ll[r] = 0;
+    uint32_t row_nar = 0, col_nar = 0;
+    auto step = [&](int st, const Frag& cur, Frag& ahead) {
+        if (st >= steps) return;
+        fetch(st + 2, ahead);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            row_nar |= pm_marker_bits((uint32_t)cur.ah[q]);
+            col_nar |= pm_marker_bits((uint32_t)cur.bh[q]);
+        }
+        hh = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur.ah, cur.bh, hh, 0, 0, 0);
+        xx = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur.ah, cur.bl, xx, 0, 0, 0);
+        ll = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur.al, cur.bl, ll, 0, 0, 0);
+        xx = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur.al, cur.bh, xx, 0, 0, 0);
+    };
+    fetch(0, f[0]);
+    fetch(1, f[1]);
+    for (int st = 0; st < steps; st += 3) {
+        step(st, f[0], f[2]);
+        step(st + 1, f[1], f[0]);
+        step(st + 2, f[2], f[1]);
+    }
+    __syncthreads();  // the flags are clear
+    if (row_nar & 0x80808080u) rown[lane & 31] = 1;
+    if (col_nar & 0x80808080u) coln[lane & 31] = 1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int lr = (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+        vals[kg][lr * 32 + (lane & 31)] = ((uint32_t)hh[r] << 14) + ((uint32_t)xx[r] << 7) + (uint32_t)ll[r];
+    }
+    __syncthreads();
+    const int lc = t & 31, n = tn * 32 + lc;
+    if (n >= N) return;
+    bool cnar = coln[lc] != 0;
+    uint32_t badd = 0;
+    if (bias) {
+        const uint32_t bp = bias[n];
+        if (bp == 0x80u) cnar = true;
+        else badd = (uint32_t)((int32_t)Arith<P8>::stage(bp) << P8::MAXS);  // + bias * 1
+    }
+#pragma unroll
+    for (int lr = t >> 5; lr < 32; lr += 2 * KG) {
+        const int m = tm * 32 + lr;
+        if (m >= M) continue;
+        uint32_t q = badd;
+#pragma unroll
+        for (int k = 0; k < KG; ++k) q += vals[k][lr * 32 + lc];
+        const bool nar = cnar || rown[lr] != 0;
+        const int64_t at = (int64_t)m * ldc + n;
+        if (fout == 0) {
+            ((uint8_t*)C)[at] = (uint8_t)(nar ? 0x80u : p8_round_quire((int32_t)q));
+        } else {
+            const uint32_t q1[1] = {q};
+            round_store<QuireAccum<P8>, 1>(q1, nar, fout, C, at);
+        }
+    }
+}
+
 // ---- host side ----
 
 struct P8MfmaLayout {
@@ -374,6 +462,13 @@ inline bool p8_mfma_fits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
     if (tiles >= PM_MIN_TILES) return M >= PM_MIN_MN && N >= PM_MIN_MN;
     return M >= PM_MIN_MN && N >= PM_MIN_MN && M * N < ((int64_t)1 << 24) && p8_mfma_slices(M, N, K) >= 2;
+}
+
+// Tiles of 32 x 32 for which p8_mfma_small_kernel serves: below, slices give more workgroups (us, slices and it: 64 tiles, K = 16384 25.3 and 32.9; 128,
+// 8192 23.2 and 22.4); above, 64 x 64 read their operands half as often (1536 x 1536 x 1536, 2304 tiles, 31.3 and 33.3).
+inline bool p8_mfma_small(int64_t M, int64_t N) {
+    const int64_t tiles = ((M + 31) / 32) * ((N + 31) / 32);
+    return tiles >= 128 && tiles <= 1024;
 }
 
 // The largest tile that still gives every compute unit two workgroups; 64 x 64 otherwise.
@@ -420,6 +515,12 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     const unsigned blocks0 = (unsigned)((l.RBA + 7) / 8) * (unsigned)l.KB, blocks1 = (unsigned)((l.RBB + 7) / 8) * (unsigned)l.KB;
     hipLaunchKernelGGL(p8_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, verdict);
     PNN_CHECK_LAUNCH();
+    if (!verdict && p8_mfma_small(M, N)) {
+        const int tiles_m = (int)((M + 31) / 32), tiles_n = (int)((N + 31) / 32);
+        hipLaunchKernelGGL(p8_mfma_small_kernel<8>, dim3((unsigned)(tiles_m * tiles_n)), dim3(512), 0, stream, Ad, Bd, l.RBA, l.RBB, l.KB, bias, C, ldc, fout, (int)M,
+                           (int)N, tiles_m, tiles_n);
+        return hipGetLastError();
+    }
     const int tiles_m = l.RBA / (2 * l.BI), tiles_n = l.RBB / (2 * l.BJ);
     if (l.splits > 1) {
         SplitWs ws;

@@ -69,3 +69,19 @@ def test_convolution(fmt, kind, layer):
     dw, db = pn.posit_conv2d_bwd_weight(dyd, xd, desc, fmt, fmt, with_bias=True)
     want = fast.conv2d_bwd_weight(dy, x, d, fmt, fmt, with_bias=True)
     assert len(mismatches(to_np(dw, fmt), want[0])) == 0 and len(mismatches(to_np(db, fmt), want[1])) == 0
+
+
+@pytest.mark.parametrize("size", [(513, 511, 2049), (512, 1024, 1030), (130, 1030, 4000), (1024, 1023, 513), (353, 353, 5000)])
+@pytest.mark.parametrize("order", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_posit8_0_few_tiles(size, order):
+    """posit<8,0> on 128 to 1024 tiles of 32 x 32: edges of tiles, k blocks that do not divide by the waves, NaR, biases, output formats."""
+    M, N, K = size
+    ta, tb = map(bool, order)
+    rng = np.random.default_rng(K)
+    A, B = rand_patterns(rng, (K, M) if ta else (M, K), "p8", allow_nar=False), rand_patterns(rng, (N, K) if tb else (K, N), "p8", allow_nar=False)
+    bias = rand_patterns(rng, (N,), "p8", special=0.1) if order != (0, 0) else None
+    A[(K - 1, 3) if ta else (3, K - 1)] = B[(N - 1, K // 2) if tb else (K // 2, N - 1)] = 0x80
+    for fout in ("p8", "p16", "p32"):
+        got = to_np(pn.posit_gemm(to_dev(A), to_dev(B), "p8", fout, trans_a=ta, trans_b=tb, bias=None if bias is None else to_dev(bias)), fout)
+        want, _ = fast.gemm(A, B, "p8", fout, trans_a=ta, trans_b=tb, bias=bias)
+        assert len(mismatches(got, want)) == 0, fout
