@@ -49,6 +49,7 @@ struct PwOperand {
 };
 
 // Decode pass over both operands (blockIdx.z picks one): 64 x 64 element tiles.
+template <int UNUSED = 0>  // a template so that every translation unit may include this header
 __global__ __launch_bounds__(256) void pw_predecode_kernel(PwOperand opa, PwOperand opb, int64_t K, int64_t Kp) {
     constexpr int PT = 64;
     __shared__ double tile[PT][PT + 1];
@@ -440,7 +441,7 @@ inline hipError_t launch_pw_gemm(hipStream_t st, int transA, int transB, const v
     PwOperand oa{(const uint16_t*)A, lda, M, (double*)base, p.Mp, (uint32_t*)(base + p.bits_a_off), transA ? 0 : 1};
     PwOperand ob{(const uint16_t*)B, ldb, N, (double*)(base + p.b_off), p.Np, (uint32_t*)(base + p.bits_b_off), transB ? 1 : 0};
     const int64_t rmax = p.Mp > p.Np ? p.Mp : p.Np;
-    hipLaunchKernelGGL(pw_predecode_kernel, dim3((unsigned)(rmax / 64), (unsigned)((p.Kp + 63) / 64), 2), dim3(256), 0, st, oa, ob, K, p.Kp);
+    hipLaunchKernelGGL(pw_predecode_kernel<0>, dim3((unsigned)(rmax / 64), (unsigned)((p.Kp + 63) / 64), 2), dim3(256), 0, st, oa, ob, K, p.Kp);
     PNN_CHECK_LAUNCH();
     PwGemm g;
     g.Ap = oa.dst;

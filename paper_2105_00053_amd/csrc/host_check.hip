@@ -6,11 +6,13 @@
 #include "conv_p8.h"
 #include "api_common.h"
 #include "dig_planes.h"
+#include "direct_conv.h"
 #include "direct_mfma.h"
 #include "conv_desc.h"
 #include "gemm_p8_f6.h"
 #include "conv_p8_mfma.h"
 #include "conv_dig_mfma.h"
+#include "gemm_choice.h"
 #include "gemm_dig_mfma.h"
 #include "p16_window_arith.h"
 #include "noquire_arith.h"
@@ -291,7 +293,41 @@ int host_direct_plan(int64_t M, int64_t N, int64_t K, int64_t* out) {
     double us;
     const DirectPlan p = direct_plan<F>(M, N, K, &us);
     out[0] = p.variant; out[1] = p.splits; out[2] = p.k_per_split; out[3] = (int64_t)p.ws_bytes; out[4] = Arith<F>::L;
+    out[5] = (int64_t)(1000 * us); out[6] = (int64_t)(1000 * prepared_us<F>(M, N, K, SIZE_MAX));
     return p.variant != DIRECT_NONE;
+}
+
+// The order of gemm_dispatch; see hostcheck_gemm_route.
+template <class F>
+int host_gemm_route(int64_t M, int64_t N, int64_t K, bool bias) {
+    constexpr bool p8 = F::N == 8 && F::ES == 0;
+    const DirectPlan d = direct_gemm_plan<F>(M, N, K, SIZE_MAX);
+    if (d.variant != DIRECT_NONE) return d.splits > 1 ? 5 : d.variant;
+    if (F::N == 32 && p32_direct_fits(M, N, K) && !bias) return 6;
+    if (dig_gemm_fits<F>(M, N, K, SIZE_MAX) && (F::N != 32 || !bias)) return 10;
+    if (F::N == 8 && p8_small_gemm_fits(M, N, K)) return 20;
+    if (p8 && p8_f6_fits(M, N, K, SIZE_MAX)) return 21;
+    if (p8 && p8_mfma_fits(M, N, K)) return p8_mfma_small(M, N) ? 23 : 22;
+    if (p8 && use_p8_w4(M, N, K)) return 24;
+    if (p8 && use_p8_kernel(M, N)) return p8_packed_gemm_fits(M, N, K) ? 26 : 25;
+    if (F::N == 8) return 27;
+    if (F::N == 32 && p32_lds_fits(M, N, K)) return 30;
+    if (F::N == 16 && pw_fits(M, N, K)) return 31;
+    if (bucket_pre_format<F>() && bucket_pre_fits<F>(M, N, K)) return 32;
+    return 33;
+}
+
+template <class F>
+int host_direct_conv_plan(int which, const ConvGeom& g, bool with_bias, int64_t* out) {
+    if constexpr (F::N > 16) return 0;
+    else {
+        double us;
+        const DirectConvPlan cut = direct_conv_cut<F>(which, g, with_bias, &us), p = direct_conv_plan<F>(which, g, with_bias);
+        const DirectPlan& c = cut.cut;
+        out[0] = c.variant; out[1] = c.splits; out[2] = c.k_per_split; out[3] = (int64_t)c.ws_bytes;
+        out[4] = (int64_t)(1000 * us); out[5] = (int64_t)(1000 * conv_prepared_us<F>(which, g, with_bias));
+        return p.cut.variant != DIRECT_NONE;
+    }
 }
 
 extern "C" {
@@ -645,9 +681,27 @@ int hostcheck_direct_digits(int fmt, int64_t count, const uint32_t* patterns, ui
     return 0;
 }
 
-// variant, slices, reduction indices of a slice, workspace bytes, limbs of a partial quire
+// variant, slices, reduction indices of a slice, workspace bytes, limbs of a partial quire, estimates of this and of the other kernels in ns
 int hostcheck_direct_plan(int fmt, int64_t M, int64_t N, int64_t K, int64_t* out) {
     PNN_DISPATCH_POSIT(fmt, return host_direct_plan<F>(M, N, K, out))
+    return 0;
+}
+
+// The kernel that takes a product of contiguous operands with the workspace it asks for: 1 to 4 a DirectVariant, 5 the same in slices,
+// 6 posit<32,2> straight from the patterns; 10 digit planes; 20 a thread group per output; posit<8,0>: 21 the 6-bit matrix cores, 22 the int8
+// ones, 23 with 32 x 32 tiles, 24 the 64 x 64 kernel of the vector ALU, 25 the 128 x 128 one, 26 packed operands; 27 byte gather; 30 posit<32,2>
+// in LDS, 31 two buckets of posit<16,1>, 32 operands decoded once, 33 the general kernel.
+int hostcheck_gemm_route(int fmt, int64_t M, int64_t N, int64_t K, int bias) {
+    PNN_DISPATCH_POSIT(fmt, return host_gemm_route<F>(M, N, K, bias != 0))
+    return 0;
+}
+
+// Cut of a convolution pass on the direct kernels: variant, slices, reduction indices of a slice, workspace bytes, estimates of this and of the
+// other kernels in ns.  Returns whether it serves.
+int hostcheck_direct_conv_plan(int fmt, int which, const pnn_conv2d_desc* d, int with_bias, int64_t* out) {
+    ConvGeom g;
+    if (!conv_geom(d, &g)) return 0;
+    PNN_DISPATCH_POSIT(fmt, return host_direct_conv_plan<F>(which, g, with_bias != 0, out))
     return 0;
 }
 
