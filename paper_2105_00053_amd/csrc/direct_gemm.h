@@ -8,6 +8,7 @@ namespace pnn {
 
 constexpr int DIRECT_MAXK = 11904;                  // longest reduction of one workgroup: 11 digit pairs * 2^14 * K < 2^31
 constexpr int64_t DIRECT_EXTENT = (int64_t)1 << 31;  // most bytes of an operand: offsets are 32 bits
+constexpr int64_t GRID_THREADS = (int64_t)1 << 32;   // a dimension of a launch has fewer threads than this
 
 // Waves of a workgroup: 16 x 16 outputs and 8 or 4 waves that share the reduction; 64 x 16 and a wave for each block; 32 x 32 with
 // every pattern converted once.
@@ -41,6 +42,16 @@ inline const DirectCost* direct_cost() {
 template <class F>
 constexpr int direct_shared_groups() { return 2 * F::MAXS + 1 > 62 ? 1 : 2; }  // of four waves; more than eight planes take the LDS of two groups
 
+// Rows and columns of a workgroup, waves that share its reduction; waves.
+struct DirectShape { int tr, tc, kg, waves; };
+template <class F>
+constexpr DirectShape direct_shape(int variant) {
+    return variant == DIRECT_W8 ? DirectShape{16, 16, 8, 8} : variant == DIRECT_W4 ? DirectShape{16, 16, 4, 4} : variant == DIRECT_COL ? DirectShape{64, 16, 1, 4}
+           : DirectShape{32, 32, direct_shared_groups<F>(), 4 * direct_shared_groups<F>()};
+}
+// All tiles are in one dimension of the grid; outputs beyond it go to the kernels that serve otherwise (posit<8,0>, 131072 x 131072: 2^24 tiles of 512 threads).
+inline bool direct_grid_fits(const DirectShape& s, int64_t M, int64_t N) { return ((M + s.tr - 1) / s.tr) * ((N + s.tc - 1) / s.tc) < GRID_THREADS / (64 * s.waves); }
+
 // The fastest way by these estimates, and its us.  posit<32,2> does not have one.
 template <class F>
 inline DirectPlan direct_plan(int64_t M, int64_t N, int64_t K, double* us) {
@@ -54,10 +65,10 @@ inline DirectPlan direct_plan(int64_t M, int64_t N, int64_t K, double* us) {
         return c.base + c.unit * tiles * (double)nkb * 1e-3 + c.step * (double)((kb + kg - 1) / kg) + c.group * tiles * (double)slices * 1e-3;
     };
     if (K <= DIRECT_MAXK) {
-        const int shape[4][3] = {{16, 16, 8}, {16, 16, 4}, {64, 16, 1}, {32, 32, direct_shared_groups<F>()}};
         for (int v = 0; v < 4; ++v) {
-            const double t = estimate(cost[v], shape[v][0], shape[v][1], shape[v][2], nkb, 1);
-            if (t < *us) {
+            const DirectShape s = direct_shape<F>(DIRECT_W8 + v);
+            const double t = estimate(cost[v], s.tr, s.tc, s.kg, nkb, 1);
+            if (t < *us && direct_grid_fits(s, M, N)) {
                 *us = t;
                 best.variant = DIRECT_W8 + v;
             }

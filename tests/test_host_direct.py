@@ -52,3 +52,23 @@ def test_slices_cover_the_reduction_and_fit_the_workspace(hc, fmt):  # noqa: F81
             assert ws == 0
     assert sliced > 50
     assert not hc.hostcheck_direct_plan(CODE["p32"], 64, 64, 64, out)
+
+
+TILE = {1: (16, 16, 512), 2: (16, 16, 256), 3: (64, 16, 256)}  # rows, columns and threads of a workgroup by variant
+
+
+def _threads(fmt, variant, M, N):
+    tr, tc, threads = TILE.get(variant, (32, 32, 256 if fmt in ("p10_2", "p12_2") else 512))
+    return -(-M // tr) * -(-N // tc) * threads
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_outputs_beyond_one_launch_are_left_to_other_kernels(hc, fmt):  # noqa: F811
+    """A dimension of a launch holds fewer than 2^32 threads: 98304 x 98304 and 131072 x 131072 outputs, thin ones, and the largest that are accepted."""
+    hc.hostcheck_direct_plan.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p]
+    out = (ctypes.c_int64 * 7)()
+    for M, N, K in ((98304, 98304, 32), (131072, 131072, 64), (65536, 65536, 64), (65536, 65535, 64), (1 << 20, 1 << 16, 20), (1 << 28, 16, 8), (1 << 28, 10, 40),
+                    (1 << 30, 3, 16), (1 << 20, 1 << 19, 16)):
+        if hc.hostcheck_direct_plan(CODE[fmt], M, N, K, out):
+            assert _threads(fmt, out[0], M, N) < 1 << 32, (M, N, K, out[0])
+    assert hc.hostcheck_direct_plan(CODE[fmt], 8192, 8192, 64, out)
