@@ -60,11 +60,11 @@ inline DirectConvPlan direct_conv_cut(int which, const ConvGeom& g, bool with_bi
     auto tiles = [&](int tr, int tc) { return 1e-3 * (double)((p.M + tr - 1) / tr) * (double)((p.N + tc - 1) / tc); };
     if (which < 2) {
         if (d.K > DIRECT_MAXK) return p;
-        const int shape[4][3] = {{16, 16, 8}, {16, 16, 4}, {64, 16, 1}, {32, 32, direct_shared_groups<F>()}};
         for (int v = 0; v < 4; ++v) {
+            const DirectShape s = direct_shape<F>(DIRECT_W8 + v);
             const DirectCost& c = cost.pass[which][v];
-            const double n = tiles(shape[v][0], shape[v][1]), t = c.base + (c.unit * nkb + c.group) * n + c.step * (double)(((int64_t)nkb + shape[v][2] - 1) / shape[v][2]);
-            if (t < *us) {
+            const double n = tiles(s.tr, s.tc), t = c.base + (c.unit * nkb + c.group) * n + c.step * (double)(((int64_t)nkb + s.kg - 1) / s.kg);
+            if (t < *us && direct_grid_fits(s, d.M, d.N)) {
                 *us = t;
                 p.cut.variant = DIRECT_W8 + v;
             }
@@ -72,6 +72,7 @@ inline DirectConvPlan direct_conv_cut(int which, const ConvGeom& g, bool with_bi
         return p;
     }
     const double n = tiles(16, 16);
+    if (!direct_grid_fits(direct_shape<F>(DIRECT_W8), p.M, p.N)) return p;
     for (int64_t s = 1; s <= 256; s *= 2) {
         const int64_t kps = s == 1 ? d.K : ((d.K + s - 1) / s + 63) / 64 * 64, slices = (d.K + kps - 1) / kps;
         const size_t bytes = slices > 1 ? (size_t)slices * ((size_t)p.M * p.N * Arith<F>::L + p.M + p.N) * sizeof(uint32_t) : 0;

@@ -72,3 +72,26 @@ def test_outputs_beyond_one_launch_are_left_to_other_kernels(hc, fmt):  # noqa: 
         if hc.hostcheck_direct_plan(CODE[fmt], M, N, K, out):
             assert _threads(fmt, out[0], M, N) < 1 << 32, (M, N, K, out[0])
     assert hc.hostcheck_direct_plan(CODE[fmt], 8192, 8192, 64, out)
+
+
+class _Desc(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("N", "C", "H", "W", "K", "R", "S", "pad_h", "pad_w", "stride_h", "stride_w")]
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_passes_beyond_one_launch_are_left_to_other_kernels(hc, fmt):  # noqa: F811
+    """As above: many positions of few channels, whose tiles hold mostly padding, and weight gradients of many channels."""
+    hc.hostcheck_direct_conv_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    out = (ctypes.c_int64 * 6)()
+    layers = [(4000, 1, 500, 500, 1, 3, 3, 1, 1, 1, 1), (1000, 3, 512, 512, 2, 1, 1, 0, 0, 1, 1), (1000, 2, 512, 512, 3, 1, 1, 0, 0, 1, 1),
+              (8000, 1, 364, 364, 1, 1, 1, 0, 0, 1, 1), (1, 1, 1, 1, 300000000, 1, 1, 0, 0, 1, 1), (2, 1, 3, 3, 50000000, 2, 2, 0, 0, 1, 1), (1, 1048575, 1, 1, 1000, 1, 1, 0, 0, 1, 1)]
+    for layer in layers:
+        d = _Desc(*layer)
+        rows = (d.N * (d.H + 2 * d.pad_h - d.R + 1) * (d.W + 2 * d.pad_w - d.S + 1), d.N * d.H * d.W, d.K)
+        for which in range(3):
+            cols = (d.K, d.C, d.C * d.R * d.S + 1)[which]
+            hc.hostcheck_direct_conv_plan(CODE[fmt], which, ctypes.byref(d), 1, out)  # the cut, whether or not it is the one taken
+            if out[0]:
+                assert _threads(fmt, out[0], rows[which], cols) < 1 << 32, (layer, which, out[0])
+    d = _Desc(16, 3, 20, 20, 8, 3, 3, 1, 1, 1, 1)
+    assert all(hc.hostcheck_direct_conv_plan(CODE[fmt], which, ctypes.byref(d), 1, out) or out[0] for which in range(3))
