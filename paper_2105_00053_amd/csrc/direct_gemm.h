@@ -8,7 +8,6 @@ namespace pnn {
 
 constexpr int DIRECT_MAXK = 11904;                  // longest reduction of one workgroup: 11 digit pairs * 2^14 * K < 2^31
 constexpr int64_t DIRECT_EXTENT = (int64_t)1 << 31;  // most bytes of an operand: offsets are 32 bits
-constexpr int64_t GRID_THREADS = (int64_t)1 << 32;   // a dimension of a launch has fewer threads than this
 
 // Waves of a workgroup: 16 x 16 outputs and 8 or 4 waves that share the reduction; 64 x 16 and a wave for each block; 32 x 32 with
 // every pattern converted once.

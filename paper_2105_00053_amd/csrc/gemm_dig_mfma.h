@@ -460,8 +460,9 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 4 : 2)) void dig_gemm_pair_kernel(D
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     // XCD-aware order, as in gemm_p8_mfma.h: each XCD a contiguous run of tiles, walked in bands of 8 tile-rows
     const int nblk = g.tiles_m * g.tiles_n;
-    int lid = blockIdx.x;
-    if ((nblk & 7) == 0) lid = (blockIdx.x & 7) * (nblk >> 3) + (blockIdx.x >> 3);
+    int lid = dig_tile_id();
+    if (lid >= nblk) return;
+    if ((nblk & 7) == 0) lid = (lid & 7) * (nblk >> 3) + (lid >> 3);
     const int band = lid / (8 * g.tiles_n);
     const int band_rows = (g.tiles_m - band * 8) < 8 ? (g.tiles_m - band * 8) : 8;
     const int in_band = lid - band * 8 * g.tiles_n;
@@ -913,7 +914,7 @@ inline hipError_t launch_dig_whole(hipStream_t stream, DigGemmArgs g) {
     }
     if constexpr (NP >= 4) {
         g.tiles_n = (g.N + 31) / 32;
-        hipLaunchKernelGGL(dig_gemm_pair_kernel<NP>, dim3((unsigned)(g.tiles_m * g.tiles_n), (unsigned)g.splits), dim3(256), 0, stream, g);
+        hipLaunchKernelGGL(dig_gemm_pair_kernel<NP>, dig_tile_grid((int64_t)g.tiles_m * g.tiles_n, g.splits), dim3(256), 0, stream, g);
     }
     return hipGetLastError();
 }

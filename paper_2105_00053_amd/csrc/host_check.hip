@@ -696,6 +696,12 @@ int hostcheck_gemm_route(int fmt, int64_t M, int64_t N, int64_t K, int bias) {
     return 0;
 }
 
+// Launch dimensions of the digit kernels for as many tiles and slices
+void hostcheck_dig_tile_grid(int64_t tiles, int slices, int64_t* out) {
+    const dim3 g = dig_tile_grid(tiles, slices);
+    out[0] = g.x; out[1] = g.y; out[2] = g.z;
+}
+
 // Cut of a convolution pass on the direct kernels: variant, slices, reduction indices of a slice, workspace bytes, estimates of this and of the
 // other kernels in ns.  Returns whether it serves.
 int hostcheck_direct_conv_plan(int fmt, int which, const pnn_conv2d_desc* d, int with_bias, int64_t* out) {

@@ -692,6 +692,8 @@ hipError_t launch_split_merge(hipStream_t stream, const SplitWs& ws, int splits,
     return hipGetLastError();
 }
 
+constexpr int64_t GRID_THREADS = (int64_t)1 << 32;  // a dimension of a launch has fewer threads than this
+
 struct GemmPlan {
     int splits;
     int64_t k_per_split;

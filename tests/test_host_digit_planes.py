@@ -117,3 +117,16 @@ def test_rounding_through_binary64(hc, fmt, fout):  # noqa: F811
         for h, l, bias, g in zip(his, los, biases, got.tolist()):
             b = Fraction(0) if bias == 0 else po.decode(bias, f)
             assert g == po.round_to_posit(Fraction(h + l) / Fraction(2) ** qfrac + b, fo), (qfrac, h, l, bias)
+
+
+@pytest.mark.parametrize("tiles", [1, 7, 255, 2 ** 24 - 9, 2 ** 24 - 8, 2 ** 24 - 7, 2 ** 24, 2 ** 25, 2 ** 25 + 1, 2 ** 29])
+def test_every_tile_has_a_workgroup_within_the_limits_of_a_launch(hc, tiles):  # noqa: F811
+    """Fewer than 2^32 threads in a dimension: outputs of 2^35 and more in tiles of 64 x 32 take a second one."""
+    out = (ctypes.c_int64 * 3)()
+    hc.hostcheck_dig_tile_grid.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
+    hc.hostcheck_dig_tile_grid.restype = None
+    hc.hostcheck_dig_tile_grid(tiles, 3, out)
+    x, y, z = out
+    assert x * 256 < 2 ** 32 and y == 3 and z < 65536 and x * z >= tiles and x * z < 2 ** 31
+    assert z == 1 or x % 8 == 0
+    assert z > 1 or x == tiles
