@@ -562,15 +562,19 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 3 : 2)) void dig_conv_kernel(DigCon
     typedef DigConvShape<WY> Sh;
     const bool mark = a.nar.w && __builtin_amdgcn_readfirstlane(a.info->nar[1]);
     // a position's row tiles and the positions that share its taps on one XCD; nothing is shared by a single row of 1 x 1 tiles
-    const int tile = a.tiles_m > 1 || a.K16 > a.Cg ? dig_xcd_order((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x, tm = tile % a.tiles_m, tn = tile / a.tiles_m;
+    const int tiles = a.tiles_m * ((a.P + Sh::TC - 1) / Sh::TC), id = dig_tile_id();
+    if (id >= tiles) return;
+    const int tile = a.tiles_m > 1 || a.K16 > a.Cg ? dig_xcd_order(id, tiles) : id, tm = tile % a.tiles_m, tn = tile / a.tiles_m;
     if (__builtin_amdgcn_readfirstlane(a.info->np) == a.np) dig_conv_tile<NP, WY>(a, tm, tn);
     if (mark) bwd_data_nar_tile<Sh::TR, Sh::TC>(a.nar, a.out, tm * Sh::TR, tn * Sh::TC);
 }
 
+template <int WY>
+inline dim3 dig_conv_grid(int tiles_m, int64_t P) { return dig_tile_grid(tiles_m * ((P + DigConvShape<WY>::TC - 1) / DigConvShape<WY>::TC)); }
+
 template <int NP, int WY>
 inline hipError_t launch_dig_conv_shape(hipStream_t stream, const DigConvArgs& a) {
-    typedef DigConvShape<WY> Sh;
-    hipLaunchKernelGGL((dig_conv_kernel<NP, WY>), dim3((unsigned)(a.tiles_m * ((a.P + Sh::TC - 1) / Sh::TC))), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((dig_conv_kernel<NP, WY>), dig_conv_grid<WY>(a.tiles_m, a.P), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -318,6 +318,20 @@ int host_gemm_route(int64_t M, int64_t N, int64_t K, bool bias) {
 }
 
 template <class F>
+int64_t host_dig_conv_grid(int which, const ConvGeom& g, int64_t* out) {
+    if constexpr (dig_conv_format<F>()) {
+        const DigConvPlan p = dig_conv_plan<F>(which, g);
+        if (!p.ok) return 0;
+        const int tiles_m = p.RBA / p.WY, tc = p.WY == 1 ? DigConvShape<1>::TC : DigConvShape<2>::TC;
+        const dim3 grid = p.WY == 1 ? dig_conv_grid<1>(tiles_m, p.P) : dig_conv_grid<2>(tiles_m, p.P);
+        out[0] = grid.x; out[1] = grid.y; out[2] = grid.z;
+        return tiles_m * ((p.P + tc - 1) / tc);
+    } else {
+        return 0;
+    }
+}
+
+template <class F>
 int host_direct_conv_plan(int which, const ConvGeom& g, bool with_bias, int64_t* out) {
     if constexpr (F::N > 16) return 0;
     else {
@@ -700,6 +714,14 @@ int hostcheck_gemm_route(int fmt, int64_t M, int64_t N, int64_t K, int bias) {
 void hostcheck_dig_tile_grid(int64_t tiles, int slices, int64_t* out) {
     const dim3 g = dig_tile_grid(tiles, slices);
     out[0] = g.x; out[1] = g.y; out[2] = g.z;
+}
+
+// Launch dimensions of the digit kernels' forward or backward-data pass; returns its tiles, 0 if they do not serve it.
+int64_t hostcheck_dig_conv_grid(int fmt, int which, const pnn_conv2d_desc* d, int64_t* out) {
+    ConvGeom g;
+    if (!conv_geom(d, &g)) return 0;
+    PNN_DISPATCH_POSIT(fmt, return host_dig_conv_grid<F>(which, g, out))
+    return 0;
 }
 
 // Cut of a convolution pass on the direct kernels: variant, slices, reduction indices of a slice, workspace bytes, estimates of this and of the

@@ -108,3 +108,18 @@ def test_layers_that_stay_with_the_byte_gather_kernel(hc, fmt, which, layer, ser
     else:
         hc.hostcheck_conv_gather_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
         assert bool(hc.hostcheck_conv_gather_plan(CODE[fmt], which, ctypes.byref(d), (ctypes.c_int64 * 12)())) == served
+
+
+@pytest.mark.parametrize("fmt", ["p8_2", "p12_1", "p16"])
+@pytest.mark.parametrize("which", [0, 1])
+def test_passes_of_many_outputs_fit_a_launch(hc, fmt, which):  # noqa: F811
+    """2^35 outputs and more in tiles of 64 x 32 or 32 x 64: fewer than 2^32 threads in a dimension, and a workgroup for every tile."""
+    hc.hostcheck_dig_conv_grid.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    hc.hostcheck_dig_conv_grid.restype = ctypes.c_int64
+    out = (ctypes.c_int64 * 3)()
+    for n, few, many, h in ((256, 16, 2048, 256), (200, 16, 4099, 300), (1000, 1, 2049, 181), (256, 32, 64, 64)):
+        d = binding.ConvDesc(n, *((few, h, h, many) if which == 0 else (many, h, h, few)), 1, 1, 0, 0, 1, 1)
+        tiles = hc.hostcheck_dig_conv_grid(CODE[fmt], which, ctypes.byref(d), out)
+        x, y, z = out
+        assert tiles > 0 and x * 256 < 1 << 32 and y == 1 and z < 65536 and tiles <= x * z < 1 << 31
+        assert (z > 1) == (h > 100)
