@@ -72,17 +72,28 @@ inline double prepared_us(int64_t M, int64_t N, int64_t K, size_t limit) {
     return -1;
 }
 
+// Most outputs of a reduction of up to half a k block: the block's other half is zeros here, the general kernel stops at a multiple of 16.  us, general
+// kernel and this one, N(0, 1): 2048 x 2048 x 16, posit<16,1>, 51.4 and 74.9, (12,1) 43.8 and 64.1, (12,2) 94 and 132, (10,2) 51 and 70, (10,1)
+// 42.7 and 40.3 (the second operand transposed 1.25 times as long); x 31 (12,1) 57.0 and 57.8, (12,2) 126 and 129, posit<16,1> 70.9 and 68.8, at 4096 x 4096 201 and 220,
+// 498 and 506, 254 and 261, (10,2) 256 and 248, (10,1) 197 and 127; x 33 all faster here (posit<16,1> 1024 x 1024 0.61 of the time, 3000 x 3000 0.76).
+template <class F>
+constexpr int64_t direct_short_outputs(int64_t K) {
+    if (K > 32 || (F::N == 8 && K >= 16)) return INT64_MAX;
+    if (K <= 16 || (F::N == 12 && F::ES == 2)) return (int64_t)1 << 19;
+    return F::N == 10 ? INT64_MAX : (int64_t)1 << 21;
+}
+
 // Products that go to the matrix cores straight from their patterns, in one launch.  Against the kernels that serve otherwise, 500
 // products of 8 to 4096 a side per format: faster by 1.6 (8 bits) and 4.6 to 6.3 times (10 to 16 bits) in the geometric mean, p16 48 x 368 x 340
 // 161 -> 8.4 us, posit<8,0> 850 x 160 x 1632 78 -> 9.7; what stays behind: estimates within a tenth of each other (8 bits with short table
 // entries: a fifth, strided operands cost them more), products of few outputs of the 8-bit formats (a thread group per output: 12 x 11 x 3737 7.8 us
-// there, 9.7 here) and reductions too short for a k block of 64 (1279 x 2486 x 11, p16, 52 and 57).
+// there, 9.7 here) and reductions too short for a k block of 64 (direct_short_outputs).
 template <class F>
 inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit) {
     const DirectPlan none{DIRECT_NONE, 1, 0, 0};
     if constexpr (F::N > 16) return none;
     else {
-        if (K < 16 && M * N > ((int64_t)1 << 19)) return none;
+        if (M * N > direct_short_outputs<F>(K)) return none;
         if (F::N == 8) {
             if (M * N < 2048 || (M * N < 4096 && K > 1024)) return none;
             if (K < 32 && M * N <= ((int64_t)1 << 19) && (F::ES == 2 || N < 32)) return none;

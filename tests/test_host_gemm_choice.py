@@ -1,0 +1,22 @@
+"""Which kernel a product goes to, without a GPU: both sides of each rule at sizes that were timed on both kernels."""
+import ctypes
+
+import pytest
+
+from test_host_logic import CODE, hc  # noqa: F401
+
+DIRECT = (1, 2, 3, 4, 5)  # straight from the patterns
+
+
+def _route(hc, fmt, M, N, K, bias=0):  # noqa: F811
+    hc.hostcheck_gemm_route.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int]
+    return hc.hostcheck_gemm_route(CODE[fmt], M, N, K, bias)
+
+
+@pytest.mark.parametrize("fmt,M,N,K,direct", [
+    ("p12_1", 2048, 2048, 16, False), ("p16", 1024, 1024, 16, False), ("p12_2", 1129, 862, 16, False), ("p10_2", 4096, 4096, 16, False),
+    ("p12_1", 4096, 4096, 24, False), ("p16", 8192, 8192, 31, False), ("p12_2", 2048, 2048, 20, False), ("p12_1", 3000, 3000, 32, False),
+    ("p12_1", 1129, 862, 17, True), ("p16", 1024, 1024, 31, True), ("p10_1", 4096, 4096, 24, True), ("p10_2", 2048, 2048, 17, True),
+    ("p12_2", 500, 500, 16, True), ("p16", 700, 700, 8, True), ("p12_1", 4096, 4096, 48, True), ("p16", 3000, 3000, 33, True), ("p8_2", 3000, 3000, 16, True)])
+def test_short_reductions_of_many_outputs(hc, fmt, M, N, K, direct):  # noqa: F811
+    assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
