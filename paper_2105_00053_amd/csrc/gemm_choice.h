@@ -83,6 +83,13 @@ constexpr int64_t direct_short_outputs(int64_t K) {
     return F::N == 10 ? INT64_MAX : (int64_t)1 << 21;
 }
 
+// posit<8,0> below the reductions of the matrix-core kernels (256): from 3 x 2^20 outputs on the vector ALU's 128 x 128 tiles have a full round of workgroups, and
+// the kernel straight from the patterns, bound by its conversions and stores, has no latency left to save.  us, those tiles and direct: 32 indices,
+// 1448 x 1448 123 and 18 (16 indices 34 and 15), 2048 x 2048 14 and 27, 4096 x 4096 27 and 82, 8192 x 8192 80 and 318; 64, 3191 x 2865 35 and 44, 4096 x 4096 36 and 76; 129,
+// 2048 x 2048 24 and 30, 4096 x 4096 75 and 118; 255, 1500 x 1500 41 and 21, 4096 x 4096 112 and 136.  1190 products of 2^18 to 2^26.5 outputs, three orders:
+// 486 of them go direct, 8 of these are more than 3 % behind (at most 6); without a limit 485 were, by up to 4 times.  Sides of at most 64 do not have those tiles.
+inline bool p8_direct_outputs(int64_t M, int64_t N, int64_t K) { return !use_p8_kernel(M, N) || K >= 256 || M * N <= ((int64_t)3 << 20); }
+
 // Products that go to the matrix cores straight from their patterns, in one launch.  Against the kernels that serve otherwise, 500
 // products of 8 to 4096 a side per format: faster by 1.6 (8 bits) and 4.6 to 6.3 times (10 to 16 bits) in the geometric mean, p16 48 x 368 x 340
 // 161 -> 8.4 us, posit<8,0> 850 x 160 x 1632 78 -> 9.7; what stays behind: estimates within a tenth of each other (8 bits with short table
@@ -97,12 +104,13 @@ inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit
         if (F::N == 8) {
             if (M * N < 2048 || (M * N < 4096 && K > 1024)) return none;
             if (K < 32 && M * N <= ((int64_t)1 << 19) && (F::ES == 2 || N < 32)) return none;
+            if (F::ES == 0 && !p8_direct_outputs(M, N, K)) return none;
         }
         double us;
         const DirectPlan p = direct_plan<F>(M, N, K, &us);
         if (p.variant == DIRECT_NONE || p.ws_bytes > limit) return none;
         const double prepared = prepared_us<F>(M, N, K, limit);
-        // other kernels: the vector ALU at some 10 TMAC/s and less
+        // other kernels: the vector ALU at some 10 TMAC/s and less, thin posit<8,0> products and those of few outputs among them
         if (prepared < 0) return K <= 4096 || (double)M * (double)N * (double)K < 1e9 ? p : none;
         return us < (F::N == 8 && F::ES < 2 ? 0.8 : 0.92) * prepared ? p : none;
     }

@@ -20,3 +20,11 @@ def _route(hc, fmt, M, N, K, bias=0):  # noqa: F811
     ("p12_2", 500, 500, 16, True), ("p16", 700, 700, 8, True), ("p12_1", 4096, 4096, 48, True), ("p16", 3000, 3000, 33, True), ("p8_2", 3000, 3000, 16, True)])
 def test_short_reductions_of_many_outputs(hc, fmt, M, N, K, direct):  # noqa: F811
     assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
+
+
+@pytest.mark.parametrize("M,N,K,direct", [
+    (8192, 8192, 16, False), (8192, 8192, 255, False), (4096, 4096, 32, False), (4096, 4096, 129, False), (2048, 2048, 32, False), (3191, 2865, 64, False),
+    (16384, 16384, 64, False), (2966, 6249, 82, False), (2048, 2048, 129, False), (1448, 1448, 32, True), (1536, 1536, 200, True), (1500, 1500, 255, True),
+    (1024, 1024, 16, True), (100, 20000, 200, True), (20000, 64, 255, True), (65, 65, 129, True)])
+def test_posit8_0_short_reductions_of_many_outputs(hc, M, N, K, direct):  # noqa: F811
+    assert (_route(hc, "p8", M, N, K) in DIRECT) == direct
