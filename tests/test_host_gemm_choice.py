@@ -28,3 +28,10 @@ def test_short_reductions_of_many_outputs(hc, fmt, M, N, K, direct):  # noqa: F8
     (1024, 1024, 16, True), (100, 20000, 200, True), (20000, 64, 255, True), (65, 65, 129, True)])
 def test_posit8_0_short_reductions_of_many_outputs(hc, M, N, K, direct):  # noqa: F811
     assert (_route(hc, "p8", M, N, K) in DIRECT) == direct
+
+
+@pytest.mark.parametrize("fmt", ["p8", "p8_1"])
+@pytest.mark.parametrize("M,N,K,direct", [(48, 48, 4, False), (250, 250, 16, False), (128, 128, 28, False), (700, 700, 8, False), (2823, 6, 32, False), (64, 84, 24, False),
+                                          (48, 48, 32, True), (250, 250, 31, True), (700, 700, 12, True), (64, 120, 400, True), (3936, 12, 224, True)])
+def test_short_reductions_of_few_products(hc, fmt, M, N, K, direct):  # noqa: F811
+    assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
