@@ -56,17 +56,21 @@ inline bool dig_gemm_fits(int64_t M, int64_t N, int64_t K, size_t limit) {
 }
 
 // us of a product on the kernel that takes it if the direct one does not, where that is a matrix-core kernel or, for (10,2) and
-// (12,2), the one with operands decoded once; fitted to products of 2^13 to 2^30 multiply-adds, off by 7 to 15 % (posit<8,0>: rows of
-// odd lengths are decoded byte by byte, 208 x 813 x 1840 18.1 us there and 15.9 from the patterns).  Negative: another kernel.
-// From 2^29 on the matrix-core kernels with digits written once are the faster ones throughout: zero.
+// (12,2), the one with operands decoded once; fitted to products of 2^13 to 2^30 multiply-adds, off by 7 to 15 %.  posit<8,0>: 207 products of 2^25 to
+// 2^29, off by 14 % with 32 x 32 tiles, 10 % with 64 x 64, whose fewer outputs bring longer reductions and slices (811 x 1936 x 256 14.2 us, 6768 x 256 x 272 15.7).
+// Negative: another kernel.  From 2^29 on the matrix-core kernels with digits written once are the faster ones throughout: zero.
 template <class F>
 inline double prepared_us(int64_t M, int64_t N, int64_t K, size_t limit) {
-    const double g = (double)M * (double)N * (double)K / (1 << 30), k = 1e-3 * (double)K;
-    if (F::N == 8 && F::ES == 0) return p8_f6_fits(M, N, K, limit) ? 0 : !p8_mfma_fits(M, N, K) ? -1 : g >= 0.5 ? 0 : p8_mfma_small(M, N) ? 11 + 5 * g + 1.2 * k + ((N | K) & 3 ? 5 : 0) : 17 + 19 * g;
+    const double g = (double)M * (double)N * (double)K / (1 << 30), k = 1e-3 * (double)K, mn = (double)M * (double)N / (1 << 20);
+    if (F::N == 8 && F::ES == 0) {
+        if (p8_f6_fits(M, N, K, limit)) return 0;
+        if (!p8_mfma_fits(M, N, K)) return -1;
+        return g >= 0.5 ? 0 : p8_mfma_small(M, N) ? 7 + 11 * g + 1.2 * k + 1.9 * mn : 15 + 17 * g + 0.2 * k - 5 * mn;
+    }
     if (dig_gemm_fits<F>(M, N, K, limit)) {
         if (g >= 0.5) return 0;
         if (F::N == 8) return F::ES == 1 ? 16 + 15.7 * g + 3.8 * k : 17.5 + 20 * g + 2.4 * k;
-        return 16.3 + 20 * g + 4 * k + 2.7 * (double)M * (double)N / (1 << 20);
+        return 16.3 + 20 * g + 4 * k + 2.7 * mn;
     }
     if (bucket_pre_fits<F>(M, N, K)) return F::N == 10 ? 32 + 353 * g + 8 * k : 38 + 500 * g + 9 * k;
     return -1;

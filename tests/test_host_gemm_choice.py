@@ -35,3 +35,8 @@ def test_posit8_0_short_reductions_of_many_outputs(hc, M, N, K, direct):  # noqa
                                           (48, 48, 32, True), (250, 250, 31, True), (700, 700, 12, True), (64, 120, 400, True), (3936, 12, 224, True)])
 def test_short_reductions_of_few_products(hc, fmt, M, N, K, direct):  # noqa: F811
     assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
+
+
+@pytest.mark.parametrize("M,N,K,route", [(811, 1936, 256, 22), (6768, 256, 272, 22), (704, 2577, 293, 22), (1026, 1359, 347, 22), (512, 512, 2048, 23), (260, 816, 2048, 23)])
+def test_posit8_0_products_that_stay_with_prepared_digits(hc, M, N, K, route):  # noqa: F811
+    assert _route(hc, "p8", M, N, K) == route
