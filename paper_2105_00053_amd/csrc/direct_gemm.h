@@ -87,6 +87,12 @@ inline DirectPlan direct_plan(int64_t M, int64_t N, int64_t K, double* us) {
     return best;
 }
 
+// Whether an estimate (us) is enough below the other kernels'.  It falls behind as products grow: a tenth too long at 2^25 multiply-adds, a fifth too short at 2^28 and
+// more, where rounds of workgroups and the operands' second reading from the caches count.  981 products of (8,1), (8,2), (10,1), (12,1) and posit<16,1>, 2^24 to 2^29.5,
+// timed on both: 16 chosen with a loss of more than 3 % (without this correction and a margin of 8 %, 20 % for (8,1), 42: (10,1) 4560 x 416 x 224 25 us
+// prepared and 34 direct, (12,1) 5431 x 151 x 104 19.4 and 23.3), a mean of 1.4 % lost to the better choice.
+inline bool direct_pays(double us, double macs, double other) { return us * (1 + 0.3 * macs / (1 << 30)) < 0.88 * other; }
+
 // Whether the operands lie within what the kernel's offsets reach; pitches are not known to the plan.
 inline bool direct_extent_fits(int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t elem) {
     const int64_t a = (transA ? K : M), b = (transB ? N : K), most = DIRECT_EXTENT / elem;

@@ -96,8 +96,7 @@ inline bool p8_direct_outputs(int64_t M, int64_t N, int64_t K) { return !use_p8_
 
 // Products that go to the matrix cores straight from their patterns, in one launch.  Against the kernels that serve otherwise, 500
 // products of 8 to 4096 a side per format: faster by 1.6 (8 bits) and 4.6 to 6.3 times (10 to 16 bits) in the geometric mean, p16 48 x 368 x 340
-// 161 -> 8.4 us, posit<8,0> 850 x 160 x 1632 78 -> 9.7; what stays behind: estimates within a tenth of each other (8 bits with short table
-// entries: a fifth, strided operands cost them more), products of few outputs of the 8-bit formats (a thread group per output: 12 x 11 x 3737 7.8 us
+// 161 -> 8.4 us, posit<8,0> 850 x 160 x 1632 78 -> 9.7; what stays behind: estimates close to each other (direct_pays), products of few outputs of the 8-bit formats (a thread group per output: 12 x 11 x 3737 7.8 us
 // there, 9.7 here) and reductions too short for a k block of 64: direct_short_outputs, and of few products of 8 bits, for which a workgroup's table and the barriers around it are
 // the call (posit<8,0>, us in a replayed graph, where launches do not hide it, others and direct: 48 x 48 x 4 2.4 and 3.8, 250 x 250 x 16 3.4 and 4.4, 700 x 700 x 8 4.7 and 5.1, x 12 5.9 and
 // 5.2; (8,1) 128 x 128 x 8 3.1 and 4.4; 250 x 250 x 32 6.1 and 4.6; posit<8,0> 2823 x 6 x 32 4.2 and 5.5, 4194 x 5 x 40 4.6 and 5.6).
@@ -119,7 +118,7 @@ inline DirectPlan direct_gemm_plan(int64_t M, int64_t N, int64_t K, size_t limit
         const double prepared = prepared_us<F>(M, N, K, limit);
         // other kernels: the vector ALU at some 10 TMAC/s and less, thin posit<8,0> products and those of few outputs among them
         if (prepared < 0) return K <= 4096 || (double)M * (double)N * (double)K < 1e9 ? p : none;
-        return us < (F::N == 8 && F::ES < 2 ? 0.8 : 0.92) * prepared ? p : none;
+        return direct_pays(us, (double)M * (double)N * (double)K, prepared) ? p : none;
     }
 }
 

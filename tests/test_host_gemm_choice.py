@@ -40,3 +40,10 @@ def test_short_reductions_of_few_products(hc, fmt, M, N, K, direct):  # noqa: F8
 @pytest.mark.parametrize("M,N,K,route", [(811, 1936, 256, 22), (6768, 256, 272, 22), (704, 2577, 293, 22), (1026, 1359, 347, 22), (512, 512, 2048, 23), (260, 816, 2048, 23)])
 def test_posit8_0_products_that_stay_with_prepared_digits(hc, M, N, K, route):  # noqa: F811
     assert _route(hc, "p8", M, N, K) == route
+
+
+@pytest.mark.parametrize("fmt,M,N,K,direct", [
+    ("p10_1", 4560, 416, 224, False), ("p10_1", 3655, 397, 345, False), ("p10_1", 1872, 1120, 192, False), ("p12_1", 5431, 151, 104, False),
+    ("p12_1", 333, 555, 777, True), ("p16", 48, 368, 340, True), ("p10_1", 512, 512, 512, True), ("p8_1", 512, 512, 512, True), ("p12_2", 512, 512, 512, True)])
+def test_products_between_the_direct_kernel_and_digit_planes(hc, fmt, M, N, K, direct):  # noqa: F811
+    assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
