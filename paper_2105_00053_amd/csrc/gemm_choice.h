@@ -65,7 +65,7 @@ inline double prepared_us(int64_t M, int64_t N, int64_t K, size_t limit) {
     if (F::N == 8 && F::ES == 0) {
         if (p8_f6_fits(M, N, K, limit)) return 0;
         if (!p8_mfma_fits(M, N, K)) return -1;
-        return g >= 0.5 ? 0 : p8_mfma_small(M, N) ? 7 + 11 * g + 1.2 * k + 1.9 * mn : 15 + 17 * g + 0.2 * k - 5 * mn;
+        return g >= 0.5 ? 0 : p8_mfma_small(M, N, K) ? 7 + 11 * g + 1.2 * k + 1.9 * mn : 15 + 17 * g + 0.2 * k - 5 * mn;
     }
     if (dig_gemm_fits<F>(M, N, K, limit)) {
         if (g >= 0.5) return 0;

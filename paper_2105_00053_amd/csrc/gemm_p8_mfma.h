@@ -464,11 +464,13 @@ inline bool p8_mfma_fits(int64_t M, int64_t N, int64_t K) {
     return M >= PM_MIN_MN && N >= PM_MIN_MN && M * N < ((int64_t)1 << 24) && p8_mfma_slices(M, N, K) >= 2;
 }
 
-// Tiles of 32 x 32 for which p8_mfma_small_kernel serves: below, slices give more workgroups (us, slices and it: 64 tiles, K = 16384 25.3 and 32.9; 128,
-// 8192 23.2 and 22.4); above, 64 x 64 read their operands half as often (1536 x 1536 x 1536, 2304 tiles, 31.3 and 33.3).
-inline bool p8_mfma_small(int64_t M, int64_t N) {
+// Tiles of 32 x 32 for which p8_mfma_small_kernel serves: below 128, slices give more workgroups (us, slices and it: 64 tiles, K = 16384 25.3 and 32.9); above
+// 1024, 64 x 64 read their operands half as often (1536 x 1536 x 1536, 2304 tiles, 31.3 and 33.3).  Fewer tiles than compute units leave the rest idle however long the
+// reduction, which slices do not: 256 x 512 (128 tiles), K = 8192 22.7 and 22.0, 16384 31.0 and 33.2, 65536 88 and 114; 480 x 544 (255), 16384 47.8 and
+// 47.2, 32768 80.7 and 84.4; from 256 tiles on it gains at every length (512 x 512, 65536 138 and 133; 640 x 640 496 and 237).
+inline bool p8_mfma_small(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + 31) / 32) * ((N + 31) / 32);
-    return tiles >= 128 && tiles <= 1024;
+    return tiles >= 128 && tiles <= 1024 && (tiles >= 256 || K <= 64 * tiles);
 }
 
 // The largest tile that still gives every compute unit two workgroups; 64 x 64 otherwise.
@@ -515,7 +517,7 @@ inline hipError_t launch_p8_mfma_gemm(hipStream_t stream, int transA, int transB
     const unsigned blocks0 = (unsigned)((l.RBA + 7) / 8) * (unsigned)l.KB, blocks1 = (unsigned)((l.RBB + 7) / 8) * (unsigned)l.KB;
     hipLaunchKernelGGL(p8_digits_kernel<0>, dim3(blocks0 + blocks1), dim3(256), 0, stream, ja, jb, blocks0, verdict);
     PNN_CHECK_LAUNCH();
-    if (!verdict && p8_mfma_small(M, N)) {
+    if (!verdict && p8_mfma_small(M, N, K)) {
         const int tiles_m = (int)((M + 31) / 32), tiles_n = (int)((N + 31) / 32);
         hipLaunchKernelGGL(p8_mfma_small_kernel<8>, dim3((unsigned)(tiles_m * tiles_n)), dim3(512), 0, stream, Ad, Bd, l.RBA, l.RBB, l.KB, bias, C, ldc, fout, (int)M,
                            (int)N, tiles_m, tiles_n);

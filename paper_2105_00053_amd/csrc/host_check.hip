@@ -307,7 +307,7 @@ int host_gemm_route(int64_t M, int64_t N, int64_t K, bool bias) {
     if (dig_gemm_fits<F>(M, N, K, SIZE_MAX) && (F::N != 32 || !bias)) return 10;
     if (F::N == 8 && p8_small_gemm_fits(M, N, K)) return 20;
     if (p8 && p8_f6_fits(M, N, K, SIZE_MAX)) return 21;
-    if (p8 && p8_mfma_fits(M, N, K)) return p8_mfma_small(M, N) ? 23 : 22;
+    if (p8 && p8_mfma_fits(M, N, K)) return p8_mfma_small(M, N, K) ? 23 : 22;
     if (p8 && use_p8_w4(M, N, K)) return 24;
     if (p8 && use_p8_kernel(M, N)) return p8_packed_gemm_fits(M, N, K) ? 26 : 25;
     if (F::N == 8) return 27;

@@ -37,7 +37,9 @@ def test_short_reductions_of_few_products(hc, fmt, M, N, K, direct):  # noqa: F8
     assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
 
 
-@pytest.mark.parametrize("M,N,K,route", [(811, 1936, 256, 22), (6768, 256, 272, 22), (704, 2577, 293, 22), (1026, 1359, 347, 22), (512, 512, 2048, 23), (260, 816, 2048, 23)])
+@pytest.mark.parametrize("M,N,K,route", [(811, 1936, 256, 22), (6768, 256, 272, 22), (704, 2577, 293, 22), (1026, 1359, 347, 22), (512, 512, 2048, 23), (260, 816, 2048, 23),
+                                         (256, 512, 8192, 23), (256, 512, 16384, 22), (256, 512, 65536, 22), (480, 544, 32768, 22), (512, 512, 65536, 23), (640, 640, 8192, 23),
+                                         (1536, 1536, 1536, 22)])
 def test_posit8_0_products_that_stay_with_prepared_digits(hc, M, N, K, route):  # noqa: F811
     assert _route(hc, "p8", M, N, K) == route
 
