@@ -45,4 +45,17 @@ inline void discard_stale_hip_error() { (void)hipGetLastError(); }
         default: { typedef P12_2 F; CALL; } break;            \
     }
 
+// Rounding and conversion beyond Table 1: a kernel with formats known at run time, one element a thread; formats as constants, 16 bytes a thread (rounding of
+// binary32 and the narrowing copies of mixed-precision training); a table in LDS for 8-bit sources.  The last two start later -- a thread's four or eight elements in a row, the
+// table -- and overtake where the first has more than the chip's threads.  us in a replayed graph, first and the other: f32 to (8,2), 100 elements 1.8 and 2.0,
+// 50176 2.0 and 2.4, 300000 2.5 and 2.5, 10^6 4.0 and 3.0, 2^24 41 and 20; (12,2) to (8,2) 100 1.9 and 3.3, 200003 2.4 and 3.4, 700000 3.6 and 3.6, 2 x 10^6 6.8 and 5.0;
+// (8,2) to (12,2) 100 1.9 and 2.1, 131072 2.2 and 2.2, 500000 3.1 and 2.3, 2^24 47 and 10.
+enum MapChoice { MAP_RUNTIME, MAP_TYPED, MAP_TABLE };
+inline MapChoice map_choice(int src, int dst, int64_t n) {
+    const bool rounding = src == PNN_F32 && dst >= PNN_POSIT8_1 && dst <= PNN_POSIT12_2;
+    const bool narrowing = (dst == PNN_POSIT8_1 && (src == PNN_POSIT12_1 || src == PNN_POSIT10_1)) || (dst == PNN_POSIT8_2 && (src == PNN_POSIT12_2 || src == PNN_POSIT10_2));
+    if (rounding || narrowing) return n >= (rounding ? 393216 : 720896) ? MAP_TYPED : MAP_RUNTIME;
+    return elem_size(src) == 1 && n >= 163840 ? MAP_TABLE : MAP_RUNTIME;
+}
+
 }  // namespace pnn

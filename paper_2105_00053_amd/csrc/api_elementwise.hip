@@ -287,26 +287,28 @@ inline MapRT make_map(int src, int dst) {
     return m;
 }
 
-// Formats outside Table 1.  Rounding and the narrowing copies of mixed-precision training with the formats as constants, 8-bit sources through
-// the table, the rest with formats known at run time.  13.4 M elements, us: posit(10,2) to (8,2) 36.9 with formats known at run time, 19.4 as constants; f32 to
+// Formats outside Table 1 (map_choice).  13.4 M elements, us: posit(10,2) to (8,2) 36.9 with formats known at run time, 19.4 as constants; f32 to
 // (8,2) 32.9 and 15.9; (8,2) to (12,2) 36.9, through the table 8.5.
 inline int launch_map_rt(hipStream_t st, int src, int dst, int64_t n, const void* s, void* d) {
-    if (src == PNN_F32) {
+    const MapChoice choice = map_choice(src, dst, n);
+    if (choice == MAP_TYPED && src == PNN_F32) {
         switch (dst) {
             case PNN_POSIT8_1: return launch_map<uint32_t, uint8_t>(st, s, d, n, RoundF32<P8_1>());
             case PNN_POSIT8_2: return launch_map<uint32_t, uint8_t>(st, s, d, n, RoundF32<P8_2>());
             case PNN_POSIT10_1: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P10_1>());
             case PNN_POSIT10_2: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P10_2>());
             case PNN_POSIT12_1: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P12_1>());
-            case PNN_POSIT12_2: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P12_2>());
+            default: return launch_map<uint32_t, uint16_t>(st, s, d, n, RoundF32<P12_2>());
         }
     }
-    if (src == PNN_POSIT12_2 && dst == PNN_POSIT8_2) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P12_2, P8_2>());
-    if (src == PNN_POSIT10_2 && dst == PNN_POSIT8_2) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P10_2, P8_2>());
-    if (src == PNN_POSIT12_1 && dst == PNN_POSIT8_1) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P12_1, P8_1>());
-    if (src == PNN_POSIT10_1 && dst == PNN_POSIT8_1) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P10_1, P8_1>());
+    if (choice == MAP_TYPED) {
+        if (src == PNN_POSIT12_2) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P12_2, P8_2>());
+        if (src == PNN_POSIT10_2) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P10_2, P8_2>());
+        if (src == PNN_POSIT12_1) return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P12_1, P8_1>());
+        return launch_map<uint16_t, uint8_t>(st, s, d, n, PositToPosit<P10_1, P8_1>());
+    }
     const MapRT op = make_map(src, dst);
-    if (elem_size(src) == 1) {
+    if (choice == MAP_TABLE) {
         switch (elem_size(dst)) {
             case 1: return launch_map_p8<uint8_t>(st, s, d, n, op);
             case 2: return launch_map_p8<uint16_t>(st, s, d, n, op);

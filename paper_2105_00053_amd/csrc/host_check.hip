@@ -710,6 +710,9 @@ int hostcheck_gemm_route(int fmt, int64_t M, int64_t N, int64_t K, int bias) {
     return 0;
 }
 
+// The kernel of a rounding or conversion beyond Table 1 (MapChoice)
+int hostcheck_map_choice(int src, int dst, int64_t n) { return map_choice(src, dst, n); }
+
 // Launch dimensions of the digit kernels for as many tiles and slices
 void hostcheck_dig_tile_grid(int64_t tiles, int slices, int64_t* out) {
     const dim3 g = dig_tile_grid(tiles, slices);

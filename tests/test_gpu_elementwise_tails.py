@@ -42,6 +42,31 @@ def test_round(dst, shift):
         assert len(mismatches(to_np(pn.posit_round(d, dst), dst), fast.round_from_float(x, dst))) == 0, n
 
 
+# where the kernels with formats as constants and the table take over, vectors whole and with a remainder
+LARGE = [163839, 163840, 163857, 393215, 393216, 393219, 720895, 720896, 720903]
+
+
+@pytest.mark.parametrize("pair", [("p12_2", "p8_2"), ("p10_2", "p8_2"), ("p12_1", "p8_1"), ("p10_1", "p8_1"), ("p8_1", "p12_1"), ("p8_2", "p8_1"), ("p8", "p10_2"), ("p8_2", "p32")])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_convert_large(pair, shift):
+    src, dst = pair
+    rng = np.random.default_rng(7)
+    for n in LARGE:
+        x = rand_patterns(rng, (n,), src, special=0.1)
+        assert len(mismatches(to_np(pn.posit_convert(_at(x, shift), src, dst), dst), fast.convert(x, src, dst))) == 0, n
+
+
+@pytest.mark.parametrize("dst", ["p8_1", "p8_2", "p10_1", "p10_2", "p12_1", "p12_2"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_round_large(dst, shift):
+    rng = np.random.default_rng(6)
+    for n in LARGE[3:6]:
+        x = (rng.standard_normal(n) * 10.0 ** rng.integers(-12, 12, n)).astype(np.float32)
+        x[rng.integers(n, size=4)] = [np.nan, np.inf, 0.0, -0.0]
+        d = torch.from_numpy(np.concatenate([x[:1].repeat(shift), x])).cuda()[shift:]
+        assert len(mismatches(to_np(pn.posit_round(d, dst), dst), fast.round_from_float(x, dst))) == 0, n
+
+
 @pytest.mark.parametrize("pair", [("p8", "p16", "p8"), ("p16", "p16", None), ("p16", "p32", "p16"), ("p8", "p8", None), ("p32", "p32", "p8")])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_axpy(pair, shift):
