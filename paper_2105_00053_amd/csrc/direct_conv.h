@@ -87,8 +87,21 @@ inline DirectConvPlan direct_conv_cut(int which, const ConvGeom& g, bool with_bi
     return p;
 }
 
+// Most outputs of a forward or backward-data pass with a reduction of up to half a k block, where the general kernel serves it otherwise (see direct_short_outputs; gathered
+// operands cost this kernel more).  us, general and direct: 1 x 1 forward, (12,2), 158 images of 9 channels at 40 x 40 to 54 541 and 784, 285 of 4 at 35 x 35 to 52, stride 2,
+// 164 and 271; backward-data, stride 2, posit<8,0>, 190 of 98 at 37 x 37 to 7 132 and 243, posit<16,1>, 12 of 81 at 53 x 53 to 4 68 and 87; (12,2), 14 of 50 at 39 x 39 to 5
+// 59 and 77; 5 of 104 at 55 x 55 to 13, (10,2), 51 and 53.  Below, of 590 timed passes, two were more than 3 % behind.
+constexpr double CONV_GENERAL_US = 1e9;
+template <class F>
+constexpr int64_t direct_conv_short_outputs(int64_t K) {
+    constexpr bool longest = F::N == 12 && F::ES == 2;  // eleven planes
+    if (K > 32) return INT64_MAX;
+    if (K <= 16) return (int64_t)1 << (longest ? 18 : 19);
+    return longest ? (int64_t)1 << 19 : F::N == 10 ? INT64_MAX : (int64_t)1 << 22;
+}
+
 // us of the kernels that take a pass otherwise: rewritten operands on the matrix cores (fitted to 23 to 58 layers each, off by 6 to 14 %), the
-// byte gather of (8,1) and (8,2), the dot products of posit<8,0> (12 to 25 %, hence a tenth less).  The general kernel, a tenth of their rate and less: 10^9.
+// byte gather of (8,1) and (8,2), the dot products of posit<8,0> (12 to 25 %, hence a tenth less).  The general kernel, a tenth of their rate and less: CONV_GENERAL_US.
 template <class F>
 inline double conv_prepared_us(int which, const ConvGeom& g, bool with_bias) {
     constexpr bool p8 = F::N == 8 && F::ES == 0;
@@ -107,7 +120,7 @@ inline double conv_prepared_us(int which, const ConvGeom& g, bool with_bias) {
         if constexpr (F::N == 8 && F::ES != 0) {
             if (p8_conv_eligible(2, g)) return b8_conv_us<F>(true, (int)d.N, g.K, (int)d.K) - (with_bias ? 0.0 : 8.0);
         }
-        return p8 && p8_conv_eligible(2, g) ? 20 + 1e-9 * 60 * (double)d.M * (double)d.N * P : 1e9;
+        return p8 && p8_conv_eligible(2, g) ? 20 + 1e-9 * 60 * (double)d.M * (double)d.N * P : CONV_GENERAL_US;
     }
     bool planes = false;
     if (p8) planes = p8_conv_eligible(which, g) && p8_conv_mfma_plan(which, g).ok;
@@ -130,7 +143,7 @@ inline double conv_prepared_us(int which, const ConvGeom& g, bool with_bias) {
         const double outputs = 1e-6 * P * (double)d.N, macs = 1e-3 * outputs * (double)d.K, k = 1e-3 * (double)d.K;
         return 0.9 * (which == 1 ? 14.8 + 1.9 * outputs + 19 * macs + 29 * k : g.sh == 1 && g.sw == 1 ? 14 + 1.45 * outputs + 49 * macs + 23 * k : 9.3 + 0.58 * outputs + 28.5 * macs + 100 * k);
     }
-    return 1e9;
+    return CONV_GENERAL_US;
 }
 
 // Layers that go to the matrix cores straight from their patterns.  Against the kernels that serve otherwise, 980 passes of 2^17 to 2^29
@@ -140,7 +153,9 @@ template <class F>
 inline DirectConvPlan direct_conv_plan(int which, const ConvGeom& g, bool with_bias) {
     double us;
     DirectConvPlan p = direct_conv_cut<F>(which, g, with_bias, &us);
-    if (p.cut.variant != DIRECT_NONE && us >= 0.9 * conv_prepared_us<F>(which, g, with_bias)) p.cut = DirectPlan{DIRECT_NONE, 1, 0, 0};
+    if (p.cut.variant == DIRECT_NONE) return p;
+    const double other = conv_prepared_us<F>(which, g, with_bias);
+    if (us >= 0.9 * other || (other == CONV_GENERAL_US && (int64_t)p.M * p.N > direct_conv_short_outputs<F>(p.K))) p.cut = DirectPlan{DIRECT_NONE, 1, 0, 0};
     return p;
 }
 

@@ -123,3 +123,20 @@ def test_passes_of_many_outputs_fit_a_launch(hc, fmt, which):  # noqa: F811
         x, y, z = out
         assert tiles > 0 and x * 256 < 1 << 32 and y == 1 and z < 65536 and tiles <= x * z < 1 << 31
         assert (z > 1) == (h > 100)
+
+
+def _direct(hc, fmt, which, layer, with_bias=0):  # noqa: F811
+    """Whether a layer (N, C, H, K, R, pad, stride) goes straight from its patterns."""
+    n, c, h, k, r, pad, stride = layer
+    hc.hostcheck_direct_conv_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    d = binding.ConvDesc(n, c, h, h, k, r, r, pad, pad, stride, stride)
+    return bool(hc.hostcheck_direct_conv_plan(CODE[fmt], which, ctypes.byref(d), with_bias, (ctypes.c_int64 * 6)()))
+
+
+@pytest.mark.parametrize("fmt,which,layer,direct", [
+    ("p12_2", 0, (158, 9, 40, 54, 1, 0, 1), False), ("p12_2", 0, (285, 4, 35, 52, 1, 0, 2), False), ("p8", 1, (190, 98, 37, 7, 1, 0, 2), False),
+    ("p16", 1, (12, 81, 53, 4, 1, 0, 2), False), ("p12_2", 1, (14, 50, 39, 5, 1, 0, 1), False), ("p12_2", 1, (198, 104, 24, 20, 1, 0, 1), False),
+    ("p12_2", 0, (8, 3, 28, 6, 5, 2, 1), True), ("p16", 0, (5, 3, 20, 20, 1, 0, 2), True), ("p10_2", 0, (64, 3, 32, 32, 3, 1, 1), True), ("p16", 1, (32, 6, 14, 16, 5, 0, 2), True)])
+def test_short_reductions_of_many_outputs_stay_with_the_general_kernel(hc, fmt, which, layer, direct):  # noqa: F811
+    """Both sides of the rule at layers timed on both kernels."""
+    assert _direct(hc, fmt, which, layer) == direct
