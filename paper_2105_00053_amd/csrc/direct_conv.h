@@ -147,15 +147,16 @@ inline double conv_prepared_us(int which, const ConvGeom& g, bool with_bias) {
 }
 
 // Layers that go to the matrix cores straight from their patterns.  Against the kernels that serve otherwise, 980 passes of 2^17 to 2^29
-// multiply-adds over nine formats: 0.51 of their time in the geometric mean ((10,1) to (12,2) 0.22, 196 of posit<8,0> 0.61, four of these
-// slower by 4 to 7 %: 14.5 us and 15.5).  An estimate has to be a tenth below the other one, about what either is off by.
+// multiply-adds over nine formats: 0.51 of their time in the geometric mean ((10,1) to (12,2) 0.22, 196 of posit<8,0> 0.61).  direct_pays, as for products: of 1800 passes timed
+// on all kernels 1414 go direct, 7 of these more than 3 % slower than before there was this kernel (with an uncorrected estimate a tenth below the other 13, up to 21 %: posit(10,1)
+// backward-weight of 196 images of 50 channels at 34 x 34 to 8, 3 x 3, 110 us and 133).
 template <class F>
 inline DirectConvPlan direct_conv_plan(int which, const ConvGeom& g, bool with_bias) {
     double us;
     DirectConvPlan p = direct_conv_cut<F>(which, g, with_bias, &us);
     if (p.cut.variant == DIRECT_NONE) return p;
     const double other = conv_prepared_us<F>(which, g, with_bias);
-    if (us >= 0.9 * other || (other == CONV_GENERAL_US && (int64_t)p.M * p.N > direct_conv_short_outputs<F>(p.K))) p.cut = DirectPlan{DIRECT_NONE, 1, 0, 0};
+    if (!direct_pays(us, (double)p.M * (double)p.N * (double)p.K, other) || (other == CONV_GENERAL_US && (int64_t)p.M * p.N > direct_conv_short_outputs<F>(p.K))) p.cut = DirectPlan{DIRECT_NONE, 1, 0, 0};
     return p;
 }
 

@@ -140,3 +140,11 @@ def _direct(hc, fmt, which, layer, with_bias=0):  # noqa: F811
 def test_short_reductions_of_many_outputs_stay_with_the_general_kernel(hc, fmt, which, layer, direct):  # noqa: F811
     """Both sides of the rule at layers timed on both kernels."""
     assert _direct(hc, fmt, which, layer) == direct
+
+
+@pytest.mark.parametrize("fmt,which,layer,direct", [
+    ("p10_1", 2, (196, 50, 34, 8, 3, 0, 1), False), ("p12_1", 2, (21, 30, 45, 44, 3, 0, 1), False), ("p8_1", 2, (189, 41, 31, 5, 5, 0, 1), False),
+    ("p12_1", 2, (133, 66, 21, 146, 1, 0, 1), False), ("p10_1", 2, (124, 7, 53, 37, 3, 0, 1), False), ("p8_1", 2, (102, 33, 32, 13, 5, 0, 1), False),
+    ("p8", 2, (64, 6, 14, 16, 5, 0, 1), True), ("p16", 2, (64, 1, 28, 6, 5, 2, 1), True), ("p12_1", 2, (32, 16, 12, 16, 3, 1, 1), True), ("p8_2", 2, (64, 6, 14, 16, 5, 0, 1), True)])
+def test_weight_gradients_between_the_direct_kernel_and_digit_planes(hc, fmt, which, layer, direct):  # noqa: F811
+    assert _direct(hc, fmt, which, layer, 1) == direct
