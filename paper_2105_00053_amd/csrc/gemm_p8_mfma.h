@@ -464,13 +464,17 @@ inline bool p8_mfma_fits(int64_t M, int64_t N, int64_t K) {
     return M >= PM_MIN_MN && N >= PM_MIN_MN && M * N < ((int64_t)1 << 24) && p8_mfma_slices(M, N, K) >= 2;
 }
 
-// Tiles of 32 x 32 for which p8_mfma_small_kernel serves: below 128, slices give more workgroups (us, slices and it: 64 tiles, K = 16384 25.3 and 32.9); above
-// 1024, 64 x 64 read their operands half as often (1536 x 1536 x 1536, 2304 tiles, 31.3 and 33.3).  Fewer tiles than compute units leave the rest idle however long the
-// reduction, which slices do not: 256 x 512 (128 tiles), K = 8192 22.7 and 22.0, 16384 31.0 and 33.2, 65536 88 and 114; 480 x 544 (255), 16384 47.8 and
-// 47.2, 32768 80.7 and 84.4; from 256 tiles on it gains at every length (512 x 512, 65536 138 and 133; 640 x 640 496 and 237).
+// Tiles of 32 x 32 for which p8_mfma_small_kernel serves, by 2559 products timed with it and with 64 x 64 tiles (us, 64 x 64 and it).  Below 128, slices of those give more
+// workgroups (64 tiles, K = 16384 25.3 and 32.9).  Where the 64 x 64 tiles come in slices (fewer than 81) they load all compute units evenly at any length; up to 256 tiles this kernel
+// saves the merge and gives it back over a long reduction, with idle units (256 x 512, 128 tiles, K = 8192 22.7 and 22.0, 65536 88 and 114; 224 x 1152, 252 tiles, 15600 41 and
+// 59) unless there is one for each (512 x 512, 65536 138 and 133); beyond 256 some compute units have twice the work of others (282 tiles, K = 16496 46 and 81; 3000 and
+// less: 87 products 20 % faster, the slowest 3 % behind).  Where they come whole, up to 768 tiles at any length (640 x 640 x 8192 71.7 and 35.6, x 65536 496 and 237), then 64 x 64
+// read their operands half as often: 769 to 1024 at 3072 and less 18 % faster, none behind; above 6000 every third behind, by up to 30 %.
 inline bool p8_mfma_small(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + 31) / 32) * ((N + 31) / 32);
-    return tiles >= 128 && tiles <= 1024 && (tiles >= 256 || K <= 64 * tiles);
+    if (tiles < 128 || tiles > 1024) return false;
+    if (((M + 63) / 64) * ((N + 63) / 64) >= PM_MIN_TILES) return tiles <= 768 || K <= 3072;
+    return tiles > 256 ? K <= 3072 : tiles == 256 || K <= (64 * tiles < 8192 ? 64 * tiles : 8192);
 }
 
 // The largest tile that still gives every compute unit two workgroups; 64 x 64 otherwise.

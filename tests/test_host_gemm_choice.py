@@ -49,3 +49,10 @@ def test_posit8_0_products_that_stay_with_prepared_digits(hc, M, N, K, route):  
     ("p12_1", 333, 555, 777, True), ("p16", 48, 368, 340, True), ("p10_1", 512, 512, 512, True), ("p8_1", 512, 512, 512, True), ("p12_2", 512, 512, 512, True)])
 def test_products_between_the_direct_kernel_and_digit_planes(hc, fmt, M, N, K, direct):  # noqa: F811
     assert (_route(hc, fmt, M, N, K) in DIRECT) == direct
+
+
+@pytest.mark.parametrize("M,N,K,route", [
+    (187, 1504, 16496, 22), (480, 608, 49792, 22), (224, 1152, 15600, 22), (219, 992, 9008, 22), (896, 320, 4096, 22), (1000, 1000, 8192, 22), (512, 512, 40000, 23),
+    (320, 992, 3000, 23), (224, 1216, 2048, 23), (672, 471, 22752, 23), (544, 539, 30144, 23), (768, 1024, 8192, 23), (1000, 1000, 3000, 23), (1024, 1024, 3072, 23)])
+def test_posit8_0_tiles_of_32_x_32_or_slices(hc, M, N, K, route):  # noqa: F811
+    assert _route(hc, "p8", M, N, K) == route
