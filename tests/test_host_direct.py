@@ -95,3 +95,17 @@ def test_passes_beyond_one_launch_are_left_to_other_kernels(hc, fmt):  # noqa: F
                 assert _threads(fmt, out[0], rows[which], cols) < 1 << 32, (layer, which, out[0])
     d = _Desc(16, 3, 20, 20, 8, 3, 3, 1, 1, 1, 1)
     assert all(hc.hostcheck_direct_conv_plan(CODE[fmt], which, ctypes.byref(d), 1, out) or out[0] for which in range(3))
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_sums_of_the_longest_reduction_stay_within_int32(hc, fmt):  # noqa: F811
+    """A sum has at most one pair of digits per plane, each digit at most 128 in magnitude; also for two planes."""
+    hc.hostcheck_direct_digits.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
+    n = 1 << BITS[fmt]
+    pats, words = np.arange(n, dtype=np.uint32), np.zeros((n, 3), dtype=np.uint32)
+    planes = hc.hostcheck_direct_digits(CODE[fmt], n, _p(pats), _p(words))
+    assert planes == {"p8": 2, "p8_1": 4, "p8_2": 7, "p10_1": 5, "p10_2": 9, "p12_1": 6, "p12_2": 11, "p16": 8}[fmt]
+    assert 11904 * planes * 2 ** 14 < 2 ** 31
+    out = (ctypes.c_int64 * 7)()
+    hc.hostcheck_direct_plan.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p]
+    assert hc.hostcheck_direct_plan(CODE[fmt], 300, 300, 11904, out) and not hc.hostcheck_direct_plan(CODE[fmt], 300, 300, 11905, out)
