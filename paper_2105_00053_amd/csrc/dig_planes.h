@@ -368,12 +368,12 @@ __device__ __forceinline__ void dig_mma_below(int g0, uint32_t ma, uint32_t mb, 
 }
 
 // Launch of one workgroup of 256 threads per tile and slice (y); z counts what one dimension does not hold (2^36 outputs in tiles of 64 x 32 are 2^25 workgroups).
+constexpr int64_t DIG_TILES_X = ((GRID_THREADS - 1) / 256) & ~(int64_t)7;  // whole rounds over the XCDs
 inline dim3 dig_tile_grid(int64_t tiles, int slices = 1) {
-    constexpr int64_t MOST = ((GRID_THREADS - 1) / 256) & ~(int64_t)7;  // whole rounds over the XCDs
-    return dim3((unsigned)(tiles < MOST ? tiles : MOST), (unsigned)slices, (unsigned)((tiles + MOST - 1) / MOST));
+    return dim3((unsigned)(tiles < DIG_TILES_X ? tiles : DIG_TILES_X), (unsigned)slices, (unsigned)((tiles + DIG_TILES_X - 1) / DIG_TILES_X));
 }
 // This workgroup's tile in launch order; from the number of tiles on there is none.
-__device__ __forceinline__ int dig_tile_id() { return (int)(blockIdx.x + blockIdx.z * gridDim.x); }
+__device__ __forceinline__ int dig_tile_id() { return (int)(blockIdx.x + blockIdx.z * (unsigned)DIG_TILES_X); }
 
 // Workgroup `id` of `total` in an order that gives each of the eight XCDs, which take workgroups in turn, a contiguous run, so that
 // neighbours share an L2.

@@ -438,7 +438,8 @@ __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : 2)) void dig_gemm_kernel(D
 // other workgroups multiply meanwhile.  Blocks of 32 x 32 outputs per wave left one wave to a SIMD with eight planes, which waited for every barrier, LDS read
 // and rounding alone.  us a call, 1 % of extremes, 32 x 32 -> now: posit<16,1> 1024^3 65.5 and 58.7, 971 x 1044 x 976 111 and 81, 4096^3 2697 and 2145,
 // posit(8,2) 512 x 512 x 8192 274 and 172; posit<32,2>, N(0, 1), 1024^3 52.7 and 47.5.
-template <int NP>
+// MANY: tiles in two dimensions of the launch.
+template <int NP, bool MANY>
 __global__ __launch_bounds__(256, (NP <= 4 ? 4 : 2)) void dig_gemm_pair_kernel(DigGemmArgs g) {
     typedef DigGroups<NP> D;
     constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), TR = 64, TC = 32;
@@ -460,8 +461,8 @@ __global__ __launch_bounds__(256, (NP <= 4 ? 4 : 2)) void dig_gemm_pair_kernel(D
     const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     // XCD-aware order, as in gemm_p8_mfma.h: each XCD a contiguous run of tiles, walked in bands of 8 tile-rows
     const int nblk = g.tiles_m * g.tiles_n;
-    int lid = dig_tile_id();
-    if (lid >= nblk) return;
+    int lid = MANY ? dig_tile_id() : (int)blockIdx.x;
+    if (MANY && lid >= nblk) return;
     if ((nblk & 7) == 0) lid = (lid & 7) * (nblk >> 3) + (lid >> 3);
     const int band = lid / (8 * g.tiles_n);
     const int band_rows = (g.tiles_m - band * 8) < 8 ? (g.tiles_m - band * 8) : 8;
@@ -914,7 +915,9 @@ inline hipError_t launch_dig_whole(hipStream_t stream, DigGemmArgs g) {
     }
     if constexpr (NP >= 4) {
         g.tiles_n = (g.N + 31) / 32;
-        hipLaunchKernelGGL(dig_gemm_pair_kernel<NP>, dig_tile_grid((int64_t)g.tiles_m * g.tiles_n, g.splits), dim3(256), 0, stream, g);
+        const dim3 grid = dig_tile_grid((int64_t)g.tiles_m * g.tiles_n, g.splits);
+        if (grid.z > 1) hipLaunchKernelGGL((dig_gemm_pair_kernel<NP, true>), grid, dim3(256), 0, stream, g);
+        else hipLaunchKernelGGL((dig_gemm_pair_kernel<NP, false>), grid, dim3(256), 0, stream, g);
     }
     return hipGetLastError();
 }
