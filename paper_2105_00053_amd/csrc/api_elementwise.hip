@@ -7,9 +7,10 @@
 
 namespace pnn {
 
-// One launch: thread i < nvec a vector of V elements, the threads behind them one element each of what is left (all of them where a
-// pointer is not aligned, nvec = 0).  A launch of their own for the last elements cost 3 us of a call's 8 (posit<8,0> -> <16,1>, 892177
-// elements: 8.4 us; now 5.2; f32 -> posit<16,1>, 13400003: 19.1 and 17.3).
+// One launch: thread i < nvec a vector of V elements, the threads behind them one element each of what is left.  A launch of their own for the last elements cost 3 us of
+// a call's 8 (posit<8,0> -> <16,1>, 892177 elements: 8.4 us; now 5.2; f32 -> posit<16,1>, 13400003: 19.1 and 17.3).  Where a pointer is not aligned all elements are vectors
+// of one: as the elements behind no vector at all they shared the registers of the vector's code (us, so and with V = 1: axpy posit<8,0>, 16 549 120 elements, 63 and 55; f32 ->
+// posit<8,0>, 330801, 2.3 and 2.1).
 template <class TS, class TD, int V, class Op>
 __global__ __launch_bounds__(256) void map_vec_kernel(const TS* __restrict__ src, TD* __restrict__ dst, int64_t nvec, int64_t n, Op op) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -64,7 +65,11 @@ int launch_map(hipStream_t st, const void* src, void* dst, int64_t n, Op op) {
     constexpr int WIDE = sizeof(TS) > sizeof(TD) ? sizeof(TS) : sizeof(TD);
     constexpr int V = 16 / WIDE;
     if (n <= 0) return PNN_OK;
-    const int64_t nvec = aligned(src, sizeof(TS) * V) && aligned(dst, sizeof(TD) * V) ? n / V : 0;
+    if (!aligned(src, sizeof(TS) * V) || !aligned(dst, sizeof(TD) * V)) {
+        hipLaunchKernelGGL((map_vec_kernel<TS, TD, 1, Op>), dim3(map_blocks(n, n, 1)), dim3(256), 0, st, (const TS*)src, (TD*)dst, n, n, op);
+        return hip_status(hipGetLastError());
+    }
+    const int64_t nvec = n / V;
     hipLaunchKernelGGL((map_vec_kernel<TS, TD, V, Op>), dim3(map_blocks(nvec, n, V)), dim3(256), 0, st, (const TS*)src, (TD*)dst, nvec, n, op);
     return hip_status(hipGetLastError());
 }
@@ -107,7 +112,12 @@ int launch_axpy(hipStream_t st, uint32_t alpha, int64_t n, const void* x, void* 
     PositToPosit<FY, FC> cp;
     if (n <= 0) return PNN_OK;
     const bool ok = aligned(x, sizeof(TX) * V) && aligned(y, sizeof(TY) * V) && (!yc || aligned(yc, sizeof(TC) * V));
-    const int64_t nvec = ok ? n / V : 0;
+    if (!ok) {
+        hipLaunchKernelGGL((axpy_vec_kernel<TX, TY, TC, 1, Axpy<FX, FY>, PositToPosit<FY, FC>>), dim3(map_blocks(n, n, 1)), dim3(256), 0, st, (const TX*)x, (TY*)y, (TC*)yc, n,
+                           n, op, cp);
+        return hip_status(hipGetLastError());
+    }
+    const int64_t nvec = n / V;
     hipLaunchKernelGGL((axpy_vec_kernel<TX, TY, TC, V, Axpy<FX, FY>, PositToPosit<FY, FC>>), dim3(map_blocks(nvec, n, V)), dim3(256), 0, st, (const TX*)x,
                        (TY*)y, (TC*)yc, nvec, n, op, cp);
     return hip_status(hipGetLastError());
