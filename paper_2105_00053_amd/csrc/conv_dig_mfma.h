@@ -40,7 +40,7 @@ struct DigConvPlan {
     int sh, sw;
     int WK, WC;                // the weight tensor is [WK][WC][R][S]
     int Cg, K16, KB;           // channel groups of 16, reduction length in 16s, k blocks of 32
-    int WY, RBA;               // waves along the rows, padded row blocks of the weights
+    int WY, RBA;               // row blocks of 32 of a workgroup (DigConvShape), padded row blocks of the weights
     int64_t P;                 // output positions NI * HO * WO
     size_t w_bytes, act_bytes;
     // behind the planes: 256 bytes of zeros, 256 of decision, the scan's results
@@ -51,8 +51,9 @@ struct DigConvPlan {
 // like b8_conv_us to layers whose operands four planes hold (off by 8 to 19 %).  Short reductions and one or two input channels
 // under a large filter stay there: posit(8,1) backward-data of 64 images of 16 channels at 16 x 16 to 16, 1 x 1, 12.7 us there
 // and 19.6 here; forward of 32 images of 1 channel at 32 x 32 to 32, 7 x 7, 20 and 36.  The factors are those that lost least
-// over 2370 layers timed on both: 15 of 1675 backward-data passes more than 6 % slower than here, 27 than there (estimates
-// alike: 28 and 14; at 1.05 and 1.2: 78 and 8; posit(8,2), 24 images of 13 channels at 14 x 14 to 9, 5 x 5, 43 there and 26 here).  Weights over
+// over 2370 layers timed on both with blocks of 32 x 128 outputs: 15 of 1675 backward-data passes more than 6 % slower than here, 27 than there (estimates
+// alike: 28 and 14; at 1.05 and 1.2: 78 and 8; posit(8,2), 24 images of 13 channels at 14 x 14 to 9, 5 x 5, 43 there and 26 here).  With the blocks of 16 x 32 per wave the line
+// lies where it did: of 1685 layers of all three passes timed on both, 10 more than 3 % slower than on the other, a mean of 0.1 % lost.  Weights over
 // most of the range of posit(8,2) take the wide kernel, at up to twice the time.
 template <class F>
 inline bool dig_conv_pays(const DigConvPlan& p) {
@@ -292,9 +293,9 @@ struct DigConvShape {
 // Four planes: a ring of two pairs, the next one copied while a pair is multiplied.  Eight planes: room for one pair, whose 24 operand
 // quads go to registers before the next pair's copies start; the other workgroup multiplies meanwhile.
 // Prologue and rounding weigh as much as the matrix instructions of a short reduction: four planes are all multiplied, and outputs of at most 16 bits
-// are rounded through binary64 in registers and stored from there (128 images of 32 channels at 32 x 32, posit(8,2), 3 x 3 to 32 channels: 31 us, with
-// integers of 96 bits through LDS 36).  Eight planes without NaR: only the planes that hold digits (weights over most of the range of posit(8,2) 46 us, all 8 x 8
-// pairs 61).  us a call, 32 x 32 -> now: posit<16,1> backward-data of 100 images of 30 channels at 27 x 27 to 45, 3 x 3, 54.9 and 45.9; forward of 46 of 48 at
+// are rounded through binary64 in registers and stored from there (the kernel alone with blocks of 32 x 32, 128 images of 32 channels at 32 x 32, posit(8,2), 3 x 3 to 32
+// channels: 31 us, with integers of 96 bits through LDS 36).  Eight planes without NaR: only the planes that hold digits (with the same blocks, weights over most of the range
+// of posit(8,2) 46 us, all 8 x 8 pairs 61; the call then and now, patterns at random for weights, 119 and 90).  us a call, 32 x 32 -> now: posit<16,1> backward-data of 100 images of 30 channels at 27 x 27 to 45, 3 x 3, 54.9 and 45.9; forward of 46 of 48 at
 // 22 x 22 to 39, 5 x 5, stride 2, 49.0 and 34.0.  An odd last block (dig_single_mma; beside a block of
 // zeros before): posit(12,1) backward-data of 10 of 48 at 43 x 43 to 24, 3 x 3, 25.0 and 23.6.
 // SHORT, four planes and at most two k blocks: nothing follows the one pair, so LDS has room for it alone (26 KB) and a fourth workgroup shares the CU.  Such a
@@ -648,8 +649,8 @@ struct DigConvBwPlan {
     int M, N, crs;             // outputs: K x CRS, or K x (CRS + 1) with the bias gradient as the last column
     int NG;                    // groups of 16 images
     int K16;                   // reduction length in 16s: OH OW NG
-    int WY, RBA, KB;           // waves along the rows, row blocks of dy's planes, k blocks (= splits * kb_per_split)
-    int tiles_m, tiles_n;
+    int WY, RBA, KB;           // row blocks of 32 of a workgroup (DigConvShape), row blocks of dy's planes, k blocks (= splits * kb_per_split)
+    int tiles_m, tiles_n;      // column tiles twice as wide as a workgroup's
     int splits, kb_per_split;
     size_t a_bytes, x_bytes, ones_bytes, part_bytes;
     // behind the planes and the blocks of ones: 256 bytes of zeros, 256 of decision, the scan's results, the partial sums
@@ -691,7 +692,7 @@ inline DigConvBwPlan dig_conv_bw_plan(const ConvGeom& g, bool with_bias) {
     p.tiles_n = (p.N + tc - 1) / tc;
     p.RBA = p.tiles_m * p.WY;
     const int64_t kb_total = (k16 + 1) / 2, tiles = (int64_t)p.tiles_m * p.tiles_n;
-    int64_t splits = (512 + tiles - 1) / tiles;                    // about two workgroups per compute unit
+    int64_t splits = (512 + tiles - 1) / tiles;                    // 512 pairs of workgroups: four to a compute unit
     if (splits > kb_total / 8) splits = kb_total / 8;              // at least 8 k blocks per slice
     if (splits < (kb_total + 510) / 511) splits = (kb_total + 510) / 511;  // and at most what int32 sums hold
     if (splits < 1) splits = 1;

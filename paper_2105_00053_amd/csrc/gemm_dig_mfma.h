@@ -227,9 +227,10 @@ __device__ __forceinline__ void dig_round_column(const DigGemmArgs& g, int at, i
 // S - 1 blocks ahead.  The waves of a workgroup leave each barrier together and would all wait for their LDS reads
 // together, so the operand registers of a step are read during the step before (two sets).  What a step costs beside its
 // matrix instructions is scalar code, hence the straight-line loop over a fixed set of planes (DigGroups).  Registers decide
-// how many waves a SIMD holds: 5 sums three, 7 sums two; for more see dig_gemm_pair_kernel.
+// how many waves a SIMD holds: 5 sums three, 7 sums two; more planes go to dig_gemm_pair_kernel.
 template <int NP, int KG, int S>
 __global__ __launch_bounds__(256 * KG, (NP <= 3 ? 3 : 2)) void dig_gemm_kernel(DigGemmArgs g) {
+    static_assert(NP == 3 || NP == 4, "planes whose sums leave room for two waves on a SIMD");
     typedef DigGroups<NP> D;
     constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>();
     constexpr int RPB = 4 * NP;  // runs of 1 KB per k block: two row blocks and two column blocks of NP planes
