@@ -8,8 +8,8 @@ gradient included (posit_cross_entropy in the posit<16,1> loss format).  The
 kernels of a step are issued on one stream (moving the weight-gradient branch
 to a second stream was measured and lost: cross-stream waits cost more than
 they hide).  GraphedStep captures the whole step once as a HIP graph and
-replays it: the LeNet-5-shaped step, about fifty short kernels, is bound by
-the host-side launches and runs 1.6x faster replayed; the CifarNet-shaped
+replays it: the LeNet-5-shaped step, about forty-five short kernels, is bound by
+the host-side launches and runs 1.4 to 1.5x as fast replayed; the CifarNet-shaped
 step is bound by its kernels and gains nothing.
 
 Formats (mixed precision of Sec. 3.3 / Fig. 3) are those of the Net: activations, weight
