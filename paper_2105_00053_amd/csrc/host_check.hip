@@ -293,7 +293,6 @@ int host_direct_plan(int64_t M, int64_t N, int64_t K, int64_t* out) {
     double us;
     const DirectPlan p = direct_plan<F>(M, N, K, &us);
     out[0] = p.variant; out[1] = p.splits; out[2] = p.k_per_split; out[3] = (int64_t)p.ws_bytes; out[4] = Arith<F>::L;
-    out[5] = (int64_t)(1000 * us); out[6] = (int64_t)(1000 * prepared_us<F>(M, N, K, SIZE_MAX));
     return p.variant != DIRECT_NONE;
 }
 
@@ -695,7 +694,7 @@ int hostcheck_direct_digits(int fmt, int64_t count, const uint32_t* patterns, ui
     return 0;
 }
 
-// variant, slices, reduction indices of a slice, workspace bytes, limbs of a partial quire, estimates of this and of the other kernels in ns
+// variant, slices, reduction indices of a slice, workspace bytes, limbs of a partial quire
 int hostcheck_direct_plan(int fmt, int64_t M, int64_t N, int64_t K, int64_t* out) {
     PNN_DISPATCH_POSIT(fmt, return host_direct_plan<F>(M, N, K, out))
     return 0;
