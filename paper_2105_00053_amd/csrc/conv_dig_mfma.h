@@ -298,25 +298,24 @@ struct DigConvShape {
 // of posit(8,2) 46 us, all 8 x 8 pairs 61; the call then and now, patterns at random for weights, 119 and 90).  us a call, 32 x 32 -> now: posit<16,1> backward-data of 100 images of 30 channels at 27 x 27 to 45, 3 x 3, 54.9 and 45.9; forward of 46 of 48 at
 // 22 x 22 to 39, 5 x 5, stride 2, 49.0 and 34.0.  An odd last block (dig_single_mma; beside a block of
 // zeros before): posit(12,1) backward-data of 10 of 48 at 43 x 43 to 24, 3 x 3, 25.0 and 23.6.
-// SHORT, four planes and at most two k blocks: nothing follows the one pair, so LDS has room for it alone (26 KB) and a fourth workgroup shares the CU.  Such a
-// workgroup is a chain of latencies, table, copies, store, and what hides them is its number: posit(12,1), backward-data of 74 images of 4 channels at 51 x 51 to
-// 21, 1 x 1, 43.7 us with blocks of 32 x 32, 48.1 with three workgroups, 43.5 with four; 1763 such layers 1.00 of the 32 x 32 blocks' time with three (680 more than
-// 3 % slower), 0.96 with four (29).  Beyond two blocks the loop's registers for a fourth spill: five blocks, 0.93 with three and 0.97 with four.
-// What is left: between 768 and 1024 workgroups of 32 x 64 with three to eight blocks the last of two rounds is short (62 of 97 layers 3 to 9 % slower than with the
-// 32 x 32 blocks, which held 1024 such halves at once).
-template <int NP, int WY, bool SHORT>
+// ONE: four planes with one pair in LDS (30 KB, read and refilled as with eight planes) and a fourth workgroup on the CU, whose registers the bias, fetched behind the loop, leaves
+// free.  us a call, 32 x 32 blocks, two pairs, one: posit(12,1) backward-data of 74 images of 4 channels at 51 x 51 to 21, 1 x 1, 43.7, 48.1, 43.5; 3490 passes of
+// three k blocks and more 0.82 of the time of the 32 x 32 blocks in the mean, 0.85 with two pairs, 1 and 107 of them more than 3 % slower than with those (most where 768
+// workgroups, three to a CU, leave a short second round); 1763 of one or two k blocks 0.94 and 1.00, 9 and 680.  Two pairs stay where one round of three holds the launch and the reduction is long enough for its copies to
+// run ahead: up to 768 workgroups and more than 8 k blocks, 19 to 48 blocks 2 % and longer ones 4 % faster than with one pair.
+template <int NP, int WY, bool ONE>
 __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int tn) {
     typedef DigConvShape<WY> Sh;
     constexpr int NC = 2 * NP - 1, L = dig_limbs<NP>(), NA = Sh::NA, NB = Sh::NB, TR = Sh::TR, TC = Sh::TC, WAVES = 4, THREADS = 256;
-    constexpr int PAIRS = NP <= 4 && !SHORT ? 2 : 1;  // held in LDS
+    constexpr int PAIRS = NP <= 4 && !ONE ? 2 : 1;  // held in LDS
     constexpr int RPB = (NA + NB) * NP;           // runs of 1 KB per k block
     static_assert((NA * NP) % WAVES == 0 && (NB * NP) % WAVES == 0 && WAVES % NB == 0, "copies spread evenly over the waves");
     constexpr int ARUNS = NA * NP / WAVES;        // weight runs copied by a wave
     constexpr int GRUNS = NB * NP / WAVES;        // gathered runs: planes of one column block
-    // one LDS object (see dig_gemm_kernel): the ring and the (tap, channel group) table; 52 KB, three workgroups to a CU, or 26 KB.  Behind the
+    // one LDS object (see dig_gemm_kernel): the ring and the (tap, channel group) table; 52 KB, three workgroups to a CU, or 30 KB.  Behind the
     // loop the outputs' integers, the bias addends and the NaR flags take the ring.
     constexpr int VALS = L * TR * TC / 4, BEHIND = VALS + TR + (TR + TC) / 4;  // words of 16 bytes
-    constexpr int PAIRW = 2 * PAIRS * RPB * 64, RING = PAIRW > BEHIND ? PAIRW : BEHIND, KTAB = SHORT ? 2 : DCM_MAXK16 / 2;
+    constexpr int PAIRW = 2 * PAIRS * RPB * 64, RING = PAIRW > BEHIND ? PAIRW : BEHIND, KTAB = DCM_MAXK16 / 2;
     __shared__ uint4 lds[RING + KTAB];
     uint4* const stage = lds;
     int2* const ktab = reinterpret_cast<int2*>(lds + RING);
@@ -398,10 +397,10 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int 
     const bool by_f64 = NP <= 4 && a.fout.n <= 16;
     __syncthreads();  // ktab
     issue(0);
-    // the bias while the first blocks come in
     uint32_t bias_nar = 0;
     uint4 bias_add = make_uint4(0, 0, 0, 0);
-    if (a.bias && t < TR && tm * TR + t < a.MO) {
+    auto load_bias = [&]() {
+        if (!a.bias || t >= TR || tm * TR + t >= a.MO) return;
         const uint32_t bp = dig_load_pattern(a.bias, tm * TR + t, a.fin.n);
         bias_nar = bp == a.fin.nar() ? 1u : 0u;
         if (by_f64) {
@@ -411,7 +410,8 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int 
             const unsigned __int128 v = (unsigned __int128)dig_bias_value(bp, a.fin);
             bias_add = make_uint4((uint32_t)v, (uint32_t)(v >> 32), (uint32_t)(v >> 64), (uint32_t)(v >> 96));
         }
-    }
+    };
+    if (!ONE) load_bias();  // while the first blocks come in
 
     dig_v4i acc[2][NC];
 #pragma unroll
@@ -434,7 +434,7 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int 
             const int half = (p & (PAIRS - 1)) * (2 * RPB * 64);
             DigPair<NP> f;
             f.template load<0, TA, TB>(sa0 + half, sb0 + half);
-            if (PAIRS == 1 && !SHORT && p + 1 < pairs) {
+            if (PAIRS == 1 && p + 1 < pairs) {
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): read; behind the barrier everyone has
                 pcm_ring_barrier();
@@ -458,6 +458,7 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int 
         dig_single_mma<NP>(sa0 + at, sb0 + at, lane, a_nar, b_nar, row_nar, col_nar, acc);
     }
     __syncthreads();  // the last pair is read: the ring is free
+    if (ONE) load_bias();
     if (t < TR) {
         rowv[t] = bias_nar;
         badd[t] = bias_add;
@@ -563,15 +564,15 @@ __device__ __forceinline__ void dig_conv_tile(const DigConvArgs& a, int tm, int 
 // The last launch of a backward-data call also marks what NaR weights reach, tile by tile: behind its own work, or, if another
 // launch did that, right away (100 images of 30 channels at 27 x 27 to 45, posit<16,1>: 57.6 us with a launch of its own, 56.6 so;
 // the posit<8,0> kernel, which has no spare launch, lost 1 to 4 % on large layers by it).
-template <int NP, int WY, bool SHORT>
-__global__ __launch_bounds__(256, (NP > 4 ? 2 : SHORT ? 4 : 3)) void dig_conv_kernel(DigConvArgs a) {
+template <int NP, int WY, bool ONE>
+__global__ __launch_bounds__(256, (NP > 4 ? 2 : ONE ? 4 : 3)) void dig_conv_kernel(DigConvArgs a) {
     typedef DigConvShape<WY> Sh;
     const bool mark = a.nar.w && __builtin_amdgcn_readfirstlane(a.info->nar[1]);
     // a position's row tiles and the positions that share its taps on one XCD; nothing is shared by a single row of 1 x 1 tiles
     const int tiles = a.tiles_m * ((a.P + Sh::TC - 1) / Sh::TC), id = dig_tile_id();
     if (id >= tiles) return;
     const int tile = a.tiles_m > 1 || a.K16 > a.Cg ? dig_xcd_order(id, tiles) : id, tm = tile % a.tiles_m, tn = tile / a.tiles_m;
-    if (__builtin_amdgcn_readfirstlane(a.info->np) == a.np) dig_conv_tile<NP, WY, SHORT>(a, tm, tn);
+    if (__builtin_amdgcn_readfirstlane(a.info->np) == a.np) dig_conv_tile<NP, WY, ONE>(a, tm, tn);
     if (mark) bwd_data_nar_tile<Sh::TR, Sh::TC>(a.nar, a.out, tm * Sh::TR, tn * Sh::TC);
 }
 
@@ -581,7 +582,7 @@ inline dim3 dig_conv_grid(int tiles_m, int64_t P) { return dig_tile_grid(tiles_m
 template <int NP, int WY>
 inline hipError_t launch_dig_conv_shape(hipStream_t stream, const DigConvArgs& a) {
     const dim3 grid = dig_conv_grid<WY>(a.tiles_m, a.P);
-    if (NP <= 4 && a.KB <= 2) hipLaunchKernelGGL((dig_conv_kernel<NP, WY, NP <= 4>), grid, dim3(256), 0, stream, a);
+    if (NP <= 4 && (a.KB <= 8 || (int64_t)grid.x * grid.z > 768)) hipLaunchKernelGGL((dig_conv_kernel<NP, WY, NP <= 4>), grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((dig_conv_kernel<NP, WY, false>), grid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }

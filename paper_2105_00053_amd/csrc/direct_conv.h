@@ -111,7 +111,7 @@ constexpr int64_t direct_conv_short_outputs(int64_t K) {
     return longest ? (int64_t)1 << 19 : F::N == 10 ? INT64_MAX : (int64_t)1 << 22;
 }
 
-// us of the kernels that take a pass otherwise: rewritten operands on the matrix cores (fitted to 90 to 980 layers each, off by 7 to 13 %), the
+// us of the kernels that take a pass otherwise: rewritten operands on the matrix cores (fitted to 90 to 1910 layers each, off by 7 to 13 %), the
 // byte gather of (8,1) and (8,2), the dot products of posit<8,0> (15 to 30 %).  The general kernel, a tenth of their rate and less: CONV_GENERAL_US.
 // planes: whether it is the first of these.
 template <class F>
@@ -142,12 +142,12 @@ inline double conv_prepared_us(int which, const ConvGeom& g, bool with_bias, boo
     if (planes) {  // launches, a workgroup's k blocks, the rounds of workgroups behind the first, the rewritten tensor, the outputs
         const int ci = which == 0 ? g.C : g.K, mo = which == 0 ? g.K : g.C, wy = mo > 32 ? 2 : 1, tc = (p8 ? 128 : 64) / wy, cg = (ci + 15) / 16;
         const double kb = (double)(((int64_t)g.R * g.S * cg + 1) / 2), pixels = which == 0 ? (double)g.N * g.H * g.W : (double)g.N * g.OH * g.OW;
-        const double groups = (double)((mo + 32 * wy - 1) / (32 * wy)) * (double)(((int64_t)d.M + tc - 1) / tc), at_once = p8 ? 256 : kb <= 2 ? 1024 : 768;
+        const double groups = (double)((mo + 32 * wy - 1) / (32 * wy)) * (double)(((int64_t)d.M + tc - 1) / tc), at_once = p8 ? 256 : kb <= 8 || groups > 768 ? 1024 : 768;
         const double rounds = groups > at_once ? groups / at_once - 1 : 0, mb = pixels * cg * 16 / (1 << 20), out = (double)d.M * mo * (F::N == 8 ? 1 : 2) / (1 << 20);
         static const float C[4][2][6] = {{{7.88f, 0.481f, 0.148f, 0.711f, 1.01f, 0.f}, {8.85f, 0.513f, 0.166f, 0.651f, 1.f, 0.f}},
-                                         {{14.1f, 0.397f, 0.669f, 1.53f, 3.39f, 2.34f}, {13.2f, 0.372f, 0.674f, 1.46f, 2.85f, 2.09f}},
-                                         {{16.3f, 0.375f, 0.616f, 2.59f, 2.98f, 2.03f}, {15.8f, 0.323f, 0.634f, 2.98f, 2.75f, 1.3f}},
-                                         {{15.4f, 0.39f, 0.659f, 2.65f, 3.45f, 1.46f}, {14.6f, 0.365f, 0.67f, 1.83f, 3.56f, 1.3f}}};
+                                         {{15.1f, 0.48f, 0.615f, 3.03f, 2.77f, 1.71f}, {14.4f, 0.396f, 0.686f, 1.93f, 3.23f, 1.31f}},
+                                         {{17.4f, 0.401f, 0.716f, 2.96f, 3.09f, 1.6f}, {15.f, 0.438f, 0.648f, 2.59f, 3.46f, 1.45f}},
+                                         {{16.1f, 0.439f, 0.633f, 4.02f, 3.04f, 1.01f}, {15.f, 0.387f, 0.671f, 2.89f, 3.45f, 0.825f}}};
         const float* c = C[F::N == 8 ? F::ES : 3][which];
         return c[0] + c[1] * kb + (c[2] * kb + c[3]) * rounds + c[4] * mb + c[5] * out;
     }

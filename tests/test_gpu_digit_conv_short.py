@@ -1,4 +1,4 @@
-"""GPU parity of the digit-plane convolutions with reductions of one and two k blocks of 32 (and three, which take the longer ring) against the C++ oracle, bit for
+"""GPU parity of the digit-plane convolutions that hold one pair of k blocks of 32 in LDS, reductions of one block to fourteen, against the C++ oracle, bit for
 bit: both shapes of a workgroup, ragged positions, biases, NaR on either side, operands that four planes hold and that take the wide kernel."""
 import ctypes
 
@@ -13,17 +13,17 @@ from test_host_logic import CODE, hc  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-# gathered channels, outputs' channels, filter: 1, 1, 2, 2, 3 and 2 k blocks
-LAYERS = [(16, 40, 1), (30, 100, 1), (33, 24, 1), (64, 70, 1), (65, 40, 1), (7, 18, 2)]
+# gathered channels, outputs' channels, filter: 1, 1, 2, 2, 3, 2, 5, 9 and 14 k blocks
+LAYERS = [(16, 40, 1), (30, 100, 1), (33, 24, 1), (64, 70, 1), (65, 40, 1), (7, 18, 2), (5, 20, 3), (20, 40, 3), (33, 24, 3)]
 
 
-CASES = [(False, f, w, l) for f in ("p8_2", "p12_1", "p16") for w in (0, 1) for l in LAYERS] + [(True, "p10_1", w, l) for w in (0, 1) for l in LAYERS[:4:2]]
+CASES = [(False, f, w, l) for f in ("p8_2", "p12_1", "p16") for w in (0, 1) for l in LAYERS] + [(True, "p10_1", w, l) for w in (0, 1) for l in LAYERS[:4:2] + LAYERS[7:8]]
 
 
 @pytest.mark.parametrize("wide,fmt,which,layer", CASES)
 def test_passes(hc, wide, fmt, which, layer):  # noqa: F811
     ci, mo, r = layer
-    n, h = 70, 33 if r == 1 else 36
+    n, h = (70, 33) if r == 1 else (70, 36) if r == 2 else (52, 33)  # more than 768 workgroups
     c, k = (ci, mo) if which == 0 else (mo, ci)
     d = dict(N=n, C=c, H=h, W=h, K=k, R=r, S=r, pad_h=0, pad_w=0, stride_h=1, stride_w=1)
     desc = pn.ConvDesc(n, c, h, h, k, r, r, 0, 0, 1, 1)
