@@ -155,6 +155,7 @@ def test_weight_gradients_between_the_direct_kernel_and_digit_planes(hc, fmt, wh
     ("p8_1", 1, (132, 19, 32, 97, 1, 0, 1), False), ("p16", 2, (14, 18, 40, 131, 1, 0, 1), False), ("p8_1", 2, (144, 8, 60, 5, 5, 2, 1), False),
     ("p12_1", 2, (62, 83, 25, 96, 1, 0, 1), False), ("p8_1", 1, (155, 18, 50, 114, 1, 0, 1), False), ("p8_2", 0, (71, 27, 5, 144, 1, 0, 1), False),
     ("p8_2", 0, (28, 6, 9, 120, 1, 0, 1), False), ("p8_1", 0, (235, 84, 38, 23, 1, 0, 1), False), ("p16", 0, (199, 118, 40, 42, 1, 0, 2), False),
+    ("p8", 0, (104, 65, 8, 118, 5, 2, 1), False), ("p8", 1, (196, 2, 8, 126, 5, 2, 1), False), ("p8", 1, (107, 98, 5, 122, 5, 0, 1), False),
     ("p16", 0, (9, 17, 26, 5, 3, 1, 1), True), ("p8_1", 2, (259, 5, 10, 106, 3, 1, 1), True), ("p10_1", 0, (63, 4, 8, 12, 5, 2, 1), True),
     ("p8_1", 1, (11, 7, 33, 10, 3, 0, 1), True), ("p12_1", 2, (235, 24, 26, 2, 1, 0, 1), True), ("p12_1", 0, (20, 29, 38, 11, 1, 0, 1), True)])
 def test_layers_between_the_direct_kernel_and_the_kernels_of_16_x_32_blocks(hc, fmt, which, layer, direct):  # noqa: F811
