@@ -288,15 +288,15 @@ struct DigConvShape {
 };
 
 // A wave owns 16 x 32 outputs, two blocks of v_mfma_i32_16x16x64_i8 whose 2 NP - 1 sums take 56 registers for four planes and 120 for
-// eight, so that three and two workgroups share a CU (with blocks of 32 x 32 outputs two and one, and twice the outputs in a workgroup:
+// eight, so that three or four and two workgroups share a CU (with blocks of 32 x 32 outputs two and one, and twice the outputs in a workgroup:
 // a last round of workgroups twice as long).  A step takes a pair of k blocks of 32: a lane's 16 reduction indices come from block l / 32 of it.
-// Four planes: a ring of two pairs, the next one copied while a pair is multiplied.  Eight planes: room for one pair, whose 24 operand
-// quads go to registers before the next pair's copies start; the other workgroup multiplies meanwhile.
+// Room for one pair, whose operand quads (24 with eight planes) go to registers before the next pair's copies start; the other workgroups multiply meanwhile.  Or, four
+// planes, a ring of two pairs, the next one copied while a pair is multiplied.
 // Prologue and rounding weigh as much as the matrix instructions of a short reduction: four planes are all multiplied, and outputs of at most 16 bits
 // are rounded through binary64 in registers and stored from there (the kernel alone with blocks of 32 x 32, 128 images of 32 channels at 32 x 32, posit(8,2), 3 x 3 to 32
 // channels: 31 us, with integers of 96 bits through LDS 36).  Eight planes without NaR: only the planes that hold digits (with the same blocks, weights over most of the range
-// of posit(8,2) 46 us, all 8 x 8 pairs 61; the call then and now, patterns at random for weights, 119 and 90).  us a call, 32 x 32 -> now: posit<16,1> backward-data of 100 images of 30 channels at 27 x 27 to 45, 3 x 3, 54.9 and 45.9; forward of 46 of 48 at
-// 22 x 22 to 39, 5 x 5, stride 2, 49.0 and 34.0.  An odd last block (dig_single_mma; beside a block of
+// of posit(8,2) 46 us, all 8 x 8 pairs 61; the call then and now, patterns at random for weights, 119 and 90).  us a call, 32 x 32 -> now: posit<16,1> backward-data of 100 images of 30 channels at 27 x 27 to 45, 3 x 3, 54.9 and 45.3; forward of 46 of 48 at
+// 22 x 22 to 39, 5 x 5, stride 2, 49.0 and 32.0.  An odd last block (dig_single_mma; beside a block of
 // zeros before): posit(12,1) backward-data of 10 of 48 at 43 x 43 to 24, 3 x 3, 25.0 and 23.6.
 // ONE: four planes with one pair in LDS (30 KB, read and refilled as with eight planes) and a fourth workgroup on the CU, whose registers the bias, fetched behind the loop, leaves
 // free.  us a call, 32 x 32 blocks, two pairs, one: posit(12,1) backward-data of 74 images of 4 channels at 51 x 51 to 21, 1 x 1, 43.7, 48.1, 43.5; 3490 passes of
